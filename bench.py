@@ -114,7 +114,8 @@ def profiled_traffic(kernel):
     import hashlib
     import re
     path = os.path.join(ROOT, "profiles", f"{kernel}_ifu_scale_hbm.md")
-    src = os.path.join(ROOT, "paper_2504_01302_amd", "csrc", "jam_kernels.hip")
+    name = "jam_cheb.hip" if kernel.startswith("k_cheb") else "jam_kernels.hip"
+    src = os.path.join(ROOT, "paper_2504_01302_amd", "csrc", name)
     if not os.path.exists(path):
         return None
     text = open(path).read()
@@ -127,7 +128,36 @@ def profiled_traffic(kernel):
     return float(b.group(1))
 
 
-KERNEL_NAMES = {0: "k_num_pix", 1: "k_num_mfma", 2: "k_num_map", 3: "k_sph_moments"}
+KERNEL_NAMES = {0: "k_num_pix", 1: "k_num_mfma", 3: "k_sph_moments",
+                4: "k_cheb_panel + k_cheb_map"}
+FP64_MFMA_PEAK = 78.6e12        # MI355X published dense FP64 matrix FLOP/s
+
+
+def compressed_flops(g):
+    """FP64 flops of one model's numerator in the compressed form: 2 x 8 x 16
+    multiply-adds per term (the panels' node weights), 16 x 16 per panel and
+    map row (the y nodes) and 16 per (panel, pixel) reached.  Panels: octaves
+    of v = u^2 / (2 sigma_j^2) above the inverse of the largest squared
+    coordinate; a panel of tracer k reaches a coordinate q where
+    (alpha_k + v_lo) q^2 <= 160."""
+    def coords(n, c):
+        m = n * g.supersample + g.psf_n - 1
+        v = (np.arange(m) - (m - 1) / 2.0) * (g.pixsize / g.supersample) + c
+        return np.unique(np.abs(v).round(12))
+    x, y = coords(g.nx, g.xc), coords(g.ny, g.yc)
+    v1 = 1.0 / max(x[-1], y[-1]) ** 2
+    from paper_2504_01302_amd import binding
+    u, _ = binding.jam_gauss_legendre(g.n_u)
+    v = (u[None, :] ** 2 / (2.0 * np.append(g.mass_sigma, g.bh_sigma)[:, None] ** 2)).ravel()
+    panel = np.unique(np.where(v < v1, 0, 1 + np.floor(np.log2(np.maximum(v, v1) / v1)).astype(int)))
+    lo = np.where(panel == 0, 0.0, v1 * 2.0 ** (panel - 1.0))
+    madds = 256.0 * g.n_lum * len(v)
+    for s, q in zip(g.lum_sigma, g.lum_q):
+        a = 0.5 / s ** 2
+        nx = np.searchsorted(x, np.sqrt(160.0 / (a + lo)))
+        ny = np.searchsorted(y, np.sqrt(160.0 / (a / q ** 2 + lo)))
+        madds += np.sum(256.0 * ny + 16.0 * nx * ny)
+    return 2.0 * madds
 
 
 def unique_units(g):
@@ -141,9 +171,10 @@ def unique_units(g):
 
 
 def roofline_fracs(w, ms_fwd, ms_fb, num_ms=None, sens_ms=None):
-    """Fractions of the FP32 matrix-core peak at the algorithmic flop counts
-    per (unique pixel, term): 2 for the forward quadrature (N = A B^T), 4 for
-    the adjoint's two contractions, 6 for a forward + adjoint step."""
+    """The direct sum's rate as fractions of the FP32 matrix-core peak, at its
+    flop counts per (unique pixel, term): 2 for the forward quadrature (N = A
+    B^T), 4 for the adjoint's two contractions, 6 for a forward + adjoint step
+    (models in the compressed form do far less, so these can exceed 1)."""
     units = float(sum(unique_units(w.geometries[i]) for i in w.geom_idx))
     out = {"units": units,
            "forward_frac": 2 * units / (ms_fwd * 1e-3) / FP32_MFMA_PEAK,
@@ -596,7 +627,11 @@ def main():
     # (graph replays are not bracketed by the kernel timer)
     avg_num_s = (num_ms / num_n) * 1e-3 if num_n else None
     form_used = 1 if a.form == 1 else 2
-    if form_used == 2:
+    compressed = ctx.plan_info(w.geom_idx).get("num_kernel") == 4
+    if compressed:
+        flops = compressed_flops(g) * n
+        roof = dict(bound="mfma", peak=FP64_MFMA_PEAK / 1e12)
+    elif form_used == 2:
         flops = 2.0 * n_pix * T * n
         roof = dict(bound="mfma", peak=FP32_MFMA_PEAK / 1e12)
     else:
@@ -604,8 +639,8 @@ def main():
         roof = dict(bound="alu", peak=FP32_VECTOR_PEAK / 1e12)
     achieved = flops / avg_num_s / 1e12 if avg_num_s else None
     kname = KERNEL_NAMES.get(ctx.plan_info(w.geom_idx).get("num_kernel"), "k_num_pix")
-    traffic = profiled_traffic(kname) if (form_used == 2 and n == 1 and a.launch == 0
-                                          and not a.autotune) else None
+    traffic = profiled_traffic("k_cheb_map" if compressed else kname) if (
+        form_used == 2 and n == 1 and a.launch == 0 and not a.autotune) else None
     roof.update(achieved=achieved, unit="TFLOP/s",
                 frac=achieved / roof["peak"] if achieved else None, traffic=traffic,
                 kernel=kname, avg_launch_ms=avg_num_s * 1e3 if avg_num_s else None,
@@ -622,7 +657,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (f64 set-up, SB, bins)",
+        "dtype": "f64" if compressed else "f32 (f64 set-up, SB, bins)",
         "data": "synthetic",
         "config": {"workload": "IFU-scale JAM-cyl forward: 40 lum x 40 mass Gaussians + BH, "
                                "200x200 px at 0.025\" with 2x supersampling, 128 u-nodes, "

@@ -1,0 +1,45 @@
+// Device helpers shared by the gfx950 kernel files.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace jam {
+namespace {
+
+constexpr double kPi = 3.14159265358979323846;
+constexpr double kLog2e = 1.44269504088896340736;
+
+// G in pc (km/s)^2 / Msun: IAU nominal GM_sun over (1 pc in m) * 1e6, with
+// 1 pc = 648000/pi au and the IAU au.
+constexpr double kGMsun = 1.3271244e20;
+constexpr double kAu = 149597870700.0;
+
+__device__ inline double grav_const() { return kGMsun / (kAu * 648000.0 / kPi * 1.0e6); }
+
+__device__ inline double wave_sum(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// FP64 reciprocal and reciprocal square root: the hardware approximations
+// refined by two Newton steps (a few FP64 ulp; the coefficients they feed are
+// stored as FP32).  Arguments are positive and finite.
+__device__ inline double rcp64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  double e = fma(-x, r, 1.0);
+  r = fma(r, e, r);
+  e = fma(-x, r, 1.0);
+  return fma(r, e, r);
+}
+__device__ inline double rsq64(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  double e = fma(-x * y, y, 1.0);
+  y = fma(0.5 * y, e, y);
+  e = fma(-x * y, y, 1.0);
+  return fma(0.5 * y, e, y);
+}
+
+constexpr double kSqrtPi = 1.77245385090551602730;
+
+}  // namespace
+}  // namespace jam

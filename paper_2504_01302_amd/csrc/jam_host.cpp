@@ -97,6 +97,13 @@ struct GeomHost {
   // spherically aligned model: polar table radii and the 8-node rule
   double sph_lnr0 = 0, sph_dlnr = 0, sph_sig_max = 0;
   double gl8_x[8] = {}, gl8_w[8] = {};
+  // compressed cylindrical form (GeomDev)
+  int cheb_np = 0, cheb_pieces = 0;
+  bool cheb_fwd = false, cheb_adj = false;   // the faster form in a large batch
+  std::vector<double> cheb_lo, cheb_xi, cheb_E, cheb_Ek, cheb_Gk;
+  std::vector<int> cheb_ptr, cheb_id, cheb_h, cheb_ch, cheb_pc, cheb_jp, cheb_jx;
+  std::vector<unsigned char> cheb_px, cheb_py;
+  std::vector<unsigned short> cheb_ux;
 };
 
 jam_status validate(const jam_geometry &g, int gi) {
@@ -301,6 +308,152 @@ void build_spherical(GeomHost &o) {
   }
 }
 
+// The compressed form's cost against the direct forms', in ns of one SIMD per
+// tracer, forward and adjoint: the direct forms pay per (term, 32x32 block);
+// the compressed form per term, per panel (set-up, node transforms), per panel
+// and 16 map rows (the node contraction and its exponentials), and per panel
+// and block (FP64 MFMAs, about half of the pairs being reached).
+struct ChebCost { double direct, term, panel, row, tile; };
+// Fitted to forward and adjoint times of 1 to 256 models, 26 to 202 distinct
+// coordinates an axis and 48 to 7808 terms per tracer.
+constexpr ChebCost kChebFwd{24.0, 24.0, 1500.0, 380.0, 370.0};
+constexpr ChebCost kChebAdj{40.0, 45.0, 5200.0, 520.0, 600.0};
+double cheb_direct_ns(const GeomHost &o, const ChebCost &c) {
+  const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32;
+  return c.direct * o.J1 * o.n_u * bx * by;
+}
+double cheb_ns(const GeomHost &o, const ChebCost &c, int panels) {
+  const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32;
+  return c.term * o.J1 * o.n_u + panels * (c.panel + c.row * 2.0 * by + c.tile * bx * by);
+}
+
+// Tables of the compressed cylindrical form (GeomDev): panels of v = r u^2,
+// the first [0, 1 / M2) with M2 the map's largest squared coordinate, then a
+// factor kChebR wide each; empty ones are left out.
+// Unique-pixel maps with at most this many distinct |x'| and |y'| (one 32x32
+// matrix-core block) take the small-map form: terms computed in place by the
+// numerator, sensitivities and chain fused in the adjoint (for at most
+// jam::kSmallAdjMass mass Gaussians, the BH included).
+constexpr int kSmallMap = 32;
+constexpr double kChebCut = 160.0; // a unit is zero where its exponent exceeds this (FP32 sums
+                                   // underflow at 87)
+void build_cheb(GeomHost &o) {
+  o.cheb_np = 0;
+  if (o.n_ux <= kSmallMap && o.n_uy <= kSmallMap && o.J1 <= jam::kSmallAdjMass) return;
+  const double m2 = std::max(o.xs.back() * o.xs.back(), o.ys.back() * o.ys.back());
+  if (!(m2 > 0.0) || !std::isfinite(1.0 / m2)) return;
+  const double v1 = 1.0 / m2;
+  const int nt = o.J1 * o.n_u;
+  std::vector<int> panel(nt);
+  std::vector<double> vt(nt);
+  int count[jam::kChebMaxPanels] = {}, top = 0;
+  double edge[jam::kChebMaxPanels + 1];
+  edge[0] = 0.0;
+  for (int e = 1; e <= jam::kChebMaxPanels; ++e) edge[e] = v1 * std::pow(jam::kChebR, e - 1);
+  for (int j = 0; j < o.J1; ++j) {
+    const double sig = j < o.J ? o.mass_sigma[j] : o.bh_sigma;
+    const double r = 0.5 / (sig * sig);
+    for (int n = 0; n < o.n_u; ++n) {
+      const double v = r * (o.u[n] * o.u[n]);
+      if (!(v < edge[jam::kChebMaxPanels])) return;
+      const int e = (int)(std::upper_bound(edge, edge + jam::kChebMaxPanels, v) - edge) - 1;
+      vt[j * o.n_u + n] = v;
+      panel[j * o.n_u + n] = e;
+      count[e]++;
+      top = std::max(top, e);
+    }
+  }
+  std::vector<int> index(top + 1, -1);
+  int np = 0;
+  for (int e = 0; e <= top; ++e)
+    if (count[e]) index[e] = np++;
+  o.cheb_fwd = cheb_ns(o, kChebFwd, np) < cheb_direct_ns(o, kChebFwd);
+  o.cheb_adj = cheb_ns(o, kChebAdj, np) < cheb_direct_ns(o, kChebAdj);
+  if (!o.cheb_fwd && !o.cheb_adj) return;
+  o.cheb_lo.assign(2 * np, 0.0);
+  o.cheb_ptr.assign(np + 1, 0);
+  for (int e = 0; e <= top; ++e) {
+    const int P = index[e];
+    if (P < 0) continue;
+    o.cheb_lo[P] = edge[e];
+    o.cheb_lo[np + P] = edge[e + 1];
+    o.cheb_ptr[P + 1] = o.cheb_ptr[P] + count[e];
+  }
+  o.cheb_id.resize(nt);
+  o.cheb_xi.resize(nt);
+  std::vector<int> fill(o.cheb_ptr.begin(), o.cheb_ptr.end() - 1);
+  const double lr = std::log(jam::kChebR);
+  for (int j = 0; j < o.J1; ++j)
+    for (int n = 0; n < o.n_u; ++n) {
+      const int t = j * o.n_u + n, P = index[panel[t]], at = fill[P]++;
+      const double lo = o.cheb_lo[P];
+      o.cheb_id[at] = j << 10 | n;
+      o.cheb_xi[at] = lo == 0.0 ? 2.0 * (vt[t] / v1) - 1.0 : 2.0 * (std::log(vt[t] / lo) / lr) - 1.0;
+    }
+  // chunks of 64 terms within a panel and their runs of equal j
+  o.cheb_ch.assign(np + 1, 0);
+  std::vector<std::vector<int>> of_j(o.J1);
+  for (int P = 0; P < np; ++P) {
+    for (int e = o.cheb_ptr[P]; e < o.cheb_ptr[P + 1]; ++e) {
+      if ((e - o.cheb_ptr[P]) % 64 == 0) {
+        o.cheb_pc.push_back(o.cheb_pieces);
+      } else if (o.cheb_id[e] >> 10 == o.cheb_id[e - 1] >> 10) {
+        continue;
+      }
+      of_j[o.cheb_id[e] >> 10].push_back(o.cheb_pieces++);
+    }
+    o.cheb_ch[P + 1] = (int)o.cheb_pc.size();
+  }
+  o.cheb_jp.assign(1, 0);
+  for (auto &v : of_j) {
+    o.cheb_jx.insert(o.cheb_jx.end(), v.begin(), v.end());
+    o.cheb_jp.push_back((int)o.cheb_jx.size());
+  }
+  const int ntx = (o.n_ux + 31) / 32, nty = (o.n_uy + 31) / 32, ldx = 32 * ntx, ldy = 32 * nty;
+  o.cheb_E.assign((size_t)np * 2 * jam::kChebP * ldx, 0.0);
+  for (int P = 0; P < np; ++P)
+    for (int m = 0; m < jam::kChebP; ++m) {
+      const double x = 0.5 * (std::cos(kPi * (m + 0.5) / jam::kChebP) + 1.0);
+      const double lo = o.cheb_lo[P], v = lo == 0.0 ? x * v1 : lo * std::exp(lr * x);
+      double *row = o.cheb_E.data() + (size_t)(P * 2 * jam::kChebP + m) * ldx;
+      double *sq = row + (size_t)jam::kChebP * ldx;
+      for (int i = 0; i < o.n_ux; ++i) {
+        const double x2 = o.xs[i] * o.xs[i];
+        row[i] = std::exp(-v * x2);
+        sq[i] = x2 * row[i];
+      }
+    }
+  o.cheb_Ek.assign((size_t)o.K * ldx, 0.0);
+  o.cheb_Gk.assign((size_t)o.K * ldy, 0.0);
+  o.cheb_px.assign((size_t)o.K * ntx, 0);
+  o.cheb_py.assign((size_t)o.K * nty, 0);
+  o.cheb_ux.assign((size_t)o.K * np, 0);
+  o.cheb_h.assign((size_t)o.K * np + 1, 0);
+  for (int k = 0; k < o.K; ++k) {
+    const double a = 0.5 / (o.lum_sigma[k] * o.lum_sigma[k]), ay = a / (o.lum_q[k] * o.lum_q[k]);
+    for (int i = 0; i < o.n_ux; ++i) o.cheb_Ek[(size_t)k * ldx + i] = std::exp(-a * (o.xs[i] * o.xs[i]));
+    for (int i = 0; i < o.n_uy; ++i) o.cheb_Gk[(size_t)k * ldy + i] = std::exp(-ay * (o.ys[i] * o.ys[i]));
+    // panels reaching a tile: by its smallest coordinate (d >= v, so the
+    // panel's lower end in v bounds its decay in y too)
+    auto reach = [&](double alpha, double q) {
+      int c = 0;
+      while (c < np && (alpha + o.cheb_lo[c]) * (q * q) <= kChebCut) ++c;
+      return (unsigned char)c;
+    };
+    for (int t = 0; t < ntx; ++t) o.cheb_px[(size_t)k * ntx + t] = reach(a, o.xs[32 * t]);
+    for (int t = 0; t < nty; ++t) o.cheb_py[(size_t)k * nty + t] = reach(ay, o.ys[32 * t]);
+    for (int P = 0; P < np; ++P) {
+      int tiles = 0, cols = 0;
+      while (cols < ntx && o.cheb_px[(size_t)k * ntx + cols] > P) ++cols;
+      if (cols > 0)
+        while (tiles < nty && o.cheb_py[(size_t)k * nty + tiles] > P) ++tiles;
+      o.cheb_ux[(size_t)k * np + P] = (unsigned short)cols;
+      o.cheb_h[(size_t)k * np + P + 1] = o.cheb_h[(size_t)k * np + P] + tiles;
+    }
+  }
+  o.cheb_np = np;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // How a plan schedules its numerator (what the autotuner varies).
@@ -313,8 +466,9 @@ struct Tune {
                     // per-pixel item; 0 = derived from the batch
   int launch = 0;   // 0 one workgroup per item; 1 persistent grid pulling items from a
                     // device queue
-  int map = 0;      // derived from the batch, not tuned: 1 when rule 1 runs every model
-                    // with the whole-map matrix-core kernel (all maps of 7 x 7 blocks)
+  int cheb = -1;    // derived from the batch, not tuned (-1: still to be derived): the
+                    // compressed form for the forward (1) and the adjoint (2) of the models
+                    // whose geometry it suits
 };
 
 // Every pointer a captured graph was recorded with (parameters, outputs,
@@ -347,12 +501,22 @@ struct Plan {
   jam::Item *d_terms = nullptr, *d_pix = nullptr, *d_num = nullptr, *d_bins = nullptr,
             *d_maps = nullptr, *d_chain = nullptr, *d_sens = nullptr, *d_sb = nullptr,
             *d_red = nullptr, *d_sph = nullptr, *d_pro = nullptr, *d_adj = nullptr,
-            *d_redf = nullptr, *d_sensw = nullptr, *d_sgrid = nullptr, *d_sgred = nullptr,
+            *d_sensw = nullptr, *d_sgrid = nullptr, *d_sgred = nullptr,
             *d_sgred6 = nullptr, *d_pcot = nullptr, *d_pfix = nullptr, *d_sgs = nullptr,
-            *d_sphm = nullptr;
+            *d_sphm = nullptr, *d_cpan = nullptr, *d_csum = nullptr, *d_cadj = nullptr,
+            *d_ctmap = nullptr, *d_crows = nullptr;
+  jam::ChebItem *d_cmap = nullptr;
+  // compressed forward: models taken together, [first, end) of their items
+  // and how many of the panel items a block's waves share; the groups share
+  // one H region
+  struct ChebGroup { int pan0, pan1, map0, map1, pan_share; };
+  std::vector<ChebGroup> cheb_groups;
   int n_terms = 0, n_pix = 0, n_num = 0, n_bins = 0, n_maps = 0, n_chain = 0, n_sens = 0,
-      n_sb = 0, n_red = 0, n_sph = 0, n_pro = 0, n_adj = 0, n_redf = 0, n_sensw = 0,
-      n_sgrid = 0, n_sgred = 0, n_sgred6 = 0, n_pcot = 0, n_pfix = 0, n_sgs = 0, n_sphm = 0;
+      n_sb = 0, n_red = 0, n_sph = 0, n_pro = 0, n_adj = 0, n_sensw = 0,
+      n_sgrid = 0, n_sgred = 0, n_sgred6 = 0, n_pcot = 0, n_pfix = 0, n_sgs = 0, n_sphm = 0,
+      n_cpan = 0, n_csum = 0, n_cadj = 0, n_cmap = 0, n_ctmap = 0, n_crows = 0;
+  int cadj_share = 0, cheb_waves = 4, cadj_waves = 4;   // shared adjoint items, waves per block
+  int n_cheb = 0;        // models of the compressed form
   int n_bins_wave = 0;   // leading bin items summed one bin per wave
   bool spherical = false;
   bool fused_prologue = true;
@@ -365,6 +529,8 @@ struct Plan {
          off_vtmp = 0,
          off_cot = 0,
          off_sbp = 0,
+         off_cheb = 0,
+         off_chebt = 0,
          ws_fwd = 0, ws_vjp = 0;
   // captured evaluations (forward, adjoint, forward + chi^2, adjoint of chi^2)
   hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -464,18 +630,6 @@ constexpr size_t kMaxPlans = 8;
 // launch (each term block recomputes its (k, j) pairs' set-up, which costs
 // latency per block but saves two launches).
 constexpr int kFusedPrologueModels = 32;
-// Unique-pixel maps with at most this many distinct |x'| and |y'| (one 32x32
-// matrix-core block) take the small-map form: terms computed in place by the
-// numerator, sensitivities and chain fused in the adjoint (for at most
-// jam::kSmallAdjMass mass Gaussians, the BH included).
-constexpr int kSmallMap = 32;
-// Whole-map numerator: longest slice, in units of 64 terms, summed in FP32.
-constexpr int kMapMaxUnits = 32;
-// Does a geometry's map suit the whole-map matrix-core numerator?
-bool map_fits(int n_ux, int n_uy) {
-  const int bx = (n_ux + 31) / 32, by = (n_uy + 31) / 32;
-  return bx == jam::kMapBlocks && by == jam::kMapBlocks;
-}
 // Geometries whose bins have at most this many weights each sum every bin
 // with one wave (4 bins per workgroup) instead of a whole workgroup.
 constexpr int kBinWaveNnz = 2048;
@@ -491,9 +645,8 @@ struct WaveTile {
 };
 
 struct NumChoice {
-  int kind;      // 0 per-pixel VALU, 2 matrix-core wave tiles
+  int kind;      // 0 per-pixel VALU, 2 matrix-core wave tiles, 5 compressed (no items here)
   bool gen = false;   // matrix core on a map of one 32x32 block, terms computed in place
-  bool map = false;   // matrix core, one workgroup per whole map and slice
   int n_slices;
   int units;     // slice units of the whole term range
   std::vector<WaveTile> tiles;   // matrix core
@@ -525,16 +678,13 @@ NumChoice choose_numerator(const GeomHost &g, const Tune &t, int gran) {
     return c;
   }
   const int chunks = (g.T + 63) / 64;
-  c.kind = 2;
-  if (t.map) {
-    // FP32 accumulation over a slice: at most kMapMaxUnits x 64 terms
-    const int per = std::max(1, std::min(kMapMaxUnits, gran));
-    c.map = true;
-    c.n_slices = std::max(1, (chunks + per - 1) / per);
-    c.units = chunks;
-    c.tiles.push_back({0, 0, (g.n_ux + 31) / 32, (g.n_uy + 31) / 32});
+  if ((t.cheb & 1) && g.cheb_fwd) {
+    c.kind = 5;
+    c.n_slices = 0;
+    c.units = 0;
     return c;
   }
+  c.kind = 2;
   const int per = std::max(4, gran);
   c.gen = g.n_ux <= kSmallMap && g.n_uy <= kSmallMap && g.J1 <= jam::kSmallAdjMass;
   c.n_slices = std::max(1, (chunks + per - 1) / per);
@@ -563,12 +713,6 @@ double num_item_cost(const GeomHost &g, const NumChoice &c, int slice, int tile)
   // (dependent descriptor and coordinate loads, first chunk), the four-wave
   // sum and the tile store
   const WaveTile &w = c.tiles[tile];
-  if (c.map) {
-    // every wave runs every chunk for its quarter of the blocks; the
-    // workgroup generates the operands of all rows and columns once
-    const int nblk = w.BX * w.BY;
-    return cnt * (1.5 * ((nblk + 3) / 4) + 0.75) + 8.0;
-  }
   // terms computed in place: their FP64 set-up per chunk
   const double gen = c.gen ? 0.5 : 0.0;
   return ((cnt + 3) / 4) * (1.5 * w.BX * w.BY + 0.75 * (w.BX + w.BY) + gen) + 8.0;
@@ -619,7 +763,7 @@ int default_gran(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune 
     }
   }
   // jobs a worker holds at once
-  const double per_slot = t.rule == 0 ? ctx->occ_num_pix : (t.map ? 1 : ctx->occ_num_mfma);
+  const double per_slot = t.rule == 0 ? ctx->occ_num_pix : ctx->occ_num_mfma;
   const double g0 = std::max(1.0, std::ceil(work / (slots * per_slot)));
   std::vector<int> cands;
   for (int k = -8; k <= 16; ++k)
@@ -628,9 +772,6 @@ int default_gran(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune 
     const int s_max = std::min(4096, (int)(4 * per_slot) * slots / std::max(1, big_tiles) + 1);
     for (int sl = 1; sl <= s_max; ++sl) cands.push_back((big_units + sl - 1) / sl);
   }
-  // whole-map slices are capped (FP32 accumulation): every length up to the cap
-  if (t.map)
-    for (int gr = 1; gr <= kMapMaxUnits; ++gr) cands.push_back(gr);
   std::sort(cands.begin(), cands.end());
   cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
   double best = 1e300;
@@ -717,25 +858,59 @@ void wide_items(const std::vector<WidePart> &parts, int n_cu, std::vector<jam::I
   sort_by_cost(out, cost);
 }
 
+// Panels of tracer k that reach a tile of the compressed form's map, and
+// every tile's total over the tracers.
+int cheb_reach(const GeomHost &g, int k, int tile) {
+  const int ntx = (g.n_ux + 31) / 32, nty = (g.n_uy + 31) / 32;
+  return std::min(g.cheb_px[(size_t)k * ntx + tile % ntx], g.cheb_py[(size_t)k * nty + tile / ntx]);
+}
+template <typename F>
+void for_cheb_tiles(const GeomHost &g, F f) {
+  const int tiles = ((g.n_ux + 31) / 32) * ((g.n_uy + 31) / 32);
+  for (int t = 0; t < tiles; ++t) {
+    int units = 0;
+    for (int k = 0; k < g.K; ++k) units += cheb_reach(g, k, t);
+    f(t, units);
+  }
+}
+
+constexpr double kShareTerms = 512.0;
+
+// Whether a batch takes the compressed form, forward (1) and adjoint (2).  The
+// forward has one launch more than the direct one and, in a single model,
+// fewer workgroups to hide its latency, so its gain on the whole chip has to
+// exceed kChebLatencyNs: one model of 102 x 102 distinct pixels, 16 x 31 x 112
+// terms takes 45.7 us compressed and 49.3 direct, 66 x 66 with 12 x 61 x 128
+// terms 51.6 and 50.3.  The adjoint's launches are the direct one's.
+constexpr double kChebLatencyNs = 17000.0;
+int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
+  if (t.rule != 1 || ctx->opt.alignment == 1) return 0;
+  double gain_f = 0.0, gain_a = 0.0;
+  for (int m = 0; m < n; ++m) {
+    const GeomHost &g = ctx->gh[geom_idx[m]];
+    if (g.cheb_fwd) gain_f += g.K * (cheb_direct_ns(g, kChebFwd) - cheb_ns(g, kChebFwd, g.cheb_np));
+    if (g.cheb_adj) gain_a += g.K * (cheb_direct_ns(g, kChebAdj) - cheb_ns(g, kChebAdj, g.cheb_np));
+  }
+  const double simds = 4.0 * ctx->n_cu;
+  return (gain_f > simds * kChebLatencyNs ? 1 : 0) | (gain_a > 0.0 ? 2 : 0);
+}
+
+// h_limit: a group of compressed models is closed once its H takes this many
+// doubles (a single model's is never split).
 jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tune &tune_in,
-                      std::unique_ptr<Plan> &out) {
+                      std::unique_ptr<Plan> &out, int64_t h_limit = INT64_MAX) {
   auto p = std::make_unique<Plan>();
   p->key.assign(geom_idx, geom_idx + n);
   p->n = n;
   p->tune = tune_in;
-  p->tune.map = 0;
-  if (p->tune.rule == 1 && ctx->opt.alignment != 1) {
-    bool all = true;
-    for (int m = 0; m < n && all; ++m)
-      all = map_fits(ctx->gh[geom_idx[m]].n_ux, ctx->gh[geom_idx[m]].n_uy);
-    p->tune.map = all ? 1 : 0;
-  }
+  if (p->tune.cheb < 0) p->tune.cheb = choose_cheb(ctx, n, geom_idx, p->tune);
   if (p->tune.gran <= 0) p->tune.gran = default_gran(ctx, n, geom_idx, p->tune);
   const Tune &tune = p->tune;
   std::vector<jam::ModelDev> md(n);
   std::vector<jam::Item> it_terms, it_pix, it_num, it_bins, it_maps, it_chain, it_sens, it_sb,
-      it_red, it_sph, it_pro, it_adj, it_redf, it_sensw, it_sgrid, it_sgred, it_sgred6, it_pcot,
-      it_pfix, it_sgs, it_sphm;
+      it_red, it_sph, it_pro, it_adj, it_sensw, it_sgrid, it_sgred, it_sgred6, it_pcot,
+      it_pfix, it_sgs, it_sphm, it_cpan, it_csum, it_cadj, it_ctmap, it_crows, it_sbpro;
+  std::vector<jam::ChebItem> it_cmap;
   std::vector<double> c_num, c_sens, c_sensw;
   // wide-sensitivity parts (model, part, x tiles, 32-term groups); their
   // items are cut after the model loop (wide_items)
@@ -743,6 +918,63 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   int64_t gauss = 0, terms = 0, pixd = 0, part = 0, bins = 0, sens = 0, sph = 0, sbp = 0,
           sgrid = 0, sgrid6 = 0, sgcot = 0;
   const bool spherical = ctx->opt.alignment == 1;
+  // compressed form: units per map item, two items per compute unit where
+  // the batch is small enough (a unit on a tile is 16 FP64 MFMAs of a wave)
+  auto fwd_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && (tune.cheb & 1) && g.cheb_fwd; };
+  auto adj_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && (tune.cheb & 2) && g.cheb_adj; };
+  int64_t cheb_units = 0, cheb_panels = 0, cadj_panels = 0;
+  int cheb_most = 0;   // terms of the largest panel
+  for (int m = 0; m < n; ++m) {
+    const GeomHost &g = ctx->gh[geom_idx[m]];
+    if (fwd_cheb(g)) {
+      for_cheb_tiles(g, [&](int, int units) { cheb_units += units; });
+      cheb_panels += (int64_t)g.K * g.cheb_np;
+    }
+    if (adj_cheb(g)) cadj_panels += (int64_t)g.K * g.cheb_np;
+    for (int P = 0; P < g.cheb_np; ++P) cheb_most = std::max(cheb_most, g.cheb_ptr[P + 1] - g.cheb_ptr[P]);
+  }
+  const int cheb_per = (int)std::max<int64_t>(
+      16, std::min<int64_t>(160, (cheb_units + 2 * ctx->n_cu - 1) / (2 * ctx->n_cu)));
+  // A block's waves share a unit whose panel has more than kShareTerms
+  // terms, and every unit of a batch too small to give each SIMD one (eight
+  // waves then, where a panel has enough terms for them).
+  const bool share_f = cheb_panels <= 4 * (int64_t)ctx->n_cu, share_a = cadj_panels <= 4 * (int64_t)ctx->n_cu;
+  p->cheb_waves = share_f && cheb_most > 512 ? 8 : 4;
+  p->cadj_waves = share_a && cheb_most > 512 ? 8 : 4;
+  int64_t cheb_h = 0, cheb_hmax = 0, cheb_t = 0;
+  std::vector<double> c_cpan, c_cadj;
+  Plan::ChebGroup grp{};
+  // shared items first, largest first, then the others as they come
+  auto order_units = [&](std::vector<jam::Item> &v, std::vector<double> &cost, int first) {
+    std::vector<jam::Item> sub, rest;
+    std::vector<double> cs;
+    for (size_t i = first; i < v.size(); ++i) {
+      if (v[i].c & 1) {
+        sub.push_back(v[i]);
+        cs.push_back(cost[i]);
+      } else {
+        rest.push_back(v[i]);
+      }
+    }
+    sort_by_cost(sub, cs);
+    std::copy(sub.begin(), sub.end(), v.begin() + first);
+    std::copy(rest.begin(), rest.end(), v.begin() + first + sub.size());
+    return (int)sub.size();
+  };
+  auto close_group = [&]() {
+    grp.pan1 = (int)it_cpan.size();
+    grp.map1 = (int)it_cmap.size();
+    if (grp.pan1 > grp.pan0 || grp.map1 > grp.map0) {
+      grp.pan_share = order_units(it_cpan, c_cpan, grp.pan0);
+      std::stable_sort(it_cmap.begin() + grp.map0, it_cmap.end(),
+                       [](const jam::ChebItem &a, const jam::ChebItem &b) { return a.count > b.count; });
+      p->cheb_groups.push_back(grp);
+    }
+    grp.pan0 = grp.pan1;
+    grp.map0 = grp.map1;
+    cheb_hmax = std::max(cheb_hmax, cheb_h);
+    cheb_h = 0;
+  };
   // spherical forward: the potential grid (form 1: sums at every node)
   const bool use_sgrid = spherical && ctx->opt.form != 1;
   for (int m = 0; m < n; ++m) {
@@ -757,15 +989,15 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     const NumChoice nc = choose_numerator(g, tune, tune.gran);
     d.n_slices = nc.n_slices;
     const bool small = !spherical && nc.gen;
-    d.form = nc.kind == 0 ? 1 : (small ? 3 : (nc.map ? 4 : 2));
-    d.part_f32 = nc.map ? 1 : 0;
+    const bool cheb = !spherical && nc.kind == 5, cadj = adj_cheb(g);
+    d.form = nc.kind == 0 ? 1 : (cheb ? 5 : (small ? 3 : 2));
     // adjoint sensitivity blocks: one (per-pixel), none (small map), one per
     // x tile (one tile), one per part of up to four x tiles (wide)
     // (the wide form pays off where each term group runs over many y steps:
     // its per-group epilogue and accumulator set-up are fixed costs)
     const int n_xt = (g.n_ux + 31) / 32;
-    const bool wide = !spherical && !small && d.form != 1 && n_xt >= 2 && g.n_uy >= kWideMinY;
-    d.n_sens_parts = d.form == 1 ? 1 : (small ? 0 : (wide ? (n_xt + 3) / 4 : n_xt));
+    const bool wide = !spherical && !small && !cadj && d.form != 1 && n_xt >= 2 && g.n_uy >= kWideMinY;
+    d.n_sens_parts = d.form == 1 ? 1 : (small || cadj ? 0 : (wide ? (n_xt + 3) / 4 : n_xt));
     d.n_xt = (g.n_ux + 31) / 32;
     d.n_yt = (g.n_uy + 31) / 32;
     d.gauss_off = gauss;
@@ -808,11 +1040,60 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     const int tsph = jam::sph_terms_padded(g.J1, g.n_u);
     // spherical: float4 terms, then floats; small maps compute their terms in
     // place; cylindrical tables are zero-padded to a multiple of 32 terms
-    terms += spherical ? tsph + tsph / 4 : (small ? 0 : jam::padded_terms(g.T));
+    terms += spherical ? tsph + tsph / 4 : (small || (cheb && cadj) ? 0 : jam::padded_terms(g.T));
     pixd += 4 * (int64_t)g.n_pix;
-    // padded to whole blocks; FP32 partials (whole-map numerator) take half
-    const int64_t part_elems = (int64_t)d.n_slices * (32 * d.n_xt) * (32 * d.n_yt);
-    part += nc.map ? (part_elems + 1) / 2 : part_elems;
+    // padded to whole blocks
+    part += (int64_t)d.n_slices * (32 * d.n_xt) * (32 * d.n_yt);
+    const int np = g.cheb_np;
+    if (cheb || cadj)
+      for (int k = 0; k < g.K; ++k)
+        for (int P = 0; P < np; ++P) {
+          const int nyt = g.cheb_h[k * np + P + 1] - g.cheb_h[k * np + P];
+          const double terms_p = g.cheb_ptr[P + 1] - g.cheb_ptr[P];
+          if (cheb && nyt > 0) {
+            it_cpan.push_back({m, k, P, share_f || terms_p > kShareTerms});
+            c_cpan.push_back(terms_p + 40.0 * nyt);
+          }
+          if (cadj) {
+            // a small batch's long panels in slices of one chunk per wave
+            const int sl = share_a ? (int)std::min(1024.0, std::ceil(terms_p / (64.0 * p->cadj_waves))) : 1;
+            for (int q = 0; q < sl; ++q) {
+              it_cadj.push_back({m, k, P, (share_a || terms_p > kShareTerms) | q << 1 | sl << 16});
+              c_cadj.push_back(terms_p / sl + 30.0 * nyt);
+            }
+          }
+        }
+    if (cheb) {
+      const int64_t hm = (int64_t)g.cheb_h.back() * 512;
+      d.cheb_off = cheb_h;
+      cheb_h += hm;
+      p->n_cheb++;
+      // runs of equal length, a multiple of four units (four waves share one)
+      int slot = 0;
+      for_cheb_tiles(g, [&](int tile, int units) {
+        const int s0 = slot, runs = (units + cheb_per - 1) / cheb_per;
+        const int len = runs ? ((units + runs - 1) / runs + 3) / 4 * 4 : 0;
+        // a run starts at unit at = 0, len, 2 len, ... of the tile
+        for (int k = 0, first = 0, at = 0; at < units; ++k) {
+          const int reach = cheb_reach(g, k, tile);
+          for (; at < first + reach; at += len)
+            it_cmap.push_back({m, tile, k, at - first, std::min(len, units - at), slot++});
+          first += reach;
+        }
+        for (int q = 0; q < 4; ++q) it_csum.push_back({m, 4 * tile + q, s0, slot - s0});
+      });
+      part += (int64_t)slot * 1024;
+      if (cheb_h >= h_limit) close_group();
+    }
+    if (cadj) {
+      d.chebt_off = cheb_t;
+      cheb_t += (int64_t)g.cheb_h.back() * 512;
+      for (int ty = 0; ty < d.n_yt; ++ty)
+        for (int k = 0; k < g.K; ++k)
+          if (cheb_reach(g, k, ty * d.n_xt) > 0) it_ctmap.push_back({m, ty, k, 0});
+      for (int k = 0; k < g.K; ++k)
+        for (int jb = 0; jb < (g.J1 + 63) / 64; ++jb) it_crows.push_back({m, k, jb, 0});
+    }
     bins += 2 * (int64_t)g.n_bins;
     if (spherical) {
       // term sensitivities: point ranges, or (with the potential grid) parts
@@ -820,13 +1101,14 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
       d.n_sens_parts = use_sgrid ? jam::kSphIParts : jam::sph_ranges(g.K);
       sens += jam::sph_adj_size(g.K, g.n_pix, tsph, d.n_sens_parts);
     } else {
-      sens += 3 * (int64_t)d.n_sens_parts * g.T + (int64_t)g.K * 3 * g.J1;
+      sens += 3 * (int64_t)d.n_sens_parts * g.T + (int64_t)g.K * 3 * g.J1 +
+              (cadj ? 3 * (int64_t)g.K * g.cheb_pieces : 0);
     }
     p->total_lum += g.K;
     p->total_mass += g.J;
     p->total_bins += g.n_bins;
     p->total_map += (int64_t)g.nxp * g.nyp;
-    if (!small)
+    if (!small && !(cheb && cadj))
       for (int tb = 0; tb < ((spherical ? tsph : g.T) + 255) / 256; ++tb)
         it_terms.push_back({m, tb, 0, 0});
     if (spherical && use_sgrid) {
@@ -842,6 +1124,8 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
           it_sens.push_back({m, tt, r, 0});
           c_sens.push_back((double)jam::sph_range_len(g.K, d.n_sens_parts));
         }
+    } else if (cadj) {
+      // it_cadj
     } else if (small) {
       // fused sensitivities + chain: items of whole tracers, about 8192
       // terms each
@@ -865,12 +1149,13 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
         }
     }
     for (int pb = 0; pb < (g.n_pix + 255) / 256; ++pb) it_pix.push_back({m, pb, 0, 0});
-    if (nc.map)   // FP32 partials, reduced over the padded layout
-      for (int pb = 0; pb < (g.n_ux * 32 * d.n_yt + 255) / 256; ++pb) it_redf.push_back({m, pb, 0, 0});
-    else
+    if (!cheb)   // summed by k_cheb_sum
       for (int pb = 0; pb < (g.n_pix + 63) / 64; ++pb) it_red.push_back({m, pb, 0, 0});
     for (int rb = 0; rb < (g.n_uy + 7) / 8; ++rb)
-      for (int cb = 0; cb < (g.n_ux + 63) / 64; ++cb) it_sb.push_back({m, rb, cb, 0});
+      for (int cb = 0; cb < (g.n_ux + 63) / 64; ++cb) {
+        it_sb.push_back({m, rb, cb, 0});
+        if (!cheb) it_sbpro.push_back({m, rb, cb, 0});
+      }
     for (int s = 0; s < d.n_slices; ++s)
       for (int tl = 0; tl < nc.n_tiles(); ++tl) {
         if (nc.kind == 0) {
@@ -878,7 +1163,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
         } else {
           const WaveTile &w = nc.tiles[tl];
           it_num.push_back({m, w.bx | (w.by << 16), s,
-                            nc.map ? 7 : (small ? 6 : 2 + (w.BX - 1) + 2 * (w.BY - 1))});
+                            small ? 6 : 2 + (w.BX - 1) + 2 * (w.BY - 1)});
         }
         c_num.push_back(num_item_cost(g, nc, s, tl));
       }
@@ -887,10 +1172,12 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     else
       for (int b = 0; b < g.n_bins; ++b) it_bins.push_back({m, b, 0, 0});
     for (int r = 0; r < g.nyp; ++r) it_maps.push_back({m, r, 0, 0});
-    if (!spherical && !small)
+    if (!spherical && !small && !cadj)
       for (int k = 0; k < g.K; ++k)
         for (int jb = 0; jb < (g.J1 + 3) / 4; ++jb) it_chain.push_back({m, k, jb, 0});
   }
+  close_group();
+  p->cadj_share = order_units(it_cadj, c_cadj, 0);
   if (p->total_bins > INT32_MAX || p->total_lum > INT32_MAX || p->total_mass > INT32_MAX)
     return fail(JAM_E_UNSUPPORTED, "batch too large");
   // prologue of the cylindrical model: a few models run set-up, terms and
@@ -900,7 +1187,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   if (p->fused_prologue)
     for (int m = 0; m < n; ++m) it_pro.push_back({m, 0, 0, 0});
   for (const jam::Item &t : it_terms) it_pro.push_back({t.m, t.a, 0, p->fused_prologue ? 1 : 3});
-  for (const jam::Item &t : it_sb) it_pro.push_back({t.m, t.a, t.b, 2});
+  for (const jam::Item &t : it_sbpro) it_pro.push_back({t.m, t.a, t.b, 2});
   // bin items: the one-bin-per-wave ones first (a launch of 256-thread
   // blocks), then the one-bin-per-block ones (1024-thread blocks)
   std::stable_partition(it_bins.begin(), it_bins.end(), [](const jam::Item &t) { return t.c == 1; });
@@ -910,12 +1197,14 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   sort_by_cost(it_sens, c_sens);
   wide_items(wide_parts, ctx->n_cu, it_sensw);
 
-  constexpr int kLists = 21;
+  constexpr int kLists = 25;
   std::vector<jam::Item> *lists[kLists] = {&it_terms, &it_pix, &it_num, &it_bins,
                                            &it_maps,  &it_chain, &it_sens, &it_sb,
-                                           &it_red,   &it_sph, &it_pro, &it_adj, &it_redf,
+                                           &it_red,   &it_sph, &it_pro, &it_adj,
                                            &it_sensw, &it_sgrid, &it_sgred, &it_sgred6,
-                                           &it_pcot,  &it_pfix,  &it_sgs,  &it_sphm};
+                                           &it_pcot,  &it_pfix,  &it_sgs,  &it_sphm, &it_cpan,
+                                           &it_csum,  &it_cadj,  &it_ctmap, &it_crows};
+  if (it_cmap.size() > (size_t)INT32_MAX) return fail(JAM_E_UNSUPPORTED, "batch too large");
   for (auto *l : lists)
     if (l->size() > (size_t)INT32_MAX) return fail(JAM_E_UNSUPPORTED, "batch too large");
   // one device arena: models then the item lists
@@ -927,7 +1216,11 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     o_it[i] = off;
     off = align256(off + sizeof(jam::Item) * std::max<size_t>(1, lists[i]->size()));
   }
+  const size_t o_cmap = off;
+  off = align256(off + sizeof(jam::ChebItem) * std::max<size_t>(1, it_cmap.size()));
   std::vector<char> stage(off, 0);
+  if (!it_cmap.empty())
+    std::memcpy(stage.data() + o_cmap, it_cmap.data(), sizeof(jam::ChebItem) * it_cmap.size());
   std::memcpy(stage.data() + o_models, md.data(), sizeof(jam::ModelDev) * n);
   for (int i = 0; i < kLists; ++i)
     if (!lists[i]->empty())
@@ -938,21 +1231,25 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->d_models = (jam::ModelDev *)(base + o_models);
   jam::Item **dl[kLists] = {&p->d_terms, &p->d_pix,  &p->d_num, &p->d_bins,
                             &p->d_maps,  &p->d_chain, &p->d_sens, &p->d_sb,
-                            &p->d_red,   &p->d_sph,   &p->d_pro,  &p->d_adj, &p->d_redf,
+                            &p->d_red,   &p->d_sph,   &p->d_pro,  &p->d_adj,
                             &p->d_sensw, &p->d_sgrid, &p->d_sgred, &p->d_sgred6,
-                            &p->d_pcot,  &p->d_pfix,  &p->d_sgs,  &p->d_sphm};
+                            &p->d_pcot,  &p->d_pfix,  &p->d_sgs,  &p->d_sphm, &p->d_cpan,
+                            &p->d_csum,  &p->d_cadj,  &p->d_ctmap, &p->d_crows};
+  p->d_cmap = (jam::ChebItem *)(base + o_cmap);
+  p->n_cmap = (int)it_cmap.size();
   int *cnt[kLists] = {&p->n_terms, &p->n_pix,  &p->n_num, &p->n_bins,
                       &p->n_maps,  &p->n_chain, &p->n_sens, &p->n_sb,
-                      &p->n_red,   &p->n_sph,   &p->n_pro,  &p->n_adj, &p->n_redf,
+                      &p->n_red,   &p->n_sph,   &p->n_pro,  &p->n_adj,
                       &p->n_sensw, &p->n_sgrid, &p->n_sgred, &p->n_sgred6,
-                      &p->n_pcot,  &p->n_pfix,  &p->n_sgs,  &p->n_sphm};
+                      &p->n_pcot,  &p->n_pfix,  &p->n_sgs,  &p->n_sphm, &p->n_cpan,
+                      &p->n_csum,  &p->n_cadj,  &p->n_ctmap, &p->n_crows};
   for (int i = 0; i < kLists; ++i) {
     *dl[i] = (jam::Item *)(base + o_it[i]);
     *cnt[i] = (int)lists[i]->size();
   }
   const int num_wg = p->n_num;   // one workgroup per numerator item
   if (tune.launch == 1) {
-    const int occ = tune.rule == 0 ? ctx->occ_num_pix : (tune.map ? 1 : ctx->occ_num_mfma);
+    const int occ = tune.rule == 0 ? ctx->occ_num_pix : ctx->occ_num_mfma;
     p->grid_num = std::max(1, std::min(num_wg, ctx->n_cu * occ));
     p->grid_sens = std::max(1, std::min(p->n_sens, ctx->n_cu * ctx->occ_sens));
   } else {
@@ -971,6 +1268,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->off_vfwd = w;   w = align256(w + sizeof(double) * p->total_bins);
   p->off_sph = w;    w = align256(w + sizeof(double) * sph);
   p->off_sgrid = w;  w = align256(w + sizeof(float) * sgrid);
+  p->off_cheb = w;   w = align256(w + sizeof(double) * cheb_hmax);
   p->ws_fwd = w;
   p->spherical = spherical;
   p->off_sens = w;   w = align256(w + sizeof(double) * sens);
@@ -979,6 +1277,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->off_sbp = w;    w = align256(w + sizeof(double) * sbp);
   p->off_sgrid6 = w; w = align256(w + sizeof(float) * sgrid6);
   p->off_sgcot = w;  w = align256(w + sizeof(double) * sgcot);
+  p->off_chebt = w;  w = align256(w + sizeof(double) * cheb_t);
   p->ws_vjp = w;
   out = std::move(p);
   return JAM_OK;
@@ -986,6 +1285,27 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
 
 jam::ParamsDev params_of(const jam_batch *b) {
   return jam::ParamsDev{b->inc, b->mass_scale, b->m_bh, b->beta, b->lum_I0, b->mass_S0};
+}
+
+// The numerator kernels of a cylindrical batch, up to the partial maps.
+void launch_numerator(jam_ctx *ctx, Plan *p, char *ws, hipStream_t st) {
+  const int *st_ws = (const int *)(ws + p->off_status);
+  int *queue = p->tune.launch == 1 ? (int *)(ws + p->off_queue) : nullptr;
+  const double *gauss = (const double *)(ws + p->off_gauss);
+  const float4 *terms = (const float4 *)(ws + p->off_terms);
+  double *part = (double *)(ws + p->off_part);
+  double *H = (double *)(ws + p->off_cheb);
+  for (const Plan::ChebGroup &q : p->cheb_groups) {
+    if (q.pan1 > q.pan0)
+      jam::launch_cheb_panel(ctx->d_geoms, p->d_models, p->d_cpan + q.pan0, q.pan1 - q.pan0,
+                             q.pan_share, p->cheb_waves, gauss, st_ws, H, st);
+    if (q.map1 > q.map0)
+      jam::launch_cheb_map(ctx->d_geoms, p->d_models, p->d_cmap + q.map0, q.map1 - q.map0, H, st_ws,
+                           part, st);
+  }
+  if (!p->n_num) return;
+  jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, gauss, st_ws, part, queue,
+                    p->grid_num, p->tune.rule == 1, st);
 }
 
 // Set-up, term table and SB map; optionally the numerator map.  Leaves N and
@@ -1006,7 +1326,8 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
   } else {
     if (!p->fused_prologue)
       jam::launch_setup(ctx->d_geoms, p->d_models, p->n, pd, gauss, st_ws, status, queue, st);
-    jam::launch_prologue(ctx->d_geoms, p->d_models, p->d_pro, p->n_pro, pd, gauss, st_ws, status,
+    if (p->n_pro)
+      jam::launch_prologue(ctx->d_geoms, p->d_models, p->d_pro, p->n_pro, pd, gauss, st_ws, status,
                          queue, terms, pix, p->fused_prologue, st);
   }
   if (p->spherical) {
@@ -1028,17 +1349,13 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
   }
   if (need_numerator) {
     const bool timed = ctx->t_num.begin(st, capturing);
-    if (p->tune.map)
-      jam::launch_num_map(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, st_ws, part,
-                          p->tune.launch == 1 ? queue : nullptr, p->grid_num, st);
-    else
-      jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, gauss, st_ws, part,
-                      p->tune.launch == 1 ? queue : nullptr, p->grid_num, p->tune.rule == 1, st);
+    launch_numerator(ctx, p, ws, st);
     if (timed) ctx->t_num.end(st);
     if (p->n_red) jam::launch_reduce(ctx->d_geoms, p->d_models, p->d_red, p->n_red, part, pix, st);
-    if (p->n_redf)
-      jam::launch_reduce_f32(ctx->d_geoms, p->d_models, p->d_redf, p->n_redf, part, pix, st);
   }
+  if (p->n_csum)
+    jam::launch_cheb_sum(ctx->d_geoms, p->d_models, p->d_csum, p->n_csum, pd,
+                         need_numerator ? part : nullptr, pix, st);
 }
 
 void launch_eval(jam_ctx *ctx, Plan *p, const jam_batch *b, double *vrms2, int32_t *status,
@@ -1129,6 +1446,15 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
     jam::launch_sens_wide(ctx->d_geoms, p->d_models, p->d_sensw, p->n_sensw,
                           (const float4 *)(w + p->off_terms), pix, st_ws, sens, nullptr,
                           p->n_sensw, st);
+  if (p->n_cadj) {
+    double *T = (double *)(w + p->off_chebt);
+    const double *gauss = (const double *)(w + p->off_gauss);
+    if (p->n_ctmap)
+      jam::launch_cheb_tmap(ctx->d_geoms, p->d_models, p->d_ctmap, p->n_ctmap, pix, st_ws, T, st);
+    jam::launch_cheb_adj(ctx->d_geoms, p->d_models, p->d_cadj, p->n_cadj, p->cadj_share,
+                         p->cadj_waves, pd, gauss, st_ws, T, sens, st);
+    jam::launch_cheb_rows(ctx->d_geoms, p->d_models, p->d_crows, p->n_crows, gauss, st_ws, sens, st);
+  }
   if (p->n_adj)
     jam::launch_adj_small(ctx->d_geoms, p->d_models, p->d_adj, p->n_adj, pd, pix, st_ws, sens, st);
   if (timed) ctx->t_sens.end(st);
@@ -1246,18 +1572,7 @@ jam_status autotune(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Tune &best
     for (int rep = 0; rep < 3; ++rep) {
       launch_forward_maps(ctx, p, pd, nullptr, w, st, false, true);
       (void)hipEventRecord(e0, st);
-      if (p->tune.map)
-        jam::launch_num_map(ctx->d_geoms, p->d_models, p->d_num, p->n_num,
-                            (const float4 *)(w + p->off_terms), (const int *)(w + p->off_status),
-                            (double *)(w + p->off_part),
-                            p->tune.launch == 1 ? (int *)(w + p->off_queue) : nullptr,
-                            p->grid_num, st);
-      else
-        jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num,
-                        (const float4 *)(w + p->off_terms), (const double *)(w + p->off_gauss),
-                        (const int *)(w + p->off_status),
-                        (double *)(w + p->off_part), p->tune.launch == 1 ? (int *)(w + p->off_queue) : nullptr,
-                        p->grid_num, p->tune.rule == 1, st);
+      launch_numerator(ctx, p, w, st);
       (void)hipEventRecord(e1, st);
       if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
         cleanup();
@@ -1275,6 +1590,16 @@ jam_status autotune(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Tune &best
   if (e != hipSuccess) return fail(JAM_E_DEVICE, "autotune: %s", hipGetErrorString(e));
   best = plans[best_i]->tune;
   return JAM_OK;
+}
+
+// All maps of seven 32-blocks an axis, few enough for the fixed scratch.
+bool large_maps(const jam_ctx *ctx, int n, const int32_t *geom_idx) {
+  if (n > 40) return false;
+  for (int m = 0; m < n; ++m) {
+    const GeomHost &g = ctx->gh[geom_idx[m]];
+    if ((g.n_ux + 31) / 32 != 7 || (g.n_uy + 31) / 32 != 7) return false;
+  }
+  return ctx->opt.alignment != 1;
 }
 
 jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan *&out) {
@@ -1312,8 +1637,39 @@ jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan 
     }
   }
   std::unique_ptr<Plan> p;
-  const jam_status s = build_plan(ctx, n, geom_idx, t, p);
+  jam_status s = build_plan(ctx, n, geom_idx, t, p);
   if (s != JAM_OK) return s;
+  if (p->n_cheb && p->ws_fwd > kScratchBytes) {
+    // A batch whose direct forms fit the allocation-free entry point's
+    // scratch has to fit it in the compressed form too: with its models in
+    // groups that share the H region if that suffices, else direct.
+    Tune td = t;
+    td.cheb = p->tune.cheb & ~1;
+    std::unique_ptr<Plan> direct;
+    if ((s = build_plan(ctx, n, geom_idx, td, direct)) != JAM_OK) return s;
+    if (direct->ws_fwd <= kScratchBytes) {
+      // closing a group at h_limit leaves it at most one model over
+      const size_t rest = p->off_cheb + 4096;   // the regions before H
+      int64_t big = 0;
+      for (int m = 0; m < n; ++m)
+        if (ctx->gh[geom_idx[m]].cheb_fwd)
+          big = std::max(big, (int64_t)ctx->gh[geom_idx[m]].cheb_h.back() * 512);
+      const int64_t room = rest < kScratchBytes ? (int64_t)((kScratchBytes - rest) / 8) : 0;
+      if (room >= big && (s = build_plan(ctx, n, geom_idx, t, p, room - big)) != JAM_OK) return s;
+      if (p->ws_fwd > kScratchBytes) p = std::move(direct);
+    }
+  }
+  // the same for large maps' tiles, whose partial maps shrink with longer slices
+  for (int gran = p->tune.gran; !p->n_cheb && t.rule == 1 && p->ws_fwd > kScratchBytes &&
+                                gran < (1 << 20) && large_maps(ctx, n, geom_idx);) {
+    Tune tl = p->tune;
+    tl.gran = gran *= 2;
+    std::unique_ptr<Plan> longer;
+    if ((s = build_plan(ctx, n, geom_idx, tl, longer)) != JAM_OK) return s;
+    const bool less = longer->ws_fwd < p->ws_fwd;
+    if (longer->ws_fwd <= kScratchBytes) p = std::move(longer);
+    if (!less) break;
+  }
   out = p.get();
   ctx->plans.push_front(std::move(p));
   while (ctx->plans.size() > kMaxPlans) ctx->plans.pop_back();
@@ -1589,6 +1945,7 @@ jam_status jam_create(int32_t n_geom, const jam_geometry *geoms, const jam_optio
           try {
             build_geometry(geoms[i], ctx->gh[i]);
             build_spherical(ctx->gh[i]);
+            if (ctx->opt.alignment == 0 && ctx->opt.form != 1) build_cheb(ctx->gh[i]);
           } catch (...) {   // out of host memory: reported below, never past the thread
             failed[t] = i;
             return;
@@ -1603,7 +1960,7 @@ jam_status jam_create(int32_t n_geom, const jam_geometry *geoms, const jam_optio
   }
   // device arena: GeomDev array then every geometry's arrays
   size_t off = align256(sizeof(jam::GeomDev) * n_geom);
-  struct Offs { size_t ls, lq, li, ms, mq, mS, u, w, xs, ys, ux, uy, bp, bpix, bw, pp, pb, pw; };
+  struct Offs { size_t ls, lq, li, ms, mq, mS, u, w, xs, ys, ux, uy, bp, bpix, bw, pp, pb, pw, cl, cx, cE, cEk, cGk, cp, ci, ch, cch, cpc, cjp, cjx, cpx, cpy, cux; };
   std::vector<Offs> offs(n_geom);
   auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + std::max<size_t>(bytes, 8)); return o; };
   for (int i = 0; i < n_geom; ++i) {
@@ -1616,6 +1973,13 @@ jam_status jam_create(int32_t n_geom, const jam_geometry *geoms, const jam_optio
     o.ux = take(4 * g.nxp); o.uy = take(4 * g.nyp);
     o.bp = take(4 * g.bin_ptr.size()); o.bpix = take(4 * g.bin_pix.size()); o.bw = take(8 * g.bin_w.size());
     o.pp = take(4 * g.pix_ptr.size()); o.pb = take(4 * g.pix_bin.size()); o.pw = take(8 * g.pix_w.size());
+    o.cl = take(8 * g.cheb_lo.size()); o.cx = take(8 * g.cheb_xi.size());
+    o.cE = take(8 * g.cheb_E.size()); o.cEk = take(8 * g.cheb_Ek.size());
+    o.cGk = take(8 * g.cheb_Gk.size());  o.cp = take(4 * g.cheb_ptr.size());
+    o.ci = take(4 * g.cheb_id.size()); o.ch = take(4 * g.cheb_h.size());
+    o.cch = take(4 * g.cheb_ch.size()); o.cpc = take(4 * g.cheb_pc.size());
+    o.cjp = take(4 * g.cheb_jp.size()); o.cjx = take(4 * g.cheb_jx.size());
+    o.cux = take(2 * g.cheb_ux.size()); o.cpx = take(g.cheb_px.size()); o.cpy = take(g.cheb_py.size());
   }
   std::vector<char> stage(off, 0);
   HIP_TRY(hipMalloc(&ctx->arena, off));
@@ -1651,6 +2015,23 @@ jam_status jam_create(int32_t n_geom, const jam_geometry *geoms, const jam_optio
     d.pix_ptr = (const int *)put(o.pp, g.pix_ptr.data(), 4 * g.pix_ptr.size());
     d.pix_bin = (const int *)put(o.pb, g.pix_bin.data(), 4 * g.pix_bin.size());
     d.pix_w = (const double *)put(o.pw, g.pix_w.data(), 8 * g.pix_w.size());
+    d.cheb_np = g.cheb_np;
+    d.cheb_pieces = g.cheb_pieces;
+    d.cheb_lo = (const double *)put(o.cl, g.cheb_lo.data(), 8 * g.cheb_lo.size());
+    d.cheb_xi = (const double *)put(o.cx, g.cheb_xi.data(), 8 * g.cheb_xi.size());
+    d.cheb_E = (const double *)put(o.cE, g.cheb_E.data(), 8 * g.cheb_E.size());
+    d.cheb_Ek = (const double *)put(o.cEk, g.cheb_Ek.data(), 8 * g.cheb_Ek.size());
+    d.cheb_Gk = (const double *)put(o.cGk, g.cheb_Gk.data(), 8 * g.cheb_Gk.size());
+    d.cheb_ch = (const int *)put(o.cch, g.cheb_ch.data(), 4 * g.cheb_ch.size());
+    d.cheb_pc = (const int *)put(o.cpc, g.cheb_pc.data(), 4 * g.cheb_pc.size());
+    d.cheb_jp = (const int *)put(o.cjp, g.cheb_jp.data(), 4 * g.cheb_jp.size());
+    d.cheb_jx = (const int *)put(o.cjx, g.cheb_jx.data(), 4 * g.cheb_jx.size());
+    d.cheb_ux = (const unsigned short *)put(o.cux, g.cheb_ux.data(), 2 * g.cheb_ux.size());
+    d.cheb_ptr = (const int *)put(o.cp, g.cheb_ptr.data(), 4 * g.cheb_ptr.size());
+    d.cheb_id = (const int *)put(o.ci, g.cheb_id.data(), 4 * g.cheb_id.size());
+    d.cheb_h = (const int *)put(o.ch, g.cheb_h.data(), 4 * g.cheb_h.size());
+    d.cheb_px = (const unsigned char *)put(o.cpx, g.cheb_px.data(), g.cheb_px.size());
+    d.cheb_py = (const unsigned char *)put(o.cpy, g.cheb_py.data(), g.cheb_py.size());
     d.sph_lnr0 = g.sph_lnr0;
     d.sph_dlnr = g.sph_dlnr;
     d.sph_sig_max = g.sph_sig_max;
@@ -2028,11 +2409,11 @@ jam_status jam_plan_info(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, int32
   info[1] = p->tune.tau;
   info[2] = p->tune.gran;
   info[3] = p->tune.launch;
-  info[4] = p->n_num;
-  info[5] = p->grid_num;
-  info[6] = p->n_sens + p->n_sensw + p->n_adj;
-  info[7] = (p->n_sens ? p->grid_sens : 0) + p->n_sensw + p->n_adj;
-  info[8] = p->spherical ? 3 : (p->tune.rule == 0 ? 0 : (p->tune.map ? 2 : 1));
+  info[4] = p->n_num + p->n_cmap;
+  info[5] = (p->n_num || !p->n_cmap ? p->grid_num : 0) + p->n_cmap;
+  info[6] = p->n_sens + p->n_sensw + p->n_adj + p->n_cadj;
+  info[7] = (p->n_sens ? p->grid_sens : 0) + p->n_sensw + p->n_adj + p->n_cadj;
+  info[8] = p->spherical ? 3 : (p->tune.rule == 0 ? 0 : (p->n_cheb == p->n ? 4 : 1));
   return JAM_OK;
 }
 

@@ -36,6 +36,24 @@ struct GeomDev {
   // composite quadratures.
   double sph_lnr0, sph_dlnr, sph_sig_max;
   double gl8_x[8], gl8_w[8];
+  // Compressed cylindrical form (cheb_np = 0: the geometry has none): panels
+  // of v = r_j u_n^2, [cheb_lo[P], cheb_lo[cheb_np + P]); the (j, n) pairs
+  // j << 10 | n sorted by panel and j, panel P's at cheb_ptr[P] ..
+  // cheb_ptr[P + 1], and their Chebyshev variable in the panel; the panels'
+  // node exponentials, rows P * 16 + m: exp(-v_m x^2) and P * 16 + 8 + m: x^2
+  // times it, [cheb_np * 16][32 n_xt], exp(-alpha_k x^2) [K][32 n_xt] and
+  // exp(-gamma0_k y^2) [K][32 n_yt], all zero past the map; how many panels of
+  // tracer k reach 32-wide tile column tx, cheb_px[k * n_xt + tx] (always the
+  // first ones), and tile row ty; per unit u = k * cheb_np + P the tile
+  // columns it reaches, cheb_ux, and the number of preceding (unit, y tile)
+  // blocks, cheb_h [K * cheb_np + 1].  Adjoint: 64-term chunks of the panels
+  // (panel P's from cheb_ch[P]), their runs of equal j ("pieces", chunk c's
+  // from cheb_pc[c]), and mass Gaussian j's pieces cheb_jx[cheb_jp[j] ..].
+  int cheb_np, cheb_pieces;
+  const double *cheb_lo, *cheb_xi, *cheb_E, *cheb_Ek, *cheb_Gk;
+  const int *cheb_ptr, *cheb_id, *cheb_h, *cheb_ch, *cheb_pc, *cheb_jp, *cheb_jx;
+  const unsigned char *cheb_px, *cheb_py;
+  const unsigned short *cheb_ux;
 };
 
 // Spherically aligned model: polar table of kSphNR radii x kSphNT angles on
@@ -63,9 +81,8 @@ struct ModelDev {
                      // stored padded to 32 n_xt x 32 n_yt per slice)
   int form;          // 1 per-pixel VALU, 2 separable MFMA (wave tiles), 3 separable MFMA
                      // on a map of one 32x32 block with terms computed in place (no term
-                     // table), 4 separable MFMA with one workgroup per whole map
+                     // table), 5 compressed (jam_cheb.hip)
   int n_sens_parts;  // partial sensitivity blocks summed by the chain kernel
-  int part_f32;      // 1: the split-term partial maps are FP32 (whole-map numerator)
   int sgrid_slices;  // spherical forward: term slices of the potential grid (0: no grid)
   int64_t gauss_off; // doubles, per-Gaussian derived quantities
   int64_t term_off;  // float4 entries, term table (cylindrical: padded_terms(T) entries,
@@ -81,6 +98,8 @@ struct ModelDev {
                      // [sgrid_slices][kSphGridN][kSphGridN][2] (slice 0 holds the sums)
   int64_t sgrid6_off;// floats, the adjoint's grid [sgrid_slices][kSphGridN][kSphGridN][8]
   int64_t sgcot_off; // doubles, the adjoint's grid cotangent (sph_gcot_size)
+  int64_t cheb_off;  // doubles, H blocks [unit, y tile][16][32] of the compressed form
+  int64_t chebt_off; // doubles, T blocks [unit, y tile][32][16] of its adjoint
 };
 // Entries of a cylindrical model's term table: T rounded up to a multiple of
 // 32, so that kernels reading whole chunks of 32 terms stay inside it.
@@ -120,6 +139,13 @@ struct MgeConst {
 // indices (pixel block, tile, slice, bin, ...).
 struct Item {
   int m, a, b, c;
+};
+
+// Compressed form, a run of units on one 32x32 tile of the map: `count`
+// consecutive (tracer, panel) units that reach the tile, tracer-major, from
+// panel p0 of tracer k0; writes partial tile `slot` of the model.
+struct ChebItem {
+  int m, tile, k0, p0, count, slot;
 };
 
 // Per-model parameters as the caller passed them (device pointers).
@@ -165,22 +191,35 @@ void launch_sb(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, Pa
 void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                 const float4 *terms, const double *gauss, const int *st_ws, double *part,
                 int *queue, int grid, bool mfma, hipStream_t st);
-// Whole-map matrix-core numerator (maps of exactly kMapBlocks x kMapBlocks
-// blocks of 32x32): items (m, 0, slice, 7), one workgroup per item (queue as
-// launch_num); FP32 partial maps.
-constexpr int kMapBlocks = 7;
-void launch_num_map(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                    const float4 *terms, const int *st_ws, double *part, int *queue, int grid,
-                    hipStream_t st);
 int occupancy_num(bool mfma);   // resident numerator workgroups per CU
 int occupancy_sens();   // resident sensitivity workgroups per CU
+// Compressed cylindrical form (jam_cheb.hip), after the set-up: panels
+// (items (m, k, panel), the first n_share with all `waves` (4 or 8) waves of a
+// block each, the others a wave each) into H, the map's tiles, and their sum
+// over slots with the surface brightness (items (m, tile * 4 + quarter, first
+// slot, slots); part = NULL: the surface brightness only).  The adjoint: the
+// lambda contraction over x (items (m, tile row, k)) into T, the terms'
+// sensitivities and chain (items (m, k, panel), every panel), and the chain
+// rows (items (m, k, block of 64 mass Gaussians)).
+constexpr int kChebP = 8;            // Chebyshev nodes per panel
+constexpr double kChebR = 2.0;       // panel width in v, as a ratio
+constexpr int kChebMaxPanels = 64;
+void launch_cheb_panel(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int n_share,
+                       int waves, const double *gauss, const int *st_ws, double *H, hipStream_t st);
+void launch_cheb_map(const GeomDev *g, const ModelDev *m, const ChebItem *it, int n_it,
+                     const double *H, const int *st_ws, double *part, hipStream_t st);
+void launch_cheb_sum(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, ParamsDev p,
+                     const double *part, double *pix, hipStream_t st);
+void launch_cheb_tmap(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                      const double *pix, const int *st_ws, double *T, hipStream_t st);
+void launch_cheb_adj(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int n_share,
+                     int waves, ParamsDev p, const double *gauss, const int *st_ws, const double *T,
+                     double *sens, hipStream_t st);
+void launch_cheb_rows(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                      const double *gauss, const int *st_ws, double *sens, hipStream_t st);
 // Items (m, 64-pixel block).
 void launch_reduce(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                    const double *part, double *pix, hipStream_t st);
-// FP32 partial maps (whole-map numerator): items (m, block of 256 positions
-// of the padded partial layout).
-void launch_reduce_f32(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                       const double *part, double *pix, hipStream_t st);
 // Bin items: the first n_wave are (m, first bin, 1) items of up to 4 bins,
 // one per wave; the rest (m, bin, 0) items of one bin each.
 void launch_bins(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int n_wave,

@@ -21,6 +21,7 @@
 // integrand sums run in FP32 per (k, j) group of u-nodes and are folded into
 // FP64 accumulators; the surface brightness, bin sums and the final division
 // are FP64.
+#include "jam_device.h"
 #include "jam_internal.h"
 
 #include <hip/hip_runtime.h>
@@ -31,15 +32,6 @@
 namespace jam {
 
 namespace {
-
-constexpr double kPi = 3.14159265358979323846;
-constexpr double kLog2e = 1.44269504088896340736;
-// G in pc (km/s)^2 / Msun: IAU nominal GM_sun over (1 pc in m) * 1e6, with
-// 1 pc = 648000/pi au and the IAU au.
-constexpr double kGMsun = 1.3271244e20;
-constexpr double kAu = 149597870700.0;
-
-__device__ inline double grav_const() { return kGMsun / (kAu * 648000.0 / kPi * 1.0e6); }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -66,11 +58,6 @@ __device__ double block_sum256(double v, double *sh) {
   double r = sh[0];
   __syncthreads();
   return r;
-}
-
-__device__ inline double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
 }
 
 // Eight wave sums at once, in a fixed order: three halving exchanges (lanes
@@ -227,26 +214,6 @@ __global__ void __launch_bounds__(256) k_sb_adj(const GeomDev *__restrict__ geom
 // Term table: FP64 coefficients of every (k, j, n) term, stored as FP32
 // (-c1 log2e, -gamma log2e, C0, C1).  Term t = (k * J1 + j) * n_u + n.
 // ---------------------------------------------------------------------------
-// FP64 reciprocal and reciprocal square root: the hardware approximations
-// refined by two Newton steps (a few FP64 ulp; the coefficients they feed are
-// stored as FP32).  Arguments are positive and finite.
-__device__ inline double rcp64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ inline double rsq64(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-x * y, y, 1.0);
-  y = fma(0.5 * y, e, y);
-  e = fma(-x * y, y, 1.0);
-  return fma(0.5 * y, e, y);
-}
-
-constexpr double kSqrtPi = 1.77245385090551602730;
-
 __device__ inline void term_coeffs(double alpha, double alphaq, double nu0, double b, double r,
                                    double e2, double Kp, double si2, double ci2, double u,
                                    double wq, double &c1, double &gam, double &C0, double &C1) {
@@ -763,278 +730,6 @@ __global__ void __launch_bounds__(256, 2) k_num_mfma(const GeomDev *__restrict__
   }
 }
 
-// ---------------------------------------------------------------------------
-// Whole-map matrix-core numerator.  One workgroup of eight waves (two per
-// SIMD) computes one slice of the terms for the model's entire unique-pixel
-// map (n_xt x n_yt = 7 x 7 blocks of 32x32).  Per chunk of 32 terms the 512
-// threads generate the operands of every block once (row i of A =
-// 2^(cx x^2)(C0 + C1 x^2) and column i of B = 2^(cy y^2), thread i % 256
-// for terms 4 (i / 256) .. + 3 of each group of eight) into LDS, double
-// buffered, while the waves run the previous chunk's MFMAs.  Operand rows
-// hold a chunk's 32 terms contiguously (plus 4 floats of padding), so one
-// 16-byte LDS read gives a lane its value for four MFMA steps: in a group of
-// eight terms, half-wave kh supplies term 4 kh + j at step j, in A and B
-// alike (the contraction index is a sum, so any consistent assignment is
-// exact).  Wave w owns the six consecutive row-major blocks 6w .. 6w + 5 and
-// accumulates them over the whole slice in FP32 matrix-core accumulators;
-// the 49th block (6, 6) is shared out by steps (wave w takes steps 2w, 2w + 1
-// of every chunk) and its eight partial sums are added in wave order.  Every
-// SIMD so carries 12.25 blocks, and while one of its waves waits on operand
-// generation the other keeps the matrix core busy.  The slice's partial map
-// is stored in FP32 and the slices are summed in FP64 by k_reduce_f32 in a
-// fixed order.  Term coefficients are read straight from the term table at
-// wave-uniform addresses (scalar loads), a group ahead.  Rows and columns
-// past the map get exact zero operands (exponent offset -inf); terms past T
-// are the table's zero padding.
-// ---------------------------------------------------------------------------
-constexpr int kMapC = 32;                 // terms per chunk
-constexpr int kMapLd = kMapC + 4;         // floats per operand row (a chunk + padding)
-constexpr int kMapWaves = 8;
-constexpr int kMapThreads = 64 * kMapWaves;
-
-struct MapLds {
-  float a[2][256][kMapLd];                // [buffer][x row][term]
-  float b[2][256][kMapLd];                // [buffer][y column][term]
-};
-
-template <int W>
-__device__ __forceinline__ void num_map_item(const Item it, const ModelDev &md, const GeomDev &g,
-                                             const float4 *__restrict__ terms,
-                                             const int *__restrict__ st_ws,
-                                             double *__restrict__ part, MapLds &L) {
-  constexpr int NXB = kMapBlocks, NYB = kMapBlocks, NBLK = NXB * NYB;
-  static_assert(32 * NXB <= 256 && 32 * NYB <= 256, "one operand row per thread");
-  constexpr int NB = (NBLK - 1) / kMapWaves, Q0 = W * NB;            // owned blocks
-  static_assert(NB * kMapWaves == NBLK - 1, "the last block is the shared one");
-  constexpr int BX0 = Q0 / NYB, NR = (Q0 + NB - 1) / NYB - BX0 + 1;   // rows of this wave
-  constexpr bool OWN_LAST_ROW = BX0 + NR == NXB;
-  constexpr int NG = kMapC / 8;                                       // groups per chunk
-  constexpr int SPW = kMapC / 2 / kMapWaves;     // steps of the shared block per wave
-  static_assert(SPW == 2, "a wave's shared steps lie in one group");
-  constexpr int QS = W * SPW / 4;                // the group holding them
-  constexpr int H = W / 4;                       // generates terms 4H .. 4H + 3 of a group
-  const int tid = threadIdx.x, row = tid & 255;
-  const int lane = tid & 63, c32 = lane & 31, kh = lane >> 5;
-  int ts, te;
-  slice_range(g.T, md.n_slices, it.b, ts, te, kMapC);
-  const int n_ch = (st_ws[it.m] == 0) ? (te - ts + kMapC - 1) / kMapC : 0;   // uniform
-  const float4 *tb = terms + md.term_off;
-  // this thread's generated row / column
-  float x2 = 0.f, xoff = -__builtin_inff(), y2 = 0.f, yoff = -__builtin_inff();
-  if (row < g.n_ux) { const double x = g.xs[row]; x2 = (float)(x * x); xoff = 0.f; }
-  if (row < g.n_uy) { const double y = g.ys[row]; y2 = (float)(y * y); yoff = 0.f; }
-  // coefficients of term 8q + 4H + k of chunk ch (only called with n_ch > 0).
-  // Slices end on a multiple of 32 terms or at T, and the table is zero from
-  // T to the next multiple of 32, so a whole chunk is always in the table and
-  // its terms past the slice are zero; the chunk after the last one repeats it.
-  auto coef = [&](int ch, int q, int k) {
-    return tb[ts + min(ch, n_ch - 1) * kMapC + 8 * q + 4 * H + k];
-  };
-  auto gen_a = [&](float4 c) { return fast_exp2(fmaf(c.x, x2, xoff)) * fmaf(c.w, x2, c.z); };
-  auto gen_b = [&](float4 c) { return fast_exp2(fmaf(c.y, y2, yoff)); };
-  const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  v16f acc[NB], acc_s = zero;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) acc[i] = zero;
-  if (n_ch > 0) {
-#pragma unroll
-    for (int q = 0; q < NG; ++q) {
-      float4 c[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) c[k] = coef(0, q, k);
-      const int k4 = 8 * q + 4 * H;
-      *reinterpret_cast<float4 *>(&L.a[0][row][k4]) =
-          make_float4(gen_a(c[0]), gen_a(c[1]), gen_a(c[2]), gen_a(c[3]));
-      *reinterpret_cast<float4 *>(&L.b[0][row][k4]) =
-          make_float4(gen_b(c[0]), gen_b(c[1]), gen_b(c[2]), gen_b(c[3]));
-    }
-  }
-  __syncthreads();
-  for (int ch = 0; ch < n_ch; ++ch) {
-    const int cur = ch & 1, nxt = cur ^ 1;
-    // operands of this wave's block rows (and, in group QS, of the last
-    // row) and of every block column for the eight terms of group q
-    float4 av[2][NR], bv[2][NYB], al[2];
-    auto rd = [&](int u, int q) {
-#pragma unroll
-      for (int r = 0; r < NR; ++r)
-        av[u][r] = *reinterpret_cast<const float4 *>(&L.a[cur][32 * (BX0 + r) + c32][8 * q + 4 * kh]);
-#pragma unroll
-      for (int c = 0; c < NYB; ++c)
-        bv[u][c] = *reinterpret_cast<const float4 *>(&L.b[cur][32 * c + c32][8 * q + 4 * kh]);
-      if (!OWN_LAST_ROW && q == QS)
-        al[u] = *reinterpret_cast<const float4 *>(&L.a[cur][32 * (NXB - 1) + c32][8 * q + 4 * kh]);
-    };
-    // coefficients of the next chunk's group (after the last chunk, the last
-    // chunk's again: what they generate is never read)
-    float4 cq[4], cn[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) cq[k] = coef(ch + 1, 0, k);
-    rd(0, 0);
-#pragma unroll
-    for (int q = 0; q < NG; ++q) {
-      const int u = q & 1;
-      // the next group's reads and coefficients go out before this group's
-      // MFMAs; the scheduling barriers keep them there
-      if (q + 1 < NG) {
-        rd(u ^ 1, q + 1);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) cn[k] = coef(ch + 1, q + 1, k);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      float ga[4], gb[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const float4 &xa = av[u][(Q0 + i) / NYB - BX0];
-          const float4 &yb = bv[u][(Q0 + i) % NYB];
-          const float fa = j == 0 ? xa.x : j == 1 ? xa.y : j == 2 ? xa.z : xa.w;
-          const float fb = j == 0 ? yb.x : j == 1 ? yb.y : j == 2 ? yb.z : yb.w;
-          acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb, acc[i], 0, 0, 0);
-        }
-        if ((4 * q + j) / SPW == W) {              // this wave's steps of the shared block
-          const float4 &xa = OWN_LAST_ROW ? av[u][NR - 1] : al[u];
-          const float4 &yb = bv[u][NYB - 1];
-          const float fa = j == 0 ? xa.x : j == 1 ? xa.y : j == 2 ? xa.z : xa.w;
-          const float fb = j == 0 ? yb.x : j == 1 ? yb.y : j == 2 ? yb.z : yb.w;
-          acc_s = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb, acc_s, 0, 0, 0);
-        }
-        // one term of the next chunk's group q beside the MFMAs
-        ga[j] = gen_a(cq[j]);
-        gb[j] = gen_b(cq[j]);
-      }
-      const int k4 = 8 * q + 4 * H;
-      *reinterpret_cast<float4 *>(&L.a[nxt][row][k4]) = make_float4(ga[0], ga[1], ga[2], ga[3]);
-      *reinterpret_cast<float4 *>(&L.b[nxt][row][k4]) = make_float4(gb[0], gb[1], gb[2], gb[3]);
-      __builtin_amdgcn_sched_barrier(0);
-      if (q + 1 < NG) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) cq[k] = cn[k];
-      }
-    }
-    __syncthreads();
-  }
-  // FP32 partial map of the slice, padded and transposed as k_reduce_f32 reads it
-  float *pf = reinterpret_cast<float *>(part + md.part_off) + it.b * part_slice_size(md);
-  const int ldh = 32 * NYB;
-  auto store = [&](int blk, const v16f &v) {
-    float *o = pf + (int64_t)(32 * (blk / NYB) + 4 * kh) * ldh + 32 * (blk % NYB) + c32;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[(int64_t)((r & 3) + 8 * (r >> 2)) * ldh] = v[r];
-  };
-#pragma unroll
-  for (int i = 0; i < NB; ++i) store(Q0 + i, acc[i]);
-  // the shared block: the eight waves' partial sums in wave order (the
-  // operand buffers are free after the last chunk's barrier)
-  float *red = &L.a[0][0][0];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) red[(W * 16 + r) * 64 + lane] = acc_s[r];
-  __syncthreads();
-  if (W == kMapWaves - 1) {
-    v16f s = zero;
-#pragma unroll
-    for (int w = 0; w < kMapWaves; ++w)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] += red[(w * 16 + r) * 64 + lane];
-    store(NBLK - 1, s);
-  }
-}
-
-__global__ void __launch_bounds__(kMapThreads, 1) k_num_map(const GeomDev *__restrict__ geoms,
-                                                           const ModelDev *__restrict__ models,
-                                                           const Item *__restrict__ items, int n_it,
-                                                           const float4 *__restrict__ terms,
-                                                           const int *__restrict__ st_ws,
-                                                           double *__restrict__ part, int *queue) {
-  __shared__ __attribute__((aligned(16))) MapLds L;
-  __shared__ int next;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int i = blockIdx.x;
-  for (;;) {
-    if (queue) {
-      if (threadIdx.x == 0) next = atomicAdd(queue, 1);
-      __syncthreads();
-      i = __builtin_amdgcn_readfirstlane(next);
-      __syncthreads();
-    }
-    if (i >= n_it) break;
-    const Item it = items[i];
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    // the map shape is 7 x 7 blocks (checked on the host)
-    switch (wave) {
-      case 0: num_map_item<0>(it, md, g, terms, st_ws, part, L); break;
-      case 1: num_map_item<1>(it, md, g, terms, st_ws, part, L); break;
-      case 2: num_map_item<2>(it, md, g, terms, st_ws, part, L); break;
-      case 3: num_map_item<3>(it, md, g, terms, st_ws, part, L); break;
-      case 4: num_map_item<4>(it, md, g, terms, st_ws, part, L); break;
-      case 5: num_map_item<5>(it, md, g, terms, st_ws, part, L); break;
-      case 6: num_map_item<6>(it, md, g, terms, st_ws, part, L); break;
-      default: num_map_item<7>(it, md, g, terms, st_ws, part, L); break;
-    }
-    __syncthreads();
-    if (!queue) i += gridDim.x;
-  }
-}
-
-// Sum FP32 split-term partial maps (whole-map numerator) in FP64, in a fixed
-// order, into the N map.  Item (m, block of 256 consecutive positions of the
-// padded partial layout, x * 32 n_yt + y): lane l holds positions 4l..4l+3
-// (one float4 per slice), wave w of 8 takes slices w, w + 8, ... in order
-// with 16 loads in flight, and the eight waves' sums are added in wave order.
-__global__ void __launch_bounds__(512) k_reduce_f32(const GeomDev *__restrict__ geoms,
-                                                    const ModelDev *__restrict__ models,
-                                                    const Item *__restrict__ items, int n_it,
-                                                    const double *__restrict__ part,
-                                                    double *__restrict__ pix) {
-  __shared__ double red[8][256];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    const int ldh = 32 * md.n_yt;
-    const int p0 = it.a * 256 + 4 * lane;
-    const bool valid = p0 < g.n_ux * ldh;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (valid) {
-      const float *pp = reinterpret_cast<const float *>(part + md.part_off) + p0;
-      const int64_t stride = part_slice_size(md);
-      for (int s0 = wave; s0 < md.n_slices; s0 += 8 * 16) {
-        float4 v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const int sl = s0 + 8 * k;
-          v[k] = sl < md.n_slices ? *reinterpret_cast<const float4 *>(pp + sl * stride)
-                                  : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          acc[0] += (double)v[k].x;
-          acc[1] += (double)v[k].y;
-          acc[2] += (double)v[k].z;
-          acc[3] += (double)v[k].w;
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) red[wave][4 * lane + c] = acc[c];
-    __syncthreads();
-    if (threadIdx.x < 256) {
-      const int q = it.a * 256 + threadIdx.x;
-      const int x = q / ldh, y = q % ldh;
-      if (x < g.n_ux && y < g.n_uy) {
-        double v = red[0][threadIdx.x];
-        for (int w = 1; w < 8; ++w) v += red[w][threadIdx.x];
-        pix[md.pix_off + (int64_t)y * g.n_ux + x] = v;
-      }
-    }
-    __syncthreads();
-  }
-}
-
 // Sum the split-term partials in a fixed order into the N map.  Item
 // (m, block of 64 pixels in the partial maps' order, y fastest); the four
 // waves take every fourth slice and their sums are combined in a fixed order.
@@ -1058,30 +753,16 @@ __global__ void __launch_bounds__(256) k_reduce(const GeomDev *__restrict__ geom
       const int64_t off = (int64_t)x * (32 * md.n_yt) + y;
       const int64_t stride = part_slice_size(md);
       // eight slices' loads in flight, added in slice order
-      if (md.part_f32) {
-        const float *pp = reinterpret_cast<const float *>(part + md.part_off) + off;
-        for (int s0 = wave; s0 < md.n_slices; s0 += 32) {
-          double v[8];
+      const double *pp = part + md.part_off + off;
+      for (int s0 = wave; s0 < md.n_slices; s0 += 32) {
+        double v[8];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int s = s0 + 4 * k;
-            v[k] = s < md.n_slices ? (double)pp[s * stride] : 0.0;
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) acc += v[k];
+        for (int k = 0; k < 8; ++k) {
+          const int s = s0 + 4 * k;
+          v[k] = s < md.n_slices ? pp[s * stride] : 0.0;
         }
-      } else {
-        const double *pp = part + md.part_off + off;
-        for (int s0 = wave; s0 < md.n_slices; s0 += 32) {
-          double v[8];
 #pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const int s = s0 + 4 * k;
-            v[k] = s < md.n_slices ? pp[s * stride] : 0.0;
-          }
-#pragma unroll
-          for (int k = 0; k < 8; ++k) acc += v[k];
-        }
+        for (int k = 0; k < 8; ++k) acc += v[k];
       }
     }
     if (wave > 0) red[wave - 1][lane] = acc;
@@ -4417,17 +4098,6 @@ void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
   else
     hipLaunchKernelGGL(k_num_pix, dim3(grid_of(grid)), dim3(256), 0, st, g, m, it, n_it, terms,
                        st_ws, part, queue);
-}
-void launch_num_map(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                    const float4 *terms, const int *st_ws, double *part, int *queue, int grid,
-                    hipStream_t st) {
-  hipLaunchKernelGGL(k_num_map, dim3(grid_of(grid)), dim3(kMapThreads), 0, st, g, m, it, n_it,
-                     terms, st_ws, part, queue);
-}
-void launch_reduce_f32(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                       const double *part, double *pix, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_f32, dim3(grid_of(n_it)), dim3(512), 0, st, g, m, it, n_it, part,
-                     pix);
 }
 void launch_reduce(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                    const double *part, double *pix, hipStream_t st) {

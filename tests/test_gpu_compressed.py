@@ -1,0 +1,170 @@
+"""The compressed cylindrical form (terms interpolated onto Chebyshev nodes of
+their exponents, all FP64) against the FP64 oracle, forward and adjoint, where
+it can go wrong: tile edges, off-centre and elongated fields, more than 256
+columns, the widest node sets (inclination at the deprojection limit), the
+black hole alone, tracers whose light ends inside the field, a batch mixed
+with the other forms.
+
+Bars: the interpolants of one term are within 2 rho^-8, rho = 9 (eight nodes
+an octave in v: exp(-z e^s) is bounded by 1 for |Im s| < pi / 2), about 5e-8 of
+the term, with alternating signs over the terms; V per bin within 1e-7, the
+gradient in norm within 1e-7 (the FP32 forms are held to 1e-5 and 1e-4)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import jam as ojam
+from paper_2504_01302_amd import binding, inputs
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("inc", "beta", "mass_scale", "m_bh", "lum_I0", "mass_S0")
+
+
+def _dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+# name: geometry sizes, inclination as cos i = q_min - margin (None: drawn)
+CASES = {
+    "33x33": (dict(n_lum=2, n_mass=13, nx=64, ny=64, n_u=160, pixsize=0.05, psf_n=3), None),
+    "32x129": (dict(n_lum=2, n_mass=14, nx=62, ny=256, n_u=160, pixsize=0.05, psf_n=3), None),
+    "off_centre": (dict(n_lum=2, n_mass=13, nx=70, ny=41, n_u=150, pixsize=0.04, psf_n=3,
+                        xc=0.013, yc=-0.007), None),
+    "off_the_galaxy": (dict(n_lum=3, n_mass=13, nx=40, ny=66, n_u=150, pixsize=0.04, psf_n=1,
+                            xc=2.5, yc=1.1), None),
+    "over_256_columns": (dict(n_lum=2, n_mass=13, nx=290, ny=35, n_u=160, pixsize=0.03, psf_n=3,
+                              xc=0.011), None),
+    "black_hole_alone": (dict(n_lum=3, n_mass=0, nx=140, ny=140, n_u=1024, pixsize=0.05, psf_n=3), None),
+    "limit_1e-2": (dict(n_lum=3, n_mass=13, nx=66, ny=70, n_u=160, pixsize=0.05, psf_n=3), 1e-2),
+    "limit_1e-4": (dict(n_lum=3, n_mass=13, nx=66, ny=70, n_u=160, pixsize=0.05, psf_n=3), 1e-4),
+    "limit_1e-8": (dict(n_lum=3, n_mass=13, nx=66, ny=70, n_u=160, pixsize=0.05, psf_n=3), 1e-8),
+}
+
+
+def _model(name, seed=0):
+    kw, margin = CASES[name]
+    g = inputs.small_geometry(seed=300 + seed, n_bins=5, **kw)
+    p = inputs.small_params(g, seed=400 + seed)
+    if margin is not None:
+        q = float(np.concatenate([g.lum_q, g.mass_q]).min())
+        p = inputs.with_overrides(p, inc=float(np.arccos(q - margin)))
+    return g, p
+
+
+def _run(g, p, cot, dev, n=1000):
+    """The model as the last of a batch of n copies with other black holes (a
+    batch large enough for the compressed form to be chosen)."""
+    ps = [inputs.with_overrides(p, m_bh=p.m_bh * (1.0 + 0.001 * (n - 1 - m))) for m in range(n)]
+    w = inputs.Workload("compressed", [g], np.zeros(n, np.int32), ps)
+    ctx = binding.Context([g])
+    kernel = ctx.plan_info(w.geom_idx)["num_kernel"]
+    t = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, t["inc"], t["mass_scale"], t["m_bh"], t["beta"], t["lum_I0"], t["mass_S0"])
+    V, st = ctx.eval_batch(*args)
+    cot = torch.as_tensor(np.tile(cot, n), device=dev)
+    gr = ctx.vjp(*args, V, cot)
+    gr2 = ctx.vjp(*args, None, cot)         # V recomputed inside
+    torch.cuda.synchronize()
+    assert np.all(st.cpu().numpy() == 0)
+    for k in KEYS:
+        assert torch.equal(gr[k], gr2[k]), k
+    out = V.cpu().numpy()[-g.n_bins:], {k: v.cpu().numpy()[len(v) // n * (n - 1):]
+                                        for k, v in gr.items()}, kernel
+    ctx.close()
+    return out
+
+
+def _check(name, g, p, cot, V, grad):
+    ref, gref = ojam.vrms2_and_grad(g, p, cot)
+    rel = np.max(np.abs(V / ref.numpy() - 1))
+    a = np.concatenate([np.atleast_1d(grad[k]) for k in KEYS])
+    b = np.concatenate([np.atleast_1d(gref[k].numpy()) for k in KEYS])
+    gerr = np.linalg.norm(a - b) / np.linalg.norm(b)
+    print(f"{name}: V {rel:.2e}, gradient {gerr:.2e}")
+    assert rel <= 1e-7 and gerr <= 1e-7
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_compressed_matches_oracle(name):
+    dev = _dev()
+    g, p = _model(name)
+    cot = np.random.default_rng(5).standard_normal(g.n_bins)
+    V, grad, kernel = _run(g, p, cot, dev)
+    assert kernel == 4
+    _check(name, g, p, cot, V, grad)
+
+
+def test_compact_light_on_a_wide_field():
+    """Tracers that end inside the field (units that reach no outer tile), with
+    a wide one that carries the outer bins."""
+    dev = _dev()
+    g, p = _model("33x33", seed=1)
+    g.lum_sigma[:] = (0.02, 1.5)
+    cot = np.random.default_rng(6).standard_normal(g.n_bins)
+    V, grad, kernel = _run(g, p, cot, dev)
+    assert kernel == 4
+    _check("compact light", g, p, cot, V, grad)
+
+
+def test_mixed_batch_and_invalid_model():
+    """Compressed, small-map and invalid models in one batch: each as it is
+    alone; the invalid one NaN."""
+    dev = _dev()
+    a, pa = _model("off_centre")
+    b, pb = _model("33x33")
+    c = inputs.small_geometry(seed=9)
+    pc = inputs.small_params(c, seed=9)
+    bad = inputs.with_overrides(pb, inc=0.2)
+    n = 600
+    gs, gi, ps = [a, b, c], [0, 1, 2, 1] * n, [pa, pb, pc, bad] * n
+    rng = np.random.default_rng(7)
+    cots = [rng.standard_normal(gs[i].n_bins) for i in gi]
+    w = inputs.Workload("mixed", gs, np.asarray(gi, np.int32), ps)
+    ctx = binding.Context(gs)
+    t = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, t["inc"], t["mass_scale"], t["m_bh"], t["beta"], t["lum_I0"], t["mass_S0"])
+    V, st = ctx.eval_batch(*args)
+    g = ctx.vjp(*args, V, torch.as_tensor(np.concatenate(cots), device=dev))
+    torch.cuda.synchronize()
+    assert st.cpu().tolist() == [0, 0, 0, 2] * n
+    V = V.cpu().numpy()
+    nb = [gs[i].n_bins for i in gi]
+    o = np.cumsum([0] + nb)
+    assert np.all(np.isnan(V[o[3]:o[4]])) and np.isnan(g["inc"][3].item())
+    ol = np.cumsum([0] + [gs[i].n_lum for i in gi])
+    om = np.cumsum([0] + [gs[i].n_mass for i in gi])
+    for m in range(2):
+        gm = dict(inc=g["inc"][m].item(), mass_scale=g["mass_scale"][m].item(),
+                  m_bh=g["m_bh"][m].item(), beta=g["beta"][ol[m]:ol[m + 1]].cpu().numpy(),
+                  lum_I0=g["lum_I0"][ol[m]:ol[m + 1]].cpu().numpy(),
+                  mass_S0=g["mass_S0"][om[m]:om[m + 1]].cpu().numpy())
+        _check(f"model {m}", gs[gi[m]], ps[m], cots[m], V[o[m]:o[m + 1]], gm)
+    ctx.close()
+
+
+def test_noalloc_takes_what_the_direct_forms_fit():
+    """A composition whose direct forms fit the allocation-free entry point's
+    scratch stays accepted by it: the compressed models then share their
+    workspace in groups, with the same results bit for bit."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=320, n_lum=20, n_mass=9, nx=70, ny=41, n_u=120, pixsize=0.04,
+                              psf_n=3, n_bins=5, xc=0.013, yc=-0.007)
+    n = 36
+    ps = [inputs.small_params(g, seed=500 + m) for m in range(n)]
+    w = inputs.Workload("many", [g], np.zeros(n, np.int32), ps)
+    ctx = binding.Context([g])
+    t = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, t["inc"], t["mass_scale"], t["m_bh"], t["beta"], t["lum_I0"], t["mass_S0"])
+    V, st = ctx.eval_batch(*args)
+    assert ctx.plan_info(w.geom_idx)["num_kernel"] == 4
+    ws = binding.jam_workspace_size(ctx.handle, w.geom_idx, False)
+    assert 40 << 20 < ws <= 64 << 20
+    V2, st2 = torch.full_like(V, float("nan")), torch.empty_like(st)
+    binding.jam_eval_batch_noalloc(ctx.handle, *args, V2, st2,
+                                   torch.cuda.current_stream(dev).cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(V, V2) and torch.equal(st, st2)
+    ctx.close()
