@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(HERE, "libjam.so")
 
-SOURCES = ["jam_host.cpp", "jam_kernels.hip", "jam_cheb.hip"]
+SOURCES = ["jam_host.cpp", "jam_kernels.hip", "jam_cheb.hip", "jam_polar.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -502,8 +502,8 @@ struct Plan {
             *d_maps = nullptr, *d_chain = nullptr, *d_sens = nullptr, *d_sb = nullptr,
             *d_red = nullptr, *d_sph = nullptr, *d_pro = nullptr, *d_adj = nullptr,
             *d_sensw = nullptr, *d_sgrid = nullptr, *d_sgred = nullptr,
-            *d_sgred6 = nullptr, *d_pcot = nullptr, *d_pfix = nullptr, *d_sgs = nullptr,
-            *d_sphm = nullptr, *d_cpan = nullptr, *d_csum = nullptr, *d_cadj = nullptr,
+            *d_sgred3 = nullptr, *d_pcot = nullptr, *d_pfix = nullptr, *d_sgs = nullptr,
+            *d_sphm = nullptr, *d_ptab = nullptr, *d_srow = nullptr, *d_cpan = nullptr, *d_csum = nullptr, *d_cadj = nullptr,
             *d_ctmap = nullptr, *d_crows = nullptr;
   jam::ChebItem *d_cmap = nullptr;
   // compressed forward: models taken together, [first, end) of their items
@@ -513,7 +513,7 @@ struct Plan {
   std::vector<ChebGroup> cheb_groups;
   int n_terms = 0, n_pix = 0, n_num = 0, n_bins = 0, n_maps = 0, n_chain = 0, n_sens = 0,
       n_sb = 0, n_red = 0, n_sph = 0, n_pro = 0, n_adj = 0, n_sensw = 0,
-      n_sgrid = 0, n_sgred = 0, n_sgred6 = 0, n_pcot = 0, n_pfix = 0, n_sgs = 0, n_sphm = 0,
+      n_sgrid = 0, n_sgred = 0, n_sgred3 = 0, n_pcot = 0, n_pfix = 0, n_sgs = 0, n_sphm = 0, n_ptab = 0, n_srow = 0,
       n_cpan = 0, n_csum = 0, n_cadj = 0, n_cmap = 0, n_ctmap = 0, n_crows = 0;
   int cadj_share = 0, cheb_waves = 4, cadj_waves = 4;   // shared adjoint items, waves per block
   int n_cheb = 0;        // models of the compressed form
@@ -524,7 +524,7 @@ struct Plan {
   int64_t total_bins = 0, total_lum = 0, total_mass = 0, total_map = 0;
   // workspace regions (bytes)
   size_t off_status = 0, off_queue = 0, off_gauss = 0, off_terms = 0, off_pix = 0, off_part = 0,
-         off_bins = 0, off_vfwd = 0, off_sph = 0, off_sgrid = 0, off_sgrid6 = 0, off_sgcot = 0,
+         off_bins = 0, off_vfwd = 0, off_sph = 0, off_sgrid = 0, off_sgrid3 = 0, off_sgcot = 0, off_pol = 0,
          off_sens = 0,
          off_vtmp = 0,
          off_cot = 0,
@@ -908,15 +908,15 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   const Tune &tune = p->tune;
   std::vector<jam::ModelDev> md(n);
   std::vector<jam::Item> it_terms, it_pix, it_num, it_bins, it_maps, it_chain, it_sens, it_sb,
-      it_red, it_sph, it_pro, it_adj, it_sensw, it_sgrid, it_sgred, it_sgred6, it_pcot,
-      it_pfix, it_sgs, it_sphm, it_cpan, it_csum, it_cadj, it_ctmap, it_crows, it_sbpro;
+      it_red, it_sph, it_pro, it_adj, it_sensw, it_sgrid, it_sgred, it_sgred3, it_pcot,
+      it_pfix, it_sgs, it_sphm, it_ptab, it_srow, it_cpan, it_csum, it_cadj, it_ctmap, it_crows, it_sbpro;
   std::vector<jam::ChebItem> it_cmap;
   std::vector<double> c_num, c_sens, c_sensw;
   // wide-sensitivity parts (model, part, x tiles, 32-term groups); their
   // items are cut after the model loop (wide_items)
   std::vector<WidePart> wide_parts;
   int64_t gauss = 0, terms = 0, pixd = 0, part = 0, bins = 0, sens = 0, sph = 0, sbp = 0,
-          sgrid = 0, sgrid6 = 0, sgcot = 0;
+          sgrid = 0, sgrid3 = 0, sgcot = 0, pol = 0;
   const bool spherical = ctx->opt.alignment == 1;
   // compressed form: units per map item, two items per compute unit where
   // the batch is small enough (a unit on a tile is 16 FP64 MFMAs of a wave)
@@ -1012,35 +1012,37 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     sbp += (int64_t)g.K * jam::sb_tiles(g.n_ux, g.n_uy);
     if (spherical) {
       sph += (int64_t)jam::kSphNR * jam::kSphNT * 3;
-      for (int q = 0; q < jam::kSphNR * jam::kSphNT; ++q) it_sph.push_back({m, q, 0, 0});
-      // forward moments: four table points per item (a wave each)
-      for (int q = 0; q < jam::kSphNR * jam::kSphNT / 4; ++q) it_sphm.push_back({m, q, 0, 0});
+      if (!use_sgrid)
+        for (int q = 0; q < jam::kSphCells; ++q) it_sph.push_back({m, q, 0, 0});
+      for (int q = 0; q < jam::kSphCells / 64; ++q) it_srow.push_back({m, q, 0, 0});
+      // moments at the nodes: four table points (a wave each)
+      if (!use_sgrid)
+        for (int q = 0; q < jam::kSphCells / 4; ++q) it_sphm.push_back({m, q, 0, 0});
     }
     if (use_sgrid) {
-      // forward grid: 2 floats per point; the adjoint's: 8
-      const int64_t nn2 = 2 * (int64_t)jam::kSphGridN * jam::kSphGridN;
-      const int64_t nn8 = 4 * nn2;
-      // term slices of at least ten 64-term chunks, at most eight (a
-      // property of the model alone, so that its grid, and everything
-      // computed from it, is the same in any batch)
-      const int sl = std::max(1, std::min(8, jam::sph_terms_padded(g.J1, g.n_u) / 640));
+      const int64_t pts = (int64_t)jam::kPolN * jam::kPolC;
+      const int sl = jam::pol_slices(jam::sph_terms_padded(g.J1, g.n_u));
       d.sgrid_slices = sl;
       d.sgrid_off = sgrid;
-      d.sgrid6_off = sgrid6;
-      sgrid += sl * nn2;
-      sgrid6 += sl * nn8;
-      for (int tile = 0; tile < jam::kSphGridTiles; ++tile)
-        for (int q = 0; q < sl; ++q) it_sgrid.push_back({m, tile, q, 0});
+      d.sgrid3_off = sgrid3;
+      d.pol_off = pol;
+      sgrid += sl * 2 * pts;
+      sgrid3 += sl * 3 * pts;
+      pol += jam::pol_size(g.K);
+      for (int q = 0; q < jam::pol_groups(g.K) * jam::kSphNR / 4; ++q) it_sphm.push_back({m, q, 0, 0});
+      for (int q = 0; q < jam::kSphCells / 16; ++q) it_ptab.push_back({m, q, 0, 0});
+      for (int row = 0; row < jam::kPolN / 4; ++row)
+        for (int q = 0; q < sl; ++q) it_sgrid.push_back({m, row, q, 0});
       if (sl > 1) {
-        for (int64_t bq = 0; bq < (nn2 + 1023) / 1024; ++bq) it_sgred.push_back({m, (int)bq, 0, 0});
-        for (int64_t bq = 0; bq < (nn8 + 1023) / 1024; ++bq) it_sgred6.push_back({m, (int)bq, 0, 0});
+        for (int b = 0; b < 2 * pts / 1024; ++b) it_sgred.push_back({m, b, 0, 0});
+        for (int b = 0; b < 3 * pts / 1024; ++b) it_sgred3.push_back({m, b, 0, 0});
       }
     }
     gauss += jam::gauss_size(g.K, g.J1);
     const int tsph = jam::sph_terms_padded(g.J1, g.n_u);
     // spherical: float4 terms, then floats; small maps compute their terms in
     // place; cylindrical tables are zero-padded to a multiple of 32 terms
-    terms += spherical ? tsph + tsph / 4 : (small || (cheb && cadj) ? 0 : jam::padded_terms(g.T));
+    terms += spherical ? tsph + (use_sgrid ? tsph / 2 : tsph / 4) : (small || (cheb && cadj) ? 0 : jam::padded_terms(g.T));
     pixd += 4 * (int64_t)g.n_pix;
     // padded to whole blocks
     part += (int64_t)d.n_slices * (32 * d.n_xt) * (32 * d.n_yt);
@@ -1098,7 +1100,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     if (spherical) {
       // term sensitivities: point ranges, or (with the potential grid) parts
       // of the grid rows
-      d.n_sens_parts = use_sgrid ? jam::kSphIParts : jam::sph_ranges(g.K);
+      d.n_sens_parts = use_sgrid ? jam::kPolParts : jam::sph_ranges(g.K);
       sens += jam::sph_adj_size(g.K, g.n_pix, tsph, d.n_sens_parts);
     } else {
       sens += 3 * (int64_t)d.n_sens_parts * g.T + (int64_t)g.K * 3 * g.J1 +
@@ -1113,11 +1115,14 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
         it_terms.push_back({m, tb, 0, 0});
     if (spherical && use_sgrid) {
       d.sgcot_off = sgcot;
-      sgcot += jam::sph_gcot_size(g.K);
-      for (int q = 0; q < jam::sph_pitems(g.K); ++q) it_pcot.push_back({m, q, 0, 0});
-      for (int b = 0; b < jam::kSphGridN * jam::kSphGridN / 1024; ++b) it_pfix.push_back({m, b, 0, 0});
-      for (int tb = 0; tb < tsph / 32; ++tb)
-        for (int ip = 0; ip < jam::kSphIParts; ++ip) it_sgs.push_back({m, tb, ip, 0});
+      sgcot += jam::pol_cot_size(g.K);
+      // from the outer rows in: they hold more nodes (the rules of all radii
+      // inside reach them), and the short items then fill the tail
+      for (int b = jam::kPolBins - 1; b >= 0; --b)
+        for (int q = 0; q < jam::pol_cot_groups(g.K); ++q) it_pcot.push_back({m, b, q, 0});
+      for (int b = 0; b < jam::kPolN * jam::kPolC / 256; ++b) it_pfix.push_back({m, b, 0, 0});
+      for (int tb = 0; tb < (tsph + 511) / 512; ++tb)
+        for (int ip = 0; ip < jam::kPolParts; ++ip) it_sgs.push_back({m, tb, ip, 0});
     } else if (spherical) {
       for (int tt = 0; tt < (tsph + 255) / 256; ++tt)
         for (int r = 0; r < d.n_sens_parts; ++r) {
@@ -1197,12 +1202,12 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   sort_by_cost(it_sens, c_sens);
   wide_items(wide_parts, ctx->n_cu, it_sensw);
 
-  constexpr int kLists = 25;
+  constexpr int kLists = 27;
   std::vector<jam::Item> *lists[kLists] = {&it_terms, &it_pix, &it_num, &it_bins,
                                            &it_maps,  &it_chain, &it_sens, &it_sb,
                                            &it_red,   &it_sph, &it_pro, &it_adj,
-                                           &it_sensw, &it_sgrid, &it_sgred, &it_sgred6,
-                                           &it_pcot,  &it_pfix,  &it_sgs,  &it_sphm, &it_cpan,
+                                           &it_sensw, &it_sgrid, &it_sgred, &it_sgred3,
+                                           &it_pcot,  &it_pfix,  &it_sgs,  &it_sphm, &it_ptab, &it_srow, &it_cpan,
                                            &it_csum,  &it_cadj,  &it_ctmap, &it_crows};
   if (it_cmap.size() > (size_t)INT32_MAX) return fail(JAM_E_UNSUPPORTED, "batch too large");
   for (auto *l : lists)
@@ -1232,16 +1237,16 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   jam::Item **dl[kLists] = {&p->d_terms, &p->d_pix,  &p->d_num, &p->d_bins,
                             &p->d_maps,  &p->d_chain, &p->d_sens, &p->d_sb,
                             &p->d_red,   &p->d_sph,   &p->d_pro,  &p->d_adj,
-                            &p->d_sensw, &p->d_sgrid, &p->d_sgred, &p->d_sgred6,
-                            &p->d_pcot,  &p->d_pfix,  &p->d_sgs,  &p->d_sphm, &p->d_cpan,
+                            &p->d_sensw, &p->d_sgrid, &p->d_sgred, &p->d_sgred3,
+                            &p->d_pcot,  &p->d_pfix,  &p->d_sgs,  &p->d_sphm, &p->d_ptab, &p->d_srow, &p->d_cpan,
                             &p->d_csum,  &p->d_cadj,  &p->d_ctmap, &p->d_crows};
   p->d_cmap = (jam::ChebItem *)(base + o_cmap);
   p->n_cmap = (int)it_cmap.size();
   int *cnt[kLists] = {&p->n_terms, &p->n_pix,  &p->n_num, &p->n_bins,
                       &p->n_maps,  &p->n_chain, &p->n_sens, &p->n_sb,
                       &p->n_red,   &p->n_sph,   &p->n_pro,  &p->n_adj,
-                      &p->n_sensw, &p->n_sgrid, &p->n_sgred, &p->n_sgred6,
-                      &p->n_pcot,  &p->n_pfix,  &p->n_sgs,  &p->n_sphm, &p->n_cpan,
+                      &p->n_sensw, &p->n_sgrid, &p->n_sgred, &p->n_sgred3,
+                      &p->n_pcot,  &p->n_pfix,  &p->n_sgs,  &p->n_sphm, &p->n_ptab, &p->n_srow, &p->n_cpan,
                       &p->n_csum,  &p->n_cadj,  &p->n_ctmap, &p->n_crows};
   for (int i = 0; i < kLists; ++i) {
     *dl[i] = (jam::Item *)(base + o_it[i]);
@@ -1268,6 +1273,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->off_vfwd = w;   w = align256(w + sizeof(double) * p->total_bins);
   p->off_sph = w;    w = align256(w + sizeof(double) * sph);
   p->off_sgrid = w;  w = align256(w + sizeof(float) * sgrid);
+  p->off_pol = w;    w = align256(w + sizeof(double) * pol);
   p->off_cheb = w;   w = align256(w + sizeof(double) * cheb_hmax);
   p->ws_fwd = w;
   p->spherical = spherical;
@@ -1275,7 +1281,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->off_vtmp = w;   w = align256(w + sizeof(double) * p->total_bins);
   p->off_cot = w;    w = align256(w + sizeof(double) * p->total_bins);
   p->off_sbp = w;    w = align256(w + sizeof(double) * sbp);
-  p->off_sgrid6 = w; w = align256(w + sizeof(float) * sgrid6);
+  p->off_sgrid3 = w; w = align256(w + sizeof(float) * sgrid3);
   p->off_sgcot = w;  w = align256(w + sizeof(double) * sgcot);
   p->off_chebt = w;  w = align256(w + sizeof(double) * cheb_t);
   p->ws_vjp = w;
@@ -1321,7 +1327,7 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
   if (p->spherical) {
     jam::launch_setup(ctx->d_geoms, p->d_models, p->n, pd, gauss, st_ws, status, queue, st);
     jam::launch_sph_terms(ctx->d_geoms, p->d_models, p->d_terms, p->n_terms, gauss, st_ws, terms,
-                          st);
+                          (double *)(ws + p->off_pol), st);
     jam::launch_sb(ctx->d_geoms, p->d_models, p->d_sb, p->n_sb, pd, pix, st);
   } else {
     if (!p->fused_prologue)
@@ -1336,13 +1342,16 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
     float *sgrid = p->n_sgrid ? (float *)(ws + p->off_sgrid) : nullptr;
     const bool timed = ctx->t_num.begin(st, capturing);
     if (sgrid) {
-      jam::launch_sph_grid(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, gauss, terms, st_ws,
-                           sgrid, false, st);
-      if (p->n_sgred)
-        jam::launch_sph_grid_reduce(p->d_models, p->d_sgred, p->n_sgred, st_ws, sgrid, false, st);
+      double *pol = (double *)(ws + p->off_pol);
+      jam::launch_pol_grid(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, p->d_sgred,
+                           p->n_sgred, terms, st_ws, pol, sgrid, false, st);
+      jam::launch_pol_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, p->d_ptab,
+                              p->n_ptab, gauss, terms, st_ws, sgrid, pol, tabs, nullptr, nullptr,
+                              st);
+    } else {
+      jam::launch_sph_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, gauss, terms, st_ws,
+                              tabs, st);
     }
-    jam::launch_sph_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, gauss, terms, st_ws,
-                            sgrid, tabs, st);
     if (timed) ctx->t_num.end(st);
     jam::launch_sph_num(ctx->d_geoms, p->d_models, p->d_red, p->n_red, gauss, st_ws, tabs, pix, st);
     return;
@@ -1389,16 +1398,18 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
     const double *gauss = (const double *)(w + p->off_gauss);
     double *tabs = (double *)(w + p->off_sph);
     const float4 *terms = (const float4 *)(w + p->off_terms);
-    float *sgrid6 = p->n_sgrid ? (float *)(w + p->off_sgrid6) : nullptr;
-    if (sgrid6) {
-      jam::launch_sph_grid(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, gauss, terms, st_ws,
-                           sgrid6, true, st);
-      if (p->n_sgred6)
-        jam::launch_sph_grid_reduce(p->d_models, p->d_sgred6, p->n_sgred6, st_ws, sgrid6, true,
-                                    st);
+    float *sgrid3 = p->n_sgrid ? (float *)(w + p->off_sgrid3) : nullptr;
+    if (sgrid3) {
+      double *pol = (double *)(w + p->off_pol);
+      jam::launch_pol_grid(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, p->d_sgred3,
+                           p->n_sgred3, terms, st_ws, pol, sgrid3, true, st);
+      jam::launch_pol_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, p->d_ptab,
+                              p->n_ptab, gauss, terms, st_ws, sgrid3, pol, tabs, sens,
+                              (double *)(w + p->off_sgcot), st);
+    } else {
+      jam::launch_sph_moments_jac(ctx->d_geoms, p->d_models, p->d_sph, p->n_sph, gauss, terms,
+                                  st_ws, tabs, sens, st);
     }
-    jam::launch_sph_moments_jac(ctx->d_geoms, p->d_models, p->d_sph, p->n_sph, gauss, terms,
-                                st_ws, sgrid6, tabs, (double *)(w + p->off_sens), st);
     if (recompute && !fwd_v)
       jam::launch_sph_num(ctx->d_geoms, p->d_models, p->d_red, p->n_red, gauss, st_ws, tabs, pix,
                           st);
@@ -1427,13 +1438,20 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
                          grads->mass_S0};
   if (p->spherical) {
     const bool ts = ctx->t_sens.begin(st, capturing);
-    jam::launch_sph_adjoint(ctx->d_geoms, p->d_models, p->n, p->d_red, p->n_red, p->d_sph,
-                            p->n_sph, p->d_sens, p->n_sens, p->d_terms, p->n_terms, p->d_pcot,
-                            p->n_pcot, p->d_pfix, p->n_pfix, p->d_sgs, p->n_sgs, pd,
-                            (const double *)(w + p->off_gauss),
-                            (const float4 *)(w + p->off_terms), st_ws,
-                            (const double *)(w + p->off_sph), pix, sbp, sens,
-                            p->n_sgs ? (double *)(w + p->off_sgcot) : nullptr, gd, st);
+    const double *gauss = (const double *)(w + p->off_gauss);
+    const float4 *terms = (const float4 *)(w + p->off_terms);
+    jam::launch_sph_adjoint(ctx->d_geoms, p->d_models, p->n, p->d_red, p->n_red, p->d_srow, p->n_srow,
+                            gauss, st_ws, (const double *)(w + p->off_sph), pix, sens, st);
+    if (p->n_pcot)
+      jam::launch_pol_adjoint(ctx->d_geoms, p->d_models, p->d_pcot, p->n_pcot, p->d_pfix, p->n_pfix,
+                              p->d_sgs, p->n_sgs, gauss, terms, st_ws,
+                              (const double *)(w + p->off_pol), sens,
+                              (double *)(w + p->off_sgcot), st);
+    else
+      jam::launch_sph_sens(ctx->d_geoms, p->d_models, p->d_sens, p->n_sens, gauss, terms, st_ws,
+                           sens, st);
+    jam::launch_sph_chain(ctx->d_geoms, p->d_models, p->n, p->d_terms, p->n_terms, pd, gauss, terms,
+                          st_ws, sbp, sens, gd, st);
     if (ts) ctx->t_sens.end(st);
     return;
   }

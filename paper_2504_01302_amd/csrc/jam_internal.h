@@ -64,7 +64,8 @@ constexpr int kSphNT = 24;
 constexpr int kSphSeg = 8;
 constexpr int kSphNodes = 8 * kSphSeg;   // 64
 // (j, u) terms of the spherical potential integrals, padded to whole groups
-// of 64; the per-model term region holds that many float4 plus as many floats.
+// of 64; the per-model term region holds that many float4 plus as many floats,
+// and as many floats again with the potential grid.
 __host__ __device__ inline int sph_terms_padded(int J1, int n_u) {
   return (J1 * n_u + 63) / 64 * 64;
 }
@@ -95,9 +96,10 @@ struct ModelDev {
   int64_t sph_off;   // doubles, spherical moment table [kSphNR][kSphNT][3]
   int64_t sbp_off;   // doubles, surface-brightness adjoint partials [K][sb items]
   int64_t sgrid_off; // floats, spherical forward potential grid
-                     // [sgrid_slices][kSphGridN][kSphGridN][2] (slice 0 holds the sums)
-  int64_t sgrid6_off;// floats, the adjoint's grid [sgrid_slices][kSphGridN][kSphGridN][8]
-  int64_t sgcot_off; // doubles, the adjoint's grid cotangent (sph_gcot_size)
+                     // [sgrid_slices][kPolN][kPolC][2] (slice 0 holds the sums)
+  int64_t sgrid3_off;// floats, the adjoint's grid [sgrid_slices][kPolN][kPolC][3]
+  int64_t sgcot_off; // doubles, the adjoint's node table and grid cotangent (pol_cot_size)
+  int64_t pol_off;   // doubles, the grid's scales and the moments' partials (pol_size)
   int64_t cheb_off;  // doubles, H blocks [unit, y tile][16][32] of the compressed form
   int64_t chebt_off; // doubles, T blocks [unit, y tile][32][16] of its adjoint
 };
@@ -270,28 +272,66 @@ void launch_grads(const GeomDev *g, const ModelDev *m, int n, ParamsDev p, doubl
 // block), the line-of-sight integral of the projected table into the
 // unique-pixel N map.
 void launch_sph_terms(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                      const double *gauss, const int *st_ws, float4 *terms, hipStream_t st);
-// Items (m, group of four table points), a wave per point.  With sgrid !=
-// NULL the moments take G and G_theta at the characteristic nodes from the
-// model's potential grid instead of summing the terms there.
+                      const double *gauss, const int *st_ws, float4 *terms, double *pol,
+                      hipStream_t st);
+// Here the (j, u) terms are summed at every node: items (m, group of four
+// table points), a wave per point.
 void launch_sph_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                        const double *gauss, const float4 *terms, const int *st_ws, double *table,
+                        hipStream_t st);
+// Potential grid of the spherical model (jam_polar.hip): the tracer-free
+// (j, u) sums on kPolN radii x kPolC angles, kPolPr x 8 interpolation points.
+constexpr int kPolN = 384, kPolC = 64, kPolPr = 6;
+// Term slices of its evaluation, about seven 64-term groups each.  Like the
+// tracer groups below a property of the model alone, so that its grid, and
+// everything computed from it, is the same in any batch.
+__host__ __device__ inline int pol_slices(int Tp) {
+  const int s = Tp / 440;
+  return s < 1 ? 1 : (s > 16 ? 16 : s);
+}
+// Tracers per moments wave, and groups: at most 20 groups, which bounds the
+// partials.  Per model (doubles): the scales, then [groups][cells][3].
+constexpr int kPolScales = 8;
+__host__ __device__ inline int pol_group_len(int K) { return (K + 19) / 20; }
+__host__ __device__ inline int pol_groups(int K) {
+  return (K + pol_group_len(K) - 1) / pol_group_len(K);
+}
+__host__ __device__ inline int64_t pol_size(int K) {
+  return kPolScales + 3LL * kSphNR * kSphNT * pol_groups(K);
+}
+// Grid cotangent: bins of kPolR stencil rows, tiles of the kPolR + 5 grid rows
+// they touch, tracer groups of at least two tracers, at most twenty.  Per model
+// (doubles): the node table [K][kSphNR][64][3], the tiles [groups][bins], the
+// FP32 grid cotangent [kPolN][kPolC][2].
+constexpr int kPolR = 8, kPolBins = (kPolN - 6 + kPolR) / kPolR;
+constexpr int kPolTile = (kPolR + 5) * kPolC * 2;
+constexpr int kPolParts = 32;   // row parts of the term sensitivities
+__host__ __device__ inline int pol_cot_len(int K) { return K > 40 ? (K + 19) / 20 : 2; }
+__host__ __device__ inline int pol_cot_groups(int K) {
+  return (K + pol_cot_len(K) - 1) / pol_cot_len(K);
+}
+__host__ __device__ inline int64_t pol_nodes(int K) { return 3LL * kSphNR * kSphNodes * K; }
+__host__ __device__ inline int64_t pol_cot_size(int K) {
+  return pol_nodes(K) + (int64_t)pol_cot_groups(K) * kPolBins * kPolTile + kPolN * kPolC;
+}
+// Items (m, four grid rows, term slice), and where there are several slices
+// (m, block of 1024 floats) for their sum.
+void launch_pol_grid(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                     const Item *it_sum, int n_sum, const float4 *terms, const int *st_ws,
+                     const double *pol, float *sgrid, bool adjoint, hipStream_t st);
+// The moment table: items (m, four (tracer group, radius) units) and (m, 16
+// cells).  With sens != NULL the adjoint's forward pass, from the adjoint's
+// grid: also SphAdj::jac, gphi and the node table in pcot.
+void launch_pol_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                        const Item *it_tab, int n_tab, const double *gauss, const float4 *terms,
+                        const int *st_ws, const float *sgrid, double *pol, double *table,
+                        double *sens, double *pcot, hipStream_t st);
+// Term sensitivities through the grid, from SphAdj::dtab: items (m, row bin,
+// tracer group), (m, 256 grid points) and (m, 512-term tile, row part).
+void launch_pol_adjoint(const GeomDev *g, const ModelDev *m, const Item *it_spread, int n_spread,
+                        const Item *it_sum, int n_sum, const Item *it_sens, int n_sens,
                         const double *gauss, const float4 *terms, const int *st_ws,
-                        const float *sgrid, double *table, hipStream_t st);
-// Potential grid of the spherical model: the tracer-free (j, u) sums G and
-// G_theta (forward), or those and their four coefficient-weighted sums for
-// the R'^2, z'^2 derivatives (adjoint), on kSphGridN x kSphGridN points
-// asinh-spaced in R and in z, as FP32 matrix-core contractions over the
-// terms.  Items (m, 64 x 64 tile, term slice) write slice partials; with more
-// than one slice the reduce items (m, block of 1024 floats) sum them in order
-// into slice 0.
-constexpr int kSphGridN = 512;
-constexpr int kSphGridTile = 64;
-constexpr int kSphGridTiles = (kSphGridN / kSphGridTile) * (kSphGridN / kSphGridTile);
-void launch_sph_grid(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                     const double *gauss, const float4 *terms, const int *st_ws, float *sgrid,
-                     bool adjoint, hipStream_t st);
-void launch_sph_grid_reduce(const ModelDev *m, const Item *it, int n_it, const int *st_ws,
-                            float *sgrid, bool adjoint, hipStream_t st);
+                        const double *pol, double *sens, double *pcot, hipStream_t st);
 void launch_sph_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                     const double *gauss, const int *st_ws, const double *table, double *pix,
                     hipStream_t st);
@@ -300,31 +340,29 @@ void launch_sph_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_i
 // the tile of lambda_I exp(-x^2 / 2 sigma'^2 - y^2 / 2 sigma'^2 q'^2).
 void launch_sb_adjoint(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                        const int *st_ws, const double *pix, double *sbp, hipStream_t st);
-// Adjoint of the spherically aligned model, after the bin adjoint has filled
-// lambda_N and lambda_I: zero the table cotangents (block per model), the
-// line-of-sight adjoint (items (m, 64-pixel block)), the characteristic
-// integrals' adjoint (items as launch_sph_moments), the term-major
-// sensitivities over point ranges (items (m, 256-term tile, range)) and over
-// the table points (items (m, 256-term tile)), the per-term chain (items (m,
-// 256-term tile)), and the per-model gradients (block per model; they read
-// the surface-brightness partials sbp).
 // The moment table together with the cotangent-free node sums of its
-// adjoint (SphAdj::jac, gphi), for the adjoint's forward pass; with sgrid6
-// != NULL the six node sums come from the model's adjoint grid.
+// adjoint (SphAdj::jac, gphi), for the adjoint's forward pass: items (m,
+// table point).
 void launch_sph_moments_jac(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                             const double *gauss, const float4 *terms, const int *st_ws,
-                            const float *sgrid6, double *table, double *sens, hipStream_t st);
-// With sgcot != NULL the term sensitivities go through the potential grid
-// (items it_pcot (m, point item), it_pfix (m, 1024 grid points), it_sgs (m,
-// 32-term block, row part)) instead of the point-range items it_sens.
-void launch_sph_adjoint(const GeomDev *g, const ModelDev *m, int n, const Item *it_los,
-                        int n_los, const Item *it_cell, int n_cell, const Item *it_sens,
-                        int n_sens, const Item *it_tile, int n_tile, const Item *it_pcot,
-                        int n_pcot, const Item *it_pfix, int n_pfix, const Item *it_sgs,
-                        int n_sgs, ParamsDev p, const double *gauss, const float4 *terms,
-                        const int *st_ws, const double *table, const double *pix,
-                        const double *sbp, double *sens, double *sgcot, GradsDev out,
-                        hipStream_t st);
+                            double *table, double *sens, hipStream_t st);
+// Adjoint of the spherically aligned model, after the bin adjoint has filled
+// lambda_N and lambda_I: zero the table cotangents (block per model), the
+// line-of-sight adjoint (items (m, 64-pixel block)) and the rows of the
+// characteristic integrals' adjoint (items (m, 64 table points)); the term-major
+// sensitivities over point ranges (items (m, 256-term tile, range)), or
+// launch_pol_adjoint; then those of the table points, the per-term chain
+// (items (m, 256-term tile)) and the per-model gradients (block per model;
+// they read the surface-brightness partials sbp).
+void launch_sph_adjoint(const GeomDev *g, const ModelDev *m, int n, const Item *it_los, int n_los,
+                        const Item *it_cell, int n_cell, const double *gauss, const int *st_ws,
+                        const double *table, const double *pix, double *sens, hipStream_t st);
+void launch_sph_sens(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                     const double *gauss, const float4 *terms, const int *st_ws, double *sens,
+                     hipStream_t st);
+void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it_tile, int n_tile,
+                      ParamsDev p, const double *gauss, const float4 *terms, const int *st_ws,
+                      const double *sbp, double *sens, GradsDev out, hipStream_t st);
 // Adjoint of the spherically aligned model.  Per model, in the sensitivity
 // region (doubles): the table cotangent [kSphNR*kSphNT][3], per (tracer,
 // cell) rows (d/dbeta, d/dalphaq, d/dnu0) [K][cells][3], line-of-sight
@@ -372,38 +410,6 @@ __host__ __device__ inline int64_t sph_range_len(int K, int n_rng) {
   const int64_t per = (sph_points(K) + n_rng - 1) / n_rng;
   return (per + 255) / 256 * 256;
 }
-// Term-major sensitivities through the potential grid: the point
-// cotangents are spread onto the grid tile by tile.  Point items of
-// kSphPtsItem points (items (m, q)) count their points per grid tile (tiles
-// of kSphTileB x kSphTileB stencil base cells), a per-model scan turns the
-// counts into positions, the point items write their point indices sorted
-// by tile, and items (m, q) over kSphPtsItem consecutive entries of that
-// list accumulate each tile's stencils in LDS and add them to the grid.
-// The fixed-point grid is converted in items (m, block of 1024 grid
-// points); the contraction runs in items (m, 32-term block, row part) over
-// kSphIParts parts of the grid rows, which are the sensitivities' ranges.
-// Workspace per model: sph_gcot_size doubles.
-constexpr int kSphPtsItem = 16384;
-constexpr int kSphIParts = 4;
-constexpr int kSphTileB = 32;
-constexpr int kSphTilesAx = (kSphGridN - 2 + kSphTileB - 1) / kSphTileB;
-constexpr int kSphTiles = kSphTilesAx * kSphTilesAx;
-__host__ __device__ inline int sph_pitems(int K) {
-  return (int)((sph_points(K) + kSphPtsItem - 1) / kSphPtsItem);
-}
-// Doubles: fixed-point grid [N][N][2], FP32 grid [N][N][2], bound partials
-// [items][2] and the two scales; then int32: per (item, tile) list
-// positions [items][kSphTiles], tile offsets [kSphTiles + 1], a consistency
-// flag and the point list [points]; then one byte per point, its tile.
-static_assert(kSphTiles <= 256, "a tile index fits one byte");
-__host__ __device__ inline int64_t sph_gcot_ints(int K) {
-  return (int64_t)sph_pitems(K) * kSphTiles + kSphTiles + 2 + sph_points(K);
-}
-__host__ __device__ inline int64_t sph_gcot_size(int K) {
-  return 3LL * kSphGridN * kSphGridN + 2LL * sph_pitems(K) + 2 + (sph_gcot_ints(K) + 1) / 2 +
-         (sph_points(K) + 7) / 8;
-}
-
 // Logistic radial anisotropy profile prof[m][0..3] = (beta_0, beta_inf, r_a,
 // alpha) sampled at every tracer Gaussian's sigma into the packed beta, and
 // its adjoint grad[m][0..3] from the packed cotangent of beta.

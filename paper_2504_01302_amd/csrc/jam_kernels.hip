@@ -2042,29 +2042,54 @@ __global__ void __launch_bounds__(256) k_mge1d_vjp(int n_prof, int n_comp,
 // ---------------------------------------------------------------------------
 constexpr int kSphChunk = 1024;   // (j, u) terms staged in LDS at a time
 
+__device__ inline SphAdj sph_adj_of(double *sens, const ModelDev &md, const GeomDev &g) {
+  return sph_adj_layout(sens + md.sens_off, g.K, g.n_pix, sph_terms_padded(g.J1, g.n_u),
+                        md.n_sens_parts);
+}
+
 // FP32 coefficients of the (j, u) terms of G, G_theta and G_phi, once per
 // model: (-r_j u^2 log2e, -r_j u^2 / h log2e, gP, gT) and gF, zero-padded to
-// a whole number of 64-term groups (a zero term adds exactly nothing).
-// Item (m, block of 256 terms); thread = term.
+// a whole number of 64-term groups (a zero term adds exactly nothing).  With
+// the potential grid also T_theta's weights gT r_j u^2 (1 / h - 1), and the
+// grid's scales (first item).  Item (m, block of 256 terms); thread = term.
 __global__ void __launch_bounds__(256) k_sph_terms(const GeomDev *__restrict__ geoms,
                                                    const ModelDev *__restrict__ models,
                                                    const Item *__restrict__ items, int n_it,
                                                    const double *__restrict__ gauss,
                                                    const int *__restrict__ st_ws,
-                                                   float4 *__restrict__ terms) {
-  constexpr double kLog2e = 1.4426950408889634;
+                                                   float4 *__restrict__ terms,
+                                                   double *__restrict__ pol) {
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
     const Item it = items[i];
     const ModelDev md = models[it.m];
     const GeomDev g = geoms[md.geom];
     const int nu_n = g.n_u, T = g.J1 * nu_n, Tp = sph_terms_padded(g.J1, nu_n);
     const int t = it.a * 256 + threadIdx.x;
+    const bool grid = md.sgrid_slices > 0;
+    if (grid && it.a == 0 && threadIdx.x < 64) {
+      const double *tab = gauss + md.gauss_off, *e2 = tab + 4 * g.K + g.J1;
+      double s0 = 1.0, sk2 = 0.0;            // min q_j^2, max sigma_k^2
+      for (int j = threadIdx.x; j < g.J1; j += 64) s0 = fmin(s0, 1.0 - e2[j]);
+      for (int k = threadIdx.x; k < g.K; k += 64) sk2 = fmax(sk2, 0.5 / tab[k]);
+      for (int o = 32; o > 0; o >>= 1) {
+        s0 = fmin(s0, __shfl_xor(s0, o, 64));
+        sk2 = fmax(sk2, __shfl_xor(sk2, o, 64));
+      }
+      const double span = (kSphNR - 1) * g.sph_dlnr, rhi = exp(g.sph_lnr0 + span);
+      if (threadIdx.x == 0) {
+        double *p = pol + md.pol_off;
+        p[0] = (kPolN - 6) / (span + 0.5 * log1p(50.0 * sk2 / (rhi * rhi)));   // iX
+        p[1] = s0;
+        p[2] = (kPolC - 8) / log1p(1.0 / s0);                                  // iC
+      }
+    }
     if (t >= Tp) continue;
     float4 *tc = terms + md.term_off;
     float *tf = (float *)(tc + Tp);
     if (t >= T || st_ws[it.m] != 0) {
       tc[t] = make_float4(0.f, 0.f, 0.f, 0.f);
       tf[t] = 0.f;
+      if (grid) tf[Tp + t] = 0.f;
       continue;
     }
     const double *mt = gauss + md.gauss_off + 4 * g.K;
@@ -2072,209 +2097,11 @@ __global__ void __launch_bounds__(256) k_sph_terms(const GeomDev *__restrict__ g
     const double rj = mt[j], e2 = mt[g.J1 + j], Kp = mt[2 * g.J1 + j];
     const double u = g.u[n], u2 = u * u, wK = g.w[n] * Kp;
     const double hh = 1.0 - e2 * u2, h15 = hh * sqrt(hh);
+    const double gT = wK * e2 * 4.0 * rj * rj * u2 * u2 * u2 / (h15 * hh);
     tc[t] = make_float4((float)(-rj * u2 * kLog2e), (float)(-rj * u2 / hh * kLog2e),
-                        (float)(wK * 2.0 * rj * u2 / h15),
-                        (float)(wK * e2 * 4.0 * rj * rj * u2 * u2 * u2 / (h15 * hh)));
+                        (float)(wK * 2.0 * rj * u2 / h15), (float)gT);
     tf[t] = (float)(wK * e2 * 2.0 * rj * u2 * u2 / h15);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Potential grid.  G and G_theta do not depend on the tracer, only on the
-// point (R, z), and each (j, u) term factorises as gP 2^(cR R^2) 2^(cZ z^2)
-// (resp. gT ...).  On a tensor grid of R and z values the two sums are
-// therefore the matrix products A_G B^T and A_T B^T over the terms, with
-// A[i, t] = g_t 2^(cR_t R_i^2) and B[l, t] = 2^(cZ_t z_l^2), which run on
-// the matrix cores; the moment kernel then interpolates them at the
-// characteristic nodes.  The grid is uniform in asinh(R / aR) and
-// asinh(z / aZ): a quarter of the narrowest mass Gaussian (aR = min sigma_j
-// / 4, aZ = min sigma_j q_j / 4) near the centre, logarithmic far out, up to
-// r_max, the farthest node (sqrt(r_hi^2 + 50 max sigma_k^2)), at grid index
-// kSphGridN - 3.  4-point Lagrange interpolation in both indices (G is even
-// in R and in z, so the point below index 0 is index 1).
-// ---------------------------------------------------------------------------
-struct SphGrid {
-  double aR, aZ, iR, iZ;   // scales and grid points per unit of asinh(R / aR), asinh(z / aZ)
-};
-
-__device__ inline SphGrid sph_grid_scales(const GeomDev &g, const double *tab) {
-  const int K = g.K, J1 = g.J1;
-  const double *mt = tab + 4 * K;         // per mass Gaussian: r_j = 1 / (2 sigma_j^2), e_j^2
-  double s2 = 1e300, z2 = 1e300, sk2 = 0.0;
-  for (int j = 0; j < J1; ++j) {
-    const double sj2 = 0.5 / mt[j];
-    s2 = fmin(s2, sj2);
-    z2 = fmin(z2, sj2 * (1.0 - mt[J1 + j]));
-  }
-  for (int k = 0; k < K; ++k) sk2 = fmax(sk2, 0.5 / tab[k]);
-  const double rhi = exp(g.sph_lnr0 + (kSphNR - 1) * g.sph_dlnr);
-  const double rmax = sqrt(rhi * rhi + 50.0 * sk2);
-  SphGrid s;
-  s.aR = 0.25 * sqrt(s2);
-  s.aZ = 0.25 * sqrt(z2);
-  s.iR = (kSphGridN - 3) / asinh(rmax / s.aR);
-  s.iZ = (kSphGridN - 3) / asinh(rmax / s.aZ);
-  return s;
-}
-
-// Lagrange weights of the points -1, 0, 1, 2 at fraction f of [0, 1].
-__device__ inline void lagrange4(double f, double w[4]) {
-  const double fm = f - 1.0, fm2 = f - 2.0, fp = f + 1.0;
-  w[0] = -f * fm * fm2 * (1.0 / 6.0);
-  w[1] = fp * fm * fm2 * 0.5;
-  w[2] = -fp * f * fm2 * 0.5;
-  w[3] = fp * f * fm * (1.0 / 6.0);
-}
-
-// Values per grid point: the forward's G, G_theta (2 floats), or the
-// adjoint's G, G_theta and their coefficient-weighted sums for the R'^2 and
-// z'^2 derivatives (6 values, stored in 8 floats for two 16-byte reads).
-template <int NC> struct SphGridVals { static constexpr int S = NC == 2 ? 2 : 8; };
-
-// The NC sums at (R, z) from a model's grid sg ([N][N][S]).
-template <int NC>
-__device__ inline void sph_grid_at(const float *__restrict__ sg, const SphGrid &s, double R,
-                                   double z, double (&v)[NC]) {
-  constexpr int N = kSphGridN, S = SphGridVals<NC>::S;
-  const double x = asinh(R / s.aR) * s.iR, y = asinh(z / s.aZ) * s.iZ;
-  const int i0 = min(max((int)floor(x), 0), N - 3), l0 = min(max((int)floor(y), 0), N - 3);
-  double wx[4], wy[4];
-  lagrange4(x - i0, wx);
-  lagrange4(y - l0, wy);
-  int lb[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) lb[b] = abs(l0 - 1 + b);
-#pragma unroll
-  for (int c = 0; c < NC; ++c) v[c] = 0.0;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const float *row = sg + (int64_t)abs(i0 - 1 + a) * N * S;
-    double rv[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) rv[c] = 0.0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const float *pt = row + lb[b] * S;
-      float f[NC];
-      if constexpr (NC == 2) {
-        const float2 q = *reinterpret_cast<const float2 *>(pt);
-        f[0] = q.x; f[1] = q.y;
-      } else {
-        const float4 q0 = *reinterpret_cast<const float4 *>(pt);
-        const float4 q1 = *reinterpret_cast<const float4 *>(pt + 4);
-        f[0] = q0.x; f[1] = q0.y; f[2] = q0.z; f[3] = q0.w; f[4] = q1.x; f[5] = q1.y;
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c) rv[c] += wy[b] * (double)f[c];
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) v[c] += wx[a] * rv[c];
-  }
-}
-
-// Item (m, 64 x 64 tile, term slice): wave w computes the 32 x 32 block
-// (w & 1, w >> 1) of the tile for all NC sums, over the slice's 64-term
-// chunks (staged in LDS, shared by the four waves); lane l generates row
-// l % 32 of the A operands (one exponential, NC products) and column l % 32
-// of B for the term of its half-wave; FP32 matrix-core sums per chunk
-// folded into FP64; the slice partial is stored in FP32 ([N][N][S] per
-// slice).  The sums, per term (c.x, c.y the exponent coefficients of R'^2,
-// z'^2 with log2 e, gP = c.z, gT = c.w): G = gP E, G_theta = gT E, and for
-// the adjoint gP c.x E, gP c.y E, gT c.x E, gT c.y E.
-template <int NC>
-__global__ void __launch_bounds__(256) k_sph_grid(const GeomDev *__restrict__ geoms,
-                                                  const ModelDev *__restrict__ models,
-                                                  const Item *__restrict__ items, int n_it,
-                                                  const double *__restrict__ gauss,
-                                                  const float4 *__restrict__ terms,
-                                                  const int *__restrict__ st_ws,
-                                                  float *__restrict__ sgrid) {
-  constexpr int N = kSphGridN, NT = kSphGridN / kSphGridTile, S = SphGridVals<NC>::S;
-  __shared__ float4 cs[64];
-  const int lane = threadIdx.x & 63, c32 = lane & 31, kh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    if (st_ws[it.m] != 0) continue;         // uniform per block; the grid is not read
-    const SphGrid sc = sph_grid_scales(g, gauss + md.gauss_off);
-    const int r0 = kSphGridTile * (it.a / NT) + 32 * (wave & 1);
-    const int z0 = kSphGridTile * (it.a % NT) + 32 * (wave >> 1);
-    const double Rv = sc.aR * sinh((r0 + c32) / sc.iR), Zv = sc.aZ * sinh((z0 + c32) / sc.iZ);
-    const float R2 = (float)(Rv * Rv), Z2 = (float)(Zv * Zv);
-    const int chunks = sph_terms_padded(g.J1, g.n_u) / 64;
-    const int per = (chunks + md.sgrid_slices - 1) / md.sgrid_slices;
-    const int c0 = min(chunks, it.b * per), c1 = min(chunks, c0 + per);
-    const float4 *tc = terms + md.term_off;
-    double acc[NC][16];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[c][r] = 0.0;
-    for (int ch = c0; ch < c1; ++ch) {
-      __syncthreads();
-      if (threadIdx.x < 64) cs[threadIdx.x] = tc[64 * ch + threadIdx.x];
-      __syncthreads();
-      v16f f[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) f[c] = zero;
-#pragma unroll 4
-      for (int s2 = 0; s2 < 32; ++s2) {
-        const float4 c = cs[2 * s2 + kh];   // (cR log2e, cZ log2e, gP, gT)
-        const float e = fast_exp2(c.x * R2);
-        const float b = fast_exp2(c.y * Z2);
-        const float eP = c.z * e, eT = c.w * e;
-        f[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(eP, b, f[0], 0, 0, 0);
-        f[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(eT, b, f[1], 0, 0, 0);
-        if constexpr (NC == 6) {
-          f[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(eP * c.x, b, f[2], 0, 0, 0);
-          f[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(eP * c.y, b, f[3], 0, 0, 0);
-          f[4] = __builtin_amdgcn_mfma_f32_32x32x2f32(eT * c.x, b, f[4], 0, 0, 0);
-          f[5] = __builtin_amdgcn_mfma_f32_32x32x2f32(eT * c.y, b, f[5], 0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[c][r] += (double)f[c][r];
-    }
-    float *og = sgrid + (NC == 2 ? md.sgrid_off : md.sgrid6_off) + (int64_t)it.b * N * N * S;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float *o = og + ((int64_t)(r0 + mfma_row(r, lane)) * N + z0 + c32) * S;
-      if constexpr (NC == 2) {
-        *reinterpret_cast<float2 *>(o) = make_float2((float)acc[0][r], (float)acc[1][r]);
-      } else {
-        *reinterpret_cast<float4 *>(o) = make_float4((float)acc[0][r], (float)acc[1][r],
-                                                     (float)acc[2][r], (float)acc[3][r]);
-        *reinterpret_cast<float4 *>(o + 4) =
-            make_float4((float)acc[4][r], (float)acc[5][r], 0.f, 0.f);
-      }
-    }
-  }
-}
-
-// Item (m, block of 1024 grid floats): the slice partials summed in slice
-// order (FP64) into slice 0; len = N^2 S floats per slice, off selects the
-// forward's or the adjoint's grid.
-__global__ void __launch_bounds__(256) k_sph_grid_reduce(const ModelDev *__restrict__ models,
-                                                         const Item *__restrict__ items, int n_it,
-                                                         const int *__restrict__ st_ws,
-                                                         float *__restrict__ sgrid, int adjoint) {
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    if (st_ws[it.m] != 0) continue;
-    const ModelDev md = models[it.m];
-    const int64_t len = (int64_t)kSphGridN * kSphGridN * (adjoint ? 8 : 2);
-    float *base = sgrid + (adjoint ? md.sgrid6_off : md.sgrid_off);
-    const int64_t e1 = min(len, (int64_t)(it.a + 1) * 1024);
-    for (int64_t e = (int64_t)it.a * 1024 + threadIdx.x; e < e1; e += 256) {
-      double v = 0.0;
-      for (int sl = 0; sl < md.sgrid_slices; ++sl) v += (double)base[sl * len + e];
-      base[e] = (float)v;
-    }
+    if (grid) tf[Tp + t] = (float)(gT * rj * u2 * (e2 * u2 / hh));
   }
 }
 
@@ -2282,19 +2109,16 @@ __global__ void __launch_bounds__(256) k_sph_grid_reduce(const ModelDev *__restr
 // table point per wave, so no block-wide reductions), taking the tracers two
 // per round (each coefficient read from LDS feeds both); lane l is node l of
 // the composite Gauss-Legendre rule in tau = ln(r'/r) on [0, ln(r_max / r)],
-// r_max^2 = r^2 + 50 sigma_k^2.  Without the grid the per-model term
-// coefficients go through LDS in chunks shared by the four waves; each group
-// of 64 terms is summed in FP32 (fully unrolled, the coefficient reads are
-// wave-wide broadcasts) and folded into FP64; everything else is FP64; all
-// sums run in a fixed order.
-template <bool kGrid>
+// r_max^2 = r^2 + 50 sigma_k^2.  The per-model term coefficients go through LDS
+// in chunks shared by the four waves; each group of 64 terms is summed in
+// FP32 (fully unrolled, the coefficient reads are wave-wide broadcasts) and
+// folded into FP64; everything else is FP64; all sums run in a fixed order.
 __global__ void __launch_bounds__(256) k_sph_moments(const GeomDev *__restrict__ geoms,
                                                      const ModelDev *__restrict__ models,
                                                      const Item *__restrict__ items, int n_it,
                                                      const double *__restrict__ gauss,
                                                      const float4 *__restrict__ terms,
                                                      const int *__restrict__ st_ws,
-                                                     const float *__restrict__ sgrid,
                                                      double *__restrict__ table) {
   __shared__ float4 tc[kSphChunk];   // (-c log2e, -d log2e, gP, gT)
   __shared__ float tf[kSphChunk];    // gF
@@ -2324,11 +2148,6 @@ __global__ void __launch_bounds__(256) k_sph_moments(const GeomDev *__restrict__
     // the rule's node and weight of this lane, read from global memory (a
     // lane-dependent index into the by-value descriptor would go to scratch)
     const double glx = geoms[md.geom].gl8_x[gi], glw = geoms[md.geom].gl8_w[gi];
-    // G and G_theta at the nodes: from the model's potential grid, or summed
-    // over the terms here
-    const float *sg = kGrid ? sgrid + md.sgrid_off : nullptr;
-    SphGrid sc = {1.0, 1.0, 1.0, 1.0};
-    if (kGrid) sc = sph_grid_scales(g, tab);
     double Ar = 0.0, At = 0.0, Ap = 0.0;   // the point's moments (lane 0)
     double accF = 0.0;                      // this lane's share of G_phi
     constexpr int kTr = 2;                  // tracers per round
@@ -2370,19 +2189,8 @@ __global__ void __launch_bounds__(256) k_sph_moments(const GeomDev *__restrict__
       double accG[kTr], accT[kTr];
 #pragma unroll
       for (int u = 0; u < kTr; ++u) { accG[u] = 0.0; accT[u] = 0.0; }
-      if (kGrid) {
-#pragma unroll
-        for (int u = 0; u < kTr; ++u)
-          if (on[u]) {
-            double v[2];
-            sph_grid_at<2>(sg, sc, Rp[u], Zp[u], v);
-            accG[u] = v[0];
-            accT[u] = v[1];
-          }
-      }
-      // the terms: the node sums (without a grid) and, in the first round,
-      // G_phi at the table point
-      if (!kGrid || q == 0)
+      // the terms: the node sums and, in the first round, G_phi at the table
+      // point
       for (int c0 = 0; c0 < Tp; c0 += kSphChunk) {
         const int cn = min(kSphChunk, Tp - c0);
         __syncthreads();
@@ -2391,24 +2199,22 @@ __global__ void __launch_bounds__(256) k_sph_moments(const GeomDev *__restrict__
           tf[t] = gtf[c0 + t];
         }
         __syncthreads();
-        if (!kGrid) {
-          for (int t0 = 0; t0 < cn; t0 += 64) {
-            float sg0 = 0.f, sd0 = 0.f, sg1 = 0.f, sd1 = 0.f;
+        for (int t0 = 0; t0 < cn; t0 += 64) {
+          float sg0 = 0.f, sd0 = 0.f, sg1 = 0.f, sd1 = 0.f;
 #pragma unroll
-            for (int t = 0; t < 64; ++t) {
-              const float4 c = tc[t0 + t];
-              const float e0 = fast_exp2(fmaf(c.x, R2[0], c.y * Z2[0]));
-              const float e1 = fast_exp2(fmaf(c.x, R2[1], c.y * Z2[1]));
-              sg0 = fmaf(c.z, e0, sg0);
-              sd0 = fmaf(c.w, e0, sd0);
-              sg1 = fmaf(c.z, e1, sg1);
-              sd1 = fmaf(c.w, e1, sd1);
-            }
-            accG[0] += (double)sg0;
-            accT[0] += (double)sd0;
-            accG[1] += (double)sg1;
-            accT[1] += (double)sd1;
+          for (int t = 0; t < 64; ++t) {
+            const float4 c = tc[t0 + t];
+            const float e0 = fast_exp2(fmaf(c.x, R2[0], c.y * Z2[0]));
+            const float e1 = fast_exp2(fmaf(c.x, R2[1], c.y * Z2[1]));
+            sg0 = fmaf(c.z, e0, sg0);
+            sd0 = fmaf(c.w, e0, sd0);
+            sg1 = fmaf(c.z, e1, sg1);
+            sd1 = fmaf(c.w, e1, sd1);
           }
+          accG[0] += (double)sg0;
+          accT[0] += (double)sd0;
+          accG[1] += (double)sg1;
+          accT[1] += (double)sd1;
         }
         if (q == 0) {
           for (int t = lane; t < cn; t += 64) {
@@ -2553,10 +2359,6 @@ __device__ inline void sph_cell(const GeomDev &g, int cell, double &r, double &s
   cth = cos(th);
 }
 
-__device__ inline SphAdj sph_adj_of(double *sens, const ModelDev &md, const GeomDev &g) {
-  return sph_adj_layout(sens + md.sens_off, g.K, g.n_pix, sph_terms_padded(g.J1, g.n_u),
-                        md.n_sens_parts);
-}
 
 // Start of the line-of-sight adjoint, block per model: clears the table
 // cotangent and fixes its fixed-point scale.  Every contribution to the
@@ -2812,14 +2614,12 @@ __global__ void __launch_bounds__(256) k_sph_num_adj(const GeomDev *__restrict__
 // nu0_k (eP, eD) go to SphAdj::jac, none of which depends on the table
 // cotangent, and the cell's G_phi to SphAdj::gphi; k_sph_rows combines
 // them with the cotangent once the line-of-sight adjoint has produced it.
-template <bool kGrid>
 __global__ void __launch_bounds__(256) k_sph_moments_jac(const GeomDev *__restrict__ geoms,
                                                          const ModelDev *__restrict__ models,
                                                          const Item *__restrict__ items, int n_it,
                                                          const double *__restrict__ gauss,
                                                          const float4 *__restrict__ terms,
                                                          const int *__restrict__ st_ws,
-                                                         const float *__restrict__ sgrid6,
                                                          double *__restrict__ table,
                                                          double *__restrict__ sens) {
   __shared__ float4 tc[kSphChunk];
@@ -2840,11 +2640,6 @@ __global__ void __launch_bounds__(256) k_sph_moments_jac(const GeomDev *__restri
       continue;
     }
     const SphAdj adj = sph_adj_of(sens, md, g);
-    // the six node sums: from the model's adjoint grid, or summed over the
-    // terms here
-    const float *sg = kGrid ? sgrid6 + md.sgrid6_off : nullptr;
-    SphGrid sgs = {1.0, 1.0, 1.0, 1.0};
-    if (kGrid) sgs = sph_grid_scales(g, gauss + md.gauss_off);
     const int K = g.K, Tp = sph_terms_padded(g.J1, g.n_u);
     const float4 *gtc = terms + md.term_off;
     const float *gtf = (const float *)(gtc + Tp);
@@ -2888,18 +2683,8 @@ __global__ void __launch_bounds__(256) k_sph_moments_jac(const GeomDev *__restri
       double aG[kTr], aT[kTr], aGR[kTr], aGZ[kTr], aTR[kTr], aTZ[kTr];
 #pragma unroll
       for (int u = 0; u < kTr; ++u) aG[u] = aT[u] = aGR[u] = aGZ[u] = aTR[u] = aTZ[u] = 0.0;
-      if (kGrid) {
-#pragma unroll
-        for (int u = 0; u < kTr; ++u)
-          if (on[u]) {
-            double v[6];
-            sph_grid_at<6>(sg, sgs, nd[u].Rp, nd[u].zp, v);
-            aG[u] = v[0]; aT[u] = v[1]; aGR[u] = v[2]; aGZ[u] = v[3]; aTR[u] = v[4]; aTZ[u] = v[5];
-          }
-      }
-      // the terms: the node sums (without a grid) and, in the first round,
-      // G_phi at the table point
-      if (!kGrid || q == 0)
+      // the terms: the node sums and, in the first round, G_phi at the table
+      // point
       for (int c0 = 0; c0 < Tp; c0 += kSphChunk) {
         const int cn = min(kSphChunk, Tp - c0);
         __syncthreads();
@@ -2910,7 +2695,7 @@ __global__ void __launch_bounds__(256) k_sph_moments_jac(const GeomDev *__restri
           tf[t] = gtf[c0 + t];
         }
         __syncthreads();
-        if (!kGrid && on[0]) {
+        if (on[0]) {
           for (int t0 = 0; t0 < cn; t0 += 64) {
             float sG0 = 0.f, sT0 = 0.f, sGR0 = 0.f, sGZ0 = 0.f, sTR0 = 0.f, sTZ0 = 0.f;
             float sG1 = 0.f, sT1 = 0.f, sGR1 = 0.f, sGZ1 = 0.f, sTR1 = 0.f, sTZ1 = 0.f;
@@ -3023,28 +2808,32 @@ __global__ void __launch_bounds__(256) k_sph_moments_jac(const GeomDev *__restri
 // derivatives of the cell's L = lambda . (A_r, A_theta, A_phi) with respect
 // to beta_k, alphaq_k and nu0_k from the node sums of k_sph_moments_jac and
 // the table cotangent lambda; the A_phi term -nu R^2 G_phi adds its
-// alphaq_k, nu0_k derivatives.  Item (m, table cell), thread = tracer.
-__global__ void __launch_bounds__(64) k_sph_rows(const GeomDev *__restrict__ geoms,
-                                                 const ModelDev *__restrict__ models,
-                                                 const Item *__restrict__ items, int n_it,
-                                                 const double *__restrict__ gauss,
-                                                 const int *__restrict__ st_ws,
-                                                 double *__restrict__ sens) {
+// alphaq_k, nu0_k derivatives.  Item (m, 64 cells), lane = cell, the four
+// waves take the tracers in turn (a thread per tracer of one cell left most
+// of a wave idle: 48 models of 10 tracers 136 us, now 25).
+__global__ void __launch_bounds__(256) k_sph_rows(const GeomDev *__restrict__ geoms,
+                                                  const ModelDev *__restrict__ models,
+                                                  const Item *__restrict__ items, int n_it,
+                                                  const double *__restrict__ gauss,
+                                                  const int *__restrict__ st_ws,
+                                                  double *__restrict__ sens) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
     const Item it = items[i];
     if (st_ws[it.m] != 0) continue;          // uniform per block
     const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
+    const GeomDev &g = geoms[md.geom];
     const SphAdj adj = sph_adj_of(sens, md, g);
-    const int K = g.K, cell = it.a;
+    const int K = g.K, cell = 64 * it.a + lane;
     const double *tab = gauss + md.gauss_off;
     double r, sth, cth;
     sph_cell(g, cell, r, sth, cth);
-    const double Rp0 = r * sth, zp0 = r * cth;
+    const double R02 = (r * sth) * (r * sth), z02 = (r * cth) * (r * cth);
     const double lr = adj.dtab[3 * cell], lt = adj.dtab[3 * cell + 1], lp = adj.dtab[3 * cell + 2];
     const double Gphi = adj.gphi[cell];
-    const double lnr = log(r);
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
+    const double lnr = g.sph_lnr0 + (cell / kSphNT) * g.sph_dlnr;   // ln r (r = e^lnr)
+    for (int k = wave; k < K; k += 4) {
       const double *jr = adj.jac + ((int64_t)k * kSphCells + cell) * 8;
       const double fP = jr[0], fD = jr[1], bP = jr[2], bD = jr[3];
       const double qP = jr[4], qD = jr[5], eP = jr[6], eD = jr[7];
@@ -3056,11 +2845,11 @@ __global__ void __launch_bounds__(64) k_sph_rows(const GeomDev *__restrict__ geo
       const double muD = lp * (1.0 - be) * sth * rd;
       const double dbeta = muP * rb * bP + muD * bD - (lt + lp) * P - 2.0 * lnr * muP * P -
                            fD * lp * sth * rd * (1.0 + 3.0 * (1.0 - be) * lnr);
-      const double e0 = exp(-(tab[k] * Rp0 * Rp0 + tab[K + k] * zp0 * zp0));
+      const double e0 = exp(-(tab[k] * R02 + tab[K + k] * z02));
       double *row = adj.rows + ((int64_t)k * kSphCells + cell) * 3;
       row[0] = dbeta;
-      row[1] = (muP * rb * qP + muD * qD) + lp * Rp0 * Rp0 * Gphi * tab[2 * K + k] * e0 * zp0 * zp0;
-      row[2] = (muP * rb * eP + muD * eD) + -lp * Rp0 * Rp0 * Gphi * e0;
+      row[1] = (muP * rb * qP + muD * qD) + lp * R02 * Gphi * tab[2 * K + k] * e0 * z02;
+      row[2] = (muP * rb * eP + muD * eD) + -lp * R02 * Gphi * e0;
     }
   }
 }
@@ -3190,474 +2979,6 @@ __global__ void __launch_bounds__(256) k_sph_sens(const GeomDev *__restrict__ ge
       o[5] = SyT;
     }
     __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Term-major sensitivities through the potential grid.  With the adjoint's
-// node sums interpolated from the grid, the term sensitivities are those of
-// the grid values: the point cotangents phi, psi are spread onto the grid
-// with the interpolation's own weights (its transpose), and per term
-//   S_phi = sum_il Phi[i, l] E_t(R_i, z_l),  E_t = 2^(cx R_i^2) 2^(cy z_l^2),
-// with the R^2 and z^2 moments, is one more matrix-core contraction over the
-// grid.  The spreading adds 64-bit fixed-point integers at a per-model
-// power-of-two scale, so the grid cotangent, like the table cotangent, does
-// not depend on the order of the additions.
-// Workspace per model (8-byte slots from sgcot_off): the fixed-point grid
-// [N][N][2] (phi, psi), the FP32 grid [N][N][2], the bound partials
-// [items][2] and the two scales.
-// ---------------------------------------------------------------------------
-__device__ inline long long *sph_gcot_fixed(double *sgcot, const ModelDev &md) {
-  return reinterpret_cast<long long *>(sgcot + md.sgcot_off);
-}
-__device__ inline float *sph_gcot_float(double *sgcot, const ModelDev &md) {
-  return reinterpret_cast<float *>(sgcot + md.sgcot_off + 2LL * kSphGridN * kSphGridN);
-}
-__device__ inline double *sph_gcot_bounds(double *sgcot, const ModelDev &md) {
-  return sgcot + md.sgcot_off + 3LL * kSphGridN * kSphGridN;
-}
-
-// The int32 part of the grid-cotangent workspace: per (point item, tile)
-// list positions, tile offsets, the consistency flag, the point list; then
-// one byte per point, its tile.
-__device__ inline int *sph_gcot_int(double *sgcot, const ModelDev &md, int K) {
-  return reinterpret_cast<int *>(sph_gcot_bounds(sgcot, md) + 2LL * sph_pitems(K) + 2);
-}
-__device__ inline unsigned char *sph_gcot_ptile(double *sgcot, const ModelDev &md, int K) {
-  return reinterpret_cast<unsigned char *>(sph_gcot_int(sgcot, md, K) + sph_gcot_ints(K));
-}
-
-// The grid tile (of kSphTileB x kSphTileB stencil base cells) that holds
-// the stencil base cell of a point at (R, z): tile row b starts at
-// R = aR sinh(kSphTileB b / iR) (bR[b], b = 1 .. kSphTilesAx - 1), and
-// likewise in z (bZ).  A point within rounding of a boundary may land in
-// the neighbouring tile; the tile pass takes its stencil all the same.
-__device__ inline void sph_tile_bounds(const SphGrid &sc, double *bR, double *bZ) {
-  for (int b = threadIdx.x; b < kSphTilesAx; b += blockDim.x) {
-    bR[b] = sc.aR * sinh(kSphTileB * b / sc.iR);
-    bZ[b] = sc.aZ * sinh(kSphTileB * b / sc.iZ);
-  }
-}
-__device__ inline int sph_tile_at(const double *bR, const double *bZ, double R, double z) {
-  static_assert(kSphTilesAx == 16, "a four-step search");
-  int tx = 0, tz = 0;
-#pragma unroll
-  for (int step = 8; step >= 1; step >>= 1) {
-    if (R >= bR[tx + step]) tx += step;
-    if (z >= bZ[tz + step]) tz += step;
-  }
-  return tx * kSphTilesAx + tz;
-}
-
-// Item (m, point item q): clears a share of the fixed-point grid, sums
-// |phi|, |psi| over the item's points (fixed-order block sums), and counts
-// them per grid tile, recording each point's tile.
-__global__ void __launch_bounds__(256) k_sph_pcot_bound(const GeomDev *__restrict__ geoms,
-                                                        const ModelDev *__restrict__ models,
-                                                        const Item *__restrict__ items, int n_it,
-                                                        const double *__restrict__ gauss,
-                                                        const int *__restrict__ st_ws,
-                                                        double *__restrict__ sens,
-                                                        double *__restrict__ sgcot) {
-  static_assert(kSphTiles == 256, "one thread per tile");
-  __shared__ double sinth[kSphNT];
-  __shared__ double sh[256];
-  __shared__ double bR[kSphTilesAx], bZ[kSphTilesAx];
-  __shared__ int hist[kSphTiles];
-  if (threadIdx.x < kSphNT) sinth[threadIdx.x] = sin(threadIdx.x * (0.5 * kPi / (kSphNT - 1)));
-  __syncthreads();
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    if (st_ws[it.m] != 0) continue;          // uniform per block
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    const SphAdj adj = sph_adj_of(sens, md, g);
-    const double *tab = gauss + md.gauss_off;
-    const SphGrid sc = sph_grid_scales(g, tab);
-    const int np = sph_pitems(g.K);
-    const int64_t n2 = 2LL * kSphGridN * kSphGridN, share = (n2 + np - 1) / np;
-    long long *fx = sph_gcot_fixed(sgcot, md);
-    const int64_t e0 = (int64_t)it.a * share, e1 = min(n2, e0 + share);
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) fx[e] = 0;
-    int *gi = sph_gcot_int(sgcot, md, g.K);
-    unsigned char *ptile = sph_gcot_ptile(sgcot, md, g.K);
-    if (it.a == 0 && threadIdx.x == 0) gi[(int64_t)np * kSphTiles + kSphTiles + 1] = 0;   // flag
-    hist[threadIdx.x] = 0;
-    sph_tile_bounds(sc, bR, bZ);
-    __syncthreads();
-    const int64_t P = sph_points(g.K), p0 = (int64_t)it.a * kSphPtsItem,
-                  p1 = min(P, p0 + kSphPtsItem);
-    double sa = 0.0, sb = 0.0;
-    for (int64_t p = p0 + threadIdx.x; p < p1; p += 256) {
-      double R, z, phi, psi;
-      sph_point_cot(g, geoms + md.geom, tab, adj, sinth, p, R, z, phi, psi);
-      sa += fabs(phi);
-      sb += fabs(psi);
-      const int tile = sph_tile_at(bR, bZ, R, z);
-      ptile[p] = (unsigned char)tile;
-      atomicAdd(&hist[tile], 1);
-    }
-    sa = block_sum256(sa, sh);
-    sb = block_sum256(sb, sh);
-    if (threadIdx.x == 0) {
-      double *bnd = sph_gcot_bounds(sgcot, md);
-      bnd[2 * it.a] = sa;
-      bnd[2 * it.a + 1] = sb;
-    }
-    __syncthreads();
-    gi[(int64_t)it.a * kSphTiles + threadIdx.x] = hist[threadIdx.x];
-    __syncthreads();                         // hist, bR, bZ read before the next item
-  }
-}
-
-// Model m: the per-item tile counts become list positions, items in order
-// within a tile and tiles in order, and the tile offsets.  Thread (tile,
-// part) takes a quarter of the items; the parts are added in order.
-constexpr int kScanParts = 4;
-__global__ void __launch_bounds__(kSphTiles * kScanParts) k_sph_pcot_scan(
-    const GeomDev *__restrict__ geoms, const ModelDev *__restrict__ models, int n,
-    const int *__restrict__ st_ws, double *__restrict__ sgcot) {
-  __shared__ int part[kScanParts][kSphTiles];   // per part: its count, then its offset
-  __shared__ int tsz[kSphTiles], tot[kSphTiles];
-  const int t = threadIdx.x % kSphTiles, r = threadIdx.x / kSphTiles;
-  for (int m = blockIdx.x; m < n; m += gridDim.x) {
-    if (st_ws[m] != 0) continue;             // uniform per block
-    const ModelDev md = models[m];
-    const int K = geoms[md.geom].K;
-    const int np = sph_pitems(K);
-    int *pos = sph_gcot_int(sgcot, md, K);
-    int *toff = pos + (int64_t)np * kSphTiles;
-    const int per = (np + kScanParts - 1) / kScanParts;
-    const int q0 = min(np, r * per), q1 = min(np, q0 + per);
-    // the part's items: counts to offsets within the part
-    int acc = 0;
-    for (int q = q0; q < q1; q += 8) {
-      int v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = q + u < q1 ? pos[(int64_t)(q + u) * kSphTiles + t] : 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (q + u < q1) pos[(int64_t)(q + u) * kSphTiles + t] = acc;
-        acc += v[u];
-      }
-    }
-    __syncthreads();                         // the previous model's reads of part, tsz, tot
-    part[r][t] = acc;
-    __syncthreads();
-    if (r == 0) {
-      int s0 = 0;
-      for (int rr = 0; rr < kScanParts; ++rr) {
-        const int v = part[rr][t];
-        part[rr][t] = s0;
-        s0 += v;
-      }
-      tsz[t] = s0;
-      tot[t] = s0;
-    }
-    __syncthreads();
-    // inclusive scan of the tile sizes over the tiles
-    for (int off = 1; off < kSphTiles; off <<= 1) {
-      const int v = (r == 0 && t >= off) ? tot[t - off] : 0;
-      __syncthreads();
-      if (r == 0) tot[t] += v;
-      __syncthreads();
-    }
-    const int tile0 = tot[t] - tsz[t];
-    if (r == 0) {
-      toff[t] = tile0;
-      if (t == kSphTiles - 1) toff[kSphTiles] = tot[t];
-    }
-    const int base = tile0 + part[r][t];
-    for (int q = q0; q < q1; q += 8) {
-      int v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = q + u < q1 ? pos[(int64_t)(q + u) * kSphTiles + t] : 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (q + u < q1) pos[(int64_t)(q + u) * kSphTiles + t] = v[u] + base;
-    }
-  }
-}
-
-// Item (m, point item q): the item's point indices into the list, each at
-// its recorded tile's range for this item (the order within a range is
-// immaterial: the grid sums are exact).  A count that disagrees with the
-// counting pass sets the model's flag, and the tile pass then spreads that
-// model's points directly.
-__global__ void __launch_bounds__(256) k_sph_pcot_fill(const GeomDev *__restrict__ geoms,
-                                                       const ModelDev *__restrict__ models,
-                                                       const Item *__restrict__ items, int n_it,
-                                                       const double *__restrict__ gauss,
-                                                       const int *__restrict__ st_ws,
-                                                       double *__restrict__ sgcot) {
-  __shared__ int cur[kSphTiles], rb[kSphTiles], rl[kSphTiles];   // fill count, range
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    if (st_ws[it.m] != 0) continue;          // uniform per block
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    const int np = sph_pitems(g.K);
-    int *pos = sph_gcot_int(sgcot, md, g.K);
-    const unsigned char *ptile = sph_gcot_ptile(sgcot, md, g.K);
-    const int *toff = pos + (int64_t)np * kSphTiles;
-    int *flag = pos + (int64_t)np * kSphTiles + kSphTiles + 1;
-    int *list = flag + 1;
-    rb[threadIdx.x] = pos[(int64_t)it.a * kSphTiles + threadIdx.x];
-    rl[threadIdx.x] = it.a + 1 < np ? pos[(int64_t)(it.a + 1) * kSphTiles + threadIdx.x]
-                                    : toff[threadIdx.x + 1];
-    cur[threadIdx.x] = 0;
-    __syncthreads();                         // ranges read, cur cleared
-    const int64_t P = sph_points(g.K), p0 = (int64_t)it.a * kSphPtsItem,
-                  p1 = min(P, p0 + kSphPtsItem);
-    for (int64_t p = p0 + threadIdx.x; p < p1; p += 256) {
-      const int tile = ptile[p];
-      const int at = rb[tile] + atomicAdd(&cur[tile], 1);
-      if (at < rl[tile]) list[at] = (int)p;
-    }
-    __syncthreads();
-    if (cur[threadIdx.x] != rl[threadIdx.x] - rb[threadIdx.x]) atomicOr(flag, 1);
-    __syncthreads();                         // before the next item rewrites cur, rb, rl
-  }
-}
-
-// The power of two that maps 1.6 x bound (the interpolation weights of a
-// point sum to at most 1.25^2 in magnitude) below 2^60; NaN for a
-// non-finite bound.
-__device__ inline double sph_gcot_scale(double bound) {
-  if (bound == 0.0) return 1.0;
-  if (!(bound < __builtin_inf())) return __builtin_nan("");
-  return ldexp(1.0, min(1000, 60 - ilogb(1.6 * bound)));
-}
-
-// The point cotangents of p onto the grid through the interpolation's
-// weights, in fixed point: into the LDS block acc (rows r0 .. r0 + kL - 1,
-// columns c0 .. c0 + kL - 1) where the stencil lies inside it, else
-// straight into the grid.
-constexpr int kTileL = kSphTileB + 5;   // a tile's stencils with one cell to spare
-constexpr int kTileSub = 4;             // list parts per point item in the tile pass
-__device__ inline void sph_spread_point(const GeomDev &g, const GeomDev *__restrict__ gp,
-                                        const double *tab, const SphAdj &adj,
-                                        const double *sinth, const SphGrid &sc, double sa,
-                                        double sb, int64_t p, unsigned long long *fx,
-                                        unsigned long long *acc, int r0, int c0) {
-  constexpr int N = kSphGridN;
-  double R, z, phi, psi;
-  sph_point_cot(g, gp, tab, adj, sinth, p, R, z, phi, psi);
-  const double x = asinh(R / sc.aR) * sc.iR, y = asinh(z / sc.aZ) * sc.iZ;
-  const int i0 = min(max((int)floor(x), 0), N - 3), l0 = min(max((int)floor(y), 0), N - 3);
-  double wx[4], wy[4];
-  lagrange4(x - i0, wx);
-  lagrange4(y - l0, wy);
-  const int ra = abs(i0 - 1), ca = abs(l0 - 1);
-  const bool in = acc && ra >= r0 && i0 + 2 < r0 + kTileL && ca >= c0 && l0 + 2 < c0 + kTileL &&
-                  i0 >= r0 && l0 >= c0;
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int row = abs(i0 - 1 + a);
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int col = abs(l0 - 1 + b);
-      const double w = wx[a] * wy[b];
-      const long long va = __double2ll_rn(phi * w * sa), vb = __double2ll_rn(psi * w * sb);
-      unsigned long long *c = in ? acc + ((row - r0) * kTileL + (col - c0)) * 2
-                                 : fx + ((int64_t)row * N + col) * 2;
-      if (va) atomicAdd(c, (unsigned long long)va);
-      if (vb) atomicAdd(c + 1, (unsigned long long)vb);
-    }
-  }
-}
-
-// Item (m, q) split in kTileSub parts: part s takes entries
-// q * kSphPtsItem + s * kSphPtsItem / kTileSub onwards (kSphPtsItem /
-// kTileSub of them) of the model's tile-sorted point list.  Per tile met
-// there, the entries' stencils are summed in an LDS block (fixed point, so
-// in any order) and the block is added to the grid; with the model's flag
-// set, the same range of points is spread straight onto the grid instead.
-__global__ void __launch_bounds__(256) k_sph_pcot_tiles(const GeomDev *__restrict__ geoms,
-                                                        const ModelDev *__restrict__ models,
-                                                        const Item *__restrict__ items, int n_it,
-                                                        const double *__restrict__ gauss,
-                                                        const int *__restrict__ st_ws,
-                                                        double *__restrict__ sens,
-                                                        double *__restrict__ sgcot) {
-  constexpr int N = kSphGridN;
-  __shared__ double sinth[kSphNT];
-  __shared__ double sh[256];
-  __shared__ unsigned long long acc[kTileL * kTileL * 2];
-  __shared__ int tr[2];
-  if (threadIdx.x < kSphNT) sinth[threadIdx.x] = sin(threadIdx.x * (0.5 * kPi / (kSphNT - 1)));
-  __syncthreads();
-  constexpr int kSub = kSphPtsItem / kTileSub;
-  for (int vi = blockIdx.x; vi < n_it * kTileSub; vi += gridDim.x) {
-    const Item it = items[vi / kTileSub];
-    const int sub = vi % kTileSub;
-    if (st_ws[it.m] != 0) continue;          // uniform per block
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    const SphAdj adj = sph_adj_of(sens, md, g);
-    const double *tab = gauss + md.gauss_off;
-    const int np = sph_pitems(g.K);
-    const int64_t P = sph_points(g.K), e0 = (int64_t)it.a * kSphPtsItem + sub * kSub,
-                  e1 = min(P, e0 + kSub);
-    if (e0 >= P) continue;                   // uniform: the model's last item ends early
-    double *bnd = sph_gcot_bounds(sgcot, md);
-    double ba = 0.0, bb = 0.0;
-    for (int q = threadIdx.x; q < np; q += 256) { ba += bnd[2 * q]; bb += bnd[2 * q + 1]; }
-    ba = block_sum256(ba, sh);
-    bb = block_sum256(bb, sh);
-    const double sa = sph_gcot_scale(ba), sb = sph_gcot_scale(bb);
-    if (it.a == 0 && sub == 0 && threadIdx.x == 0) { bnd[2 * np] = sa; bnd[2 * np + 1] = sb; }
-    if (!(sa == sa) || !(sb == sb)) continue;   // uniform: a non-finite cotangent
-    const SphGrid sc = sph_grid_scales(g, tab);
-    unsigned long long *fx = reinterpret_cast<unsigned long long *>(sph_gcot_fixed(sgcot, md));
-    const int *pos = sph_gcot_int(sgcot, md, g.K);
-    const int *toff = pos + (int64_t)np * kSphTiles;
-    const int flag = toff[kSphTiles + 1];
-    const int *list = toff + kSphTiles + 2;
-    if (flag) {                              // uniform
-      for (int64_t p = e0 + threadIdx.x; p < e1; p += 256)
-        sph_spread_point(g, geoms + md.geom, tab, adj, sinth, sc, sa, sb, p, fx, nullptr, 0, 0);
-      continue;
-    }
-    // the tiles whose list ranges meet [e0, e1)
-    const int t = threadIdx.x;
-    if (toff[t] <= e0 && e0 < toff[t + 1]) tr[0] = t;
-    if (toff[t] < e1 && e1 <= toff[t + 1]) tr[1] = t;
-    __syncthreads();
-    const int ta = tr[0], tb = tr[1];
-    __syncthreads();                         // tr read before the next item writes it
-    for (int tile = ta; tile <= tb; ++tile) {
-      const int64_t s0 = max(e0, (int64_t)toff[tile]), s1 = min(e1, (int64_t)toff[tile + 1]);
-      if (s0 >= s1) continue;                // uniform
-      const int r0 = (tile / kSphTilesAx) * kSphTileB - 2, c0 = (tile % kSphTilesAx) * kSphTileB - 2;
-      for (int e = t; e < kTileL * kTileL * 2; e += 256) acc[e] = 0ull;
-      __syncthreads();
-      for (int64_t e = s0 + t; e < s1; e += 256)
-        sph_spread_point(g, geoms + md.geom, tab, adj, sinth, sc, sa, sb, list[e], fx, acc, r0, c0);
-      __syncthreads();
-      for (int e = t; e < kTileL * kTileL; e += 256) {
-        const int row = r0 + e / kTileL, col = c0 + e % kTileL;
-        const unsigned long long va = acc[2 * e], vb = acc[2 * e + 1];
-        if (row >= 0 && row < N && col >= 0 && col < N) {
-          unsigned long long *c = fx + ((int64_t)row * N + col) * 2;
-          if (va) atomicAdd(c, va);
-          if (vb) atomicAdd(c + 1, vb);
-        }
-      }
-      __syncthreads();                       // the block is read before it is cleared
-    }
-  }
-}
-
-// Item (m, block of 1024 grid points): the fixed-point grid cotangent back
-// to FP32 (NaN for a non-finite cotangent).
-__global__ void __launch_bounds__(256) k_sph_pcot_fix(const GeomDev *__restrict__ geoms,
-                                                      const ModelDev *__restrict__ models,
-                                                      const Item *__restrict__ items, int n_it,
-                                                      const int *__restrict__ st_ws,
-                                                      double *__restrict__ sgcot) {
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    if (st_ws[it.m] != 0) continue;
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    const double *bnd = sph_gcot_bounds(sgcot, md);
-    const int np = sph_pitems(g.K);
-    const double sa = bnd[2 * np], sb = bnd[2 * np + 1];
-    const long long *fx = sph_gcot_fixed(sgcot, md);
-    float *fl = sph_gcot_float(sgcot, md);
-    for (int e = it.a * 1024 + threadIdx.x; e < (it.a + 1) * 1024; e += 256) {
-      fl[2 * e] = (float)(sa == sa ? (double)fx[2 * e] / sa : sa);
-      fl[2 * e + 1] = (float)(sb == sb ? (double)fx[2 * e + 1] / sb : sb);
-    }
-  }
-}
-
-// Item (m, block of 32 terms, part ip of kSphIParts): wave w contracts grid
-// rows 32 (4 ip + w) .. + 31 with the terms' z factors, D = Phi B and
-// Dz = Phi (z^2 B) (and for psi), reading four grid columns per lane and
-// 16 bytes at a time; then per term the row sums with 2^(cx R_i^2) and
-// R_i^2 2^(cx R_i^2), FP32 per lane, FP64 across lanes and waves (fixed
-// order).  Output: the part's [S_phi, S_psi, R^2 S_phi, R^2 S_psi, z^2 S_phi,
-// z^2 S_psi] per term, as k_sph_sens's ranges.
-__global__ void __launch_bounds__(256) k_sph_sens_grid(const GeomDev *__restrict__ geoms,
-                                                       const ModelDev *__restrict__ models,
-                                                       const Item *__restrict__ items, int n_it,
-                                                       const double *__restrict__ gauss,
-                                                       const float4 *__restrict__ terms,
-                                                       const int *__restrict__ st_ws,
-                                                       double *__restrict__ sens,
-                                                       double *__restrict__ sgcot) {
-  constexpr int N = kSphGridN;
-  __shared__ __attribute__((aligned(16))) float zsq[N];
-  __shared__ float rsq[N];
-  __shared__ double red[4][6][32];
-  const int lane = threadIdx.x & 63, c32 = lane & 31, kh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const v16f zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
-    const Item it = items[i];
-    if (st_ws[it.m] != 0) continue;          // uniform per block
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    const SphGrid sc = sph_grid_scales(g, gauss + md.gauss_off);
-    __syncthreads();                         // the previous item's reads of zsq, rsq, red
-    for (int l = threadIdx.x; l < N; l += 256) {
-      const double zv = sc.aZ * sinh(l / sc.iZ), rv = sc.aR * sinh(l / sc.iR);
-      zsq[l] = (float)(zv * zv);
-      rsq[l] = (float)(rv * rv);
-    }
-    __syncthreads();
-    const int Tp = sph_terms_padded(g.J1, g.n_u);
-    const int t = 32 * it.a + c32;           // < Tp (Tp is a multiple of 64)
-    const float4 c = terms[md.term_off + t];
-    const float *fl = sph_gcot_float(sgcot, md);
-    const int row = 32 * (kSphIParts * it.b + wave) + c32;
-    const float *fr = fl + (int64_t)row * N * 2;
-    v16f dP = zero, dPz = zero, dT = zero, dTz = zero;
-    for (int q = 0; q < N / 8; ++q) {
-      const int l0 = 8 * q + 4 * kh;
-      const float4 pa = *reinterpret_cast<const float4 *>(fr + 2 * l0);
-      const float4 pb = *reinterpret_cast<const float4 *>(fr + 2 * l0 + 4);
-      const float4 zz = *reinterpret_cast<const float4 *>(&zsq[l0]);
-      const float ap[4] = {pa.x, pa.z, pb.x, pb.z}, at[4] = {pa.y, pa.w, pb.y, pb.w};
-      const float z4[4] = {zz.x, zz.y, zz.z, zz.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float b = fast_exp2(c.y * z4[j]), bz = b * z4[j];
-        dP = __builtin_amdgcn_mfma_f32_32x32x2f32(ap[j], b, dP, 0, 0, 0);
-        dPz = __builtin_amdgcn_mfma_f32_32x32x2f32(ap[j], bz, dPz, 0, 0, 0);
-        dT = __builtin_amdgcn_mfma_f32_32x32x2f32(at[j], b, dT, 0, 0, 0);
-        dTz = __builtin_amdgcn_mfma_f32_32x32x2f32(at[j], bz, dTz, 0, 0, 0);
-      }
-    }
-    // rows of this lane: 32 (4 ip + w) + mfma_row(r, lane); column = term t
-    float s[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int rbase = 32 * (kSphIParts * it.b + wave);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float r2 = rsq[rbase + mfma_row(r, lane)];
-      const float e = fast_exp2(c.x * r2);
-      s[0] = fmaf(e, dP[r], s[0]);
-      s[1] = fmaf(e, dT[r], s[1]);
-      s[2] = fmaf(e * r2, dP[r], s[2]);
-      s[3] = fmaf(e * r2, dT[r], s[3]);
-      s[4] = fmaf(e, dPz[r], s[4]);
-      s[5] = fmaf(e, dTz[r], s[5]);
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      double v = (double)s[k];
-      v += __shfl_xor(v, 32, 64);
-      if (kh == 0) red[wave][k][c32] = v;
-    }
-    __syncthreads();
-    if (wave == 0 && kh == 0) {
-      const SphAdj adj = sph_adj_of(sens, md, g);
-      double *o = adj.sparts + ((int64_t)it.b * Tp + t) * 6;
-#pragma unroll
-      for (int k = 0; k < 6; ++k) o[k] = ((red[0][k][c32] + red[1][k][c32]) + red[2][k][c32]) + red[3][k][c32];
-    }
   }
 }
 
@@ -4169,44 +3490,22 @@ void launch_sb_adjoint(const GeomDev *g, const ModelDev *m, const Item *it, int 
                      sbp);
 }
 void launch_sph_terms(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                      const double *gauss, const int *st_ws, float4 *terms, hipStream_t st) {
+                      const double *gauss, const int *st_ws, float4 *terms, double *pol,
+                      hipStream_t st) {
   hipLaunchKernelGGL(k_sph_terms, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, gauss,
-                     st_ws, terms);
+                     st_ws, terms, pol);
 }
 void launch_sph_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                        const double *gauss, const float4 *terms, const int *st_ws,
-                        const float *sgrid, double *table, hipStream_t st) {
-  if (sgrid)
-    hipLaunchKernelGGL(k_sph_moments<true>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
-                       gauss, terms, st_ws, sgrid, table);
-  else
-    hipLaunchKernelGGL(k_sph_moments<false>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it,
-                       n_it, gauss, terms, st_ws, sgrid, table);
-}
-void launch_sph_grid(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                     const double *gauss, const float4 *terms, const int *st_ws, float *sgrid,
-                     bool adjoint, hipStream_t st) {
-  if (adjoint)
-    hipLaunchKernelGGL(k_sph_grid<6>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, gauss,
-                       terms, st_ws, sgrid);
-  else
-    hipLaunchKernelGGL(k_sph_grid<2>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, gauss,
-                       terms, st_ws, sgrid);
-}
-void launch_sph_grid_reduce(const ModelDev *m, const Item *it, int n_it, const int *st_ws,
-                            float *sgrid, bool adjoint, hipStream_t st) {
-  hipLaunchKernelGGL(k_sph_grid_reduce, dim3(grid_of(n_it)), dim3(256), 0, st, m, it, n_it, st_ws,
-                     sgrid, adjoint ? 1 : 0);
+                        const double *gauss, const float4 *terms, const int *st_ws, double *table,
+                        hipStream_t st) {
+  hipLaunchKernelGGL(k_sph_moments, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, gauss,
+                     terms, st_ws, table);
 }
 void launch_sph_moments_jac(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                             const double *gauss, const float4 *terms, const int *st_ws,
-                            const float *sgrid6, double *table, double *sens, hipStream_t st) {
-  if (sgrid6)
-    hipLaunchKernelGGL(k_sph_moments_jac<true>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it,
-                       n_it, gauss, terms, st_ws, sgrid6, table, sens);
-  else
-    hipLaunchKernelGGL(k_sph_moments_jac<false>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it,
-                       n_it, gauss, terms, st_ws, sgrid6, table, sens);
+                            double *table, double *sens, hipStream_t st) {
+  hipLaunchKernelGGL(k_sph_moments_jac, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
+                     gauss, terms, st_ws, table, sens);
 }
 void launch_sph_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                     const double *gauss, const int *st_ws, const double *table, double *pix,
@@ -4214,38 +3513,26 @@ void launch_sph_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_i
   hipLaunchKernelGGL(k_sph_num, dim3(grid_of(n_it)), dim3(64 * kLosLanes), 0, st, g, m, it, n_it,
                      gauss, st_ws, table, pix);
 }
-void launch_sph_adjoint(const GeomDev *g, const ModelDev *m, int n, const Item *it_los,
-                        int n_los, const Item *it_cell, int n_cell, const Item *it_sens,
-                        int n_sens, const Item *it_tile, int n_tile, const Item *it_pcot,
-                        int n_pcot, const Item *it_pfix, int n_pfix, const Item *it_sgs,
-                        int n_sgs, ParamsDev p, const double *gauss, const float4 *terms,
-                        const int *st_ws, const double *table, const double *pix,
-                        const double *sbp, double *sens, double *sgcot, GradsDev out,
-                        hipStream_t st) {
+void launch_sph_adjoint(const GeomDev *g, const ModelDev *m, int n, const Item *it_los, int n_los,
+                        const Item *it_cell, int n_cell, const double *gauss, const int *st_ws,
+                        const double *table, const double *pix, double *sens, hipStream_t st) {
   hipLaunchKernelGGL(k_sph_zero, dim3(grid_of(n)), dim3(kZeroThreads), 0, st, g, m, n, gauss,
                      st_ws, pix, sens);
   hipLaunchKernelGGL(k_sph_num_adj, dim3(grid_of(n_los)), dim3(256), 0, st, g, m, it_los, n_los,
                      gauss, st_ws, table, pix, sens);
   hipLaunchKernelGGL(k_sph_dtab_fix, dim3(grid_of(n)), dim3(256), 0, st, g, m, n, st_ws, sens);
-  hipLaunchKernelGGL(k_sph_rows, dim3(grid_of(n_cell)), dim3(64), 0, st, g, m, it_cell, n_cell,
+  hipLaunchKernelGGL(k_sph_rows, dim3(grid_of(n_cell)), dim3(256), 0, st, g, m, it_cell, n_cell,
                      gauss, st_ws, sens);
-  if (sgcot) {
-    hipLaunchKernelGGL(k_sph_pcot_bound, dim3(grid_of(n_pcot)), dim3(256), 0, st, g, m, it_pcot,
-                       n_pcot, gauss, st_ws, sens, sgcot);
-    hipLaunchKernelGGL(k_sph_pcot_scan, dim3(grid_of(n)), dim3(kSphTiles * kScanParts), 0, st, g,
-                       m, n, st_ws, sgcot);
-    hipLaunchKernelGGL(k_sph_pcot_fill, dim3(grid_of(n_pcot)), dim3(256), 0, st, g, m, it_pcot,
-                       n_pcot, gauss, st_ws, sgcot);
-    hipLaunchKernelGGL(k_sph_pcot_tiles, dim3(grid_of(n_pcot * kTileSub)), dim3(256), 0, st, g, m,
-                       it_pcot, n_pcot, gauss, st_ws, sens, sgcot);
-    hipLaunchKernelGGL(k_sph_pcot_fix, dim3(grid_of(n_pfix)), dim3(256), 0, st, g, m, it_pfix,
-                       n_pfix, st_ws, sgcot);
-    hipLaunchKernelGGL(k_sph_sens_grid, dim3(grid_of(n_sgs)), dim3(256), 0, st, g, m, it_sgs,
-                       n_sgs, gauss, terms, st_ws, sens, sgcot);
-  } else {
-    hipLaunchKernelGGL(k_sph_sens, dim3(grid_of(n_sens)), dim3(256), 0, st, g, m, it_sens, n_sens,
-                       gauss, terms, st_ws, sens);
-  }
+}
+void launch_sph_sens(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                     const double *gauss, const float4 *terms, const int *st_ws, double *sens,
+                     hipStream_t st) {
+  hipLaunchKernelGGL(k_sph_sens, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, gauss,
+                     terms, st_ws, sens);
+}
+void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it_tile, int n_tile,
+                      ParamsDev p, const double *gauss, const float4 *terms, const int *st_ws,
+                      const double *sbp, double *sens, GradsDev out, hipStream_t st) {
   hipLaunchKernelGGL(k_sph_sens_cells, dim3(grid_of(n_tile * kSphCellParts)), dim3(256), 0, st, g,
                      m, it_tile, n_tile, gauss, terms, st_ws, sens);
   hipLaunchKernelGGL(k_sph_chain, dim3(grid_of(n_tile)), dim3(256), 0, st, g, m, it_tile, n_tile,
