@@ -119,15 +119,14 @@ typedef struct {
  *       per model and integrated along the line of sight (64 nodes);
  *       autotune and launch do not apply.  The forward takes the
  *       tracer-independent potential sums G, G_theta at the characteristic
- *       nodes from a per-model grid (512 x 512 points asinh-spaced in R and
- *       z, a matrix-core contraction over the (j, u) terms, 4-point Lagrange
- *       interpolation; within 3.4e-7 of the direct sums on the IFU-scale
- *       model); with form = 1 it sums the terms at every node instead.  The
- *       adjoint differentiates the same grid model (with form = 1, the
- *       direct sums); when jam_vjp recomputes V it takes it from the
- *       forward path (bitwise equal to jam_eval's V).  The grid's term
- *       sensitivities spread the point cotangents onto the grid as 64-bit
- *       fixed-point integers, so gradients stay bitwise reproducible.
+ *       nodes from a per-model polar grid (384 radii x 64 angles, the (j, u)
+ *       terms summed at every point, 6 x 8-point Lagrange interpolation, within
+ *       1e-7 of G at axial ratios of 0.05 and more); with form = 1 it sums the
+ *       terms at every node instead.  The adjoint differentiates the same grid
+ *       model (with form = 1, the direct sums); when jam_vjp recomputes V it
+ *       takes it from the forward path (bitwise equal to jam_eval's V).  The
+ *       grid's term sensitivities spread the point cotangents onto the grid in
+ *       a fixed order, so gradients stay bitwise reproducible.
  *       jam_vjp / jam_vjp_chi2 run the
  *       model's own adjoint (recomputing the moment table in one pass with
  *       the cotangent-free sums of its adjoint; the table cotangent is

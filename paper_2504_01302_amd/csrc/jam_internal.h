@@ -347,7 +347,7 @@ void launch_sph_moments_jac(const GeomDev *g, const ModelDev *m, const Item *it,
                             const double *gauss, const float4 *terms, const int *st_ws,
                             double *table, double *sens, hipStream_t st);
 // Adjoint of the spherically aligned model, after the bin adjoint has filled
-// lambda_N and lambda_I: zero the table cotangents (block per model), the
+// lambda_N and lambda_I: zero the table cotangents, the
 // line-of-sight adjoint (items (m, 64-pixel block)) and the rows of the
 // characteristic integrals' adjoint (items (m, 64 table points)); the term-major
 // sensitivities over point ranges (items (m, 256-term tile, range)), or
@@ -364,8 +364,9 @@ void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it
                       ParamsDev p, const double *gauss, const float4 *terms, const int *st_ws,
                       const double *sbp, double *sens, GradsDev out, hipStream_t st);
 // Adjoint of the spherically aligned model.  Per model, in the sensitivity
-// region (doubles): the table cotangent [kSphNR*kSphNT][3], per (tracer,
-// cell) rows (d/dbeta, d/dalphaq, d/dnu0) [K][cells][3], line-of-sight
+// region (doubles): the table cotangent [kSphNR*kSphNT][3], per tracer and
+// 64 cells the rows' sums (d/dbeta, d/dalphaq, d/dnu0) [K][cells/64][3],
+// line-of-sight
 // partials (d/di at fixed node scale, d/d node scale) per 64-pixel block,
 // per-term sensitivities per point range [n_rng][Tp][6] and of the cell
 // points per 256-cell part [kSphCellParts][Tp][3], per-term chain values
@@ -374,6 +375,8 @@ void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it
 // characteristic integrals' adjoint per (tracer, cell) [K][cells][8] and
 // G_phi per cell [cells].  n_rng is ModelDev::n_sens_parts.
 constexpr int kSphCells = kSphNR * kSphNT;
+constexpr int kSphRowParts = kSphCells / 64;
+static_assert(kSphRowParts * 64 == kSphCells && kSphRowParts <= 64, "a lane per part");
 // The cell sensitivities come in parts of 256 cells, summed in order.
 constexpr int kSphCellParts = kSphCells / 256;
 static_assert(kSphCellParts * 256 == kSphCells, "whole 256-cell parts");
@@ -381,7 +384,7 @@ struct SphAdj {
   double *dtab, *rows, *losp, *sparts, *cparts, *tchain, *dscale, *jac, *gphi;
 };
 __host__ __device__ inline int64_t sph_adj_size(int K, int n_pix, int Tp, int n_rng) {
-  return 3LL * kSphCells + 3LL * kSphCells * K + 2LL * ((n_pix + 63) / 64) +
+  return 3LL * kSphCells + 3LL * kSphRowParts * K + 2LL * ((n_pix + 63) / 64) +
          6LL * n_rng * Tp + (3LL * kSphCellParts + 2) * Tp + 1 + 8LL * kSphCells * K + kSphCells;
 }
 __host__ __device__ inline SphAdj sph_adj_layout(double *base, int K, int n_pix, int Tp,
@@ -389,7 +392,7 @@ __host__ __device__ inline SphAdj sph_adj_layout(double *base, int K, int n_pix,
   SphAdj a;
   a.dtab = base;
   a.rows = a.dtab + 3LL * kSphCells;
-  a.losp = a.rows + 3LL * kSphCells * K;
+  a.losp = a.rows + 3LL * kSphRowParts * K;
   a.sparts = a.losp + 2LL * ((n_pix + 63) / 64);
   a.cparts = a.sparts + 6LL * n_rng * Tp;
   a.tchain = a.cparts + 3LL * kSphCellParts * Tp;

@@ -23,6 +23,7 @@
 // are FP64.
 #include "jam_device.h"
 #include "jam_internal.h"
+#include "jam_sph_math.h"
 
 #include <hip/hip_runtime.h>
 #include <algorithm>
@@ -2299,10 +2300,8 @@ __device__ inline void sph_radial_weights(int xi, double fx, double *ew, double 
   }
 }
 
-// Angular weights, Catmull-Rom in theta over the angles yi - 1 .. yi + 2;
-// the moments are even about theta = 0 and theta = pi/2, so a missing angle
-// is the mirror image of the one inside, folded into the weights.
-__device__ inline void sph_angular_weights(int yi, double fy, double *ew, double *dew) {
+// Angular weights, Catmull-Rom in theta over the angles yi - 1 .. yi + 2.
+__device__ inline void sph_angular_weights(double fy, double *ew, double *dew) {
   const double f2 = fy * fy, f3 = f2 * fy;
   ew[0] = 0.5 * (-f3 + 2.0 * f2 - fy);
   ew[1] = 0.5 * (3.0 * f3 - 5.0 * f2 + 2.0);
@@ -2312,18 +2311,86 @@ __device__ inline void sph_angular_weights(int yi, double fy, double *ew, double
   dew[1] = 0.5 * (9.0 * f2 - 10.0 * fy);
   dew[2] = 0.5 * (-9.0 * f2 + 8.0 * fy + 1.0);
   dew[3] = 0.5 * (3.0 * f2 - 2.0 * fy);
-  if (yi == 0) {                  // angle -1 mirrors angle 1 (= yi + 1)
-    ew[2] += ew[0];
-    ew[0] = 0.0;
-    dew[2] += dew[0];
-    dew[0] = 0.0;
+}
+
+// ---------------------------------------------------------------------------
+// Line of sight.  The table of a model fits the LDS (80 KB), with a mirrored
+// column on either side (the moments are even about theta = 0 and pi / 2; slot
+// s holds angle s - 1), so that a stencil row is twelve contiguous doubles.
+// A block takes a contiguous range of the 64-pixel items, loading the table
+// where the model changes; 16 lanes per pixel, four nodes each (the adjoint
+// lays its lanes out otherwise).
+// Node quantities that no pixel changes are computed once per model.
+// ---------------------------------------------------------------------------
+constexpr int kLosThreads = 1024, kLosAdjThreads = 512, kLosBlocks = 256;
+constexpr int kLosCols = kSphNT + 2;
+
+// Nodes z' = a sinh(w), w on [-W, W] by the composite rule, a = min_k sigma_k
+// q_k / 4, a sinh(W) = 12 max_k sigma_k.
+struct LosNode {
+  double zp, wz;           // position, weight
+  double dzp, dwz;         // their derivatives with respect to a (adjoint)
+};
+struct LosModel {
+  double si, ci;
+};
+// One whole wave, lane = node.
+__device__ inline void los_setup(const GeomDev &g, const double *tab, LosNode *nodes, LosModel &m) {
+  const int K = g.K, lane = threadIdx.x & 63;
+  const double *mt = tab + 4 * K;
+  double smin = 1e300, smax = 0.0;
+  for (int k = lane; k < K; k += 64) {
+    const double sk = sqrt(0.5 / tab[k]), qk = sqrt(tab[k] / tab[K + k]);
+    smin = fmin(smin, sk * qk);
+    smax = fmax(smax, sk);
   }
-  if (yi + 2 > kSphNT - 1) {      // angle NT mirrors angle NT - 2 (= yi)
-    ew[1] += ew[3];
-    ew[3] = 0.0;
-    dew[1] += dew[3];
-    dew[3] = 0.0;
+  for (int o = 32; o > 0; o >>= 1) {
+    smin = fmin(smin, __shfl_xor(smin, o, 64));
+    smax = fmax(smax, __shfl_xor(smax, o, 64));
   }
+  const double a = 0.25 * smin, cW = 12.0 * smax, W = asinh(cW / a);
+  const double Wa = -(cW / (a * a)) / sqrt(1.0 + (cW / a) * (cW / a));   // dW/da
+  const double hw = 2.0 * W / kSphSeg, glx = g.gl8_x[lane & 7], glw = g.gl8_w[lane & 7];
+  const double om = -1.0 + ((lane >> 3) + 0.5 + 0.5 * glx) / 4.0;         // w = W om
+  const double w = -W + ((lane >> 3) + 0.5 + 0.5 * glx) * hw;
+  // sinh w, cosh w from one exponential (|w| > 0.004 W at every node)
+  const double ex = exp(w), iex = 1.0 / ex, shw = 0.5 * (ex - iex), chw = 0.5 * (ex + iex);
+  nodes[lane] = LosNode{a * shw, 0.5 * glw * hw * a * chw, shw + a * chw * om * Wa,
+                        0.5 * glw * (2.0 / kSphSeg) *
+                            (Wa * a * chw + W * chw + W * a * shw * om * Wa)};
+  if (lane == 0) m = LosModel{sqrt(mt[3 * g.J1]), sqrt(mt[3 * g.J1 + 1])};
+}
+// The whole block: table with mirrored columns to LDS.
+__device__ inline void los_table(const double *__restrict__ T, double *t) {
+  for (int e = threadIdx.x; e < kSphNR * kLosCols * 3; e += blockDim.x) {
+    const int row = e / (kLosCols * 3), q = e % (kLosCols * 3), s = q / 3, f = q % 3;
+    const int c = s == 0 ? 1 : (s == kLosCols - 1 ? kSphNT - 2 : s - 1);
+    t[e] = T[(row * kSphNT + c) * 3 + f];
+  }
+}
+// A node of a pixel: where it falls in the table.
+struct LosPoint {
+  double X, Y, Z, iR, ir;  // position; 1 / R (zero on the axis), 1 / r
+  double xf;               // radial index (fractional); fx, fy the cell fractions
+  double fx, fy;
+  int xi, yi;
+};
+__device__ __forceinline__ LosPoint los_point(const GeomDev &g, double x, double y, double zp,
+                                              const LosModel &m, double idlnr, const LosMath &mt) {
+  LosPoint p;
+  p.X = x;
+  p.Y = zp * m.si - y * m.ci;
+  p.Z = y * m.si + zp * m.ci;
+  const double R2 = fma(p.X, p.X, p.Y * p.Y), r2 = fma(p.Z, p.Z, R2);
+  p.iR = R2 > 0.0 ? rsq64(fmax(R2, 1e-300)) : 0.0;
+  p.ir = rsq64(r2);
+  p.xf = fma(0.5, pol_log(r2, mt), -g.sph_lnr0) * idlnr;
+  const double yf = los_atan(R2 * p.iR, fabs(p.Z), mt) * ((kSphNT - 1) / (0.5 * kPi));
+  p.xi = min(max((int)floor(p.xf), 0), kSphNR - 2);
+  p.yi = min((int)yf, kSphNT - 2);
+  p.fx = fmin(fmax(p.xf - p.xi, 0.0), 1.0);
+  p.fy = fmin(fmax(yf - p.yi, 0.0), 1.0);
+  return p;
 }
 
 // Node of tracer k's characteristic through table point (r, theta): the same
@@ -2360,216 +2427,245 @@ __device__ inline void sph_cell(const GeomDev &g, int cell, double &r, double &s
 }
 
 
-// Start of the line-of-sight adjoint, block per model: clears the table
-// cotangent and fixes its fixed-point scale.  Every contribution to the
-// cotangent is lambda_N w_z (n.e_f)^2 times interpolation weights, so the
+// Start of the line-of-sight adjoint, kZeroParts blocks per model: each clears
+// its share of the table cotangent and sums |lambda_N| over its share of the
+// pixels (into SphAdj::tchain, which the per-term chain writes later).
+constexpr int kZeroParts = 32;
+__global__ void __launch_bounds__(256) k_sph_zero(const GeomDev *__restrict__ geoms,
+                                                  const ModelDev *__restrict__ models, int n,
+                                                  const int *__restrict__ st_ws,
+                                                  const double *__restrict__ pix,
+                                                  double *__restrict__ sens) {
+  __shared__ double sh[4];
+  static_assert(3 * kSphCells % kZeroParts == 0, "equal shares");
+  for (int i = blockIdx.x; i < n * kZeroParts; i += gridDim.x) {
+    const int m = i / kZeroParts, part = i % kZeroParts;
+    const ModelDev md = models[m];
+    const GeomDev &g = geoms[md.geom];
+    const SphAdj adj = sph_adj_of(sens, md, g);
+    unsigned long long *d = reinterpret_cast<unsigned long long *>(adj.dtab);
+    constexpr int kShare = 3 * kSphCells / kZeroParts;
+    for (int e = threadIdx.x; e < kShare; e += 256) d[part * kShare + e] = 0ull;
+    if (st_ws[m] != 0) continue;   // uniform per block
+    const double *lam = pix + md.pix_off + 2 * (int64_t)g.n_pix;
+    double s = 0.0;
+    for (int q = part * 256 + threadIdx.x; q < g.n_pix; q += kZeroParts * 256) s += fabs(lam[q]);
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) adj.tchain[part] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+    __syncthreads();                 // sh read before the next item
+  }
+}
+
+// The table cotangent's fixed-point scale, by one whole wave.  Every
+// contribution is lambda_N w_z (n.e_f)^2 times interpolation weights, so the
 // sum of their magnitudes over all pixels, nodes and cells is at most
 // sum_p |lambda_N| x sum_nodes w_z (the node rule integrates a cosh(w) over
 // [-W, W]: 2 a sinh W = 24 max sigma_k, taken as 25) x sum |radial weights|
 // x sum |angular weights| (each below 2; sum_f (n.e_f)^2 = 1).  The scale is
 // the power of two that maps that bound below 2^61 (at most 2^1000, for
 // tiny bounds), so the 64-bit integer sums cannot overflow and do not depend
-// on the order of the additions.
-// A non-finite bound stores NaN, which k_sph_dtab_fix turns into a NaN
-// cotangent.
-constexpr int kZeroThreads = 1024;
-__global__ void __launch_bounds__(kZeroThreads) k_sph_zero(const GeomDev *__restrict__ geoms,
-                                                           const ModelDev *__restrict__ models,
-                                                           int n, const double *__restrict__ gauss,
-                                                           const int *__restrict__ st_ws,
-                                                           const double *__restrict__ pix,
-                                                           double *__restrict__ sens) {
-  constexpr int kWaves = kZeroThreads / 64;
-  __shared__ double sh[kWaves];
-  for (int m = blockIdx.x; m < n; m += gridDim.x) {
-    const ModelDev md = models[m];
-    const GeomDev g = geoms[md.geom];
-    const SphAdj adj = sph_adj_of(sens, md, g);
-    unsigned long long *d = reinterpret_cast<unsigned long long *>(adj.dtab);
-    for (int i = threadIdx.x; i < 3 * kSphCells; i += kZeroThreads) d[i] = 0ull;
-    if (st_ws[m] != 0) continue;   // uniform per block
-    const double *lam = pix + md.pix_off + 2 * (int64_t)g.n_pix;
-    // eight loads in flight per thread; partial sums added in a fixed order,
-    // then the lanes by butterflies and the waves in order
-    double sp[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int q0 = 0; q0 < g.n_pix; q0 += 8 * kZeroThreads) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int q = q0 + u * kZeroThreads + threadIdx.x;
-        if (q < g.n_pix) sp[u] += fabs(lam[q]);
-      }
-    }
-    double s = ((sp[0] + sp[1]) + (sp[2] + sp[3])) + ((sp[4] + sp[5]) + (sp[6] + sp[7]));
-    s = wave_sum(s);
-    __syncthreads();                 // the previous model's reads of sh
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      s = 0.0;
-      for (int w = 0; w < kWaves; ++w) s += sh[w];
-      const double *tab = gauss + md.gauss_off;
-      double smax = 0.0;
-      for (int k = 0; k < g.K; ++k) smax = fmax(smax, sqrt(0.5 / tab[k]));
-      const double bound = s * 25.0 * smax * 4.0;
-      double scale = __builtin_nan("");
-      if (bound == 0.0) scale = 1.0;
-      else if (bound < __builtin_inf()) scale = ldexp(1.0, min(1000, 60 - ilogb(bound)));
-      adj.dscale[0] = scale;
-    }
-  }
+// on the order of the additions.  A non-finite bound gives NaN, which
+// k_sph_dtab_fix turns into a NaN cotangent.
+__device__ inline double sph_dtab_scale(const GeomDev &g, const double *tab, const SphAdj &adj) {
+  const int lane = threadIdx.x & 63;
+  const double s = wave_sum(lane < kZeroParts ? adj.tchain[lane] : 0.0);
+  double smax = 0.0;
+  for (int k = lane; k < g.K; k += 64) smax = fmax(smax, sqrt(0.5 / tab[k]));
+  for (int o = 32; o > 0; o >>= 1) smax = fmax(smax, __shfl_xor(smax, o, 64));
+  const double bound = s * 25.0 * smax * 4.0;
+  if (bound == 0.0) return 1.0;
+  if (!(bound < __builtin_inf())) return __builtin_nan("");
+  return ldexp(1.0, min(1000, 60 - ilogb(bound)));
 }
 
-// End of the line-of-sight adjoint, block per model: the fixed-point table
-// cotangent back to FP64 in place.
+// The fixed-point table cotangent to FP64: kFixParts blocks per model.
+constexpr int kFixParts = 9;
 __global__ void __launch_bounds__(256) k_sph_dtab_fix(const GeomDev *__restrict__ geoms,
                                                       const ModelDev *__restrict__ models, int n,
                                                       const int *__restrict__ st_ws,
                                                       double *__restrict__ sens) {
-  for (int m = blockIdx.x; m < n; m += gridDim.x) {
-    if (st_ws[m] != 0) continue;   // uniform per block
+  constexpr int kShare = 3 * kSphCells / kFixParts;
+  static_assert(kShare * kFixParts == 3 * kSphCells, "equal shares");
+  for (int i = blockIdx.x; i < n * kFixParts; i += gridDim.x) {
+    const int m = i / kFixParts, e0 = (i % kFixParts) * kShare;
+    if (st_ws[m] != 0) continue;
     const ModelDev md = models[m];
-    const GeomDev g = geoms[md.geom];
-    const SphAdj adj = sph_adj_of(sens, md, g);
+    const SphAdj adj = sph_adj_of(sens, md, geoms[md.geom]);
     const double scale = adj.dscale[0];
     long long *d = reinterpret_cast<long long *>(adj.dtab);
-    for (int i = threadIdx.x; i < 3 * kSphCells; i += 256) {
-      const long long v = d[i];
-      adj.dtab[i] = scale == scale ? (double)v / scale : scale;
+    for (int e = e0 + threadIdx.x; e < e0 + kShare; e += 256) {
+      const long long v = d[e];
+      adj.dtab[e] = scale == scale ? (double)v / scale : scale;
     }
   }
 }
 
-// Line-of-sight kernels: four lanes per pixel, each taking a quarter of the
-// line-of-sight nodes.
-constexpr int kLosLanes = 4;                       // lanes per pixel
-constexpr int kLosNodes = kSphNodes / kLosLanes;   // nodes per lane
+// v rounded to an integer, |v| < 2^62: two halves by adding 1.5 x 2^52 (the
+// conversion instructions stop at 32 bits).
+__device__ __forceinline__ long long los_round(double v) {
+  constexpr double kM = 6755399441055744.0;
+  const double t = fma(v, 0x1p-30, kM), u = fma(t - kM, -0x1p30, v) + kM;
+  return (long long)__double2loint(t) * (1ll << 30) + (long long)__double2loint(u);
+}
 
-// Line-of-sight adjoint.  Item (m, 64-pixel block), one workgroup each, the
-// lanes as in k_sph_num.  The table cotangent receives lambda_N w_z
-// (n.e_f)^2 times the interpolation weights, each rounded to a 64-bit
-// fixed-point integer at the model's scale (k_sph_zero), accumulated in a
+// Line-of-sight adjoint.  Item (m, a): the pixels a, a + n, a + 2 n, .. of the
+// n = ceil(n_pix / 64) items, lane = pixel, the nodes over the waves: pixels
+// spread over the map at the same node, so that the lanes of an atomic add meet
+// few equal cells (neighbouring pixels, or the many nodes of one pixel that are
+// near the plane of the sky, share theirs).  The table cotangent receives
+// lambda_N w_z (n.e_f)^2 times the interpolation weights, each rounded to a
+// 64-bit fixed-point integer at the model's scale, accumulated in a
 // block-private LDS copy of the table (integer LDS atomics) and added to the
-// model's table once per block (integer global atomics, non-zero entries
-// only): integer sums, so the result does not depend on the order of the
-// additions.  The derivatives of the node's integrand at fixed table with
+// model's table once per block and model (integer global atomics, non-zero
+// entries only): integer sums, so the result does not depend on the order of
+// the additions.  The derivatives of the node's integrand at fixed table with
 // respect to i (line of sight and node position) and to the node scale a
-// are summed per block in a fixed order (butterflies over each wave, then
+// are summed per item in a fixed order (butterflies over each wave, then
 // the waves in order).
-__global__ void __launch_bounds__(256) k_sph_num_adj(const GeomDev *__restrict__ geoms,
-                                                     const ModelDev *__restrict__ models,
-                                                     const Item *__restrict__ items, int n_it,
-                                                     const double *__restrict__ gauss,
-                                                     const int *__restrict__ st_ws,
-                                                     const double *__restrict__ table,
-                                                     const double *__restrict__ pix,
-                                                     double *__restrict__ sens) {
+// FP64 issue bounds it, half of it the 48 roundings and LDS atomics per node.
+// Measured, 46,225 pixels: 256-thread blocks reading the table from global
+// memory with library functions and all node quantities per pixel 303 us, this
+// 205 us.
+__global__ void __launch_bounds__(kLosAdjThreads) k_sph_num_adj(
+    const GeomDev *__restrict__ geoms, const ModelDev *__restrict__ models,
+    const Item *__restrict__ items, int n_it, const double *__restrict__ gauss,
+    const int *__restrict__ st_ws, const double *__restrict__ table,
+    const double *__restrict__ pix, double *__restrict__ sens) {
+  __shared__ double T[kSphNR * kLosCols * 3];
   __shared__ unsigned long long ldt[3 * kSphCells];
-  __shared__ double wred[4][2];
-  const int pl = threadIdx.x / kLosLanes, h = threadIdx.x % kLosLanes;
-  for (int ii = blockIdx.x; ii < n_it; ii += gridDim.x) {
-    const Item it = items[ii];
-    const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
-    if (st_ws[it.m] != 0) continue;              // uniform per block
-    const SphAdj adj = sph_adj_of(sens, md, g);
-    const double scale = adj.dscale[0];
-    const bool fixed = scale == scale;           // NaN: non-finite cotangent
-    for (int i = threadIdx.x; i < 3 * kSphCells; i += 256) ldt[i] = 0ull;
-    __syncthreads();
-    const int q = it.a * 64 + pl;
-    const bool on = q < g.n_pix;
-    const int K = g.K;
-    const double *tab = gauss + md.gauss_off;
-    const double *mt = tab + 4 * K;
-    const double si = sqrt(mt[3 * g.J1]), ci = sqrt(mt[3 * g.J1 + 1]);
-    double smin = 1e300, smax = 0.0;
-    for (int k = 0; k < K; ++k) {
-      const double sk = sqrt(0.5 / tab[k]), qk = sqrt(tab[k] / tab[K + k]);
-      smin = fmin(smin, sk * qk);
-      smax = fmax(smax, sk);
+  __shared__ LosNode nodes[64];
+  __shared__ LosMath mt;
+  __shared__ LosModel lm;
+  __shared__ double wred[kLosAdjThreads / 64][2];
+  __shared__ double scale_sh;
+  constexpr int kLosNodes = kSphNodes * 64 / kLosAdjThreads;   // nodes per wave
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  los_math_fill(mt);
+  const int i0 = (int)((int64_t)n_it * blockIdx.x / gridDim.x);
+  const int i1 = (int)((int64_t)n_it * (blockIdx.x + 1) / gridDim.x);
+  int cur = -1;                                  // the model whose table is loaded
+  auto flush = [&](int m) {
+    const ModelDev md = models[m];
+    unsigned long long *dt =
+        reinterpret_cast<unsigned long long *>(sph_adj_of(sens, md, geoms[md.geom]).dtab);
+    for (int e = threadIdx.x; e < 3 * kSphCells; e += kLosAdjThreads) {
+      const unsigned long long v = ldt[e];
+      if (v != 0ull) atomicAdd(dt + e, v);
     }
-    const double a = 0.25 * smin, cW = 12.0 * smax, W = asinh(cW / a);
-    const double Wa = -(cW / (a * a)) / sqrt(1.0 + (cW / a) * (cW / a));   // dW/da
+  };
+  for (int ii = i0; ii < i1; ++ii) {
+    const Item it = items[ii];
+    if (st_ws[it.m] != 0) continue;              // uniform per block
+    const ModelDev md = models[it.m];
+    const GeomDev &g = geoms[md.geom];
+    const SphAdj adj = sph_adj_of(sens, md, g);
+    if (it.m != cur) {
+      __syncthreads();                           // the previous model's reads and sums
+      if (cur >= 0) flush(cur);
+      __syncthreads();
+      for (int e = threadIdx.x; e < 3 * kSphCells; e += kLosAdjThreads) ldt[e] = 0ull;
+      los_table(table + md.sph_off, T);
+      const double *tab = gauss + md.gauss_off;
+      if (threadIdx.x < 64) los_setup(g, tab, nodes, lm);
+      if (threadIdx.x >= 64 && threadIdx.x < 128) {
+        const double sc = sph_dtab_scale(g, tab, adj);
+        if (threadIdx.x == 64) {
+          scale_sh = sc;
+          if (it.a == 0) adj.dscale[0] = sc;     // for k_sph_dtab_fix
+        }
+      }
+      cur = it.m;
+      __syncthreads();
+    }
+    const double scale = scale_sh;
+    const bool fixed = scale == scale;           // NaN: non-finite cotangent
+    const int q = it.a + lane * ((g.n_pix + 63) / 64);
+    const bool on = q < g.n_pix;
     const double x = on ? g.xs[q % g.n_ux] : 0.0, y = on ? g.ys[q / g.n_ux] : 0.0;
     const double lamN = on ? pix[md.pix_off + 2 * (int64_t)g.n_pix + q] : 0.0;
-    const double *T = table + md.sph_off;
-    const double dth = 0.5 * kPi / (kSphNT - 1);
-    const double hw = 2.0 * W / kSphSeg;
-    const double *glx = geoms[md.geom].gl8_x, *glw = geoms[md.geom].gl8_w;
+    const double si = lm.si, ci = lm.ci, idlnr = 1.0 / g.sph_dlnr;
+    constexpr double kIdth = (kSphNT - 1) / (0.5 * kPi);
     double acc_i = 0.0, acc_a = 0.0;
-    for (int nd = h * kLosNodes; on && nd < (h + 1) * kLosNodes; ++nd) {
-      const int seg = nd >> 3, gi = nd & 7;
-      const double om = -1.0 + (seg + 0.5 + 0.5 * glx[gi]) / 4.0;   // w = W om
-      const double w = -W + (seg + 0.5 + 0.5 * glx[gi]) * hw;
-      // sinh w, cosh w from one exponential (|w| > 0.004 W at every node)
-      const double ex = exp(w), iex = 1.0 / ex;
-      const double shw = 0.5 * (ex - iex), chw = 0.5 * (ex + iex);
-      const double zp = a * shw, wz = 0.5 * glw[gi] * hw * a * chw;
-      const double X = x, Y = zp * si - y * ci, Z = y * si + zp * ci;
-      const double R = sqrt(X * X + Y * Y), r = sqrt(R * R + Z * Z);
-      const double ct = Z / r, st = R / r;
-      const double sp = R > 0.0 ? Y / R : 0.0, cp = R > 0.0 ? X / R : 0.0;
-      const double xf = (log(r) - g.sph_lnr0) / g.sph_dlnr;
-      if (xf > kSphNR - 1) continue;
-      const double yf = acos(fmin(1.0, fabs(ct))) / dth;
-      const int xi = (int)fmin(fmax(floor(xf), 0.0), (double)(kSphNR - 2));
-      const int yi = (int)fmin(fmax(floor(yf), 0.0), (double)(kSphNT - 2));
-      const double fx = fmin(fmax(xf - xi, 0.0), 1.0), fy = fmin(fmax(yf - yi, 0.0), 1.0);
-      double ew[4], dew[4], tw[4], dtw[4];
-      sph_radial_weights(xi, fx, ew, dew);
-      sph_angular_weights(yi, fy, tw, dtw);
-      const double ner = si * st * sp + ci * ct;
-      const double net = si * ct * sp - ci * st;
-      const double nep = si * cp;
+    for (int jn = 0; on && jn < kLosNodes; ++jn) {
+      const LosNode nn = nodes[kLosNodes * wave + jn];
+      const LosPoint p = los_point(g, x, y, nn.zp, lm, idlnr, mt);
+      if (p.xf > kSphNR - 1) continue;
+      const double ct = p.Z * p.ir, R2 = fma(p.X, p.X, p.Y * p.Y), R = R2 * p.iR, st = R * p.ir;
+      const double sp = p.Y * p.iR, cp = p.X * p.iR;
+      const double ner = si * st * sp + ci * ct, net = si * ct * sp - ci * st, nep = si * cp;
       const double nf[3] = {ner, net, nep};
-      // table cotangent
+      double ew[4], dew[4], tw[4], dtw[4];
+      sph_radial_weights(p.xi, p.fx, ew, dew);
+      sph_angular_weights(p.fy, tw, dtw);
+      const bool xin = p.xf >= 0.0;        // below the first radius the table is constant
       double A[3] = {0.0, 0.0, 0.0}, AL[3] = {0.0, 0.0, 0.0}, AT[3] = {0.0, 0.0, 0.0};
-      const bool xin = xf >= 0.0;          // below the first radius the table is constant
+      double base[3];
+#pragma unroll
+      for (int f = 0; f < 3; ++f) base[f] = lamN * nn.wz * nf[f] * nf[f] * scale;
+      // columns of the unmirrored cotangent
+      int lc[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int c = abs(p.yi - 1 + b);
+        lc[b] = (c > kSphNT - 1 ? 2 * (kSphNT - 1) - c : c) * 3;
+      }
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        if (ew[a] == 0.0 && dew[a] == 0.0) continue;   // out of range (folded)
+        const int row = min(max(p.xi - 1 + a, 0), kSphNR - 1);   // out of range: zero weight
+        const double *c = T + (row * kLosCols + p.yi) * 3;
+        unsigned long long *d = ldt + row * (kSphNT * 3);
+        double rt[3] = {0.0, 0.0, 0.0}, rd[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          if (tw[b] == 0.0 && dtw[b] == 0.0) continue;
-          const int64_t i0 = ((int64_t)(xi - 1 + a) * kSphNT + (yi - 1 + b)) * 3;
-          const double *c = T + i0;
-          unsigned long long *d = ldt + i0;
+        for (int b = 0; b < 4; ++b)
 #pragma unroll
           for (int f = 0; f < 3; ++f) {
-            const double cf = lamN * wz * nf[f] * nf[f] * ew[a] * tw[b];
-            if (cf != 0.0 && fixed)
-              atomicAdd(d + f, (unsigned long long)__double2ll_rn(cf * scale));
-            A[f] += ew[a] * tw[b] * c[f];
-            if (xin) AL[f] += dew[a] * tw[b] * c[f];
-            AT[f] += ew[a] * dtw[b] * c[f];
+            rt[f] = fma(tw[b], c[3 * b + f], rt[f]);
+            rd[f] = fma(dtw[b], c[3 * b + f], rd[f]);
+          }
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+          A[f] = fma(ew[a], rt[f], A[f]);
+          AL[f] = fma(dew[a], rt[f], AL[f]);
+          AT[f] = fma(ew[a], rd[f], AT[f]);
+        }
+        if (fixed) {
+#pragma unroll
+          for (int f = 0; f < 3; ++f) {
+            const double bf = base[f] * ew[a];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              atomicAdd(d + lc[b] + f, (unsigned long long)los_round(bf * tw[b]));
           }
         }
       }
       // the weight derivatives are per unit of the table's index steps
 #pragma unroll
       for (int f = 0; f < 3; ++f) {
-        AL[f] /= g.sph_dlnr;
-        AT[f] /= dth;
+        AL[f] = xin ? AL[f] * idlnr : 0.0;
+        AT[f] *= kIdth;
       }
       // derivatives of ln r and theta = atan2(R, |Z|) with respect to Y and Z
-      const double r2 = r * r, sz = Z < 0.0 ? -1.0 : 1.0;
-      const double lY = Y / r2, lZ = Z / r2;
-      const double tY = R > 0.0 ? fabs(Z) * (Y / R) / r2 : 0.0, tZ = -R * sz / r2;
-      // line-of-sight components and their derivatives (Y, Z; explicit i)
-      double nY[3] = {0.0, 0.0, 0.0}, nZ[3] = {0.0, 0.0, 0.0}, ni[3] = {0.0, 0.0, 0.0};
-      nY[0] = (si - ner * Y / r) / r;
-      nZ[0] = (ci - ner * Z / r) / r;
-      ni[0] = (ci * Y - si * Z) / r;
-      if (R > 0.0) {
-        const double rR = r * R;
-        nY[1] = ((si * Z - 2.0 * ci * Y) - net * (Y / r * R + r * Y / R)) / rR;
-        nZ[1] = (si * Y - net * (Z / r) * R) / rR;
-        ni[1] = (ci * Z * Y + si * R * R) / rR;
-        nY[2] = -si * X * Y / (R * R * R);
-        ni[2] = ci * X / R;
-      }
+      const double ir2 = p.ir * p.ir, sz = p.Z < 0.0 ? -1.0 : 1.0;
+      const double lY = p.Y * ir2, lZ = p.Z * ir2;
+      const double tY = fabs(p.Z) * sp * ir2, tZ = -R * sz * ir2;
+      // line-of-sight components and their derivatives (Y, Z; explicit i);
+      // on the axis (iR = 0) those of the angular components are left out
+      double nY[3], nZ[3], ni[3];
+      nY[0] = (si - ner * p.Y * p.ir) * p.ir;
+      nZ[0] = (ci - ner * p.Z * p.ir) * p.ir;
+      ni[0] = (ci * p.Y - si * p.Z) * p.ir;
+      const double irR = p.ir * p.iR, rr = R2 > 0.0 ? fma(p.Z, p.Z, R2) * p.ir : 0.0;
+      nY[1] = ((si * p.Z - 2.0 * ci * p.Y) - net * (p.Y * p.ir * R + rr * sp)) * irR;
+      nZ[1] = (si * p.Y - net * ct * R) * irR;
+      ni[1] = (ci * p.Z * p.Y + si * R2) * irR;
+      nY[2] = -si * cp * sp * p.iR;
+      nZ[2] = 0.0;
+      ni[2] = ci * cp;
       double F = 0.0, FY = 0.0, FZ = 0.0, Fi = 0.0;
-  #pragma unroll
+#pragma unroll
       for (int f = 0; f < 3; ++f) {
         const double dAY = AL[f] * lY + AT[f] * tY, dAZ = AL[f] * lZ + AT[f] * tZ;
         F += nf[f] * nf[f] * A[f];
@@ -2577,12 +2673,9 @@ __global__ void __launch_bounds__(256) k_sph_num_adj(const GeomDev *__restrict__
         FZ += 2.0 * nf[f] * nZ[f] * A[f] + nf[f] * nf[f] * dAZ;
         Fi += 2.0 * nf[f] * ni[f] * A[f];
       }
-      const double Yi = zp * ci + y * si, Zi = y * ci - zp * si;
-      acc_i += lamN * wz * (Fi + FY * Yi + FZ * Zi);
-      const double dzp = shw + a * chw * om * Wa;
-      const double dwz = 0.5 * glw[gi] * (2.0 / kSphSeg) *
-                         (Wa * a * chw + W * chw + W * a * shw * om * Wa);
-      acc_a += lamN * (dwz * F + wz * (FY * si + FZ * ci) * dzp);
+      const double Yi = nn.zp * ci + y * si, Zi = y * ci - nn.zp * si;
+      acc_i += lamN * nn.wz * (Fi + FY * Yi + FZ * Zi);
+      acc_a += lamN * (nn.dwz * F + nn.wz * (FY * si + FZ * ci) * nn.dzp);
     }
     // fixed-order sums: each wave's 64 lanes by a butterfly, then the waves
     acc_i = wave_sum(acc_i);
@@ -2592,17 +2685,15 @@ __global__ void __launch_bounds__(256) k_sph_num_adj(const GeomDev *__restrict__
       wred[threadIdx.x >> 6][1] = acc_a;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      adj.losp[2 * it.a] = ((wred[0][0] + wred[1][0]) + wred[2][0]) + wred[3][0];
-      adj.losp[2 * it.a + 1] = ((wred[0][1] + wred[1][1]) + wred[2][1]) + wred[3][1];
+    if (threadIdx.x < 2) {
+      double v = 0.0;
+      for (int w = 0; w < kLosAdjThreads / 64; ++w) v += wred[w][threadIdx.x];
+      adj.losp[2 * it.a + threadIdx.x] = v;
     }
-    unsigned long long *dt = reinterpret_cast<unsigned long long *>(adj.dtab);
-    for (int i = threadIdx.x; i < 3 * kSphCells; i += 256) {
-      const unsigned long long v = ldt[i];
-      if (v != 0ull) atomicAdd(dt + i, v);
-    }
-    __syncthreads();
+    __syncthreads();                             // wred read before the next item
   }
+  __syncthreads();
+  if (cur >= 0) flush(cur);
 }
 
 // Forward pass of the adjoint: the moment table (as k_sph_moments) with the
@@ -2808,8 +2899,8 @@ __global__ void __launch_bounds__(256) k_sph_moments_jac(const GeomDev *__restri
 // derivatives of the cell's L = lambda . (A_r, A_theta, A_phi) with respect
 // to beta_k, alphaq_k and nu0_k from the node sums of k_sph_moments_jac and
 // the table cotangent lambda; the A_phi term -nu R^2 G_phi adds its
-// alphaq_k, nu0_k derivatives.  Item (m, 64 cells), lane = cell, the four
-// waves take the tracers in turn (a thread per tracer of one cell left most
+// alphaq_k, nu0_k derivatives; summed over 64 cells.  Item (m, 64 cells),
+// lane = cell, the four waves take the tracers in turn (a thread per tracer of one cell left most
 // of a wave idle: 48 models of 10 tracers 136 us, now 25).
 __global__ void __launch_bounds__(256) k_sph_rows(const GeomDev *__restrict__ geoms,
                                                   const ModelDev *__restrict__ models,
@@ -2846,10 +2937,12 @@ __global__ void __launch_bounds__(256) k_sph_rows(const GeomDev *__restrict__ ge
       const double dbeta = muP * rb * bP + muD * bD - (lt + lp) * P - 2.0 * lnr * muP * P -
                            fD * lp * sth * rd * (1.0 + 3.0 * (1.0 - be) * lnr);
       const double e0 = exp(-(tab[k] * R02 + tab[K + k] * z02));
-      double *row = adj.rows + ((int64_t)k * kSphCells + cell) * 3;
-      row[0] = dbeta;
-      row[1] = (muP * rb * qP + muD * qD) + lp * R02 * Gphi * tab[2 * K + k] * e0 * z02;
-      row[2] = (muP * rb * eP + muD * eD) + -lp * R02 * Gphi * e0;
+      const double s0 = wave_sum(dbeta);
+      const double s1 =
+          wave_sum((muP * rb * qP + muD * qD) + lp * R02 * Gphi * tab[2 * K + k] * e0 * z02);
+      const double s2 = wave_sum((muP * rb * eP + muD * eD) + -lp * R02 * Gphi * e0);
+      if (lane < 3)
+        adj.rows[((int64_t)k * kSphRowParts + it.a) * 3 + lane] = lane == 0 ? s0 : (lane == 1 ? s1 : s2);
     }
   }
 }
@@ -3120,30 +3213,15 @@ __global__ void __launch_bounds__(512) k_sph_grads(const GeomDev *__restrict__ g
     // dq/di of a deprojected Gaussian of observed axis ratio qo
     auto dqdi = [&](double qo, double q) { return ci * (1.0 - qo * qo) / (q * si * si * si); };
     double di = 0.0;
-    // tracers: rows summed over cells (lanes split the cells, four cells'
-    // loads in flight, wave sum)
+    // tracers: the rows' sums over 64 cells each
     for (int k = wave; k < K; k += kW) {
       double b = 0.0, aq = 0.0, nv = 0.0;
-      if (ok)
-        for (int c0 = lane; c0 < kSphCells; c0 += 4 * 64) {
-          double vb[4], vq[4], vn[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            vb[u] = vq[u] = vn[u] = 0.0;
-            if (c0 + 64 * u < kSphCells) {
-              const double *row = adj.rows + ((int64_t)k * kSphCells + c0 + 64 * u) * 3;
-              vb[u] = row[0];
-              vq[u] = row[1];
-              vn[u] = row[2];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            b += vb[u];
-            aq += vq[u];
-            nv += vn[u];
-          }
-        }
+      if (ok && lane < kSphRowParts) {
+        const double *row = adj.rows + ((int64_t)k * kSphRowParts + lane) * 3;
+        b = row[0];
+        aq = row[1];
+        nv = row[2];
+      }
       double sb = 0.0;
       const int n_tiles = sb_tiles(g.n_ux, g.n_uy);
       if (ok)
@@ -3297,25 +3375,34 @@ __global__ void __launch_bounds__(256) k_beta_logistic_vjp(const GeomDev *__rest
 }
 
 // Line-of-sight integral of the projected moment table into the unique-pixel
-// N map.  Item (m, 64-pixel block), one workgroup each: four lanes per pixel
-// (thread = 4 pixel + h), lane h taking nodes 16 h .. 16 h + 15, and the
-// four partial sums added in a fixed order.  Nodes z' = a sinh(w), w on
-// [-W, W] by the composite rule, a = min_k sigma_k q_k / 4,
-// a sinh(W) = 12 max_k sigma_k; the table is interpolated bicubically
-// (sph_radial_weights, sph_angular_weights), the first radius standing for
-// smaller ones and zero beyond the last.  FP64.
-__global__ void __launch_bounds__(256) k_sph_num(const GeomDev *__restrict__ geoms,
-                                                 const ModelDev *__restrict__ models,
-                                                 const Item *__restrict__ items, int n_it,
-                                                 const double *__restrict__ gauss,
-                                                 const int *__restrict__ st_ws,
-                                                 const double *__restrict__ table,
-                                                 double *__restrict__ pix) {
+// N map.  Items (m, 64-pixel block), a contiguous range of them per block;
+// the table is interpolated bicubically (sph_radial_weights,
+// sph_angular_weights), the first radius standing for smaller ones and zero
+// beyond the last.  FP64, whose issue and the 24 scattered LDS reads per node
+// bound it.  Measured, 46,225 pixels: 256-thread blocks reading the table from
+// global memory with library functions and all node quantities per pixel 119
+// us, this 55.
+__global__ void __launch_bounds__(kLosThreads) k_sph_num(const GeomDev *__restrict__ geoms,
+                                                         const ModelDev *__restrict__ models,
+                                                         const Item *__restrict__ items, int n_it,
+                                                         const double *__restrict__ gauss,
+                                                         const int *__restrict__ st_ws,
+                                                         const double *__restrict__ table,
+                                                         double *__restrict__ pix) {
+  __shared__ double T[kSphNR * kLosCols * 3];
+  __shared__ LosNode nodes[64];
+  __shared__ LosMath mt;
+  __shared__ LosModel lm;
+  constexpr int kLosLanes = kLosThreads / 64, kLosNodes = kSphNodes / kLosLanes;
   const int pl = threadIdx.x / kLosLanes, h = threadIdx.x % kLosLanes;
-  for (int ii = blockIdx.x; ii < n_it; ii += gridDim.x) {
+  los_math_fill(mt);
+  const int i0 = (int)((int64_t)n_it * blockIdx.x / gridDim.x);
+  const int i1 = (int)((int64_t)n_it * (blockIdx.x + 1) / gridDim.x);
+  int cur = -1;                              // the model whose table is loaded
+  for (int ii = i0; ii < i1; ++ii) {
     const Item it = items[ii];
     const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
+    const GeomDev &g = geoms[md.geom];
     const int q = it.a * 64 + pl;
     const bool on = q < g.n_pix;
     double *Nout = pix + md.pix_off + q;
@@ -3323,63 +3410,44 @@ __global__ void __launch_bounds__(256) k_sph_num(const GeomDev *__restrict__ geo
       if (on && h == 0) *Nout = 0.0;
       continue;
     }
-    const int K = g.K;
-    const double *tab = gauss + md.gauss_off;
-    const double *mt = tab + 4 * K;
-    const double si = sqrt(mt[3 * g.J1]), ci = sqrt(mt[3 * g.J1 + 1]);
-    double smin = 1e300, smax = 0.0;
-    for (int k = 0; k < K; ++k) {
-      const double sk = sqrt(0.5 / tab[k]), qk = sqrt(tab[k] / tab[K + k]);
-      smin = fmin(smin, sk * qk);
-      smax = fmax(smax, sk);
+    if (it.m != cur) {
+      __syncthreads();                       // the previous model's reads
+      los_table(table + md.sph_off, T);
+      if (threadIdx.x < 64) los_setup(g, gauss + md.gauss_off, nodes, lm);
+      cur = it.m;
+      __syncthreads();
     }
-    const double a = 0.25 * smin, W = asinh(12.0 * smax / a);
     const double x = on ? g.xs[q % g.n_ux] : 0.0, y = on ? g.ys[q / g.n_ux] : 0.0;
-    const double *T = table + md.sph_off;
-    const double dth = 0.5 * kPi / (kSphNT - 1);
-    const double hw = 2.0 * W / kSphSeg;
-    const double *glx = geoms[md.geom].gl8_x, *glw = geoms[md.geom].gl8_w;
+    const double si = lm.si, ci = lm.ci, idlnr = 1.0 / g.sph_dlnr;
     double acc = 0.0;
-    for (int nd = h * kLosNodes; on && nd < (h + 1) * kLosNodes; ++nd) {
-      const int seg = nd >> 3, gi = nd & 7;
-      const double w = -W + (seg + 0.5 + 0.5 * glx[gi]) * hw;
-      // sinh w, cosh w from one exponential (|w| > 0.004 W at every node)
-      const double ex = exp(w), iex = 1.0 / ex;
-      const double zp = a * (0.5 * (ex - iex)), wz = 0.5 * glw[gi] * hw * a * (0.5 * (ex + iex));
-      const double X = x, Y = zp * si - y * ci, Z = y * si + zp * ci;
-      const double R = sqrt(X * X + Y * Y), r = sqrt(R * R + Z * Z);
-      const double ct = Z / r, st = R / r;
-      const double sp = R > 0.0 ? Y / R : 0.0, cp = R > 0.0 ? X / R : 0.0;
-      const double xf = (log(r) - g.sph_lnr0) / g.sph_dlnr;
-      if (xf > kSphNR - 1) continue;
-      const double yf = acos(fmin(1.0, fabs(ct))) / dth;
-      const int xi = (int)fmin(fmax(floor(xf), 0.0), (double)(kSphNR - 2));
-      const int yi = (int)fmin(fmax(floor(yf), 0.0), (double)(kSphNT - 2));
-      const double fx = fmin(fmax(xf - xi, 0.0), 1.0), fy = fmin(fmax(yf - yi, 0.0), 1.0);
+    for (int jn = 0; on && jn < kLosNodes; ++jn) {
+      const LosNode nn = nodes[kLosLanes * jn + h];
+      const LosPoint p = los_point(g, x, y, nn.zp, lm, idlnr, mt);
+      if (p.xf > kSphNR - 1) continue;
       double ew[4], dew[4], tw[4], dtw[4];
-      sph_radial_weights(xi, fx, ew, dew);
-      sph_angular_weights(yi, fy, tw, dtw);
+      sph_radial_weights(p.xi, p.fx, ew, dew);
+      sph_angular_weights(p.fy, tw, dtw);
       double A[3] = {0.0, 0.0, 0.0};
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        if (ew[a] == 0.0) continue;           // out of range (folded) or a zero weight
+        const int row = min(max(p.xi - 1 + a, 0), kSphNR - 1);   // out of range: zero weight
+        const double *c = T + (row * kLosCols + p.yi) * 3;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          if (tw[b] == 0.0) continue;
-          const double *c = T + ((int64_t)(xi - 1 + a) * kSphNT + (yi - 1 + b)) * 3;
-          const double wab = ew[a] * tw[b];
+        for (int f = 0; f < 3; ++f) {
+          double v = tw[0] * c[f];
 #pragma unroll
-          for (int f = 0; f < 3; ++f) A[f] += wab * c[f];
+          for (int b = 1; b < 4; ++b) v = fma(tw[b], c[3 * b + f], v);
+          A[f] = fma(ew[a], v, A[f]);
         }
       }
-      const double ner = si * st * sp + ci * ct;
-      const double net = si * ct * sp - ci * st;
-      const double nep = si * cp;
-      acc += wz * (ner * ner * A[0] + net * net * A[1] + nep * nep * A[2]);
+      const double ct = p.Z * p.ir, st = fma(p.X, p.X, p.Y * p.Y) * p.iR * p.ir;
+      const double sp = p.Y * p.iR, cp = p.X * p.iR;
+      const double ner = si * st * sp + ci * ct, net = si * ct * sp - ci * st, nep = si * cp;
+      acc += nn.wz * (ner * ner * A[0] + net * net * A[1] + nep * nep * A[2]);
     }
-    // (h0 + h1) + (h2 + h3) in every lane of the pixel
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
+    // over the pixel's lanes, in every lane
+#pragma unroll
+    for (int o = 1; o < kLosLanes; o <<= 1) acc += __shfl_xor(acc, o, 64);
     if (on && h == 0) *Nout = acc;
   }
 }
@@ -3510,17 +3578,17 @@ void launch_sph_moments_jac(const GeomDev *g, const ModelDev *m, const Item *it,
 void launch_sph_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                     const double *gauss, const int *st_ws, const double *table, double *pix,
                     hipStream_t st) {
-  hipLaunchKernelGGL(k_sph_num, dim3(grid_of(n_it)), dim3(64 * kLosLanes), 0, st, g, m, it, n_it,
+  hipLaunchKernelGGL(k_sph_num, dim3(grid_of(std::min(n_it, kLosBlocks))), dim3(kLosThreads), 0, st, g, m, it, n_it,
                      gauss, st_ws, table, pix);
 }
 void launch_sph_adjoint(const GeomDev *g, const ModelDev *m, int n, const Item *it_los, int n_los,
                         const Item *it_cell, int n_cell, const double *gauss, const int *st_ws,
                         const double *table, const double *pix, double *sens, hipStream_t st) {
-  hipLaunchKernelGGL(k_sph_zero, dim3(grid_of(n)), dim3(kZeroThreads), 0, st, g, m, n, gauss,
-                     st_ws, pix, sens);
-  hipLaunchKernelGGL(k_sph_num_adj, dim3(grid_of(n_los)), dim3(256), 0, st, g, m, it_los, n_los,
+  hipLaunchKernelGGL(k_sph_zero, dim3(grid_of(std::min(n, 65536) * kZeroParts)), dim3(256), 0, st,
+                     g, m, n, st_ws, pix, sens);
+  hipLaunchKernelGGL(k_sph_num_adj, dim3(grid_of(std::min(n_los, kLosBlocks))), dim3(kLosAdjThreads), 0, st, g, m, it_los, n_los,
                      gauss, st_ws, table, pix, sens);
-  hipLaunchKernelGGL(k_sph_dtab_fix, dim3(grid_of(n)), dim3(256), 0, st, g, m, n, st_ws, sens);
+  hipLaunchKernelGGL(k_sph_dtab_fix, dim3(grid_of(std::min(n, 65536) * kFixParts)), dim3(256), 0, st, g, m, n, st_ws, sens);
   hipLaunchKernelGGL(k_sph_rows, dim3(grid_of(n_cell)), dim3(256), 0, st, g, m, it_cell, n_cell,
                      gauss, st_ws, sens);
 }

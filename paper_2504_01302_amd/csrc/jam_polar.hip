@@ -24,6 +24,7 @@
 // x 512 grid in R and z left 1e-6 to 1e-5.
 #include "jam_device.h"
 #include "jam_internal.h"
+#include "jam_sph_math.h"
 
 #include <hip/hip_runtime.h>
 #include <algorithm>
@@ -40,77 +41,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Tables of what the points need: sin of the table's angles, 1 / c and
-// -log(1 / c) at the centres c of 64 mantissa intervals, and 2^(i / 32).
-// Evaluated at compile time (series that end below FP64 rounding), copied to
-// LDS by every block.
-struct alignas(16) PolMath {
-  double lg[64][2];
-  double ex[32];
-  double sn[kSphNT];
-};
-constexpr PolMath pol_math() {
-  PolMath t{};
-  for (int i = 0; i < 64; ++i) {
-    const double ic = 1.0 / (1.0 + (i + 0.5) / 64.0);
-    // -log ic = 2 atanh z
-    const double z = (1.0 - ic) / (1.0 + ic), z2 = z * z;
-    double p = 0.0;
-    for (int n = 41; n >= 1; n -= 2) p = p * z2 + 1.0 / n;
-    t.lg[i][0] = ic;
-    t.lg[i][1] = 2.0 * z * p;
-  }
-  for (int i = 0; i < 32; ++i) {
-    const double x = i * 0.02166084939249829;    // ln 2 / 32
-    double p = 1.0;
-    for (int n = 24; n >= 1; --n) p = 1.0 + p * x / n;
-    t.ex[i] = p;
-  }
-  for (int i = 0; i < kSphNT; ++i) {
-    const double x = i * (0.5 * kPi / (kSphNT - 1)), x2 = x * x;
-    double p = 1.0;
-    for (int n = 25; n >= 3; n -= 2) p = 1.0 - p * x2 / (n * (n - 1));
-    t.sn[i] = x * p;
-  }
-  return t;
-}
-__device__ constexpr PolMath kPolMath = pol_math();
-// The caller synchronises.
-__device__ inline void pol_math_fill(PolMath &t) {
-  const double *src = reinterpret_cast<const double *>(&kPolMath);
-  double *dst = reinterpret_cast<double *>(&t);
-  for (int e = threadIdx.x; e < (int)(sizeof(PolMath) / sizeof(double)); e += blockDim.x) dst[e] = src[e];
-}
-
-// log of w >= 1 to about 1e-16 absolute (a grid coordinate): exponent + table
-// + series in |r| <= 1 / 128.
-__device__ __forceinline__ double pol_log(double w, const PolMath &tb) {
-  const int hi = __double2hiint(w);
-  const double2 c = *reinterpret_cast<const double2 *>(tb.lg[(hi >> 14) & 63]);
-  const double m = __hiloint2double((hi & 0xfffff) | 0x3ff00000, __double2loint(w));
-  const double r = fma(m, c.x, -1.0);
-  double p = fma(r, 1.0 / 7.0, -1.0 / 6.0);
-  p = fma(p, r, 1.0 / 5.0);
-  p = fma(p, r, -1.0 / 4.0);
-  p = fma(p, r, 1.0 / 3.0);
-  p = fma(p, r, -1.0 / 2.0);
-  return fma((double)((hi >> 20) - 1023), 0.6931471805599453, c.y + fma(r * r, p, r));
-}
-
-// exp of x <= 0, relative error a few FP64 ulp (of the argument's rounding).
-__device__ __forceinline__ double pol_exp(double x, const PolMath &tb) {
-  x = fmax(x, -800.0);
-  const double n = rint(x * 46.16624130844683);          // 32 / ln 2
-  const double r = fma(n, -7.247021293269686e-19, fma(n, -0.02166084939249829, x));
-  double p = fma(r, 1.0 / 720.0, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  const int ni = (int)n;
-  const double t = tb.ex[ni & 31];
-  return ldexp(fma(t, fma(r * r, p, r), t), ni >> 5);
 }
 
 // Lagrange weights of P equidistant points -(P/2 - 1) .. P/2 at f.
