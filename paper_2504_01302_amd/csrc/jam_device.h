@@ -39,6 +39,13 @@ __device__ inline double rsq64(double x) {
   return fma(0.5 * y, e, y);
 }
 
+// A load through a pointer that the compiler cannot see to be global (one read
+// from a descriptor), which would otherwise be a flat load and wait for LDS too.
+__device__ __forceinline__ double load_global(const double *p) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) double *>(
+      reinterpret_cast<uintptr_t>(p));
+}
+
 constexpr double kSqrtPi = 1.77245385090551602730;
 
 }  // namespace

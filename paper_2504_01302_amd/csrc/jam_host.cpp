@@ -503,7 +503,7 @@ struct Plan {
             *d_red = nullptr, *d_sph = nullptr, *d_pro = nullptr, *d_adj = nullptr,
             *d_sensw = nullptr, *d_sgrid = nullptr, *d_sgred = nullptr,
             *d_sgred3 = nullptr, *d_pcot = nullptr, *d_pfix = nullptr, *d_sgs = nullptr,
-            *d_sphm = nullptr, *d_ptab = nullptr, *d_srow = nullptr, *d_cpan = nullptr, *d_csum = nullptr, *d_cadj = nullptr,
+            *d_sphm = nullptr, *d_ptab = nullptr, *d_srow = nullptr, *d_numsm = nullptr, *d_cpan = nullptr, *d_csum = nullptr, *d_cadj = nullptr,
             *d_ctmap = nullptr, *d_crows = nullptr;
   jam::ChebItem *d_cmap = nullptr;
   // compressed forward: models taken together, [first, end) of their items
@@ -513,10 +513,12 @@ struct Plan {
   std::vector<ChebGroup> cheb_groups;
   int n_terms = 0, n_pix = 0, n_num = 0, n_bins = 0, n_maps = 0, n_chain = 0, n_sens = 0,
       n_sb = 0, n_red = 0, n_sph = 0, n_pro = 0, n_adj = 0, n_sensw = 0,
-      n_sgrid = 0, n_sgred = 0, n_sgred3 = 0, n_pcot = 0, n_pfix = 0, n_sgs = 0, n_sphm = 0, n_ptab = 0, n_srow = 0,
+      n_sgrid = 0, n_sgred = 0, n_sgred3 = 0, n_pcot = 0, n_pfix = 0, n_sgs = 0, n_sphm = 0, n_ptab = 0, n_srow = 0, n_numsm = 0,
       n_cpan = 0, n_csum = 0, n_cadj = 0, n_cmap = 0, n_ctmap = 0, n_crows = 0;
   int cadj_share = 0, cheb_waves = 4, cadj_waves = 4;   // shared adjoint items, waves per block
   int n_cheb = 0;        // models of the compressed form
+  int numsm_ptr[jam::kSmallTilings + 1] = {};   // small-map items by tiling
+  int adj_ptr[jam::kSmallQuads + 1] = {};       // and the adjoint's by y quads (1 ..)
   int n_bins_wave = 0;   // leading bin items summed one bin per wave
   bool spherical = false;
   bool fused_prologue = true;
@@ -664,6 +666,19 @@ std::vector<std::pair<int, int>> axis_tiles(int n, int tau) {
     b += w;
   }
   return out;
+}
+
+// Small maps in 4 x 4 tiles instead of one 32 x 32 block: the width and height
+// rounded up to 12, 20 or 24 unique pixels (fewer kernels than sizes), -1: the
+// block.  A term costs the block 13.5 ns of matrix-core time, the largest
+// tiling here 9.2 ns, and 28 x 28 (49 tiles) 12.6 ns and more registers than
+// two waves a SIMD have.  The tiles' sums over their sixteen terms' blocks cost
+// an item about as much as two chunks of a wave save.
+constexpr int kSmallMinChunks = 2;
+int small_tiling(const GeomHost &g, const NumChoice &c) {
+  if (!c.gen || g.n_ux > 24 || g.n_uy > 24 || c.units < 4 * kSmallMinChunks * c.n_slices) return -1;
+  auto size = [](int n) { return n <= 12 ? 0 : (n <= 20 ? 1 : 2); };
+  return 3 * size(g.n_ux) + size(g.n_uy);
 }
 
 NumChoice choose_numerator(const GeomHost &g, const Tune &t, int gran) {
@@ -909,7 +924,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   std::vector<jam::ModelDev> md(n);
   std::vector<jam::Item> it_terms, it_pix, it_num, it_bins, it_maps, it_chain, it_sens, it_sb,
       it_red, it_sph, it_pro, it_adj, it_sensw, it_sgrid, it_sgred, it_sgred3, it_pcot,
-      it_pfix, it_sgs, it_sphm, it_ptab, it_srow, it_cpan, it_csum, it_cadj, it_ctmap, it_crows, it_sbpro;
+      it_pfix, it_sgs, it_sphm, it_ptab, it_srow, it_numsm, it_cpan, it_csum, it_cadj, it_ctmap, it_crows, it_sbpro;
   std::vector<jam::ChebItem> it_cmap;
   std::vector<double> c_num, c_sens, c_sensw;
   // wide-sensitivity parts (model, part, x tiles, 32-term groups); their
@@ -924,8 +939,10 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   auto adj_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && (tune.cheb & 2) && g.cheb_adj; };
   int64_t cheb_units = 0, cheb_panels = 0, cadj_panels = 0;
   int cheb_most = 0;   // terms of the largest panel
+  int64_t small_terms = 0;
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
+    if (g.n_ux <= kSmallMap && g.n_uy <= kSmallMap) small_terms += g.T;
     if (fwd_cheb(g)) {
       for_cheb_tiles(g, [&](int, int units) { cheb_units += units; });
       cheb_panels += (int64_t)g.K * g.cheb_np;
@@ -933,6 +950,9 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     if (adj_cheb(g)) cadj_panels += (int64_t)g.K * g.cheb_np;
     for (int P = 0; P < g.cheb_np; ++P) cheb_most = std::max(cheb_most, g.cheb_ptr[P + 1] - g.cheb_ptr[P]);
   }
+  // terms per item of the small maps' adjoint: at least two items per compute
+  // unit down to one pass of a block
+  const int adj_terms = (int)std::max<int64_t>(256, std::min<int64_t>(8192, small_terms / (2 * ctx->n_cu)));
   const int cheb_per = (int)std::max<int64_t>(
       16, std::min<int64_t>(160, (cheb_units + 2 * ctx->n_cu - 1) / (2 * ctx->n_cu)));
   // A block's waves share a unit whose panel has more than kShareTerms
@@ -1132,11 +1152,23 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     } else if (cadj) {
       // it_cadj
     } else if (small) {
-      // fused sensitivities + chain: items of whole tracers, about 8192
-      // terms each
-      const int per = std::max(1, std::min(jam::kSmallAdjTracers, 8192 / (g.J1 * g.n_u)));
-      for (int k = 0; k < g.K; k += per)
-        it_adj.push_back({m, k | (std::min(g.K, k + per) << 16), 0, 0});
+      // fused sensitivities + chain: items of whole tracers, about 8192 terms
+      // each, or in a batch too small to give the chip that many, of whole rows
+      // of one tracer
+      const int row_terms = g.n_u, quads = (g.n_uy + 3) / 4;
+      const int whole = std::max(512, adj_terms);
+      if (whole >= g.J1 * row_terms) {
+        const int per = std::max(1, std::min(jam::kSmallAdjTracers, whole / (g.J1 * row_terms)));
+        for (int k = 0; k < g.K; k += per) {
+          const int k1 = std::min(g.K, k + per);
+          it_adj.push_back({m, k | (k1 << 16), ((k1 - k) * g.J1) << 16, quads});
+        }
+      } else {
+        const int per = std::max(1, adj_terms / row_terms);
+        for (int k = 0; k < g.K; ++k)
+          for (int r = 0; r < g.J1; r += per)
+            it_adj.push_back({m, k | ((k + 1) << 16), r | (std::min(g.J1, r + per) << 16), quads});
+      }
     } else if (d.form == 1) {
       for (int tb = 0; tb < (g.T + 255) / 256; ++tb) {
         it_sens.push_back({m, tb, 0, 0});
@@ -1154,7 +1186,9 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
         }
     }
     for (int pb = 0; pb < (g.n_pix + 255) / 256; ++pb) it_pix.push_back({m, pb, 0, 0});
-    if (!cheb)   // summed by k_cheb_sum
+    // the compressed form's maps are summed by k_cheb_sum, a single slice of the
+    // small tilings is the sum
+    if (!cheb && !(small && d.n_slices == 1 && small_tiling(g, nc) >= 0))
       for (int pb = 0; pb < (g.n_pix + 63) / 64; ++pb) it_red.push_back({m, pb, 0, 0});
     for (int rb = 0; rb < (g.n_uy + 7) / 8; ++rb)
       for (int cb = 0; cb < (g.n_ux + 63) / 64; ++cb) {
@@ -1165,6 +1199,9 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
       for (int tl = 0; tl < nc.n_tiles(); ++tl) {
         if (nc.kind == 0) {
           it_num.push_back({m, tl, s, 0});
+        } else if (small_tiling(g, nc) >= 0 && small) {
+          it_numsm.push_back({m, 0, s, small_tiling(g, nc)});
+          continue;
         } else {
           const WaveTile &w = nc.tiles[tl];
           it_num.push_back({m, w.bx | (w.by << 16), s,
@@ -1199,15 +1236,23 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->n_bins_wave = (int)std::count_if(it_bins.begin(), it_bins.end(),
                                       [](const jam::Item &t) { return t.c == 1; });
   sort_by_cost(it_num, c_num);
+  std::stable_sort(it_numsm.begin(), it_numsm.end(),
+                   [](const jam::Item &a, const jam::Item &b) { return a.c < b.c; });
+  std::stable_sort(it_adj.begin(), it_adj.end(),
+                   [](const jam::Item &a, const jam::Item &b) { return a.c < b.c; });
+  for (const jam::Item &t : it_adj) ++p->adj_ptr[t.c];
+  for (int t = 0; t < jam::kSmallQuads; ++t) p->adj_ptr[t + 1] += p->adj_ptr[t];
+  for (const jam::Item &t : it_numsm) ++p->numsm_ptr[t.c + 1];
+  for (int t = 0; t < jam::kSmallTilings; ++t) p->numsm_ptr[t + 1] += p->numsm_ptr[t];
   sort_by_cost(it_sens, c_sens);
   wide_items(wide_parts, ctx->n_cu, it_sensw);
 
-  constexpr int kLists = 27;
+  constexpr int kLists = 28;
   std::vector<jam::Item> *lists[kLists] = {&it_terms, &it_pix, &it_num, &it_bins,
                                            &it_maps,  &it_chain, &it_sens, &it_sb,
                                            &it_red,   &it_sph, &it_pro, &it_adj,
                                            &it_sensw, &it_sgrid, &it_sgred, &it_sgred3,
-                                           &it_pcot,  &it_pfix,  &it_sgs,  &it_sphm, &it_ptab, &it_srow, &it_cpan,
+                                           &it_pcot,  &it_pfix,  &it_sgs,  &it_sphm, &it_ptab, &it_srow, &it_numsm, &it_cpan,
                                            &it_csum,  &it_cadj,  &it_ctmap, &it_crows};
   if (it_cmap.size() > (size_t)INT32_MAX) return fail(JAM_E_UNSUPPORTED, "batch too large");
   for (auto *l : lists)
@@ -1238,7 +1283,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
                             &p->d_maps,  &p->d_chain, &p->d_sens, &p->d_sb,
                             &p->d_red,   &p->d_sph,   &p->d_pro,  &p->d_adj,
                             &p->d_sensw, &p->d_sgrid, &p->d_sgred, &p->d_sgred3,
-                            &p->d_pcot,  &p->d_pfix,  &p->d_sgs,  &p->d_sphm, &p->d_ptab, &p->d_srow, &p->d_cpan,
+                            &p->d_pcot,  &p->d_pfix,  &p->d_sgs,  &p->d_sphm, &p->d_ptab, &p->d_srow, &p->d_numsm, &p->d_cpan,
                             &p->d_csum,  &p->d_cadj,  &p->d_ctmap, &p->d_crows};
   p->d_cmap = (jam::ChebItem *)(base + o_cmap);
   p->n_cmap = (int)it_cmap.size();
@@ -1246,7 +1291,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
                       &p->n_maps,  &p->n_chain, &p->n_sens, &p->n_sb,
                       &p->n_red,   &p->n_sph,   &p->n_pro,  &p->n_adj,
                       &p->n_sensw, &p->n_sgrid, &p->n_sgred, &p->n_sgred3,
-                      &p->n_pcot,  &p->n_pfix,  &p->n_sgs,  &p->n_sphm, &p->n_ptab, &p->n_srow, &p->n_cpan,
+                      &p->n_pcot,  &p->n_pfix,  &p->n_sgs,  &p->n_sphm, &p->n_ptab, &p->n_srow, &p->n_numsm, &p->n_cpan,
                       &p->n_csum,  &p->n_cadj,  &p->n_ctmap, &p->n_crows};
   for (int i = 0; i < kLists; ++i) {
     *dl[i] = (jam::Item *)(base + o_it[i]);
@@ -1309,6 +1354,11 @@ void launch_numerator(jam_ctx *ctx, Plan *p, char *ws, hipStream_t st) {
       jam::launch_cheb_map(ctx->d_geoms, p->d_models, p->d_cmap + q.map0, q.map1 - q.map0, H, st_ws,
                            part, st);
   }
+  for (int t = 0; t < jam::kSmallTilings; ++t)
+    if (p->numsm_ptr[t + 1] > p->numsm_ptr[t])
+      jam::launch_num_small(ctx->d_geoms, p->d_models, p->d_numsm + p->numsm_ptr[t],
+                            p->numsm_ptr[t + 1] - p->numsm_ptr[t], t, gauss, st_ws, part,
+                            (double *)(ws + p->off_pix), st);
   if (!p->n_num) return;
   jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, gauss, st_ws, part, queue,
                     p->grid_num, p->tune.rule == 1, st);
@@ -1474,7 +1524,10 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
     jam::launch_cheb_rows(ctx->d_geoms, p->d_models, p->d_crows, p->n_crows, gauss, st_ws, sens, st);
   }
   if (p->n_adj)
-    jam::launch_adj_small(ctx->d_geoms, p->d_models, p->d_adj, p->n_adj, pd, pix, st_ws, sens, st);
+    for (int t = 1; t <= jam::kSmallQuads; ++t)
+      if (p->adj_ptr[t] > p->adj_ptr[t - 1])
+        jam::launch_adj_small(ctx->d_geoms, p->d_models, p->d_adj + p->adj_ptr[t - 1],
+                              p->adj_ptr[t] - p->adj_ptr[t - 1], t, pd, pix, st_ws, sens, st);
   if (timed) ctx->t_sens.end(st);
   if (p->n_chain)
     jam::launch_chain(ctx->d_geoms, p->d_models, p->d_chain, p->n_chain, pd, sens, st_ws, st);
@@ -2427,8 +2480,8 @@ jam_status jam_plan_info(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, int32
   info[1] = p->tune.tau;
   info[2] = p->tune.gran;
   info[3] = p->tune.launch;
-  info[4] = p->n_num + p->n_cmap;
-  info[5] = (p->n_num || !p->n_cmap ? p->grid_num : 0) + p->n_cmap;
+  info[4] = p->n_num + p->n_numsm + p->n_cmap;
+  info[5] = (p->n_num || !(p->n_cmap || p->n_numsm) ? p->grid_num : 0) + p->n_numsm + p->n_cmap;
   info[6] = p->n_sens + p->n_sensw + p->n_adj + p->n_cadj;
   info[7] = (p->n_sens ? p->grid_sens : 0) + p->n_sensw + p->n_adj + p->n_cadj;
   info[8] = p->spherical ? 3 : (p->tune.rule == 0 ? 0 : (p->n_cheb == p->n ? 4 : 1));

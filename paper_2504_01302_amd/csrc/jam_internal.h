@@ -193,6 +193,13 @@ void launch_sb(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, Pa
 void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                 const float4 *terms, const double *gauss, const int *st_ws, double *part,
                 int *queue, int grid, bool mfma, hipStream_t st);
+// Small maps in 4 x 4 tiles: items (m, 0, slice, tiling) of one tiling 3 X + Y,
+// X and Y the sizes 3, 5 or 6 tiles (0, 1, 2) that cover the map's width and
+// height.  A model of one slice goes straight into its N map (no reduce items).
+constexpr int kSmallTilings = 9;
+void launch_num_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int tiling,
+                      const double *gauss, const int *st_ws, double *part, double *pix,
+                      hipStream_t st);
 int occupancy_num(bool mfma);   // resident numerator workgroups per CU
 int occupancy_sens();   // resident sensitivity workgroups per CU
 // Compressed cylindrical form (jam_cheb.hip), after the set-up: panels
@@ -261,8 +268,11 @@ void launch_chain(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
 constexpr int kSmallAdjTerms = 1024;
 constexpr int kSmallAdjTracers = 64;
 constexpr int kSmallAdjMass = 256;
-void launch_adj_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, ParamsDev p,
-                      const double *pix, const int *st_ws, double *sens, hipStream_t st);
+// (Items of maps of y_quads groups of four rows.)
+constexpr int kSmallQuads = 8;
+void launch_adj_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int y_quads,
+                      ParamsDev p, const double *pix, const int *st_ws, double *sens,
+                      hipStream_t st);
 void launch_grads(const GeomDev *g, const ModelDev *m, int n, ParamsDev p, double *sens,
                   const double *sbp, const int *st_ws, GradsDev out, hipStream_t st);
 // Spherically aligned model.  Terms: items (m, block of 256 terms), the

@@ -222,33 +222,36 @@ __device__ inline void term_coeffs(double alpha, double alphaq, double nu0, doub
   const double h = fma(-e2, u2, 1.0);
   const double ru2 = r * u2;
   c1 = alpha + ru2;
-  const double rh = rcp64(h);
+  const double rsh = rsq64(h), rh = rsh * rsh;
   const double A = fma(ru2, rh, alphaq);
   const double a = fma(c1, si2, A * ci2);
-  gam = c1 * A * rcp64(a);
+  const double rsa = rsq64(a);
+  gam = c1 * A * rsa * rsa;
   const double base = nu0 * Kp * ru2;
-  const double rsh = rsq64(h);
   const double gg = base * rcp64(A) * rh * rsh;
   const double ww = 2.0 * base * rsh;
   const double P = (ci2 + b * si2) * gg;
   const double Q = si2 * (ww - 2.0 * c1 * b * gg);
-  const double f = wq * kSqrtPi * rsq64(a);
+  const double f = wq * kSqrtPi * rsa;
   C0 = f * P;
   C1 = f * Q;
 }
 
 // Term t = (k * J1 + j) * n_u + n of a model from its Gaussian table (the
 // set-up's output), as the term table stores it.
-__device__ inline float4 term_of(const GeomDev &g, const double *__restrict__ tab, int t) {
-  const int n = t % g.n_u, kj = t / g.n_u;
-  const int j = kj % g.J1, k = kj / g.J1;
+__device__ inline float4 term_at(const GeomDev &g, const double *__restrict__ tab, int k, int j,
+                                 int n) {
   const double *mt = tab + 4 * g.K;
   double c1, gam, C0, C1;
   term_coeffs(tab[k], tab[g.K + k], tab[2 * g.K + k], tab[3 * g.K + k], mt[j], mt[g.J1 + j],
-              mt[2 * g.J1 + j], mt[3 * g.J1], mt[3 * g.J1 + 1], g.u[n], g.w[n], c1, gam, C0, C1);
+              mt[2 * g.J1 + j], mt[3 * g.J1], mt[3 * g.J1 + 1], load_global(g.u + n),
+              load_global(g.w + n), c1, gam, C0, C1);
   return make_float4((float)(-c1 * kLog2e), (float)(-gam * kLog2e), (float)C0, (float)C1);
 }
-
+__device__ inline float4 term_of(const GeomDev &g, const double *__restrict__ tab, int t) {
+  const int n = t % g.n_u, kj = t / g.n_u;
+  return term_at(g, tab, kj / g.J1, kj % g.J1, n);
+}
 
 // The per-(k, j) quantities of the set-up straight from the parameters (its
 // formulas and operation order), for kernels that run beside the set-up:
@@ -667,6 +670,149 @@ __device__ __forceinline__ void num_tile_item(const Item it, const GeomDev *__re
     }
 }
 
+// Small maps (at most 4 TX x 4 TY unique pixels), terms computed in place:
+// the map in 4 x 4 tiles by v_mfma_f32_4x4x1, whose sixteen blocks take
+// sixteen terms, each block into its own sums.  Lane l generates the rows
+// 4 i + l % 4 of A and the columns 4 j + l % 4 of B for term l / 4 of the
+// sixteen, so no operand and few tiles are padding: a 19 x 19 map takes 25
+// tiles of 4 x 4, where one 32 x 32 block is 2.8 times its pixels.  A block's
+// FP32 sums run over kSmallFold chunks' share (64 terms) and are then added
+// over the sixteen blocks in FP64, through LDS (16 registers at a time, rows
+// of 68 floats so that the sixteen registers' reads fall on different banks).
+// Waves, slices and the stored tile are those of num_tile_item.
+// Matrix and vector issue bound it about equally (25 x 8 cycles, and ten
+// exponentials and twenty multiply-adds per sixteen terms).  Measured, 4096
+// models of 10 x 13 x 100 terms on 19 x 19 pixels: the 32 x 32 block 1509 us,
+// this 930 us.
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kSmallFold = 16;   // chunks
+constexpr int kSmallRed = 9 * 64;   // doubles of a wave's sums, and of its staging (16 x 68 floats)
+
+template <int TX, int TY>
+__device__ __forceinline__ void num_small_item(const Item it, const GeomDev *__restrict__ geoms,
+                                               const ModelDev *__restrict__ models,
+                                               const double *__restrict__ gauss,
+                                               const int *__restrict__ st_ws,
+                                               double *__restrict__ part,
+                                               double *__restrict__ pix, float4 *cs, int wave,
+                                               double *red) {
+  constexpr int kTiles = TX * TY, NG = (4 * kTiles + 15) / 16, kRow = 68;
+  static_assert(16 * kRow <= 2 * kSmallRed && NG * 64 <= kSmallRed,
+                "the staging and the waves' sums fit red");
+  const int lane = threadIdx.x & 63, r4 = lane & 3, blk = lane >> 2;
+  const ModelDev md = models[it.m];
+  const GeomDev &g = geoms[md.geom];
+  float x2[TX], y2[TY];
+#pragma unroll
+  for (int i = 0; i < TX; ++i) {
+    const int xi = 4 * i + r4;
+    const double x = xi < g.n_ux ? g.xs[xi] : 0.0;
+    x2[i] = (float)(x * x);
+  }
+#pragma unroll
+  for (int j = 0; j < TY; ++j) {
+    const int yi = 4 * j + r4;
+    const double y = yi < g.n_uy ? g.ys[yi] : 0.0;
+    y2[j] = (float)(y * y);
+  }
+  int ts, te;
+  slice_range(g.T, md.n_slices, it.b, ts, te, KC2);
+  const int n_all = (st_ws[it.m] == 0) ? (te - ts + KC2 - 1) / KC2 : 0;
+  const int qn = (n_all + 3) / 4;
+  const int cb = min(n_all, wave * qn), ce = min(n_all, cb + qn);
+  const int n_ch = ce - cb;
+  const int t0 = ts + cb * KC2, t1 = min(te, ts + ce * KC2);
+  const double *gt = gauss + md.gauss_off;
+  __syncthreads();                 // the previous item's reads of red
+  // the lane's next term, 64 on from the one before (stepped, not divided);
+  // past the range a zero amplitude
+  const int nu = g.n_u, J1 = g.J1;
+  int t = t0 + lane, n = t % nu, j = (t / nu) % J1, k = t / nu / J1;
+  auto term = [&]() {
+    const float4 c = t < t1 ? term_at(g, gt, k, j, n) : make_float4(0.f, 0.f, 0.f, 0.f);
+    t += KC2;
+    n += KC2;
+    while (n >= nu) {
+      n -= nu;
+      if (++j == J1) {
+        j = 0;
+        ++k;
+      }
+    }
+    return c;
+  };
+  const v4f zero = {0.f, 0.f, 0.f, 0.f};
+  v4f acc[TX][TY];
+#pragma unroll
+  for (int i = 0; i < TX; ++i)
+#pragma unroll
+    for (int j = 0; j < TY; ++j) acc[i][j] = zero;
+  double tot[NG];
+#pragma unroll
+  for (int q = 0; q < NG; ++q) tot[q] = 0.0;
+  float *st = reinterpret_cast<float *>(red) + wave * (16 * kRow);
+  float4 cnext = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (n_ch > 0) cnext = term();
+  for (int c0 = 0; c0 < n_ch; c0 += kSmallFold) {
+    const int c1 = min(n_ch, c0 + kSmallFold);
+    for (int ch = c0; ch < c1; ++ch) {
+      cs[lane] = cnext;
+      __builtin_amdgcn_wave_barrier();
+      if (ch + 1 < n_ch) cnext = term();
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const float4 c = cs[16 * s + blk];
+        float a[TX], b[TY];
+#pragma unroll
+        for (int i = 0; i < TX; ++i) a[i] = fast_exp2(c.x * x2[i]) * fmaf(c.w, x2[i], c.z);
+#pragma unroll
+        for (int j = 0; j < TY; ++j) b[j] = fast_exp2(c.y * y2[j]);
+#pragma unroll
+        for (int i = 0; i < TX; ++i)
+#pragma unroll
+          for (int j = 0; j < TY; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    // register 4 tile + r of lane 4 blk + c: pixel (4 i + r, 4 j + c) of block blk
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int tile = (16 * q + e) / 4;
+        if (tile < kTiles) st[e * kRow + lane] = acc[tile / TY][tile % TY][e % 4];
+      }
+      __builtin_amdgcn_wave_barrier();
+      double v = 0.0;
+#pragma unroll
+      for (int b = 0; b < 16; ++b) v += (double)st[blk * kRow + 4 * b + r4];
+      tot[q] += v;
+      __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int i = 0; i < TX; ++i)
+#pragma unroll
+      for (int j = 0; j < TY; ++j) acc[i][j] = zero;
+  }
+  // fixed-order sum of the four waves
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NG; ++q) red[(wave * NG + q) * 64 + lane] = tot[q];
+  __syncthreads();
+  const int ldh = 32 * md.n_yt;
+  double *out = part + md.part_off + it.b * part_slice_size(md);
+  for (int e = threadIdx.x; e < 16 * kTiles; e += 256) {
+    // pixel (4 i + r, 4 j + c): tile 4 x 4 register r, column c
+    const int tile = e / 16, x = 4 * (tile / TY) + (e / 4) % 4, y = 4 * (tile % TY) + e % 4;
+    const double v = ((red[e] + red[NG * 64 + e]) + red[2 * NG * 64 + e]) + red[3 * NG * 64 + e];
+    if (md.n_slices > 1)
+      out[(int64_t)x * ldh + y] = v;
+    else if (x < g.n_ux && y < g.n_uy)       // the whole sum: straight into the N map
+      pix[md.pix_off + (int64_t)y * g.n_ux + x] = v;
+  }
+}
+
 // Numerator, per-pixel VALU form, over a work list of items (m, 256-pixel
 // block, slice).  With a queue, every workgroup pulls the next item from a
 // device counter (a persistent grid; items are ordered largest first);
@@ -729,6 +875,22 @@ __global__ void __launch_bounds__(256, 2) k_num_mfma(const GeomDev *__restrict__
     }
     if (!queue) i += gridDim.x;
   }
+}
+
+// (A kernel per tiling: in one kernel with a switch the compiler spills.)
+template <int TX, int TY>
+__global__ void __launch_bounds__(256, 2) k_num_small(const GeomDev *__restrict__ geoms,
+                                                   const ModelDev *__restrict__ models,
+                                                   const Item *__restrict__ items, int n_it,
+                                                   const double *__restrict__ gauss,
+                                                   const int *__restrict__ st_ws,
+                                                   double *__restrict__ part,
+                                                   double *__restrict__ pix) {
+  __shared__ __attribute__((aligned(16))) float4 cs[4][KC2];
+  __shared__ double red[4 * kSmallRed];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int i = blockIdx.x; i < n_it; i += gridDim.x)
+    num_small_item<TX, TY>(items[i], geoms, models, gauss, st_ws, part, pix, cs[wave], wave, red);
 }
 
 // Sum the split-term partials in a fixed order into the N map.  Item
@@ -1552,13 +1714,15 @@ __global__ void __launch_bounds__(256) k_chain(const GeomDev *__restrict__ geoms
 //   S0 = sum_p lambda E F,  S1 = sum_p lambda x^2 E F,
 //   Sg = sum_p lambda y^2 E F (C0 + C1 x^2),   E F = exp(-c1 x^2 - gamma y^2):
 // F(y) and y^2 F(y) for every y in registers, then per x the FP32 sums
-// g = sum_y lambda F and h = sum_y lambda y^2 F (lambda broadcast from LDS,
-// four y at a time) and the x-sums in FP32, converted to FP64; the y loops
-// are unrolled for the map's number of y quads.
+// g = sum_y lambda F and h = sum_y lambda y^2 F on the matrix cores and the
+// x-sums in FP32, converted to FP64; the y loops are unrolled for the map's
+// number of y quads.  Matrix and vector issue bound it.  Measured, 1024 models
+// of 13000 terms on 19 x 19 pixels: lambda broadcast from LDS to every lane's
+// own multiply-adds 637 us (the reads as long as the sums), this 478 us.
 // The term's chain values (those of k_chain) go through LDS and every (k, j)
-// row is summed over its u-nodes by one wave in a fixed order.  Item (m,
-// first tracer k0 | k1 << 16): tracers k0 <= k < k1 (at most
-// kSmallAdjTracers); lambda_N, the squared coordinates, every mass
+// row is summed over its u-nodes by one wave in a fixed order.  Item (m, k0 |
+// k1 << 16, r0 | r1 << 16): of the tracers k0 <= k < k1 (at most
+// kSmallAdjTracers) the (k, j) rows r0 .. r1 - 1; lambda_N, the squared coordinates, every mass
 // Gaussian's and every tracer's set-up values are staged in LDS once per
 // item, and the item's (k, j) rows, tracer-major, are taken in windows of
 // whole rows with at most kAdjTerms terms, so that the passes of 256 terms
@@ -1567,15 +1731,18 @@ __global__ void __launch_bounds__(256) k_chain(const GeomDev *__restrict__ geoms
 // ---------------------------------------------------------------------------
 constexpr int kSmallMap = 32;
 constexpr int kAdjTerms = kSmallAdjTerms;
+constexpr int kSmallLam = kSmallMap + 4;   // the four rows of a read on different banks
 
 // The three FP32 map sums of one term (lane) over NYQ quads of y (past the
-// map y^2 = 0 and lambda = 0, so the padding adds nothing) and nx values of
-// x: F(y) and y^2 F(y) in registers, per x g and h over y with lambda read
-// four at a time from LDS (the same address in every lane), then E(x).
+// map y^2 = 0 and lambda = 0, so the padding adds nothing) and nxq quads of x:
+// F(y) and y^2 F(y) in registers; per quad of x the sums g and h over y by
+// v_mfma_f32_4x4x1 with lambda(4 i + l % 4, y) as A in lane l and F as B: block
+// l / 4, column l % 4 is lane l's own term and register r its sum at x = 4 i +
+// r, so nothing moves between lanes.  lambda is read four y at a time.
 template <int NYQ>
 __device__ __forceinline__ void small_sums(float cx, float cy, float C0, float C1,
-                                           const float (*lam)[kSmallMap], const float *xsq,
-                                           const float *ysq, int nx, float &s0, float &s1,
+                                           const float (*lam)[kSmallLam], const float *xsq,
+                                           const float *ysq, int nxq, float &s0, float &s1,
                                            float &sg) {
   float F[4 * NYQ], Fy[4 * NYQ];
 #pragma unroll
@@ -1588,41 +1755,59 @@ __device__ __forceinline__ void small_sums(float cx, float cy, float C0, float C
   // reads are not hoisted out of the caller's term loop into registers
   int zoff;
   asm volatile("s_mov_b32 %0, 0" : "=s"(zoff));
+  const int r4 = threadIdx.x & 3;
   s0 = 0.f;
   s1 = 0.f;
   sg = 0.f;
-#pragma unroll 2
-  for (int xx = 0; xx < nx; ++xx) {
-    const float4 *lr = reinterpret_cast<const float4 *>(lam[xx]) + zoff;
-    float gs = 0.f, hs = 0.f;
+  // NX quads at a time: with two, four independent sums cover the matrix
+  // instructions' latency
+  auto quads = [&](int xq, auto nxt) {
+    constexpr int NX = decltype(nxt)::value;
+    v4f gs[NX], hs[NX];
+#pragma unroll
+    for (int q = 0; q < NX; ++q) gs[q] = hs[q] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int yq = 0; yq < NYQ; ++yq) {
-      const float4 l = lr[yq];
-      gs = fmaf(l.x, F[4 * yq], gs);
-      hs = fmaf(l.x, Fy[4 * yq], hs);
-      gs = fmaf(l.y, F[4 * yq + 1], gs);
-      hs = fmaf(l.y, Fy[4 * yq + 1], hs);
-      gs = fmaf(l.z, F[4 * yq + 2], gs);
-      hs = fmaf(l.z, Fy[4 * yq + 2], hs);
-      gs = fmaf(l.w, F[4 * yq + 3], gs);
-      hs = fmaf(l.w, Fy[4 * yq + 3], hs);
+      float4 l[NX];
+#pragma unroll
+      for (int q = 0; q < NX; ++q)
+        l[q] = (reinterpret_cast<const float4 *>(lam[4 * (xq + q) + r4]) + zoff)[yq];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+          const float a = c == 0 ? l[q].x : (c == 1 ? l[q].y : (c == 2 ? l[q].z : l[q].w));
+          gs[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, F[4 * yq + c], gs[q], 0, 0, 0);
+          hs[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(a, Fy[4 * yq + c], hs[q], 0, 0, 0);
+        }
     }
-    const float x2 = xsq[xx];
-    const float E = fast_exp2(cx * x2);
-    const float Eg = E * gs;
-    s0 += Eg;
-    s1 = fmaf(Eg, x2, s1);
-    sg = fmaf(E * hs, fmaf(C1, x2, C0), sg);
-  }
+#pragma unroll
+    for (int q = 0; q < NX; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float x2 = xsq[4 * (xq + q) + r];
+        const float E = fast_exp2(cx * x2);
+        const float Eg = E * gs[q][r];
+        s0 += Eg;
+        s1 = fmaf(Eg, x2, s1);
+        sg = fmaf(E * hs[q][r], fmaf(C1, x2, C0), sg);
+      }
+  };
+  int xq = 0;
+  for (; xq + 1 < nxq; xq += 2) quads(xq, std::integral_constant<int, 2>());
+  if (xq < nxq) quads(xq, std::integral_constant<int, 1>());
 }
 
-__global__ void __launch_bounds__(256) k_adj_small(const GeomDev *__restrict__ geoms,
+// (A kernel per number of y quads: in one kernel all take the largest one's
+// registers.)
+template <int NYQ>
+__global__ void __launch_bounds__(256, NYQ <= 5 ? 3 : 2) k_adj_small(const GeomDev *__restrict__ geoms,
                                                    const ModelDev *__restrict__ models,
                                                    const Item *__restrict__ items, int n_it,
                                                    ParamsDev p, const double *__restrict__ pix,
                                                    const int *__restrict__ st_ws,
                                                    double *__restrict__ sens) {
-  __shared__ __attribute__((aligned(16))) float lam[kSmallMap][kSmallMap];   // [x][y]
+  __shared__ __attribute__((aligned(16))) float lam[kSmallMap][kSmallLam];   // [x][y]
   __shared__ float xsq[kSmallMap], ysq[kSmallMap];
   // per mass Gaussian: e2, de2/di, r, K_j / M_j, M_j
   __shared__ double jv[kSmallAdjMass][5];
@@ -1635,7 +1820,7 @@ __global__ void __launch_bounds__(256) k_adj_small(const GeomDev *__restrict__ g
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
     const Item it = items[i];
     const ModelDev md = models[it.m];
-    const GeomDev g = geoms[md.geom];
+    const GeomDev &g = geoms[md.geom];
     if (st_ws[it.m] != 0) continue;   // uniform per block; k_grads writes NaN
     // block-uniform bounds in scalar registers, so the unrolled loops'
     // guards are scalar branches
@@ -1703,32 +1888,35 @@ __global__ void __launch_bounds__(256) k_adj_small(const GeomDev *__restrict__ g
       v[8] = p.lum_I0 ? p.lum_I0[md.lum_off + k] : g.lum_I0[k];
     }
     double *rows = chain_rows(sens, md, g);
-    const int n_rows = (k1 - k0) * J1;
+    const int row0 = __builtin_amdgcn_readfirstlane(it.b & 0xffff);
+    const int row1 = __builtin_amdgcn_readfirstlane(it.b >> 16);
     const int per_win = max(1, kAdjTerms / nu);   // whole rows per window
-    for (int r0 = 0; r0 < n_rows; r0 += per_win) {
-      const int nr = min(per_win, n_rows - r0);
+    const float rnu = 1.f / nu, rJ1 = 1.f / J1;
+    for (int r0 = row0; r0 < row1; r0 += per_win) {
+      const int nr = min(per_win, row1 - r0);
       const int n_terms = nr * nu;
       __syncthreads();                // staging done; earlier readers of vals done
       for (int base = 0; base < n_terms; base += 256) {
-        const int tl = base + threadIdx.x;
-        if (tl >= n_terms) break;
-        const int rr = tl / nu, n = tl - rr * nu;
-        const int row = r0 + rr, kk = row / J1, jj = row - kk * J1;
+        // lanes past the window repeat its last term: the matrix instructions
+        // take the whole wave
+        const int tq = base + threadIdx.x, tl = min(tq, n_terms - 1);
+        // (exact: at most 2^14 rows, FP32 quotients of half-integers)
+        const int rr = (int)((tl + 0.5f) * rnu), n = tl - rr * nu;
+        const int row = r0 + rr, kk = (int)((row + 0.5f) * rJ1), jj = row - kk * J1;
         const double *tk = tv[kk];
         const double *v = jv[jj];
         const double alpha = tk[0], b = tk[7];
         const dual alphaq = {tk[1], tk[2]}, nu1 = {tk[3], tk[4]}, pf = {tk[5], tk[6]};
         const double r = v[2], Mj = v[4];
-        const double u = g.u[n], wq = g.w[n], u2 = u * u;
+        const double u = load_global(g.u + n), wq = load_global(g.w + n), u2 = u * u;
         const dual h = {fma(-v[0], u2, 1.0), -u2 * v[1]};
         const double c1 = alpha + r * u2;
-        const double rhv = rcp64(h.v);
+        const double rshv = rsq64(h.v), rhv = rshv * rshv;
         const dual rh = {rhv, -rhv * rhv * h.d};
         const dual A = alphaq + (r * u2) * rh;
         const dual a = c1 * si2 + A * ci2;
-        const double rav = rcp64(a.v);
+        const double rsav = rsq64(a.v), rav = rsav * rsav;
         const dual gam = c1 * A * dual{rav, -rav * rav * a.d};
-        const double rshv = rsq64(h.v);
         const dual rsh = {rshv, -0.5 * rshv * rhv * h.d};
         const dual bse = (v[3] * r * u2) * nu1;               // per unit I0 M
         const double rAv = rcp64(A.v);
@@ -1736,28 +1924,22 @@ __global__ void __launch_bounds__(256) k_adj_small(const GeomDev *__restrict__ g
         const dual ww = 2.0 * bse * rsh;
         const dual P = pf * gg;
         const dual Q = si2 * (ww - (2.0 * c1 * b) * gg);
-        const double fv = wq * kSqrtPi * rsq64(a.v);
+        const double fv = wq * kSqrtPi * rsav;
         const dual f = {fv, -0.5 * fv * rav * a.d};
         const dual c0 = f * P, c1u = f * Q;                   // C = I0 M c
         const double amp = tk[8] * Mj;
         const float cx = (float)(-c1 * kLog2e), cy = (float)(-gam.v * kLog2e);
         const float C0 = (float)(amp * c0.v), C1 = (float)(amp * c1u.v);
         float s0, s1, sg;
-        switch ((ny + 3) >> 2) {    // uniform
-          case 1: small_sums<1>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          case 2: small_sums<2>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          case 3: small_sums<3>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          case 4: small_sums<4>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          case 5: small_sums<5>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          case 6: small_sums<6>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          case 7: small_sums<7>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-          default: small_sums<8>(cx, cy, C0, C1, lam, xsq, ysq, nx, s0, s1, sg); break;
-        }
+        const int nxq = (nx + 3) >> 2;
+        small_sums<NYQ>(cx, cy, C0, C1, lam, xsq, ysq, nxq, s0, s1, sg);
         const double S0 = s0, S1 = s1, Sg = sg;
-        vals[tl][0] = amp * (S0 * c0.d + S1 * c1u.d) - Sg * gam.d;
-        // dC0/db = f si2 g, dC1/db = -2 f si2 c1 g
-        vals[tl][1] = amp * f.v * si2.v * gg.v * (S0 - 2.0 * c1 * S1);
-        vals[tl][2] = S0 * c0.v + S1 * c1u.v;
+        if (tq < n_terms) {
+          vals[tl][0] = amp * (S0 * c0.d + S1 * c1u.d) - Sg * gam.d;
+          // dC0/db = f si2 g, dC1/db = -2 f si2 c1 g
+          vals[tl][1] = amp * f.v * si2.v * gg.v * (S0 - 2.0 * c1 * S1);
+          vals[tl][2] = S0 * c0.v + S1 * c1u.v;
+        }
       }
       __syncthreads();
       // (k, j) rows: one wave per row, lanes over the u-nodes in order, then
@@ -3488,6 +3670,28 @@ void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
     hipLaunchKernelGGL(k_num_pix, dim3(grid_of(grid)), dim3(256), 0, st, g, m, it, n_it, terms,
                        st_ws, part, queue);
 }
+template <int TX, int TY>
+static void small_kernel(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                         const double *gauss, const int *st_ws, double *part, double *pix,
+                      hipStream_t st) {
+  hipLaunchKernelGGL((k_num_small<TX, TY>), dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
+                     gauss, st_ws, part, pix);
+}
+void launch_num_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int tiling,
+                      const double *gauss, const int *st_ws, double *part, double *pix,
+                      hipStream_t st) {
+  switch (tiling) {
+    case 0: small_kernel<3, 3>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 1: small_kernel<3, 5>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 2: small_kernel<3, 6>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 3: small_kernel<5, 3>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 4: small_kernel<5, 5>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 5: small_kernel<5, 6>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 6: small_kernel<6, 3>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    case 7: small_kernel<6, 5>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+    default: small_kernel<6, 6>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+  }
+}
 void launch_reduce(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                    const double *part, double *pix, hipStream_t st) {
   hipLaunchKernelGGL(k_reduce, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, part, pix);
@@ -3538,10 +3742,26 @@ int occupancy_sens() {
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sens, 256, 0) != hipSuccess) nb = 1;
   return nb < 1 ? 1 : nb;
 }
-void launch_adj_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, ParamsDev p,
-                      const double *pix, const int *st_ws, double *sens, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_small, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, p, pix,
-                     st_ws, sens);
+template <int NYQ>
+static void adj_small_kernel(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                             ParamsDev p, const double *pix, const int *st_ws, double *sens,
+                             hipStream_t st) {
+  hipLaunchKernelGGL(k_adj_small<NYQ>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, p,
+                     pix, st_ws, sens);
+}
+void launch_adj_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int y_quads,
+                      ParamsDev p, const double *pix, const int *st_ws, double *sens,
+                      hipStream_t st) {
+  switch (y_quads) {
+    case 1: adj_small_kernel<1>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    case 2: adj_small_kernel<2>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    case 3: adj_small_kernel<3>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    case 4: adj_small_kernel<4>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    case 5: adj_small_kernel<5>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    case 6: adj_small_kernel<6>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    case 7: adj_small_kernel<7>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+    default: adj_small_kernel<8>(g, m, it, n_it, p, pix, st_ws, sens, st); break;
+  }
 }
 void launch_chain(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, ParamsDev p,
                   double *sens, const int *st_ws, hipStream_t st) {

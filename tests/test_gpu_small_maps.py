@@ -1,0 +1,72 @@
+"""Small maps (one 32 x 32 block of distinct pixels) in batches, forward and
+adjoint, against the FP64 oracle at the edges of the 4 x 4 tilings (12, 20, 24
+distinct columns or rows, remainders of four, the sizes beyond) and of the
+adjoint's groups of four rows; and the adjoint's items, whole tracers in a batch
+and rows of one tracer for a single model.
+
+Bars: the sums are FP32 with FP32 exponentials whose rounded coefficients shift
+an exponent by up to 6e-8 of itself, 20 where a term still counts: 1.2e-6 of such
+a term, 1e-7 of the sum.  Per bin 1e-6, the gradient's norm (sums of both signs)
+1e-5."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import jam as ojam
+from paper_2504_01302_amd import binding, inputs
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("inc", "beta", "mass_scale", "m_bh", "lum_I0", "mass_S0")
+
+
+def _dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def _flat(g):
+    return np.concatenate([np.ravel(np.asarray(g[k])) for k in KEYS])
+
+
+def _model(nx, ny, n_u):
+    # off centre: every column and row distinct
+    g = inputs.small_geometry(seed=nx + 40 * ny, n_lum=3, n_mass=5, nx=nx, ny=ny, psf_n=1,
+                              n_bins=3, n_u=n_u, pixsize=0.06, xc=0.007, yc=-0.011)
+    return g, inputs.small_params(g, seed=nx + ny)
+
+
+def _run(g, ps, cot, dev):
+    n = len(ps)
+    w = inputs.Workload("s", [g], np.zeros(n, np.int32), ps)
+    ctx = binding.Context([g])
+    par = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, par["inc"], par["mass_scale"], par["m_bh"], par["beta"], par["lum_I0"],
+            par["mass_S0"])
+    V, st = ctx.eval_batch(*args)
+    gr = ctx.vjp(*args, V, torch.as_tensor(np.tile(cot, n), device=dev))
+    torch.cuda.synchronize()
+    assert (st.cpu().numpy() == 0).all()
+    out = (V.cpu().numpy()[-g.n_bins:],
+           {k: gr[k].cpu().numpy().reshape(n, -1)[-1] for k in KEYS})
+    ctx.close()
+    return out
+
+
+@pytest.mark.parametrize("nx,ny,n_u", [
+    (4, 4, 40), (12, 12, 40), (13, 5, 33), (20, 20, 40), (21, 12, 40), (24, 24, 47), (5, 23, 40),
+    (25, 9, 40), (9, 32, 40), (3, 17, 64)])
+@pytest.mark.parametrize("n", [1, 2000])
+def test_tilings_vs_oracle(nx, ny, n_u, n):
+    dev = _dev()
+    g, p = _model(nx, ny, n_u)
+    cot = np.random.default_rng(5).standard_normal(g.n_bins)
+    ps = [inputs.with_overrides(p, m_bh=p.m_bh * (1.0 + 1e-3 * (n - 1 - m))) for m in range(n)]
+    V, gr = _run(g, ps, cot, dev)
+    rV, rg = ojam.vrms2_and_grad(g, p, cot)
+    err = np.max(np.abs(V / rV.numpy() - 1))
+    a, b = _flat(gr), _flat({k: v.numpy() for k, v in rg.items()})
+    gerr = np.linalg.norm(a - b) / np.linalg.norm(b)
+    print(f"{nx} x {ny}, {n}: forward {err:.2e}, gradient {gerr:.2e}")
+    assert err <= 1e-6 and gerr <= 1e-5
