@@ -2152,61 +2152,90 @@ __device__ inline cplx c_div(cplx a, cplx b) {
   return {(a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d};
 }
 
-// Thread per (profile, Gaussian n); the terms k and components c are summed
-// in a fixed order.
+// Nodes R^2 = 2 sigma_n^2 beta_k and weights, staged in LDS.
+struct MgeTables {
+  double s2[kMgeMaxSigma], scale[kMgeMaxSigma], eta[kMgeMaxTerms], bim[kMgeMaxTerms];
+};
+__device__ inline void mge_stage(const MgeConst &kc, MgeTables &t) {
+  const int e = threadIdx.x;
+  if (e < kc.n_sigma) {
+    t.s2[e] = 2.0 * kc.sigma2[e];
+    t.scale[e] = kc.scale[e];
+  }
+  if (e < kc.n_terms) {
+    t.eta[e] = kc.eta[e];
+    t.bim[e] = kc.beta_im[e];
+  }
+  __syncthreads();
+}
+constexpr int kMgeBlocks = 1 << 16;
+
+// 32 lanes per (profile, Gaussian n), the terms k over the lanes, added in a
+// fixed order.  The complex logarithms and exponentials (some 400 FP64
+// operations each) bound both kernels; with a thread per output 512 profiles
+// kept 168 waves busy here and 16 below: 34 and 301 us, now 13 and 11.
 __global__ void __launch_bounds__(256) k_mge1d(int n_prof, int n_comp,
                                                const double *__restrict__ comp, MgeConst kc,
                                                double *__restrict__ amp) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)n_prof * kc.n_sigma) return;
-  const int prof = (int)(id / kc.n_sigma), n = (int)(id % kc.n_sigma);
-  const double *cp = comp + (int64_t)prof * n_comp * 3;
-  double f = 0.0;
-  for (int k = 0; k < kc.n_terms; ++k) {
-    const cplx r2 = {2.0 * kc.sigma2[n] * kc.beta_re, 2.0 * kc.sigma2[n] * kc.beta_im[k]};
-    double fr = 0.0;   // Re F(R)
-    for (int c = 0; c < n_comp; ++c) {
-      const double a = cp[3 * c], cc = cp[3 * c + 1], p = cp[3 * c + 2];
-      const cplx L = c_log({r2.re + cc * cc, r2.im});
-      fr += a * c_exp({-p * L.re, -p * L.im}).re;
+  __shared__ MgeTables t;
+  mge_stage(kc, t);
+  const int lane = threadIdx.x & 31;
+  for (int64_t id = (int64_t)blockIdx.x * (blockDim.x / 32) + threadIdx.x / 32;
+       id < (int64_t)n_prof * kc.n_sigma; id += (int64_t)gridDim.x * (blockDim.x / 32)) {
+    const int prof = (int)(id / kc.n_sigma), n = (int)(id % kc.n_sigma);
+    const double *cp = comp + (int64_t)prof * n_comp * 3;
+    double f = 0.0;
+    for (int k = lane; k < kc.n_terms; k += 32) {
+      const cplx r2 = {t.s2[n] * kc.beta_re, t.s2[n] * t.bim[k]};
+      double fr = 0.0;   // Re F(R)
+      for (int c = 0; c < n_comp; ++c) {
+        const double a = cp[3 * c], cc = cp[3 * c + 1], p = cp[3 * c + 2];
+        const cplx L = c_log({r2.re + cc * cc, r2.im});
+        fr += a * c_exp({-p * L.re, -p * L.im}).re;
+      }
+      f += t.eta[k] * fr;
     }
-    f += kc.eta[k] * fr;
+    for (int o = 16; o > 0; o >>= 1) f += __shfl_xor(f, o, 32);
+    if (lane == 0) amp[id] = t.scale[n] * f;
   }
-  amp[id] = kc.scale[n] * f;
 }
 
-// Thread per (profile, component): its three derivatives summed over the
-// Gaussians n (weighted by the cotangent) and the terms k in a fixed order.
+// A wave per (profile, component): its three derivatives summed over the
+// Gaussians n (weighted by the cotangent) and the terms k, (n, k) pairs over
+// the lanes, in a fixed order.
 __global__ void __launch_bounds__(256) k_mge1d_vjp(int n_prof, int n_comp,
                                                    const double *__restrict__ comp, MgeConst kc,
                                                    const double *__restrict__ cot,
                                                    double *__restrict__ grad) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)n_prof * n_comp) return;
-  const int prof = (int)(id / n_comp);
-  const double *cp = comp + id * 3;
-  const double a = cp[0], cc = cp[1], p = cp[2];
-  double ga = 0.0, gc = 0.0, gp = 0.0;
-  for (int n = 0; n < kc.n_sigma; ++n) {
-    double da = 0.0, dc = 0.0, dp = 0.0;
-    for (int k = 0; k < kc.n_terms; ++k) {
-      const cplx w = {2.0 * kc.sigma2[n] * kc.beta_re + cc * cc, 2.0 * kc.sigma2[n] * kc.beta_im[k]};
+  __shared__ MgeTables t;
+  mge_stage(kc, t);
+  const int lane = threadIdx.x & 63;
+  for (int64_t id = (int64_t)blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+       id < (int64_t)n_prof * n_comp; id += (int64_t)gridDim.x * (blockDim.x / 64)) {
+    const int prof = (int)(id / n_comp);
+    const double *cp = comp + id * 3;
+    const double a = cp[0], cc = cp[1], p = cp[2];
+    double ga = 0.0, gc = 0.0, gp = 0.0;
+    for (int e = lane; e < kc.n_sigma * kc.n_terms; e += 64) {
+      const int n = e / kc.n_terms, k = e % kc.n_terms;
+      const cplx w = {t.s2[n] * kc.beta_re + cc * cc, t.s2[n] * t.bim[k]};
       const cplx L = c_log(w);
       const cplx E = c_exp({-p * L.re, -p * L.im});          // w^-p
       const cplx Ew = c_div(E, w);                            // w^-(p+1)
-      const double eta = kc.eta[k];
-      da += eta * E.re;
-      dc += eta * (-2.0 * p * cc * a) * Ew.re;
-      dp += eta * (-a) * c_mul(L, E).re;
+      const double s = t.scale[n] * cot[(int64_t)prof * kc.n_sigma + n] * t.eta[k];
+      ga += s * E.re;
+      gc += s * (-2.0 * p * cc * a) * Ew.re;
+      gp += s * (-a) * c_mul(L, E).re;
     }
-    const double s = kc.scale[n] * cot[(int64_t)prof * kc.n_sigma + n];
-    ga += s * da;
-    gc += s * dc;
-    gp += s * dp;
+    ga = wave_sum(ga);
+    gc = wave_sum(gc);
+    gp = wave_sum(gp);
+    if (lane == 0) {
+      grad[id * 3] = ga;
+      grad[id * 3 + 1] = gc;
+      grad[id * 3 + 2] = gp;
+    }
   }
-  grad[id * 3] = ga;
-  grad[id * 3 + 1] = gc;
-  grad[id * 3 + 2] = gp;
 }
 
 // ---------------------------------------------------------------------------
@@ -3840,13 +3869,13 @@ void launch_beta_logistic_vjp(const GeomDev *g, const ModelDev *m, int n, const 
 void launch_mge1d(int n_prof, int n_comp, const double *comp, const MgeConst &k, double *amp,
                   hipStream_t st) {
   const int64_t n = (int64_t)n_prof * k.n_sigma;
-  hipLaunchKernelGGL(k_mge1d, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n_prof, n_comp,
+  hipLaunchKernelGGL(k_mge1d, dim3((unsigned)std::min<int64_t>((n + 7) / 8, kMgeBlocks)), dim3(256), 0, st, n_prof, n_comp,
                      comp, k, amp);
 }
 void launch_mge1d_vjp(int n_prof, int n_comp, const double *comp, const MgeConst &k,
                       const double *cot, double *grad, hipStream_t st) {
   const int64_t n = (int64_t)n_prof * n_comp;
-  hipLaunchKernelGGL(k_mge1d_vjp, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n_prof,
+  hipLaunchKernelGGL(k_mge1d_vjp, dim3((unsigned)std::min<int64_t>((n + 3) / 4, kMgeBlocks)), dim3(256), 0, st, n_prof,
                      n_comp, comp, k, cot, grad);
 }
 void launch_chi2(const GeomDev *g, const ModelDev *m, int n, const KinDev *kin, const double *V,
