@@ -74,6 +74,16 @@ template <int Q> __device__ __forceinline__ void rotate8(double (&w)[8], int d) 
   for (int b = 0; b < 8; ++b) w[b] = u[b];
 }
 
+// Whether a tracer's density underflows to an exact zero along every
+// characteristic from radius r on: its exponent at r' >= r is at least
+// min(alpha, alphaq) r^2, and pol_exp gives zero from 746 on.  Such a (tracer,
+// radius) adds exact zeros everywhere and is left out: narrow tracers at large
+// radii, a fifth of the pairs of 48 models of 10 tracers.  Measured there with
+// them / without: moments 800 + 1230 / 684 + 1179 us, spread 1520 / 1240.
+__device__ __forceinline__ bool pol_empty(double alpha, double alphaq, double r2) {
+  return fmin(alpha, alphaq) * r2 > 750.0;
+}
+
 // Grid scales of a model (k_sph_terms): iX, s0, iC.
 struct PolScale {
   double iX, s0, iC;
@@ -275,6 +285,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     for (int k = k0; k < k1; ++k) {
       const double alpha = tab[k], alphaq = tab[K + k];
       const double kap2 = alphaq - alpha, kap = 2.0 * kap2;
+      double *jac = nullptr;
+      if constexpr (kJac)
+        jac = sph_adj_layout(sens + md.sens_off, K, g.n_pix, sph_terms_padded(g.J1, g.n_u),
+                             md.n_sens_parts).jac + ((int64_t)k * kSphCells + ir * kSphNT) * 8;
+      if (pol_empty(alpha, alphaq, r * r)) {        // uniform per wave
+        if constexpr (kJac)
+#pragma unroll
+          for (int e = 0; e < 3; ++e) jac[64 * e + lane] = 0.0;
+        continue;
+      }
       wave_sync();                          // the previous tracer's reads of W
       {
         const double omb = 1.0 / tab[3 * K + k], beta = 1.0 - omb;
@@ -409,9 +429,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
           At[t] += omb * P;
           Ap[t] += omb * P + omb * mt.sn[th] * (r / (rb2 * rbe)) * fD;
           if constexpr (kJac) {
-            double *o = sph_adj_layout(sens + md.sens_off, K, g.n_pix,
-                                       sph_terms_padded(g.J1, g.n_u), md.n_sens_parts).jac +
-                        ((int64_t)k * kSphCells + ir * kSphNT + th) * 8;
+            double *o = jac + th * 8;
             o[0] = fP;
             o[1] = fD;
 #pragma unroll
@@ -519,7 +537,7 @@ __global__ void __launch_bounds__(256) k_pol_table(
 // same result in any batch.
 // FP64 issue and the LDS adds bound it.  Measured (48 models of 10 tracers /
 // one of 40): the points sorted by tile of an R, z grid and spread with
-// fixed-point atomics 5300 / 700 us, this with k_pol_cot_sum 1550 / 203.
+// fixed-point atomics 5300 / 700 us, this with k_pol_cot_sum 1270 / 201.
 // ---------------------------------------------------------------------------
 struct SpreadWave {
   double L[2][8][kPolC + 1];              // lines of phi and psi
@@ -577,7 +595,8 @@ __global__ void __launch_bounds__(256, 3) k_pol_spread(
         // the pair's nodes lie within [x0, x0 + kSphSeg hs iX]
         const double x0 = fma(ir * g.sph_dlnr, sc.iX, 2.0), x1 = fma(kSphSeg * hs, sc.iX, x0);
         const bool top = ia + kPolR > kPolN - 4;            // the last bin takes what is clamped
-        todo = __ballot(x1 >= (double)ia - 1e-6 && (top || x0 <= (double)(ia + kPolR) + 1e-6));
+        todo = __ballot(x1 >= (double)ia - 1e-6 && (top || x0 <= (double)(ia + kPolR) + 1e-6) &&
+                        !pol_empty(tab[k], tab[K + k], r2));
       }
       while (todo != 0 || (last && qn > 0)) {
         if (todo != 0) {

@@ -22,6 +22,8 @@ def _workload(n_lum, n_mass, n_u, kind, seed):
     if kind == "round":             # q' = 1 throughout: the columns' scale s0 = 1
         g.lum_q[:] = 1.0
         g.mass_q[:] = 1.0
+    if kind == "narrow":            # nothing left of all tracers but one over most radii
+        g.lum_sigma[1:] *= 0.02
     p = inputs.small_params(g, seed=seed)
     if kind == "thin":              # axial ratios down to 0.04, at 87.5 degrees
         g.mass_q[0] = 0.06
@@ -34,6 +36,7 @@ def _workload(n_lum, n_mass, n_u, kind, seed):
     (2, 3, 100, "plain"),     # a full cotangent group; 400 terms, one slice
     (3, 8, 98, "thin"),       # a half-filled group; 882 terms: two slices, uneven chunks
     (5, 8, 64, "round"),
+    (6, 5, 64, "narrow"),     # (tracer, radius) pairs that are left out
     (21, 4, 64, "plain"),     # two tracers per moments wave, the last alone
     (41, 16, 60, "plain"),    # three tracers per cotangent group; 1020 terms: 512-term tiles
 ])
