@@ -218,6 +218,14 @@ def jam_timing(ctx: int, enable: bool):
     return a.value, b.value, c.value, d.value
 
 
+def _stream(dev) -> int:
+    """The device's current stream (0.2 us; through torch.cuda.Stream 1.9)."""
+    import torch
+    if dev.type != "cuda":
+        return torch.cuda.current_stream(dev).cuda_stream      # raises
+    return torch._C._cuda_getCurrentRawStream(dev.index)
+
+
 def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
@@ -329,7 +337,7 @@ def jam_mge1d(comp, sigma, euler_p: int = 10, out=None, stream=None):
     sig = np.ascontiguousarray(sigma, dtype=np.float64)
     amp = out if out is not None else torch.empty(comp.shape[0], len(sig), dtype=torch.float64,
                                                   device=comp.device)
-    s = stream if stream is not None else torch.cuda.current_stream(comp.device).cuda_stream
+    s = stream if stream is not None else _stream(comp.device)
     _check(load().jam_mge1d(comp.shape[0], comp.shape[1], _ptr(comp), len(sig),
                             sig.ctypes.data_as(P_double), int(euler_p), _ptr(amp), c_void_p(s)))
     return amp
@@ -342,7 +350,7 @@ def jam_mge1d_vjp(comp, sigma, cot, euler_p: int = 10, stream=None):
     cot = cot.contiguous()
     sig = np.ascontiguousarray(sigma, dtype=np.float64)
     grad = torch.empty_like(comp)
-    s = stream if stream is not None else torch.cuda.current_stream(comp.device).cuda_stream
+    s = stream if stream is not None else _stream(comp.device)
     _check(load().jam_mge1d_vjp(comp.shape[0], comp.shape[1], _ptr(comp), len(sig),
                                 sig.ctypes.data_as(P_double), int(euler_p), _ptr(cot),
                                 _ptr(grad), c_void_p(s)))
@@ -400,11 +408,11 @@ class Context:
                    stream=None, out=None, status=None):
         import torch
         dev = inc.device
-        nb, _, _ = self.sizes(geom_idx)
-        vr = out if out is not None else torch.empty(nb, dtype=torch.float64, device=dev)
+        vr = out if out is not None else torch.empty(self.sizes(geom_idx)[0], dtype=torch.float64,
+                                                     device=dev)
         st = status if status is not None else torch.empty(len(geom_idx), dtype=torch.int32, device=dev)
         ws = self.workspace(geom_idx, False, dev)
-        s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        s = stream if stream is not None else _stream(dev)
         jam_eval_batch(self.handle, geom_idx, inc, mass_scale, m_bh, beta, lum_I0, mass_S0,
                        vr, st, ws, s)
         return vr, st
@@ -422,7 +430,7 @@ class Context:
         I = torch.empty(total, dtype=torch.float64, device=dev)
         st = torch.empty(len(geom_idx), dtype=torch.int32, device=dev)
         ws = self.workspace(geom_idx, False, dev)
-        s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        s = stream if stream is not None else _stream(dev)
         jam_eval_maps(self.handle, geom_idx, inc, mass_scale, m_bh, beta, lum_I0, mass_S0,
                       N, I, st, ws, s)
         return N, I, st
@@ -436,7 +444,7 @@ class Context:
         z = lambda k: torch.empty(k, dtype=torch.float64, device=dev)
         g = dict(inc=z(n), mass_scale=z(n), m_bh=z(n), beta=z(nl), lum_I0=z(nl), mass_S0=z(nm))
         ws = self.workspace(geom_idx, True, dev)
-        s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        s = stream if stream is not None else _stream(dev)
         jam_vjp(self.handle, geom_idx, inc, mass_scale, m_bh, beta, lum_I0, mass_S0, vrms2, cot,
                 g["inc"], g["mass_scale"], g["m_bh"], g["beta"], g["lum_I0"], g["mass_S0"], ws, s)
         return g
@@ -449,7 +457,7 @@ class Context:
         prof = prof.contiguous()
         _, nl, _ = self.sizes(geom_idx)
         beta = out if out is not None else torch.empty(nl, dtype=torch.float64, device=prof.device)
-        s = stream if stream is not None else torch.cuda.current_stream(prof.device).cuda_stream
+        s = stream if stream is not None else _stream(prof.device)
         jam_beta_logistic(self.handle, geom_idx, prof, beta, s)
         return beta
 
@@ -458,7 +466,7 @@ class Context:
         import torch
         prof = prof.contiguous()
         grad = torch.empty_like(prof)
-        s = stream if stream is not None else torch.cuda.current_stream(prof.device).cuda_stream
+        s = stream if stream is not None else _stream(prof.device)
         jam_beta_logistic_vjp(self.handle, geom_idx, prof, cot.contiguous(), grad, s)
         return grad
 
@@ -471,7 +479,7 @@ class Context:
         dev = vrms2.device
         c = torch.empty(len(geom_idx), dtype=torch.float64, device=dev)
         d = torch.empty_like(vrms2) if want_grad else None
-        s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        s = stream if stream is not None else _stream(dev)
         jam_chi2(self.handle, geom_idx, vrms2, c, d, s)
         return c, d
 
@@ -484,7 +492,7 @@ class Context:
         vr = torch.empty(nb, dtype=torch.float64, device=dev) if keep_vrms2 else None
         st = torch.empty(len(geom_idx), dtype=torch.int32, device=dev)
         ws = self.workspace(geom_idx, False, dev)
-        s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        s = stream if stream is not None else _stream(dev)
         jam_eval_chi2(self.handle, geom_idx, inc, mass_scale, m_bh, beta, lum_I0, mass_S0,
                       c, vr, st, ws, s)
         return c, vr, st
@@ -498,7 +506,7 @@ class Context:
         z = lambda k: torch.empty(k, dtype=torch.float64, device=dev)
         g = dict(inc=z(n), mass_scale=z(n), m_bh=z(n), beta=z(nl), lum_I0=z(nl), mass_S0=z(nm))
         ws = self.workspace(geom_idx, True, dev)
-        s = stream if stream is not None else torch.cuda.current_stream(dev).cuda_stream
+        s = stream if stream is not None else _stream(dev)
         jam_vjp_chi2(self.handle, geom_idx, inc, mass_scale, m_bh, beta, lum_I0, mass_S0,
                      vrms2, cot, g["inc"], g["mass_scale"], g["m_bh"], g["beta"], g["lum_I0"],
                      g["mass_S0"], ws, s)
