@@ -668,17 +668,61 @@ std::vector<std::pair<int, int>> axis_tiles(int n, int tau) {
   return out;
 }
 
-// Small maps in 4 x 4 tiles instead of one 32 x 32 block: the width and height
-// rounded up to 12, 20 or 24 unique pixels (fewer kernels than sizes), -1: the
-// block.  A term costs the block 13.5 ns of matrix-core time, the largest
-// tiling here 9.2 ns, and 28 x 28 (49 tiles) 12.6 ns and more registers than
-// two waves a SIMD have.  The tiles' sums over their sixteen terms' blocks cost
-// an item about as much as two chunks of a wave save.
+// Maps in items of 4 x 4 tiles, 12, 20 or 24 pixels wide and high (fewer kernels
+// than sizes), instead of 32 x 32 blocks.  Of a map of one block, where the items
+// compute the terms in place: one item rounded up to those sizes.  A term costs
+// the block 13.5 ns of matrix-core time, the largest tiling here 9.2 ns, and 28 x
+// 28 (49 tiles) 12.6 ns and more registers than two waves a SIMD have.  The
+// tiles' sums over their sixteen terms' blocks cost an item about as much as two
+// chunks of a wave save.
+// Of a larger one (terms from their table): the items that cover it cheapest,
+// where they cost less than kSmallGain of its blocks, most of which are padding
+// just past a multiple of 32.  64 models of 10 x 13 x 40 terms, the whole call,
+// blocks / tiles: 33 x 33 67.0 / 57.7 us, 39 x 21 48.2 / 43.0, 44 x 44 68.6 /
+// 68.1, 70 x 70 117.0 / 105.9, and where the rule keeps the blocks 28 x 40 52.0 /
+// 57.7.  Each tiling is one more launch, serial with the others: in a batch of
+// several kinds only one that saves more than kSmallLaunchNs on the whole chip is
+// taken (30 models of mixed sizes: 51.0 us with three, 49.0 with none).
 constexpr int kSmallMinChunks = 2;
-int small_tiling(const GeomHost &g, const NumChoice &c) {
-  if (!c.gen || g.n_ux > 24 || g.n_uy > 24 || c.units < 4 * kSmallMinChunks * c.n_slices) return -1;
-  auto size = [](int n) { return n <= 12 ? 0 : (n <= 20 ? 1 : 2); };
-  return 3 * size(g.n_ux) + size(g.n_uy);
+constexpr double kSmallGain = 0.9;
+constexpr double kSmallLaunchNs = 6000.0;
+struct SmallTiles {
+  int tiling = -1;              // -1: 32 x 32 blocks
+  int nx = 1, ny = 1, w = 0, h = 0;   // items along x and y, their pixels
+  double gain = 0.0;                  // ns of one SIMD over the blocks
+};
+SmallTiles small_tiles(const GeomHost &g, const NumChoice &c) {
+  SmallTiles s;
+  if (c.kind != 2 || c.units < 4 * kSmallMinChunks * c.n_slices) return s;
+  if (c.gen) {
+    if (g.n_ux > 24 || g.n_uy > 24) return s;
+    auto size = [](int n) { return n <= 12 ? 0 : (n <= 20 ? 1 : 2); };
+    s.tiling = 3 * size(g.n_ux) + size(g.n_uy);
+    return s;
+  }
+  // ns per term: matrix instructions, exponentials, and per item the loop
+  double best = 0.0;
+  for (const WaveTile &t : c.tiles)
+    best += 14.5 * t.BX * t.BY + 4.1 * t.BX + 2.9 * t.BY;
+  const double blocks = best;
+  best *= kSmallGain;
+  constexpr int n4[3] = {3, 5, 6};
+  for (int X = 0; X < 3; ++X)
+    for (int Y = 0; Y < 3; ++Y) {
+      const int tx = n4[X], ty = n4[Y];
+      const int nx = (g.n_ux + 4 * tx - 1) / (4 * tx), ny = (g.n_uy + 4 * ty - 1) / (4 * ty);
+      const double cost = nx * ny * (0.256 * tx * ty + 0.51 * tx + 0.35 * ty + 1.2);
+      if (cost < best) {
+        best = cost;
+        s.gain = (blocks - cost) * g.T;
+        s.tiling = 9 + 3 * X + Y;
+        s.nx = nx;
+        s.ny = ny;
+        s.w = 4 * tx;
+        s.h = 4 * ty;
+      }
+    }
+  return s;
 }
 
 NumChoice choose_numerator(const GeomHost &g, const Tune &t, int gran) {
@@ -997,6 +1041,25 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   };
   // spherical forward: the potential grid (form 1: sums at every node)
   const bool use_sgrid = spherical && ctx->opt.form != 1;
+  std::vector<SmallTiles> tiles_of(spherical ? 0 : ctx->gh.size());
+  if (!spherical) {
+    std::vector<int> models(ctx->gh.size(), 0);
+    for (int m = 0; m < n; ++m) ++models[geom_idx[m]];
+    double gain[jam::kSmallTilings] = {};
+    int count[jam::kSmallTilings] = {};
+    for (size_t i = 0; i < models.size(); ++i) {
+      if (!models[i]) continue;
+      const GeomHost &g = ctx->gh[i];
+      SmallTiles &s = tiles_of[i] = small_tiles(g, choose_numerator(g, tune, tune.gran));
+      if (s.tiling < 0) continue;
+      gain[s.tiling] += models[i] * s.gain;
+      count[s.tiling] += models[i];
+    }
+    for (SmallTiles &s : tiles_of)
+      if (s.tiling >= 9 && count[s.tiling] < n &&
+          gain[s.tiling] < 4.0 * ctx->n_cu * kSmallLaunchNs)
+        s.tiling = -1;
+  }
   for (int m = 0; m < n; ++m) {
     const int gi = geom_idx[m];
     const GeomHost &g = ctx->gh[gi];
@@ -1188,20 +1251,23 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     for (int pb = 0; pb < (g.n_pix + 255) / 256; ++pb) it_pix.push_back({m, pb, 0, 0});
     // the compressed form's maps are summed by k_cheb_sum, a single slice of the
     // small tilings is the sum
-    if (!cheb && !(small && d.n_slices == 1 && small_tiling(g, nc) >= 0))
+    const SmallTiles tiles = spherical ? SmallTiles() : tiles_of[gi];
+    if (!cheb && !(d.n_slices == 1 && tiles.tiling >= 0))
       for (int pb = 0; pb < (g.n_pix + 63) / 64; ++pb) it_red.push_back({m, pb, 0, 0});
     for (int rb = 0; rb < (g.n_uy + 7) / 8; ++rb)
       for (int cb = 0; cb < (g.n_ux + 63) / 64; ++cb) {
         it_sb.push_back({m, rb, cb, 0});
         if (!cheb) it_sbpro.push_back({m, rb, cb, 0});
       }
-    for (int s = 0; s < d.n_slices; ++s)
+    if (tiles.tiling >= 0)
+      for (int s = 0; s < d.n_slices; ++s)
+        for (int ty = 0; ty < tiles.ny; ++ty)
+          for (int tx = 0; tx < tiles.nx; ++tx)
+            it_numsm.push_back({m, tx * tiles.w | (ty * tiles.h << 16), s, tiles.tiling});
+    for (int s = 0; s < d.n_slices && tiles.tiling < 0; ++s)
       for (int tl = 0; tl < nc.n_tiles(); ++tl) {
         if (nc.kind == 0) {
           it_num.push_back({m, tl, s, 0});
-        } else if (small_tiling(g, nc) >= 0 && small) {
-          it_numsm.push_back({m, 0, s, small_tiling(g, nc)});
-          continue;
         } else {
           const WaveTile &w = nc.tiles[tl];
           it_num.push_back({m, w.bx | (w.by << 16), s,
@@ -1357,7 +1423,7 @@ void launch_numerator(jam_ctx *ctx, Plan *p, char *ws, hipStream_t st) {
   for (int t = 0; t < jam::kSmallTilings; ++t)
     if (p->numsm_ptr[t + 1] > p->numsm_ptr[t])
       jam::launch_num_small(ctx->d_geoms, p->d_models, p->d_numsm + p->numsm_ptr[t],
-                            p->numsm_ptr[t + 1] - p->numsm_ptr[t], t, gauss, st_ws, part,
+                            p->numsm_ptr[t + 1] - p->numsm_ptr[t], t, terms, gauss, st_ws, part,
                             (double *)(ws + p->off_pix), st);
   if (!p->n_num) return;
   jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, gauss, st_ws, part, queue,

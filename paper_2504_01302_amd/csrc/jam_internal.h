@@ -193,13 +193,14 @@ void launch_sb(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, Pa
 void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                 const float4 *terms, const double *gauss, const int *st_ws, double *part,
                 int *queue, int grid, bool mfma, hipStream_t st);
-// Small maps in 4 x 4 tiles: items (m, 0, slice, tiling) of one tiling 3 X + Y,
-// X and Y the sizes 3, 5 or 6 tiles (0, 1, 2) that cover the map's width and
-// height.  A model of one slice goes straight into its N map (no reduce items).
-constexpr int kSmallTilings = 9;
+// Maps in 4 x 4 tiles: items (m, x0 | y0 << 16, slice, tiling) of one tiling 3 X
+// + Y (+ 9 with the terms from their table, else computed in place for a map of
+// one item), X and Y the item's width and height of 3, 5 or 6 tiles (0, 1, 2).
+// A model of one slice goes straight into its N map (no reduce items).
+constexpr int kSmallTilings = 18;
 void launch_num_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int tiling,
-                      const double *gauss, const int *st_ws, double *part, double *pix,
-                      hipStream_t st);
+                      const float4 *terms, const double *gauss, const int *st_ws, double *part,
+                      double *pix, hipStream_t st);
 int occupancy_num(bool mfma);   // resident numerator workgroups per CU
 int occupancy_sens();   // resident sensitivity workgroups per CU
 // Compressed cylindrical form (jam_cheb.hip), after the set-up: panels

@@ -688,9 +688,10 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int kSmallFold = 16;   // chunks
 constexpr int kSmallRed = 9 * 64;   // doubles of a wave's sums, and of its staging (16 x 68 floats)
 
-template <int TX, int TY>
+template <int TX, int TY, bool kTab>
 __device__ __forceinline__ void num_small_item(const Item it, const GeomDev *__restrict__ geoms,
                                                const ModelDev *__restrict__ models,
+                                               const float4 *__restrict__ terms,
                                                const double *__restrict__ gauss,
                                                const int *__restrict__ st_ws,
                                                double *__restrict__ part,
@@ -702,16 +703,17 @@ __device__ __forceinline__ void num_small_item(const Item it, const GeomDev *__r
   const int lane = threadIdx.x & 63, r4 = lane & 3, blk = lane >> 2;
   const ModelDev md = models[it.m];
   const GeomDev &g = geoms[md.geom];
+  const int x0 = kTab ? it.a & 0xffff : 0, y0 = kTab ? it.a >> 16 : 0;
   float x2[TX], y2[TY];
 #pragma unroll
   for (int i = 0; i < TX; ++i) {
-    const int xi = 4 * i + r4;
+    const int xi = x0 + 4 * i + r4;
     const double x = xi < g.n_ux ? g.xs[xi] : 0.0;
     x2[i] = (float)(x * x);
   }
 #pragma unroll
   for (int j = 0; j < TY; ++j) {
-    const int yi = 4 * j + r4;
+    const int yi = y0 + 4 * j + r4;
     const double y = yi < g.n_uy ? g.ys[yi] : 0.0;
     y2[j] = (float)(y * y);
   }
@@ -727,8 +729,14 @@ __device__ __forceinline__ void num_small_item(const Item it, const GeomDev *__r
   // the lane's next term, 64 on from the one before (stepped, not divided);
   // past the range a zero amplitude
   const int nu = g.n_u, J1 = g.J1;
+  const float4 *tb = terms + md.term_off;
   int t = t0 + lane, n = t % nu, j = (t / nu) % J1, k = t / nu / J1;
   auto term = [&]() {
+    if constexpr (kTab) {
+      const float4 c = t < t1 ? tb[t] : make_float4(0.f, 0.f, 0.f, 0.f);
+      t += KC2;
+      return c;
+    }
     const float4 c = t < t1 ? term_at(g, gt, k, j, n) : make_float4(0.f, 0.f, 0.f, 0.f);
     t += KC2;
     n += KC2;
@@ -804,11 +812,13 @@ __device__ __forceinline__ void num_small_item(const Item it, const GeomDev *__r
   double *out = part + md.part_off + it.b * part_slice_size(md);
   for (int e = threadIdx.x; e < 16 * kTiles; e += 256) {
     // pixel (4 i + r, 4 j + c): tile 4 x 4 register r, column c
-    const int tile = e / 16, x = 4 * (tile / TY) + (e / 4) % 4, y = 4 * (tile % TY) + e % 4;
+    const int tile = e / 16;
+    const int x = x0 + 4 * (tile / TY) + (e / 4) % 4, y = y0 + 4 * (tile % TY) + e % 4;
     const double v = ((red[e] + red[NG * 64 + e]) + red[2 * NG * 64 + e]) + red[3 * NG * 64 + e];
+    if (x >= g.n_ux || y >= g.n_uy) continue;
     if (md.n_slices > 1)
       out[(int64_t)x * ldh + y] = v;
-    else if (x < g.n_ux && y < g.n_uy)       // the whole sum: straight into the N map
+    else                                     // the whole sum: straight into the N map
       pix[md.pix_off + (int64_t)y * g.n_ux + x] = v;
   }
 }
@@ -878,10 +888,11 @@ __global__ void __launch_bounds__(256, 2) k_num_mfma(const GeomDev *__restrict__
 }
 
 // (A kernel per tiling: in one kernel with a switch the compiler spills.)
-template <int TX, int TY>
+template <int TX, int TY, bool kTab>
 __global__ void __launch_bounds__(256, 2) k_num_small(const GeomDev *__restrict__ geoms,
                                                    const ModelDev *__restrict__ models,
                                                    const Item *__restrict__ items, int n_it,
+                                                   const float4 *__restrict__ terms,
                                                    const double *__restrict__ gauss,
                                                    const int *__restrict__ st_ws,
                                                    double *__restrict__ part,
@@ -890,7 +901,7 @@ __global__ void __launch_bounds__(256, 2) k_num_small(const GeomDev *__restrict_
   __shared__ double red[4 * kSmallRed];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int i = blockIdx.x; i < n_it; i += gridDim.x)
-    num_small_item<TX, TY>(items[i], geoms, models, gauss, st_ws, part, pix, cs[wave], wave, red);
+    num_small_item<TX, TY, kTab>(items[i], geoms, models, terms, gauss, st_ws, part, pix, cs[wave], wave, red);
 }
 
 // Sum the split-term partials in a fixed order into the N map.  Item
@@ -3714,26 +3725,30 @@ void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
     hipLaunchKernelGGL(k_num_pix, dim3(grid_of(grid)), dim3(256), 0, st, g, m, it, n_it, terms,
                        st_ws, part, queue);
 }
-template <int TX, int TY>
+template <int TX, int TY, bool kTab>
 static void small_kernel(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                         const double *gauss, const int *st_ws, double *part, double *pix,
-                      hipStream_t st) {
-  hipLaunchKernelGGL((k_num_small<TX, TY>), dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
-                     gauss, st_ws, part, pix);
+                         const float4 *terms, const double *gauss, const int *st_ws, double *part,
+                         double *pix, hipStream_t st) {
+  hipLaunchKernelGGL((k_num_small<TX, TY, kTab>), dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it,
+                     n_it, terms, gauss, st_ws, part, pix);
 }
 void launch_num_small(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, int tiling,
-                      const double *gauss, const int *st_ws, double *part, double *pix,
-                      hipStream_t st) {
+                      const float4 *terms, const double *gauss, const int *st_ws, double *part,
+                      double *pix, hipStream_t st) {
   switch (tiling) {
-    case 0: small_kernel<3, 3>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 1: small_kernel<3, 5>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 2: small_kernel<3, 6>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 3: small_kernel<5, 3>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 4: small_kernel<5, 5>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 5: small_kernel<5, 6>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 6: small_kernel<6, 3>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    case 7: small_kernel<6, 5>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
-    default: small_kernel<6, 6>(g, m, it, n_it, gauss, st_ws, part, pix, st); break;
+#define JAM_TILING(n, tx, ty)                                                             \
+  case n: small_kernel<tx, ty, false>(g, m, it, n_it, terms, gauss, st_ws, part, pix, st); break; \
+  case 9 + n: small_kernel<tx, ty, true>(g, m, it, n_it, terms, gauss, st_ws, part, pix, st); break;
+    JAM_TILING(0, 3, 3)
+    JAM_TILING(1, 3, 5)
+    JAM_TILING(2, 3, 6)
+    JAM_TILING(3, 5, 3)
+    JAM_TILING(4, 5, 5)
+    JAM_TILING(5, 5, 6)
+    JAM_TILING(6, 6, 3)
+    JAM_TILING(7, 6, 5)
+    JAM_TILING(8, 6, 6)
+#undef JAM_TILING
   }
 }
 void launch_reduce(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,

@@ -70,3 +70,37 @@ def test_tilings_vs_oracle(nx, ny, n_u, n):
     gerr = np.linalg.norm(a - b) / np.linalg.norm(b)
     print(f"{nx} x {ny}, {n}: forward {err:.2e}, gradient {gerr:.2e}")
     assert err <= 1e-6 and gerr <= 1e-5
+
+
+@pytest.mark.parametrize("nx,ny,n_u,n", [
+    (33, 33, 40, 400),     # two items a side, one column of pixels past the block
+    (39, 21, 40, 400),     # 6 x 5 tiles; the last item's padding
+    (40, 24, 40, 400),     # whole items
+    (79, 33, 100, 40),     # four by two; several slices
+    (70, 67, 12, 150),     # three by three
+])
+def test_items_of_tiles_vs_oracle(nx, ny, n_u, n):
+    """Maps of more than one block whose items of 4 x 4 tiles read the terms
+    from their table: the last of n models."""
+    test_tilings_vs_oracle(nx, ny, n_u, n)
+
+
+def test_items_of_tiles_in_a_mixed_batch():
+    """Two geometries of tiles and one of blocks in one batch equal each alone:
+    the values are sums of the same terms in an order that may differ between
+    the two forms (FP32 over 64 terms), 1e-6."""
+    dev = _dev()
+    gs, ps = zip(*[_model(nx, ny, 40) for nx, ny in ((33, 33), (39, 21), (28, 40))])
+    ctx = binding.Context(list(gs))
+    idx = np.repeat(np.arange(3, dtype=np.int32), 200)
+    w = inputs.Workload("m", list(gs), idx, [ps[i] for i in idx])
+    par = binding.pack_params(w, dev, amplitudes=True)
+    keys = ("inc", "mass_scale", "m_bh", "beta", "lum_I0", "mass_S0")
+    V = ctx.eval_batch(idx, *[par[k] for k in keys])[0].cpu().numpy().reshape(600, -1)
+    for i in range(3):
+        one = inputs.Workload("o", list(gs), np.array([i], np.int32), [ps[i]])
+        par = binding.pack_params(one, dev, amplitudes=True)
+        r = ctx.eval_batch(one.geom_idx, *[par[k] for k in keys])[0].cpu().numpy()
+        assert (V[200 * i:200 * (i + 1)] == V[200 * i]).all()
+        assert np.max(np.abs(V[200 * i] / r - 1)) <= 1e-6
+    ctx.close()
