@@ -1249,10 +1249,10 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
         }
     }
     for (int pb = 0; pb < (g.n_pix + 255) / 256; ++pb) it_pix.push_back({m, pb, 0, 0});
-    // the compressed form's maps are summed by k_cheb_sum, a single slice of the
-    // small tilings is the sum
+    // the compressed form's maps are summed by k_cheb_sum, a single slice of a
+    // matrix-core form is the sum
     const SmallTiles tiles = spherical ? SmallTiles() : tiles_of[gi];
-    if (!cheb && !(d.n_slices == 1 && tiles.tiling >= 0))
+    if (spherical || (!cheb && !(d.n_slices == 1 && nc.kind == 2)))
       for (int pb = 0; pb < (g.n_pix + 63) / 64; ++pb) it_red.push_back({m, pb, 0, 0});
     for (int rb = 0; rb < (g.n_uy + 7) / 8; ++rb)
       for (int cb = 0; cb < (g.n_ux + 63) / 64; ++cb) {
@@ -1426,7 +1426,7 @@ void launch_numerator(jam_ctx *ctx, Plan *p, char *ws, hipStream_t st) {
                             p->numsm_ptr[t + 1] - p->numsm_ptr[t], t, terms, gauss, st_ws, part,
                             (double *)(ws + p->off_pix), st);
   if (!p->n_num) return;
-  jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, gauss, st_ws, part, queue,
+  jam::launch_num(ctx->d_geoms, p->d_models, p->d_num, p->n_num, terms, gauss, st_ws, part, (double *)(ws + p->off_pix), queue,
                     p->grid_num, p->tune.rule == 1, st);
 }
 

@@ -191,7 +191,7 @@ void launch_sb(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, Pa
 // workgroups pulling items from the counter; else `grid` workgroups striding
 // over the list.
 void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                const float4 *terms, const double *gauss, const int *st_ws, double *part,
+                const float4 *terms, const double *gauss, const int *st_ws, double *part, double *pix,
                 int *queue, int grid, bool mfma, hipStream_t st);
 // Maps in 4 x 4 tiles: items (m, x0 | y0 << 16, slice, tiling) of one tiling 3 X
 // + Y (+ 9 with the terms from their table, else computed in place for a map of

@@ -529,7 +529,8 @@ __device__ __forceinline__ void num_tile_item(const Item it, const GeomDev *__re
                                               const float4 *__restrict__ terms,
                                               const double *__restrict__ gauss,
                                               const int *__restrict__ st_ws,
-                                              double *__restrict__ part, float4 *cs, int wave,
+                                              double *__restrict__ part,
+                                              double *__restrict__ pix, float4 *cs, int wave,
                                               double *red) {
   const int lane = threadIdx.x & 63;
   const ModelDev md = models[it.m];
@@ -655,6 +656,23 @@ __device__ __forceinline__ void num_tile_item(const Item it, const GeomDev *__re
     }
   }
   if (wave != 0) return;
+  if (md.n_slices == 1) {
+    // the whole sum: straight into the N map (3476 models of 76 x 76 pixels: a
+    // partial map and k_reduce took 412 us beside the 1130 us of this)
+    double *o = pix + md.pix_off;
+#pragma unroll
+    for (int by = 0; by < BY; ++by) {
+      const int y = y0 + 32 * by + c32;
+#pragma unroll
+      for (int bx = 0; bx < BX; ++bx)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int x = x0 + 32 * bx + 4 * kh + (r & 3) + 8 * (r >> 2);
+          if (x < g.n_ux && y < g.n_uy) o[(int64_t)y * g.n_ux + x] = acc[bx][by][r];
+        }
+    }
+    return;
+  }
   // padded, transposed partial map: every row and column of the tile exists,
   // so the stores need no bounds checks; lanes store consecutive y
   const int ldh = 32 * md.n_yt;
@@ -861,7 +879,8 @@ __global__ void __launch_bounds__(256, 2) k_num_mfma(const GeomDev *__restrict__
                                                   const float4 *__restrict__ terms,
                                                   const double *__restrict__ gauss,
                                                   const int *__restrict__ st_ws,
-                                                  double *__restrict__ part, int *queue) {
+                                                  double *__restrict__ part,
+                                                  double *__restrict__ pix, int *queue) {
   __shared__ __attribute__((aligned(16))) float4 cs[4][KC2];
   __shared__ double red[4 * 16 * 64];
   __shared__ int next;
@@ -877,11 +896,11 @@ __global__ void __launch_bounds__(256, 2) k_num_mfma(const GeomDev *__restrict__
     if (i >= n_it) break;
     const Item it = items[i];
     switch (it.c) {
-      case 2: num_tile_item<1, 1, false>(it, geoms, models, terms, gauss, st_ws, part, cs[wave], wave, red); break;
-      case 3: num_tile_item<2, 1, false>(it, geoms, models, terms, gauss, st_ws, part, cs[wave], wave, red); break;
-      case 4: num_tile_item<1, 2, false>(it, geoms, models, terms, gauss, st_ws, part, cs[wave], wave, red); break;
-      case 6: num_tile_item<1, 1, true>(it, geoms, models, terms, gauss, st_ws, part, cs[wave], wave, red); break;
-      default: num_tile_item<2, 2, false>(it, geoms, models, terms, gauss, st_ws, part, cs[wave], wave, red); break;
+      case 2: num_tile_item<1, 1, false>(it, geoms, models, terms, gauss, st_ws, part, pix, cs[wave], wave, red); break;
+      case 3: num_tile_item<2, 1, false>(it, geoms, models, terms, gauss, st_ws, part, pix, cs[wave], wave, red); break;
+      case 4: num_tile_item<1, 2, false>(it, geoms, models, terms, gauss, st_ws, part, pix, cs[wave], wave, red); break;
+      case 6: num_tile_item<1, 1, true>(it, geoms, models, terms, gauss, st_ws, part, pix, cs[wave], wave, red); break;
+      default: num_tile_item<2, 2, false>(it, geoms, models, terms, gauss, st_ws, part, pix, cs[wave], wave, red); break;
     }
     if (!queue) i += gridDim.x;
   }
@@ -3716,11 +3735,11 @@ void launch_sb(const GeomDev *g, const ModelDev *m, const Item *it, int n_it, Pa
   hipLaunchKernelGGL(k_sb, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, p, pix);
 }
 void launch_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                const float4 *terms, const double *gauss, const int *st_ws, double *part,
+                const float4 *terms, const double *gauss, const int *st_ws, double *part, double *pix,
                 int *queue, int grid, bool mfma, hipStream_t st) {
   if (mfma)
     hipLaunchKernelGGL(k_num_mfma, dim3(grid_of(grid)), dim3(256), 0, st, g, m, it, n_it, terms,
-                       gauss, st_ws, part, queue);
+                       gauss, st_ws, part, pix, queue);
   else
     hipLaunchKernelGGL(k_num_pix, dim3(grid_of(grid)), dim3(256), 0, st, g, m, it, n_it, terms,
                        st_ws, part, queue);

@@ -212,8 +212,8 @@ __global__ void __launch_bounds__(256) k_pol_grid_sum(const ModelDev *__restrict
 // eight angles each (four waves a SIMD, but barriers and three times the rows
 // in the L1), rows prefetched a segment ahead.  Measured (48 models of 10
 // tracers / one of 40), a block per four table points and 4 x 4 scattered
-// points of the R, z grid before, this after: forward 3444 / 303 -> 797 / 90
-// us, the adjoint's pass 6417 / 498 -> 1225 / 137.
+// points of the R, z grid before, this after: forward 3444 / 303 -> 684 / 82
+// us, the adjoint's pass 6417 / 498 -> 1179 / 146.
 // ---------------------------------------------------------------------------
 template <bool kJac> struct PolWave {
   double rp2[64], s[64], w[64], wd[64];   // r'^2, (r / r')^(1 - beta), weights of P and D

@@ -104,3 +104,14 @@ def test_items_of_tiles_in_a_mixed_batch():
         assert (V[200 * i:200 * (i + 1)] == V[200 * i]).all()
         assert np.max(np.abs(V[200 * i] / r - 1)) <= 1e-6
     ctx.close()
+
+
+@pytest.mark.parametrize("nx,ny,n_u,n", [
+    (28, 40, 20, 700),     # one 32 x 64 tile
+    (64, 64, 12, 400),     # whole blocks
+    (76, 45, 12, 400),     # 64 and 32 wide tiles, both with remainders
+])
+def test_single_slice_of_blocks_vs_oracle(nx, ny, n_u, n):
+    """A batch large enough for one slice per model: the tiles go straight into
+    the map."""
+    test_tilings_vs_oracle(nx, ny, n_u, n)
