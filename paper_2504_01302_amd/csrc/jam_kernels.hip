@@ -987,6 +987,32 @@ __global__ void __launch_bounds__(256) k_reduce(const GeomDev *__restrict__ geom
   }
 }
 
+// A thread's weighted sums of N and I over the entries e, e + stride, .. below
+// e1: four accumulators, four gathers in flight, the remainder predicated: a
+// loop over it waits for each of its up to three gathers in turn.  Measured:
+// 4096 models x 20 bins 66 -> 53 us, one model of 60 bins of 6700 13.4 -> 10.9.
+template <int kStride>
+__device__ __forceinline__ void bin_sums(const GeomDev &g, const double *__restrict__ Nm,
+                                         const double *__restrict__ Im, int e, int e1, bool want_n,
+                                         double (&an)[4], double (&ai)[4]) {
+  for (; e < e1; e += 4 * kStride) {
+    double wv[4], nv[4], iv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int at = min(e + u * kStride, e1 - 1), q = g.bin_pix[at];
+      wv[u] = g.bin_w[at];
+      nv[u] = want_n ? Nm[q] : 0.0;
+      iv[u] = Im[q];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool on = e + u * kStride < e1;
+      an[u] = on ? fma(wv[u], nv[u], an[u]) : an[u];
+      ai[u] = on ? fma(wv[u], iv[u], ai[u]) : ai[u];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Bins: sums of the PSF-weighted maps per bin and their FP64 ratio.
 // Item (m, bin, 0), launched with 1024 threads: the 16 waves of the block
@@ -1015,23 +1041,7 @@ __global__ void __launch_bounds__(BS) k_bins(const GeomDev *__restrict__ geoms,
       const int b = it.a + (threadIdx.x >> 6);
       if (b >= g.n_bins) continue;   // uniform per wave; no barrier in this variant
       double an[4] = {0.0, 0.0, 0.0, 0.0}, ai[4] = {0.0, 0.0, 0.0, 0.0};
-      const int e1 = g.bin_ptr[b + 1];
-      int e = g.bin_ptr[b] + lane;
-      for (; e + 3 * 64 < e1; e += 4 * 64) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const double wv = g.bin_w[e + u * 64];
-          const int q = g.bin_pix[e + u * 64];
-          if (want_n) an[u] += wv * Nm[q];
-          ai[u] += wv * Im[q];
-        }
-      }
-      for (int u = 0; e < e1; e += 64, ++u) {
-        const double wv = g.bin_w[e];
-        const int q = g.bin_pix[e];
-        if (want_n) an[u] += wv * Nm[q];
-        ai[u] += wv * Im[q];
-      }
+      bin_sums<64>(g, Nm, Im, g.bin_ptr[b] + lane, g.bin_ptr[b + 1], want_n, an, ai);
       double sn = wave_sum((an[0] + an[1]) + (an[2] + an[3]));
       const double si = wave_sum((ai[0] + ai[1]) + (ai[2] + ai[3]));
       if (!want_n) sn = 0.0;
@@ -1048,23 +1058,7 @@ __global__ void __launch_bounds__(BS) k_bins(const GeomDev *__restrict__ geoms,
     const int b = it.a;
     // four independent accumulators keep four gathers in flight per thread
     double an[4] = {0.0, 0.0, 0.0, 0.0}, ai[4] = {0.0, 0.0, 0.0, 0.0};
-    const int e1 = g.bin_ptr[b + 1];
-    int e = g.bin_ptr[b] + threadIdx.x;
-    for (; e + 3 * BS < e1; e += 4 * BS) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double wv = g.bin_w[e + u * BS];
-        const int q = g.bin_pix[e + u * BS];
-        if (want_n) an[u] += wv * Nm[q];
-        ai[u] += wv * Im[q];
-      }
-    }
-    for (int u = 0; e < e1; e += BS, ++u) {
-      const double wv = g.bin_w[e];
-      const int q = g.bin_pix[e];
-      if (want_n) an[u] += wv * Nm[q];
-      ai[u] += wv * Im[q];
-    }
+    bin_sums<BS>(g, Nm, Im, g.bin_ptr[b] + threadIdx.x, g.bin_ptr[b + 1], want_n, an, ai);
     // deterministic two-level sums: wave butterflies, then the wave partials
     // in a fixed order
     const double an_w = wave_sum((an[0] + an[1]) + (an[2] + an[3]));
@@ -1131,20 +1125,34 @@ __global__ void __launch_bounds__(256) k_bins_adjoint(const GeomDev *__restrict_
                                                       const double *__restrict__ binws,
                                                       const int *__restrict__ st_ws,
                                                       double *__restrict__ pix) {
+  // the bins' cot / I and V once per block (the first kAdjBins bins): per entry of
+  // a pixel two gathers and a division, 27.3 us for 1024 small models, 19.3 here
+  constexpr int kAdjBins = 256;
+  __shared__ double cb[kAdjBins], vb[kAdjBins];
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
     const Item it = items[i];
     const ModelDev md = models[it.m];
     const GeomDev g = geoms[md.geom];
     const int q = it.a * 256 + threadIdx.x;
-    if (q >= g.n_pix) continue;
     const double *Ib = binws + md.bin_off + g.n_bins;
+    const bool good = st_ws[it.m] == 0;
+    __syncthreads();                 // the previous item's reads
+    for (int b = threadIdx.x; good && b < min(g.n_bins, kAdjBins); b += 256) {
+      cb[b] = cot[md.out_off + b] / Ib[b];
+      vb[b] = vrms2[md.out_off + b];
+    }
+    __syncthreads();
+    if (q >= g.n_pix) continue;
     double ln = 0.0, li = 0.0;
-    if (st_ws[it.m] == 0) {
-      for (int e = g.pix_ptr[q]; e < g.pix_ptr[q + 1]; ++e) {
+    if (good) {
+      const int e1 = g.pix_ptr[q + 1];
+      for (int e = g.pix_ptr[q]; e < e1; ++e) {
         const int b = g.pix_bin[e];
-        const double c = cot[md.out_off + b] / Ib[b];
-        ln += g.pix_w[e] * c;
-        li -= g.pix_w[e] * c * vrms2[md.out_off + b];
+        const double wv = g.pix_w[e];
+        const double c = b < kAdjBins ? cb[b] : cot[md.out_off + b] / Ib[b];
+        const double V = b < kAdjBins ? vb[b] : vrms2[md.out_off + b];
+        ln += wv * c;
+        li -= wv * c * V;
       }
     }
     pix[md.pix_off + 2 * (int64_t)g.n_pix + q] = ln;

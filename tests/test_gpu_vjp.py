@@ -155,3 +155,30 @@ def test_autograd_function_matches_vjp_and_oracle():
     _, ref = ojam.vrms2_and_grad(w.geometries[0], w.params[1], cot[1])
     _check(gs[1], {k: v.numpy() for k, v in ref.items()}, "autograd model 1")
     ctx.close()
+
+
+@pytest.mark.parametrize("n_bins", [1, 5, 256, 257, 300])
+def test_bins_beyond_a_blocks_table(n_bins):
+    """The bin adjoint keeps the first 256 bins' factors per block; forward and
+    gradient against the FP64 oracle on a map of 20 x 18 pixels (a bin may be one
+    pixel: remainders of one entry).  The bars of the FP32 numerator sums."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=n_bins, n_lum=2, n_mass=2, nx=20, ny=18, psf_n=3,
+                              n_bins=1, n_u=24, pixsize=0.06, xc=0.007, yc=-0.011)
+    g.n_bins = n_bins
+    g.bin_index = (np.arange(360, dtype=np.int32) % n_bins).reshape(g.bin_index.shape)
+    p = inputs.small_params(g, seed=3)
+    w = inputs.Workload("b", [g], np.zeros(1, np.int32), [p])
+    ctx = binding.Context([g])
+    par = binding.pack_params(w, dev, amplitudes=True)
+    keys = ("inc", "mass_scale", "m_bh", "beta", "lum_I0", "mass_S0")
+    args = (w.geom_idx,) + tuple(par[k] for k in keys)
+    V, st = ctx.eval_batch(*args)
+    cot = np.random.default_rng(1).standard_normal(g.n_bins)
+    gr = ctx.vjp(*args, V, torch.as_tensor(cot, device=dev))
+    rV, rg = ojam.vrms2_and_grad(g, p, cot)
+    ctx.close()
+    assert np.max(np.abs(V.cpu().numpy() / rV.numpy() - 1)) <= 1e-6
+    a = np.concatenate([np.ravel(gr[k].cpu().numpy()) for k in keys])
+    b = np.concatenate([np.ravel(np.asarray(rg[k])) for k in keys])
+    assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b)
