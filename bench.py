@@ -128,7 +128,7 @@ def profiled_traffic(kernel):
     return float(b.group(1))
 
 
-KERNEL_NAMES = {0: "k_num_pix", 1: "k_num_mfma", 3: "k_sph_moments",
+KERNEL_NAMES = {0: "k_num_pix", 1: "k_num_mfma", 3: "k_pol_moments",
                 4: "k_cheb_panel + k_cheb_map"}
 FP64_MFMA_PEAK = 78.6e12        # MI355X published dense FP64 matrix FLOP/s
 

@@ -343,7 +343,8 @@ jam_status jam_timing(jam_ctx *ctx, int32_t enable, double *numerator_ms,
  * numerator work items, numerator workgroups launched, adjoint work items,
  * adjoint workgroups launched, numerator kernel (0 per-pixel k_num_pix,
  * 1 matrix-core tiles k_num_mfma (also where only some of the batch's models
- * take the compressed form), 3 spherical moments k_sph_moments, 4 compressed
+ * take the compressed form, and where maps go in 4 x 4 tiles, k_num_small),
+ * 3 spherical moments k_pol_moments (form 1: k_sph_moments), 4 compressed
  * form k_cheb_panel / k_cheb_map).  info holds 9 int32 (host memory).       */
 jam_status jam_plan_info(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, int32_t *info);
 

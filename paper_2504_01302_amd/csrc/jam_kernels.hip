@@ -313,7 +313,7 @@ __device__ inline void pair_from_params(const GeomDev &g, const ModelDev &md, in
 // ---------------------------------------------------------------------------
 // Surface brightness, eq. (sb_mge_2D), FP64, on the unique-pixel map, using
 // its separability: I(x, y) = sum_k I0_k exp(-x^2/2s_k^2) exp(-y^2/2s_k^2q_k^2).
-// Item (m, block of 8 rows, block of 256 columns): the row factors are
+// Item (m, block of 8 rows, block of 64 columns): the row factors are
 // computed once per workgroup, the column factor once per thread and k.
 // pix region per model: [N | I | lambda_N | lambda_I], n_pix doubles each.
 // ---------------------------------------------------------------------------
