@@ -2025,16 +2025,16 @@ __global__ void __launch_bounds__(256, NYQ <= 5 ? 3 : 2) k_adj_small(const GeomD
   }
 }
 
-// Final per-model gradients from the chain rows.  One 1024-thread block per
+// Final per-model gradients from the chain rows.  One block of kW waves per
 // model: each wave reduces one luminous Gaussian's row at a time over the
 // mass Gaussians (lanes), then the waves reduce the mass derivatives over
 // the luminous Gaussians; partial sums are combined in a fixed order.
-__global__ void __launch_bounds__(1024) k_grads(const GeomDev *__restrict__ geoms,
+template <int kW>
+__global__ void __launch_bounds__(64 * kW) k_grads(const GeomDev *__restrict__ geoms,
                                                const ModelDev *__restrict__ models, int n,
                                                ParamsDev p, double *__restrict__ sens,
                                                const double *__restrict__ sbp,
                                                const int *__restrict__ st_ws, GradsDev out) {
-  constexpr int kW = 16;   // waves per block
   __shared__ double part[kW];
   __shared__ double mpart[kW][64];
   const int lane = threadIdx.x & 63;
@@ -3874,9 +3874,18 @@ void launch_chain(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                   double *sens, const int *st_ws, hipStream_t st) {
   hipLaunchKernelGGL(k_chain, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, p, sens, st_ws);
 }
+constexpr int kGradsWide = 256;   // models
 void launch_grads(const GeomDev *g, const ModelDev *m, int n, ParamsDev p, double *sens,
                   const double *sbp, const int *st_ws, GradsDev out, hipStream_t st) {
-  hipLaunchKernelGGL(k_grads, dim3(grid_of(n)), dim3(1024), 0, st, g, m, n, p, sens, sbp, st_ws,
+  // Sixteen waves a model for its latency while there is a CU for each; beyond
+  // that four, most of sixteen waiting for the one with the longest rows.  16 / 4
+  // waves: 512 models of 21 Gaussians 16.8 / 15.4 us, 1024 of 10 24.4 / 13.4, 3476
+  // of 9 86 / 41, 1024 of 5 to 60 55 / 45.
+  if (n > kGradsWide)
+    hipLaunchKernelGGL(k_grads<4>, dim3(grid_of(n)), dim3(256), 0, st, g, m, n, p, sens, sbp, st_ws,
+                     out);
+  else
+    hipLaunchKernelGGL(k_grads<16>, dim3(grid_of(n)), dim3(1024), 0, st, g, m, n, p, sens, sbp, st_ws,
                      out);
 }
 void launch_sb_adjoint(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,

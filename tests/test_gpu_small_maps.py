@@ -115,3 +115,20 @@ def test_single_slice_of_blocks_vs_oracle(nx, ny, n_u, n):
     """A batch large enough for one slice per model: the tiles go straight into
     the map."""
     test_tilings_vs_oracle(nx, ny, n_u, n)
+
+
+@pytest.mark.parametrize("n_lum,n_mass", [(3, 2), (4, 63), (17, 70)])
+def test_gradients_of_many_models_equal_a_single_ones(n_lum, n_mass):
+    """Beyond 256 models the reductions run on four waves a model instead of
+    sixteen: fewer and more tracers than waves, more mass Gaussians than lanes.
+    The sums differ in order, and the batch's sensitivities in their grouping of
+    FP32 sums: 1e-6 of the norm."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=n_mass, n_lum=n_lum, n_mass=n_mass, nx=9, ny=7, psf_n=1,
+                              n_bins=3, n_u=16, pixsize=0.06, xc=0.007, yc=-0.011)
+    p = inputs.small_params(g, seed=n_lum)
+    cot = np.random.default_rng(2).standard_normal(g.n_bins)
+    (V1, g1), (Vn, gn) = (_run(g, [p] * n, cot, dev) for n in (1, 257))
+    assert np.max(np.abs(Vn / V1 - 1)) <= 1e-6
+    a, b = _flat(gn), _flat(g1)
+    assert np.linalg.norm(a - b) <= 1e-6 * np.linalg.norm(b)
