@@ -1007,11 +1007,21 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->cadj_waves = share_a && cheb_most > 512 ? 8 : 4;
   int64_t cheb_h = 0, cheb_hmax = 0, cheb_t = 0;
   std::vector<double> c_cpan, c_cadj;
+  it_cpan.reserve(cheb_panels);
+  c_cpan.reserve(cheb_panels);
+  it_cadj.reserve(cadj_panels);
+  c_cadj.reserve(cadj_panels);
   Plan::ChebGroup grp{};
   // shared items first, largest first, then the others as they come
+  // (a large batch has 1e5 units and mostly none shared: they stay as they are)
   auto order_units = [&](std::vector<jam::Item> &v, std::vector<double> &cost, int first) {
+    int shared = 0;
+    for (size_t i = first; i < v.size(); ++i) shared += v[i].c & 1;
+    if (shared == 0) return 0;
     std::vector<jam::Item> sub, rest;
     std::vector<double> cs;
+    sub.reserve(shared);
+    rest.reserve(v.size() - first - shared);
     for (size_t i = first; i < v.size(); ++i) {
       if (v[i].c & 1) {
         sub.push_back(v[i]);
@@ -1334,15 +1344,15 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   }
   const size_t o_cmap = off;
   off = align256(off + sizeof(jam::ChebItem) * std::max<size_t>(1, it_cmap.size()));
-  std::vector<char> stage(off, 0);
+  const std::unique_ptr<char[]> stage(new char[off]);   // what lies between the lists is not read
   if (!it_cmap.empty())
-    std::memcpy(stage.data() + o_cmap, it_cmap.data(), sizeof(jam::ChebItem) * it_cmap.size());
-  std::memcpy(stage.data() + o_models, md.data(), sizeof(jam::ModelDev) * n);
+    std::memcpy(stage.get() + o_cmap, it_cmap.data(), sizeof(jam::ChebItem) * it_cmap.size());
+  std::memcpy(stage.get() + o_models, md.data(), sizeof(jam::ModelDev) * n);
   for (int i = 0; i < kLists; ++i)
     if (!lists[i]->empty())
-      std::memcpy(stage.data() + o_it[i], lists[i]->data(), sizeof(jam::Item) * lists[i]->size());
+      std::memcpy(stage.get() + o_it[i], lists[i]->data(), sizeof(jam::Item) * lists[i]->size());
   HIP_TRY(hipMalloc(&p->arena, off));
-  HIP_TRY(hipMemcpy(p->arena, stage.data(), off, hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(p->arena, stage.get(), off, hipMemcpyHostToDevice));
   char *base = (char *)p->arena;
   p->d_models = (jam::ModelDev *)(base + o_models);
   jam::Item **dl[kLists] = {&p->d_terms, &p->d_pix,  &p->d_num, &p->d_bins,
