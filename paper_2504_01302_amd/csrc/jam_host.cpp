@@ -533,6 +533,7 @@ struct Plan {
          off_sbp = 0,
          off_cheb = 0,
          off_chebt = 0,
+         off_terms64 = 0,
          ws_fwd = 0, ws_vjp = 0;
   // captured evaluations (forward, adjoint, forward + chi^2, adjoint of chi^2)
   hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -975,7 +976,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   // items are cut after the model loop (wide_items)
   std::vector<WidePart> wide_parts;
   int64_t gauss = 0, terms = 0, pixd = 0, part = 0, bins = 0, sens = 0, sph = 0, sbp = 0,
-          sgrid = 0, sgrid3 = 0, sgcot = 0, pol = 0;
+          sgrid = 0, sgrid3 = 0, sgcot = 0, pol = 0, terms64 = 0;
   const bool spherical = ctx->opt.alignment == 1;
   // compressed form: units per map item, two items per compute unit where
   // the batch is small enough (a unit on a tile is 16 FP64 MFMAs of a wave)
@@ -1120,7 +1121,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
       d.sgrid3_off = sgrid3;
       d.pol_off = pol;
       sgrid += sl * 2 * pts;
-      sgrid3 += sl * 3 * pts;
+      sgrid3 += sl * (int64_t)jam::kPolAdjGrid;
       pol += jam::pol_size(g.K);
       for (int q = 0; q < jam::pol_groups(g.K) * jam::kSphNR / 4; ++q) it_sphm.push_back({m, q, 0, 0});
       for (int q = 0; q < jam::kSphCells / 16; ++q) it_ptab.push_back({m, q, 0, 0});
@@ -1128,14 +1129,16 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
         for (int q = 0; q < sl; ++q) it_sgrid.push_back({m, row, q, 0});
       if (sl > 1) {
         for (int b = 0; b < 2 * pts / 1024; ++b) it_sgred.push_back({m, b, 0, 0});
-        for (int b = 0; b < 3 * pts / 1024; ++b) it_sgred3.push_back({m, b, 0, 0});
+        for (int b = 0; b < pts / 256; ++b) it_sgred3.push_back({m, b, 0, 0});
       }
     }
     gauss += jam::gauss_size(g.K, g.J1);
     const int tsph = jam::sph_terms_padded(g.J1, g.n_u);
     // spherical: float4 terms, then floats; small maps compute their terms in
     // place; cylindrical tables are zero-padded to a multiple of 32 terms
-    terms += spherical ? tsph + (use_sgrid ? tsph / 2 : tsph / 4) : (small || (cheb && cadj) ? 0 : jam::padded_terms(g.T));
+    d.term64_off = terms64;
+    if (spherical) terms64 += (int64_t)tsph * jam::kSphTermDoubles;
+    terms += spherical ? tsph + tsph / 4 : (small || (cheb && cadj) ? 0 : jam::padded_terms(g.T));
     pixd += 4 * (int64_t)g.n_pix;
     // padded to whole blocks
     part += (int64_t)d.n_slices * (32 * d.n_xt) * (32 * d.n_yt);
@@ -1402,7 +1405,8 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->off_vtmp = w;   w = align256(w + sizeof(double) * p->total_bins);
   p->off_cot = w;    w = align256(w + sizeof(double) * p->total_bins);
   p->off_sbp = w;    w = align256(w + sizeof(double) * sbp);
-  p->off_sgrid3 = w; w = align256(w + sizeof(float) * sgrid3);
+  p->off_terms64 = w; w = align256(w + sizeof(double) * terms64);
+  p->off_sgrid3 = w; w = align256(w + sizeof(double) * sgrid3);
   p->off_sgcot = w;  w = align256(w + sizeof(double) * sgcot);
   p->off_chebt = w;  w = align256(w + sizeof(double) * cheb_t);
   p->ws_vjp = w;
@@ -1443,7 +1447,8 @@ void launch_numerator(jam_ctx *ctx, Plan *p, char *ws, hipStream_t st) {
 // Set-up, term table and SB map; optionally the numerator map.  Leaves N and
 // I in the workspace pix region.
 void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_t *status,
-                         char *ws, hipStream_t st, bool need_numerator, bool capturing) {
+                         char *ws, hipStream_t st, bool need_numerator, bool capturing,
+                         bool adjoint = false) {
   int *st_ws = (int *)(ws + p->off_status);
   int *queue = (int *)(ws + p->off_queue);
   double *gauss = (double *)(ws + p->off_gauss);
@@ -1453,6 +1458,7 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
   if (p->spherical) {
     jam::launch_setup(ctx->d_geoms, p->d_models, p->n, pd, gauss, st_ws, status, queue, st);
     jam::launch_sph_terms(ctx->d_geoms, p->d_models, p->d_terms, p->n_terms, gauss, st_ws, terms,
+                          adjoint ? (double *)(ws + p->off_terms64) : nullptr,
                           (double *)(ws + p->off_pol), st);
     jam::launch_sb(ctx->d_geoms, p->d_models, p->d_sb, p->n_sb, pd, pix, st);
   } else {
@@ -1470,10 +1476,9 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
     if (sgrid) {
       double *pol = (double *)(ws + p->off_pol);
       jam::launch_pol_grid(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, p->d_sgred,
-                           p->n_sgred, terms, st_ws, pol, sgrid, false, st);
+                           p->n_sgred, terms, st_ws, pol, sgrid, st);
       jam::launch_pol_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, p->d_ptab,
-                              p->n_ptab, gauss, terms, st_ws, sgrid, pol, tabs, nullptr, nullptr,
-                              st);
+                              p->n_ptab, gauss, terms, st_ws, sgrid, pol, tabs, st);
     } else {
       jam::launch_sph_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, gauss, terms, st_ws,
                               tabs, st);
@@ -1520,19 +1525,19 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
     // grid, the forward's table and numerator map first, then the adjoint's
     // table over it), so that it equals the forward's V bit for bit
     const bool fwd_v = recompute && p->n_sgrid > 0;
-    launch_forward_maps(ctx, p, pd, nullptr, w, st, fwd_v, capturing);
+    launch_forward_maps(ctx, p, pd, nullptr, w, st, fwd_v, capturing, true);
     const double *gauss = (const double *)(w + p->off_gauss);
     double *tabs = (double *)(w + p->off_sph);
-    const float4 *terms = (const float4 *)(w + p->off_terms);
-    float *sgrid3 = p->n_sgrid ? (float *)(w + p->off_sgrid3) : nullptr;
-    if (sgrid3) {
-      double *pol = (double *)(w + p->off_pol);
-      jam::launch_pol_grid(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, p->d_sgred3,
-                           p->n_sgred3, terms, st_ws, pol, sgrid3, true, st);
-      jam::launch_pol_moments(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, p->d_ptab,
-                              p->n_ptab, gauss, terms, st_ws, sgrid3, pol, tabs, sens,
-                              (double *)(w + p->off_sgcot), st);
+    if (p->n_sgrid > 0) {
+      double *pol = (double *)(w + p->off_pol), *sgrid3 = (double *)(w + p->off_sgrid3);
+      const double *terms64 = (const double *)(w + p->off_terms64);
+      jam::launch_pol_grid_adj(ctx->d_geoms, p->d_models, p->d_sgrid, p->n_sgrid, p->d_sgred3,
+                               p->n_sgred3, terms64, st_ws, pol, sgrid3, st);
+      jam::launch_pol_moments_adj(ctx->d_geoms, p->d_models, p->d_sphm, p->n_sphm, p->d_ptab,
+                                  p->n_ptab, gauss, terms64, st_ws, sgrid3, pol, tabs, sens,
+                                  (double *)(w + p->off_sgcot), st);
     } else {
+      const float4 *terms = (const float4 *)(w + p->off_terms);
       jam::launch_sph_moments_jac(ctx->d_geoms, p->d_models, p->d_sph, p->n_sph, gauss, terms,
                                   st_ws, tabs, sens, st);
     }
@@ -1565,19 +1570,19 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
   if (p->spherical) {
     const bool ts = ctx->t_sens.begin(st, capturing);
     const double *gauss = (const double *)(w + p->off_gauss);
-    const float4 *terms = (const float4 *)(w + p->off_terms);
+    const double *terms64 = (const double *)(w + p->off_terms64);
     jam::launch_sph_adjoint(ctx->d_geoms, p->d_models, p->n, p->d_red, p->n_red, p->d_srow, p->n_srow,
                             gauss, st_ws, (const double *)(w + p->off_sph), pix, sens, st);
     if (p->n_pcot)
       jam::launch_pol_adjoint(ctx->d_geoms, p->d_models, p->d_pcot, p->n_pcot, p->d_pfix, p->n_pfix,
-                              p->d_sgs, p->n_sgs, gauss, terms, st_ws,
+                              p->d_sgs, p->n_sgs, gauss, terms64, st_ws,
                               (const double *)(w + p->off_pol), sens,
                               (double *)(w + p->off_sgcot), st);
     else
-      jam::launch_sph_sens(ctx->d_geoms, p->d_models, p->d_sens, p->n_sens, gauss, terms, st_ws,
-                           sens, st);
-    jam::launch_sph_chain(ctx->d_geoms, p->d_models, p->n, p->d_terms, p->n_terms, pd, gauss, terms,
-                          st_ws, sbp, sens, gd, st);
+      jam::launch_sph_sens(ctx->d_geoms, p->d_models, p->d_sens, p->n_sens, gauss,
+                           (const float4 *)(w + p->off_terms), st_ws, sens, st);
+    jam::launch_sph_chain(ctx->d_geoms, p->d_models, p->n, p->d_terms, p->n_terms, pd, gauss,
+                          terms64, st_ws, sbp, sens, gd, st);
     if (ts) ctx->t_sens.end(st);
     return;
   }

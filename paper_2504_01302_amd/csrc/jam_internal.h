@@ -64,11 +64,18 @@ constexpr int kSphNT = 24;
 constexpr int kSphSeg = 8;
 constexpr int kSphNodes = 8 * kSphSeg;   // 64
 // (j, u) terms of the spherical potential integrals, padded to whole groups
-// of 64; the per-model term region holds that many float4 plus as many floats,
-// and as many floats again with the potential grid.
+// of 64; the per-model term region holds that many float4 plus as many floats.
 __host__ __device__ inline int sph_terms_padded(int J1, int n_u) {
   return (J1 * n_u + 63) / 64 * 64;
 }
+
+// One spherical term in FP64, for the adjoint: exponents of R'^2 and z'^2 (base
+// 2) and the weights of G, G_theta, G_phi and T_theta = dG_theta / dR'^2 at fixed
+// r'.  Zero past the last term.
+struct SphTerm {
+  double cx, cy, gP, gT, gF, gD;
+};
+constexpr int kSphTermDoubles = sizeof(SphTerm) / sizeof(double);
 
 // One model of a prepared batch; offsets into packed inputs/outputs and into
 // the caller's workspace regions.
@@ -97,7 +104,8 @@ struct ModelDev {
   int64_t sbp_off;   // doubles, surface-brightness adjoint partials [K][sb items]
   int64_t sgrid_off; // floats, spherical forward potential grid
                      // [sgrid_slices][kPolN][kPolC][2] (slice 0 holds the sums)
-  int64_t sgrid3_off;// floats, the adjoint's grid [sgrid_slices][kPolN][kPolC][3]
+  int64_t sgrid3_off;// doubles, the adjoint's grid [sgrid_slices][kPolAdjGrid]
+  int64_t term64_off;// doubles, the adjoint's coefficients of the spherical terms (SphTerm)
   int64_t sgcot_off; // doubles, the adjoint's node table and grid cotangent (pol_cot_size)
   int64_t pol_off;   // doubles, the grid's scales and the moments' partials (pol_size)
   int64_t cheb_off;  // doubles, H blocks [unit, y tile][16][32] of the compressed form
@@ -277,14 +285,15 @@ void launch_adj_small(const GeomDev *g, const ModelDev *m, const Item *it, int n
 void launch_grads(const GeomDev *g, const ModelDev *m, int n, ParamsDev p, double *sens,
                   const double *sbp, const int *st_ws, GradsDev out, hipStream_t st);
 // Spherically aligned model.  Terms: items (m, block of 256 terms), the
-// model's FP32 (j, u) coefficients into its term region.  Moments: items (m,
+// model's FP32 (j, u) coefficients into its term region, and for the adjoint
+// (terms64 != NULL) their FP64 ones.  Moments: items (m,
 // table point i_r * kSphNT + i_theta), one workgroup each, writing A_r,
 // A_theta, A_phi into the model's table.  Numerator: items (m, 64-pixel
 // block), the line-of-sight integral of the projected table into the
 // unique-pixel N map.
 void launch_sph_terms(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                      const double *gauss, const int *st_ws, float4 *terms, double *pol,
-                      hipStream_t st);
+                      const double *gauss, const int *st_ws, float4 *terms, double *terms64,
+                      double *pol, hipStream_t st);
 // Here the (j, u) terms are summed at every node: items (m, group of four
 // table points), a wave per point.
 void launch_sph_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
@@ -293,6 +302,9 @@ void launch_sph_moments(const GeomDev *g, const ModelDev *m, const Item *it, int
 // Potential grid of the spherical model (jam_polar.hip): the tracer-free
 // (j, u) sums on kPolN radii x kPolC angles, kPolPr x 8 interpolation points.
 constexpr int kPolN = 384, kPolC = 64, kPolPr = 6;
+// The adjoint's grid, in doubles: (G, G_theta) [kPolN][kPolC] and as many floats,
+// T_theta.
+constexpr int kPolAdjGrid = kPolN * kPolC * 5 / 2;
 // Term slices of its evaluation, about seven 64-term groups each.  Like the
 // tracer groups below a property of the model alone, so that its grid, and
 // everything computed from it, is the same in any batch.
@@ -329,19 +341,27 @@ __host__ __device__ inline int64_t pol_cot_size(int K) {
 // (m, block of 1024 floats) for their sum.
 void launch_pol_grid(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                      const Item *it_sum, int n_sum, const float4 *terms, const int *st_ws,
-                     const double *pol, float *sgrid, bool adjoint, hipStream_t st);
+                     const double *pol, float *sgrid, hipStream_t st);
+// The adjoint's grid, in FP64 from terms64.
+void launch_pol_grid_adj(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                         const Item *it_sum, int n_sum, const double *terms64, const int *st_ws,
+                         const double *pol, double *sgrid3, hipStream_t st);
 // The moment table: items (m, four (tracer group, radius) units) and (m, 16
-// cells).  With sens != NULL the adjoint's forward pass, from the adjoint's
-// grid: also SphAdj::jac, gphi and the node table in pcot.
+// cells).  launch_pol_moments_adj is the adjoint's forward pass, from the
+// adjoint's grid: also SphAdj::jac, gphi and the node table in pcot.
 void launch_pol_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                         const Item *it_tab, int n_tab, const double *gauss, const float4 *terms,
                         const int *st_ws, const float *sgrid, double *pol, double *table,
-                        double *sens, double *pcot, hipStream_t st);
+                        hipStream_t st);
+void launch_pol_moments_adj(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                            const Item *it_tab, int n_tab, const double *gauss,
+                            const double *terms64, const int *st_ws, const double *sgrid3,
+                            double *pol, double *table, double *sens, double *pcot, hipStream_t st);
 // Term sensitivities through the grid, from SphAdj::dtab: items (m, row bin,
 // tracer group), (m, 256 grid points) and (m, 512-term tile, row part).
 void launch_pol_adjoint(const GeomDev *g, const ModelDev *m, const Item *it_spread, int n_spread,
                         const Item *it_sum, int n_sum, const Item *it_sens, int n_sens,
-                        const double *gauss, const float4 *terms, const int *st_ws,
+                        const double *gauss, const double *terms64, const int *st_ws,
                         const double *pol, double *sens, double *pcot, hipStream_t st);
 void launch_sph_num(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                     const double *gauss, const int *st_ws, const double *table, double *pix,
@@ -372,7 +392,7 @@ void launch_sph_sens(const GeomDev *g, const ModelDev *m, const Item *it, int n_
                      const double *gauss, const float4 *terms, const int *st_ws, double *sens,
                      hipStream_t st);
 void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it_tile, int n_tile,
-                      ParamsDev p, const double *gauss, const float4 *terms, const int *st_ws,
+                      ParamsDev p, const double *gauss, const double *terms64, const int *st_ws,
                       const double *sbp, double *sens, GradsDev out, hipStream_t st);
 // Adjoint of the spherically aligned model.  Per model, in the sensitivity
 // region (doubles): the table cotangent [kSphNR*kSphNT][3], per tracer and

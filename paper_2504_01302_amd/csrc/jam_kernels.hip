@@ -2320,15 +2320,17 @@ __device__ inline SphAdj sph_adj_of(double *sens, const ModelDev &md, const Geom
 
 // FP32 coefficients of the (j, u) terms of G, G_theta and G_phi, once per
 // model: (-r_j u^2 log2e, -r_j u^2 / h log2e, gP, gT) and gF, zero-padded to
-// a whole number of 64-term groups (a zero term adds exactly nothing).  With
-// the potential grid also T_theta's weights gT r_j u^2 (1 / h - 1), and the
-// grid's scales (first item).  Item (m, block of 256 terms); thread = term.
+// a whole number of 64-term groups (a zero term adds exactly nothing); for the
+// adjoint the same in FP64, with T_theta's weights gT r_j u^2 (1 / h - 1); and the
+// potential grid's scales (first item).  Item (m, block of 256 terms); thread =
+// term.
 __global__ void __launch_bounds__(256) k_sph_terms(const GeomDev *__restrict__ geoms,
                                                    const ModelDev *__restrict__ models,
                                                    const Item *__restrict__ items, int n_it,
                                                    const double *__restrict__ gauss,
                                                    const int *__restrict__ st_ws,
                                                    float4 *__restrict__ terms,
+                                                   double *__restrict__ terms64,
                                                    double *__restrict__ pol) {
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
     const Item it = items[i];
@@ -2357,10 +2359,11 @@ __global__ void __launch_bounds__(256) k_sph_terms(const GeomDev *__restrict__ g
     if (t >= Tp) continue;
     float4 *tc = terms + md.term_off;
     float *tf = (float *)(tc + Tp);
+    SphTerm *t64 = terms64 ? reinterpret_cast<SphTerm *>(terms64 + md.term64_off) : nullptr;
     if (t >= T || st_ws[it.m] != 0) {
       tc[t] = make_float4(0.f, 0.f, 0.f, 0.f);
       tf[t] = 0.f;
-      if (grid) tf[Tp + t] = 0.f;
+      if (t64) t64[t] = SphTerm{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
       continue;
     }
     const double *mt = gauss + md.gauss_off + 4 * g.K;
@@ -2369,10 +2372,11 @@ __global__ void __launch_bounds__(256) k_sph_terms(const GeomDev *__restrict__ g
     const double u = g.u[n], u2 = u * u, wK = g.w[n] * Kp;
     const double hh = 1.0 - e2 * u2, h15 = hh * sqrt(hh);
     const double gT = wK * e2 * 4.0 * rj * rj * u2 * u2 * u2 / (h15 * hh);
-    tc[t] = make_float4((float)(-rj * u2 * kLog2e), (float)(-rj * u2 / hh * kLog2e),
-                        (float)(wK * 2.0 * rj * u2 / h15), (float)gT);
-    tf[t] = (float)(wK * e2 * 2.0 * rj * u2 * u2 / h15);
-    if (grid) tf[Tp + t] = (float)(gT * rj * u2 * (e2 * u2 / hh));
+    const SphTerm c{-rj * u2 * kLog2e, -rj * u2 / hh * kLog2e, wK * 2.0 * rj * u2 / h15, gT,
+                    wK * e2 * 2.0 * rj * u2 * u2 / h15, gT * rj * u2 * (e2 * u2 / hh)};
+    tc[t] = make_float4((float)c.cx, (float)c.cy, (float)c.gP, (float)c.gT);
+    tf[t] = (float)c.gF;
+    if (t64) t64[t] = c;
   }
 }
 
@@ -3347,15 +3351,18 @@ __global__ void __launch_bounds__(256) k_sph_sens(const GeomDev *__restrict__ ge
 
 // Term sensitivities of the table points' G_phi term (chi = -lambda_phi nu
 // R0^2 per cell).  Item (m, 256-term tile) split in kSphCellParts parts of
-// 256 cells; thread = term.  Each part's FP32 sums go to their own slot.
+// 256 cells; thread = term.  Each part's sums go to their own slot.  FP64 but for
+// the exponential: the cells' signs differ, and FP32 sums over 256 of them left up
+// to 2e-6 in a single model's inclination derivative.
 __global__ void __launch_bounds__(256) k_sph_sens_cells(const GeomDev *__restrict__ geoms,
                                                         const ModelDev *__restrict__ models,
                                                         const Item *__restrict__ items, int n_it,
                                                         const double *__restrict__ gauss,
-                                                        const float4 *__restrict__ terms,
+                                                        const double *__restrict__ terms64,
                                                         const int *__restrict__ st_ws,
                                                         double *__restrict__ sens) {
-  __shared__ float4 pc[256];   // (R0^2, z0^2, chi, 0)
+  __shared__ double2 px[256];   // R0^2, z0^2
+  __shared__ double pc[256];    // chi
   for (int vi = blockIdx.x; vi < n_it * kSphCellParts; vi += gridDim.x) {
     const Item it = items[vi / kSphCellParts];
     const int part = vi % kSphCellParts;
@@ -3367,8 +3374,9 @@ __global__ void __launch_bounds__(256) k_sph_sens_cells(const GeomDev *__restric
     const double *tab = gauss + md.gauss_off;
     const int t = it.a * 256 + threadIdx.x;
     const bool tv = t < Tp;
-    const float4 c = tv ? terms[md.term_off + t] : make_float4(0.f, 0.f, 0.f, 0.f);
-    double SF = 0.0, SxF = 0.0, SyF = 0.0;
+    const SphTerm *tc = reinterpret_cast<const SphTerm *>(terms64 + md.term64_off);
+    const double cx = tv ? tc[t].cx : 0.0, cy = tv ? tc[t].cy : 0.0;
+    double sF = 0.0, sx = 0.0, sy = 0.0;
     {
       const int cell = part * 256 + threadIdx.x;
       double r, sth, cth;
@@ -3376,29 +3384,25 @@ __global__ void __launch_bounds__(256) k_sph_sens_cells(const GeomDev *__restric
       const double R0 = r * sth, z0 = r * cth;
       double nus = 0.0;
       for (int k = 0; k < K; ++k) nus += tab[2 * K + k] * exp(-(tab[k] * R0 * R0 + tab[K + k] * z0 * z0));
-      const double chi = -adj.dtab[3 * cell + 2] * nus * R0 * R0;
       __syncthreads();
-      pc[threadIdx.x] = make_float4((float)(R0 * R0), (float)(z0 * z0), (float)chi, 0.f);
+      px[threadIdx.x] = make_double2(R0 * R0, z0 * z0);
+      pc[threadIdx.x] = -adj.dtab[3 * cell + 2] * nus * R0 * R0;
       __syncthreads();
-      float sF = 0.f, sx = 0.f, sy = 0.f;
       if (tv) {
         for (int j = 0; j < 256; ++j) {
-          const float4 A = pc[j];
-          const float e = A.z * fast_exp2(fmaf(c.x, A.x, c.y * A.y));
+          const double2 x = px[j];
+          const double e = pc[j] * (double)fast_exp2((float)fma(cx, x.x, cy * x.y));
           sF += e;
-          sx = fmaf(A.x, e, sx);
-          sy = fmaf(A.y, e, sy);
+          sx = fma(x.x, e, sx);
+          sy = fma(x.y, e, sy);
         }
       }
-      SF += (double)sF;
-      SxF += (double)sx;
-      SyF += (double)sy;
     }
     if (tv) {
       double *o = adj.cparts + ((int64_t)part * Tp + t) * 3;
-      o[0] = SF;
-      o[1] = SxF;
-      o[2] = SyF;
+      o[0] = sF;
+      o[1] = sx;
+      o[2] = sy;
     }
     __syncthreads();
   }
@@ -3894,10 +3898,10 @@ void launch_sb_adjoint(const GeomDev *g, const ModelDev *m, const Item *it, int 
                      sbp);
 }
 void launch_sph_terms(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
-                      const double *gauss, const int *st_ws, float4 *terms, double *pol,
-                      hipStream_t st) {
+                      const double *gauss, const int *st_ws, float4 *terms, double *terms64,
+                      double *pol, hipStream_t st) {
   hipLaunchKernelGGL(k_sph_terms, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, gauss,
-                     st_ws, terms, pol);
+                     st_ws, terms, terms64, pol);
 }
 void launch_sph_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                         const double *gauss, const float4 *terms, const int *st_ws, double *table,
@@ -3935,10 +3939,10 @@ void launch_sph_sens(const GeomDev *g, const ModelDev *m, const Item *it, int n_
                      terms, st_ws, sens);
 }
 void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it_tile, int n_tile,
-                      ParamsDev p, const double *gauss, const float4 *terms, const int *st_ws,
+                      ParamsDev p, const double *gauss, const double *terms64, const int *st_ws,
                       const double *sbp, double *sens, GradsDev out, hipStream_t st) {
   hipLaunchKernelGGL(k_sph_sens_cells, dim3(grid_of(n_tile * kSphCellParts)), dim3(256), 0, st, g,
-                     m, it_tile, n_tile, gauss, terms, st_ws, sens);
+                     m, it_tile, n_tile, gauss, terms64, st_ws, sens);
   hipLaunchKernelGGL(k_sph_chain, dim3(grid_of(n_tile)), dim3(256), 0, st, g, m, it_tile, n_tile,
                      gauss, st_ws, sens);
   hipLaunchKernelGGL(k_sph_grads, dim3(grid_of(n)), dim3(512), 0, st, g, m, n, p, gauss, st_ws,

@@ -28,6 +28,7 @@
 
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 
 namespace jam {
 
@@ -109,18 +110,14 @@ __device__ inline double pol_reach(const PolScale &sc) {
 // ---------------------------------------------------------------------------
 // The grid: item (m, four rows, term slice); wave = row, lane = column.  The
 // term coefficients are uniform over the wave (scalar loads); FP32 sums of 64
-// terms folded into FP64, the slice partial stored in FP32 ([N][C][NC] per
-// slice).  NC = 2: G, G_theta; NC = 3 adds T_theta = dG_theta / dR'^2 at fixed
-// r', all the adjoint needs beside them: with R'^2 + z'^2 = r'^2 fixed,
-// dG / dR'^2 = G_theta / 2.
+// terms folded into FP64, the slice partial stored in FP32 ([N][C][2] per
+// slice: G, G_theta).
 // The exponent is not a product of a row and a column factor here, so the
-// sums run on the VALU: two FP32 operations, an exponential and NC
+// sums run on the VALU: two FP32 operations, an exponential and two
 // multiply-adds per term and point, but on 24,576 points where the R, z grid
 // took matrix products on 262,144.  Measured (48 models of 1300 terms / one
-// of 5248): the forward's two sums 683 / 72 us on that grid, 287 / 37 here;
-// the adjoint's 2262 / 211 (six sums), 331 / 41 here.
+// of 5248): 683 / 72 us on that grid, 287 / 37 here.
 // ---------------------------------------------------------------------------
-template <int NC>
 __global__ void __launch_bounds__(256) k_pol_grid(const GeomDev *__restrict__ geoms,
                                                   const ModelDev *__restrict__ models,
                                                   const Item *__restrict__ items, int n_it,
@@ -139,55 +136,117 @@ __global__ void __launch_bounds__(256) k_pol_grid(const GeomDev *__restrict__ ge
     const int row = 4 * it.a + wave;
     const double r2 = pol_row_r2(g, sc, row), z2 = r2 * pol_col_c2(sc, lane);
     const float R2 = (float)(r2 - z2), Z2 = (float)z2;
-    const int Tp = sph_terms_padded(g.J1, g.n_u), chunks = Tp / 64;
+    const int chunks = sph_terms_padded(g.J1, g.n_u) / 64;
     const int c0 = (int)((int64_t)chunks * it.b / md.sgrid_slices);
     const int c1 = (int)((int64_t)chunks * (it.b + 1) / md.sgrid_slices);
     const float4 *tc = terms + md.term_off;
-    const float *td = (const float *)(tc + Tp) + Tp;     // T_theta's weights
-    double acc[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+    double acc[2] = {0.0, 0.0};
     for (int ch = c0; ch < c1; ++ch) {
-      float f[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) f[c] = 0.f;
+      float f[2] = {0.f, 0.f};
 #pragma unroll 16
       for (int t = 64 * ch; t < 64 * ch + 64; ++t) {
         const float4 c = tc[t];
         const float e = fast_exp2(fmaf(c.x, R2, c.y * Z2));
         f[0] = fmaf(c.z, e, f[0]);
         f[1] = fmaf(c.w, e, f[1]);
-        if constexpr (NC == 3) f[2] = fmaf(td[t], e, f[2]);
       }
-#pragma unroll
-      for (int c = 0; c < NC; ++c) acc[c] += (double)f[c];
+      acc[0] += (double)f[0];
+      acc[1] += (double)f[1];
     }
-    float *o = sgrid + (NC == 2 ? md.sgrid_off : md.sgrid3_off) +
-               (int64_t)it.b * (kPolN * kPolC * NC);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) o[(row * kPolC + lane) * NC + c] = (float)acc[c];
+    float *o = sgrid + md.sgrid_off + (int64_t)it.b * (kPolN * kPolC * 2);
+    o[(row * kPolC + lane) * 2] = (float)acc[0];
+    o[(row * kPolC + lane) * 2 + 1] = (float)acc[1];
   }
 }
 
-// Item (m, block of 1024 grid floats): the slice partials summed in slice
-// order (FP64) into slice 0.
+// The adjoint's grid: G, G_theta and T_theta = dG_theta / dR'^2 at fixed r' (all
+// the adjoint needs beside them: with R'^2 + z'^2 = r'^2 fixed, dG / dR'^2 =
+// G_theta / 2), per slice (G, G_theta) [N][C] in FP64 and T_theta [N][C] in FP32.
+// A model's inclination derivative is one number in which terms hundreds of times
+// larger cancel, so exponents, sums and the stored G, G_theta are FP64; only the
+// exponential is FP32, whose rounding differs from term to term.  Relative error of
+// that derivative, 24 single models of 40 x 41 Gaussians, largest / geometric mean:
+// all FP32 1.4e-5 / 4.5e-7, FP64 sums stored in FP32 4e-6 / 1e-7, FP32 sums of 64
+// terms stored in FP64 1e-5 / 2e-7, this 6e-7 / 3e-8, FP64 exponentials as well
+// 1e-7 / 3e-9.  T_theta only enters d/dbeta, which does not cancel.  Measured (48
+// models of 1300 terms / one of 5248): all FP32 331 / 41 us, this 517 / 75, FP64
+// exponentials as well 877 / 105.
+__global__ void __launch_bounds__(256) k_pol_grid_adj(const GeomDev *__restrict__ geoms,
+                                                      const ModelDev *__restrict__ models,
+                                                      const Item *__restrict__ items, int n_it,
+                                                      const double *__restrict__ terms64,
+                                                      const int *__restrict__ st_ws,
+                                                      const double *__restrict__ pol,
+                                                      double *__restrict__ sgrid3) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
+    const Item it = items[i];
+    if (st_ws[it.m] != 0) continue;         // the grid is not read
+    const ModelDev md = models[it.m];
+    const GeomDev &g = geoms[md.geom];
+    const PolScale sc = pol_scale(pol, md);
+    const int row = 4 * it.a + wave;
+    const double r2 = pol_row_r2(g, sc, row), Z2 = r2 * pol_col_c2(sc, lane), R2 = r2 - Z2;
+    const int chunks = sph_terms_padded(g.J1, g.n_u) / 64;
+    const int c0 = (int)((int64_t)chunks * it.b / md.sgrid_slices);
+    const int c1 = (int)((int64_t)chunks * (it.b + 1) / md.sgrid_slices);
+    const SphTerm *tc = reinterpret_cast<const SphTerm *>(terms64 + md.term64_off);
+    double G = 0.0, T = 0.0, D = 0.0;
+#pragma unroll 8
+    for (int t = 64 * c0; t < 64 * c1; ++t) {
+      const double e = (double)fast_exp2((float)fma(tc[t].cx, R2, tc[t].cy * Z2));
+      G = fma(tc[t].gP, e, G);
+      T = fma(tc[t].gT, e, T);
+      D = fma(tc[t].gD, e, D);
+    }
+    double *o = sgrid3 + md.sgrid3_off + (int64_t)it.b * kPolAdjGrid;
+    reinterpret_cast<double2 *>(o)[row * kPolC + lane] = make_double2(G, T);
+    reinterpret_cast<float *>(o + 2 * kPolN * kPolC)[row * kPolC + lane] = (float)D;
+  }
+}
+
+// Item (m, block of 1024 grid floats; the adjoint's 256 grid points): the slice
+// partials summed in slice order (FP64) into slice 0.
 __global__ void __launch_bounds__(256) k_pol_grid_sum(const ModelDev *__restrict__ models,
                                                       const Item *__restrict__ items, int n_it,
                                                       const int *__restrict__ st_ws,
-                                                      float *__restrict__ sgrid, int nc) {
+                                                      float *__restrict__ sgrid) {
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
     const Item it = items[i];
     if (st_ws[it.m] != 0) continue;
     const ModelDev md = models[it.m];
-    const int64_t len = (int64_t)kPolN * kPolC * nc;
-    float4 *base = reinterpret_cast<float4 *>(sgrid + (nc == 3 ? md.sgrid3_off : md.sgrid_off)) +
-                   it.a * 256 + threadIdx.x;
+    const int64_t len = (int64_t)kPolN * kPolC * 2;
+    float4 *base = reinterpret_cast<float4 *>(sgrid + md.sgrid_off) + it.a * 256 + threadIdx.x;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
     for (int sl = 0; sl < md.sgrid_slices; ++sl) {
       const float4 q = base[sl * (len / 4)];
       v[0] += (double)q.x; v[1] += (double)q.y; v[2] += (double)q.z; v[3] += (double)q.w;
     }
     *base = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+  }
+}
+__global__ void __launch_bounds__(256) k_pol_grid_sum_adj(const ModelDev *__restrict__ models,
+                                                          const Item *__restrict__ items, int n_it,
+                                                          const int *__restrict__ st_ws,
+                                                          double *__restrict__ sgrid3) {
+  for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
+    const Item it = items[i];
+    if (st_ws[it.m] != 0) continue;
+    const ModelDev md = models[it.m];
+    const int e = it.a * 256 + threadIdx.x;
+    double *base = sgrid3 + md.sgrid3_off;
+    double2 v = make_double2(0.0, 0.0);
+    double d = 0.0;
+    for (int sl = 0; sl < md.sgrid_slices; ++sl) {
+      const double *b = base + (int64_t)sl * kPolAdjGrid;
+      const double2 q = reinterpret_cast<const double2 *>(b)[e];
+      v.x += q.x;
+      v.y += q.y;
+      d += (double)reinterpret_cast<const float *>(b + 2 * kPolN * kPolC)[e];
+    }
+    reinterpret_cast<double2 *>(base)[e] = v;
+    reinterpret_cast<float *>(base + 2 * kPolN * kPolC)[e] = (float)d;
   }
 }
 
@@ -213,7 +272,8 @@ __global__ void __launch_bounds__(256) k_pol_grid_sum(const ModelDev *__restrict
 // in the L1), rows prefetched a segment ahead.  Measured (48 models of 10
 // tracers / one of 40), a block per four table points and 4 x 4 scattered
 // points of the R, z grid before, this after: forward 3444 / 303 -> 684 / 82
-// us, the adjoint's pass 6417 / 498 -> 1179 / 146.
+// us, the adjoint's pass 6417 / 498 -> 1227 / 152 (1179 / 146 with its grid in
+// FP32).
 // ---------------------------------------------------------------------------
 template <bool kJac> struct PolWave {
   double rp2[64], s[64], w[64], wd[64];   // r'^2, (r / r')^(1 - beta), weights of P and D
@@ -251,14 +311,17 @@ __device__ __forceinline__ void pol_lines(PolWave<false> &W, const float *__rest
   }
 }
 
+// The grid's numbers: the forward's FP32, the adjoint's FP64.
+template <bool kJac> using PolGrid = std::conditional_t<kJac, double, float>;
+
 template <bool kJac>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) k_pol_moments(
     const GeomDev *__restrict__ geoms, const ModelDev *__restrict__ models,
     const Item *__restrict__ items, int n_it, const double *__restrict__ gauss,
-    const int *__restrict__ st_ws, const float *__restrict__ sgrid, double *__restrict__ pol,
-    double *__restrict__ sens, double *__restrict__ pcot) {
+    const int *__restrict__ st_ws, const PolGrid<kJac> *__restrict__ sgrid,
+    double *__restrict__ pol, double *__restrict__ sens, double *__restrict__ pcot) {
   static_assert(kSphNT == 24 && kSphNodes == 64 && kPolC == 64 && kPolPr == 6, "wave layout");
-  constexpr int NC = kJac ? 3 : 2, NS = kJac ? 6 : 2;
+  constexpr int NS = kJac ? 6 : 2;
   __shared__ PolMath mt;
   __shared__ PolWave<kJac> wv[4];
   const int lane = threadIdx.x & 63, nd = lane & 7, tl = lane >> 3;
@@ -278,7 +341,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     const double rs0 = 1.0 / sc.s0, iC = sc.iC;
     const double lnr = g.sph_lnr0 + ir * g.sph_dlnr, r = exp(lnr);
     const double glx = g.gl8_x[nd], glw = g.gl8_w[nd];
-    const float *sg = sgrid + (kJac ? md.sgrid3_off : md.sgrid_off);
+    const PolGrid<kJac> *sg = sgrid + (kJac ? md.sgrid3_off : md.sgrid_off);
     double Ar[3], At[3], Ap[3];             // lanes nd == 0: cells 8 t + tl
 #pragma unroll
     for (int t = 0; t < 3; ++t) Ar[t] = At[t] = Ap[t] = 0.0;
@@ -332,7 +395,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
           double wx[6];
           lagrange<6>(x - i0, wx);
           if (tl == 0) {
-            W.row[nd] = (i0 - 2) * (kPolC * NC);
+            W.row[nd] = (i0 - 2) * (kJac ? kPolC : kPolC * 2);
 #pragma unroll
             for (int a = 0; a < 6; ++a) W.wx[nd][a] = wx[a];
           }
@@ -342,16 +405,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
         // the columns from its first node's on
         const int c0 = __builtin_amdgcn_readfirstlane(W.c0[8 * seg]);
         if constexpr (kJac) {
-          const float *sl = sg + max(lane, c0) * 3;   // unneeded columns repeat the first
+          // unneeded columns repeat the first
+          const double2 *sl = reinterpret_cast<const double2 *>(sg) + max(lane, c0);
+          const float *sd = reinterpret_cast<const float *>(sg + 2 * kPolN * kPolC) + max(lane, c0);
 #pragma unroll 4
           for (int h = 0; h < 8; ++h) {
-            const float *p = sl + __builtin_amdgcn_readfirstlane(W.row[h]);
+            const int at = __builtin_amdgcn_readfirstlane(W.row[h]);
             double v[3] = {0.0, 0.0, 0.0};
 #pragma unroll
             for (int a = 0; a < 6; ++a) {
               const double wx = W.wx[h][a];
-#pragma unroll
-              for (int c = 0; c < 3; ++c) v[c] = fma(wx, (double)p[a * (kPolC * 3) + c], v[c]);
+              const double2 q = sl[at + a * kPolC];
+              v[0] = fma(wx, q.x, v[0]);
+              v[1] = fma(wx, q.y, v[1]);
+              v[2] = fma(wx, (double)sd[at + a * kPolC], v[2]);
             }
             W.L[h][lane] = make_double2(v[0], v[1]);
             W.L3[h][lane] = v[2];
@@ -454,13 +521,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
 }
 
 // The table: per cell the groups' partials in order and -nu R^2 G_phi.  Item
-// (m, 16 cells), a wave per cell, four cells each; G_phi's FP32 terms and the
-// tracer density summed in FP64 over the lanes in a fixed order.
+// (m, 16 cells), a wave per cell, four cells each; G_phi's terms (FP32; the
+// adjoint's exponents and sums FP64, as its grid's) and the tracer density summed in FP64 over the lanes in a fixed
+// order.
+template <bool kAdj>
 __global__ void __launch_bounds__(256) k_pol_table(
     const GeomDev *__restrict__ geoms, const ModelDev *__restrict__ models,
     const Item *__restrict__ items, int n_it, const double *__restrict__ gauss,
-    const float4 *__restrict__ terms, const int *__restrict__ st_ws, double *__restrict__ pol,
-    double *__restrict__ table, double *__restrict__ sens) {
+    const float4 *__restrict__ terms, const double *__restrict__ terms64,
+    const int *__restrict__ st_ws, double *__restrict__ pol, double *__restrict__ table,
+    double *__restrict__ sens) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int i = blockIdx.x; i < n_it; i += gridDim.x) {
@@ -474,8 +544,6 @@ __global__ void __launch_bounds__(256) k_pol_table(
       continue;
     }
     const int K = g.K, Tp = sph_terms_padded(g.J1, g.n_u);
-    const float4 *tc = terms + md.term_off;
-    const float *tf = (const float *)(tc + Tp);
     const double *tab = gauss + md.gauss_off;
     // lane c of the wave's first four: cell c's coordinates
     double r2c = 0.0, z2c = 0.0;
@@ -492,19 +560,33 @@ __global__ void __launch_bounds__(256) k_pol_table(
       nu += tab[2 * K + k] * exp(-(tab[k] * r2c + tab[K + k] * z2c));
     for (int o = 4; o < 64; o <<= 1) nu += __shfl_xor(nu, o, 64);
     double accF[4];
-    float R20[4], Z20[4];
+    PolGrid<kAdj> R20[4], Z20[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      R20[c] = (float)__shfl(r2c, c, 64);
-      Z20[c] = (float)__shfl(z2c, c, 64);
+      R20[c] = (PolGrid<kAdj>)__shfl(r2c, c, 64);
+      Z20[c] = (PolGrid<kAdj>)__shfl(z2c, c, 64);
       accF[c] = 0.0;
     }
-#pragma unroll 4
-    for (int t = lane; t < Tp; t += 64) {
-      const float4 q = tc[t];
-      const float f = tf[t];
+    if constexpr (kAdj) {
+      const SphTerm *tc = reinterpret_cast<const SphTerm *>(terms64 + md.term64_off);
+#pragma unroll 2
+      for (int t = lane; t < Tp; t += 64) {
+        const double cx = tc[t].cx, cy = tc[t].cy, f = tc[t].gF;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) accF[c] += (double)(f * fast_exp2(fmaf(q.x, R20[c], q.y * Z20[c])));
+        for (int c = 0; c < 4; ++c) 
+          accF[c] = fma(f, (double)fast_exp2((float)fma(cx, R20[c], cy * Z20[c])), accF[c]);
+      }
+    } else {
+      const float4 *tc = terms + md.term_off;
+      const float *tf = (const float *)(tc + Tp);
+#pragma unroll 4
+      for (int t = lane; t < Tp; t += 64) {
+        const float4 q = tc[t];
+        const float f = tf[t];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          accF[c] += (double)(f * fast_exp2(fmaf(q.x, R20[c], q.y * Z20[c])));
+      }
     }
     // the partials: lane = 3 c + moment
     double v = 0.0;
@@ -517,7 +599,7 @@ __global__ void __launch_bounds__(256) k_pol_table(
     for (int c = 0; c < 4; ++c) {
       const double F = wave_sum(accF[c]), nR = __shfl(nu * r2c, c, 64);
       if (lane == 3 * c + 2) sub = nR * F;
-      if (sens && lane == 0)
+      if (kAdj && lane == 0)
         sph_adj_layout(sens + md.sens_off, K, g.n_pix, Tp, md.n_sens_parts).gphi[cell0 + c] = F;
     }
     if (lane < 12) out[lane] = v - sub;
@@ -769,22 +851,23 @@ __global__ void __launch_bounds__(256) k_pol_cot_sum(const GeomDev *__restrict__
 // reads (wave-wide broadcasts; with one term per thread the reads are the
 // bound).  Per term S_phi = sum phi E, S_psi and their R'^2 and z'^2 moments,
 // FP32 over a row of 64 points, FP64 across rows.  On a row r'^2 is fixed: the
-// exponent is one multiply-add from c.x r'^2, and the R'^2 = r'^2 - z'^2
-// moments need no sums of their own.  Five FP32 operations and an exponential
-// per term and point bound it.  Measured (48 models of 1300 terms / one of
-// 5248): on the 512 x 512 grid with matrix cores 1132 / 129 us, here 325 / 52.
+// exponent, in FP64 as in k_pol_grid_adj, is one multiply-add from c.x r'^2, and
+// the R'^2 = r'^2 - z'^2 moments need no sums of their own.  An FP64 multiply-add,
+// an exponential and four FP32 multiply-adds per term and point bound it.
+// Measured (48 models of 1300 terms / one of 5248): on the 512 x 512 grid with
+// matrix cores 1132 / 129 us, here 400 / 64 (325 / 52 with FP32 exponents).
 __global__ void __launch_bounds__(256) k_pol_sens(const GeomDev *__restrict__ geoms,
                                                   const ModelDev *__restrict__ models,
                                                   const Item *__restrict__ items, int n_it,
-                                                  const float4 *__restrict__ terms,
+                                                  const double *__restrict__ terms64,
                                                   const int *__restrict__ st_ws,
                                                   const double *__restrict__ pol,
                                                   double *__restrict__ sens,
                                                   const double *__restrict__ pcot) {
   constexpr int kRows = kPolN / kPolParts;
   static_assert(kRows % 4 == 0 && kPolN % kPolParts == 0, "four rows at a time");
-  __shared__ float4 pc[4][kPolC];            // (z'^2, phi, psi, phi z'^2)
-  __shared__ float pd[4][kPolC];             // psi z'^2
+  __shared__ float4 pc[4][kPolC];            // (phi, psi, phi z'^2, psi z'^2)
+  __shared__ double pz[4][kPolC];            // z'^2
   __shared__ double rr[4];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -797,43 +880,43 @@ __global__ void __launch_bounds__(256) k_pol_sens(const GeomDev *__restrict__ ge
     const int K = g.K, Tp = sph_terms_padded(g.J1, g.n_u);
     const float2 *fl = reinterpret_cast<const float2 *>(
         pcot + md.sgcot_off + pol_nodes(K) + (int64_t)pol_cot_groups(K) * kPolBins * kPolTile);
-    float4 c[2];
-    double SP[2], ST[2], ZP[2], ZT[2], RP[2], RT[2];
+    const SphTerm *tc = reinterpret_cast<const SphTerm *>(terms64 + md.term64_off);
+    double cx[2], dz[2], SP[2], ST[2], ZP[2], ZT[2], RP[2], RT[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int t = it.a * 512 + 256 * u + threadIdx.x;
-      c[u] = t < Tp ? terms[md.term_off + t] : make_float4(0.f, 0.f, 0.f, 0.f);
+      cx[u] = t < Tp ? tc[t].cx : 0.0;
+      dz[u] = t < Tp ? tc[t].cy - cx[u] : 0.0;
       SP[u] = ST[u] = ZP[u] = ZT[u] = RP[u] = RT[u] = 0.0;
     }
-    const float dz[2] = {c[0].y - c[0].x, c[1].y - c[1].x};
     const double c2 = pol_col_c2(sc, lane), reach = pol_reach(sc);
-    float cmax = fmaxf(c[0].x, c[1].x);
-    for (int o = 32; o > 0; o >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, o, 64));
+    double cmax = fmax(cx[0], cx[1]);
+    for (int o = 32; o > 0; o >>= 1) cmax = fmax(cmax, __shfl_xor(cmax, o, 64));
     for (int q0 = it.b * kRows; q0 < (it.b + 1) * kRows; q0 += 4) {
       const double r2 = pol_row_r2(g, sc, q0 + wave), z2 = r2 * c2;
       const float2 f = fl[(q0 + wave) * kPolC + lane];
       __syncthreads();                       // the previous rows read
-      pc[wave][lane] = make_float4((float)z2, f.x, f.y, f.x * (float)z2);
-      pd[wave][lane] = f.y * (float)z2;
+      pc[wave][lane] = make_float4(f.x, f.y, f.x * (float)z2, f.y * (float)z2);
+      pz[wave][lane] = z2;
       if (lane == 0) rr[wave] = r2;
       __syncthreads();
       for (int w = 0; w < 4; ++w) {
         // a row where every term of the wave underflows adds exact zeros
-        if (cmax * (float)(rr[w] * reach) < -160.f) continue;
+        if (cmax * (rr[w] * reach) < -160.0) continue;
         float sP[2] = {0.f, 0.f}, sT[2] = {0.f, 0.f}, zP[2] = {0.f, 0.f}, zT[2] = {0.f, 0.f};
         const double r = rr[w];
-        const float a[2] = {c[0].x * (float)r, c[1].x * (float)r};
+        const double a[2] = {cx[0] * r, cx[1] * r};
 #pragma unroll 16
         for (int l = 0; l < kPolC; ++l) {
           const float4 p = pc[w][l];
-          const float q = pd[w][l];
+          const double z = pz[w][l];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            const float e = fast_exp2(fmaf(dz[u], p.x, a[u]));
-            sP[u] = fmaf(p.y, e, sP[u]);
-            sT[u] = fmaf(p.z, e, sT[u]);
-            zP[u] = fmaf(p.w, e, zP[u]);
-            zT[u] = fmaf(q, e, zT[u]);
+            const float e = fast_exp2((float)fma(dz[u], z, a[u]));
+            sP[u] = fmaf(p.x, e, sP[u]);
+            sT[u] = fmaf(p.y, e, sT[u]);
+            zP[u] = fmaf(p.z, e, zP[u]);
+            zT[u] = fmaf(p.w, e, zT[u]);
           }
         }
 #pragma unroll
@@ -871,40 +954,51 @@ unsigned grid_of(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int
 
 void launch_pol_grid(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                      const Item *it_sum, int n_sum, const float4 *terms, const int *st_ws,
-                     const double *pol, float *sgrid, bool adjoint, hipStream_t st) {
-  if (adjoint)
-    hipLaunchKernelGGL(k_pol_grid<3>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, terms,
-                       st_ws, pol, sgrid);
-  else
-    hipLaunchKernelGGL(k_pol_grid<2>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, terms,
-                       st_ws, pol, sgrid);
+                     const double *pol, float *sgrid, hipStream_t st) {
+  hipLaunchKernelGGL(k_pol_grid, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, terms,
+                     st_ws, pol, sgrid);
   if (n_sum)
     hipLaunchKernelGGL(k_pol_grid_sum, dim3(grid_of(n_sum)), dim3(256), 0, st, m, it_sum, n_sum,
-                       st_ws, sgrid, adjoint ? 3 : 2);
+                       st_ws, sgrid);
+}
+void launch_pol_grid_adj(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                         const Item *it_sum, int n_sum, const double *terms64, const int *st_ws,
+                         const double *pol, double *sgrid3, hipStream_t st) {
+  hipLaunchKernelGGL(k_pol_grid_adj, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it, terms64,
+                     st_ws, pol, sgrid3);
+  if (n_sum)
+    hipLaunchKernelGGL(k_pol_grid_sum_adj, dim3(grid_of(n_sum)), dim3(256), 0, st, m, it_sum, n_sum,
+                       st_ws, sgrid3);
 }
 void launch_pol_moments(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
                         const Item *it_tab, int n_tab, const double *gauss, const float4 *terms,
                         const int *st_ws, const float *sgrid, double *pol, double *table,
-                        double *sens, double *pcot, hipStream_t st) {
-  if (sens)
-    hipLaunchKernelGGL(k_pol_moments<true>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
-                       gauss, st_ws, sgrid, pol, sens, pcot);
-  else
-    hipLaunchKernelGGL(k_pol_moments<false>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
-                       gauss, st_ws, sgrid, pol, sens, pcot);
-  hipLaunchKernelGGL(k_pol_table, dim3(grid_of(n_tab)), dim3(256), 0, st, g, m, it_tab, n_tab,
-                     gauss, terms, st_ws, pol, table, sens);
+                        hipStream_t st) {
+  hipLaunchKernelGGL(k_pol_moments<false>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
+                     gauss, st_ws, sgrid, pol, nullptr, nullptr);
+  hipLaunchKernelGGL(k_pol_table<false>, dim3(grid_of(n_tab)), dim3(256), 0, st, g, m, it_tab,
+                     n_tab, gauss, terms, nullptr, st_ws, pol, table, nullptr);
+}
+void launch_pol_moments_adj(const GeomDev *g, const ModelDev *m, const Item *it, int n_it,
+                            const Item *it_tab, int n_tab, const double *gauss,
+                            const double *terms64, const int *st_ws, const double *sgrid3,
+                            double *pol, double *table, double *sens, double *pcot,
+                            hipStream_t st) {
+  hipLaunchKernelGGL(k_pol_moments<true>, dim3(grid_of(n_it)), dim3(256), 0, st, g, m, it, n_it,
+                     gauss, st_ws, sgrid3, pol, sens, pcot);
+  hipLaunchKernelGGL(k_pol_table<true>, dim3(grid_of(n_tab)), dim3(256), 0, st, g, m, it_tab, n_tab,
+                     gauss, nullptr, terms64, st_ws, pol, table, sens);
 }
 void launch_pol_adjoint(const GeomDev *g, const ModelDev *m, const Item *it_spread, int n_spread,
                         const Item *it_sum, int n_sum, const Item *it_sens, int n_sens,
-                        const double *gauss, const float4 *terms, const int *st_ws,
+                        const double *gauss, const double *terms64, const int *st_ws,
                         const double *pol, double *sens, double *pcot, hipStream_t st) {
   hipLaunchKernelGGL(k_pol_spread, dim3(grid_of(n_spread)), dim3(256), 0, st, g, m, it_spread,
                      n_spread, gauss, st_ws, pol, sens, pcot);
   hipLaunchKernelGGL(k_pol_cot_sum, dim3(grid_of(n_sum)), dim3(256), 0, st, g, m, it_sum, n_sum,
                      st_ws, pcot);
   hipLaunchKernelGGL(k_pol_sens, dim3(grid_of(n_sens)), dim3(256), 0, st, g, m, it_sens, n_sens,
-                     terms, st_ws, pol, sens, pcot);
+                     terms64, st_ws, pol, sens, pcot);
 }
 
 }  // namespace jam
