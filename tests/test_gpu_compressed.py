@@ -109,6 +109,30 @@ def test_compact_light_on_a_wide_field():
     _check("compact light", g, p, cot, V, grad)
 
 
+@pytest.mark.parametrize("q,n_u,margin", [(0.03, 160, None), (0.005, 160, None), (0.005, 1024, None),
+                                          (None, 160, 1e-3), (None, 160, 1e-6)])
+def test_thin_mass_seen_edge_on(q, n_u, margin):
+    """Mass Gaussians whose exponents in y exceed those in x by 1 / q^2 (the
+    linear panel's stretches): all of them thin and seen edge-on, or one, as
+    wide as the field, next to the deprojection limit."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=320, n_lum=2, n_mass=13, nx=66, ny=66, n_u=n_u, pixsize=0.08,
+                              psf_n=3, n_bins=5)
+    p = inputs.small_params(g, seed=420)
+    g.lum_q[:] = 0.8
+    if q is not None:
+        g.mass_q[:] = q
+        p = inputs.with_overrides(p, inc=np.pi / 2)
+    else:
+        j = int(np.argmin(g.mass_q))
+        g.mass_sigma[j] = 0.9 * 33 * 0.08
+        p = inputs.with_overrides(p, inc=float(np.arccos(g.mass_q[j] - margin)))
+    cot = np.random.default_rng(7).standard_normal(g.n_bins)
+    V, grad, kernel = _run(g, p, cot, dev)
+    assert kernel == 4
+    _check(f"thin {q} {n_u} {margin}", g, p, cot, V, grad)
+
+
 def test_mixed_batch_and_invalid_model():
     """Compressed, small-map and invalid models in one batch: each as it is
     alone; the invalid one NaN."""
