@@ -669,28 +669,34 @@ std::vector<std::pair<int, int>> axis_tiles(int n, int tau) {
   return out;
 }
 
-// Maps in items of 4 x 4 tiles, 12, 20 or 24 pixels wide and high (fewer kernels
-// than sizes), instead of 32 x 32 blocks.  Of a map of one block, where the items
-// compute the terms in place: one item rounded up to those sizes.  A term costs
-// the block 13.5 ns of matrix-core time, the largest tiling here 9.2 ns, and 28 x
-// 28 (49 tiles) 12.6 ns and more registers than two waves a SIMD have.  The
-// tiles' sums over their sixteen terms' blocks cost an item about as much as two
-// chunks of a wave save.
+// Maps in items of 4 x 4 tiles, 12, 20 or 24 pixels wide and high, instead of 32 x
+// 32 blocks.  Of a map of one block, where the items compute the terms in place:
+// one item rounded up to those sizes (28 x 28, 49 tiles, would cost about the block
+// and take more registers than two waves a SIMD have; 16 takes the 20-wide items:
+// three sizes are nine kernels, a fourth would make it sixteen).  The tiles' sums
+// over their sixteen terms' blocks cost an item about as much as two chunks of a
+// wave save.
 // Of a larger one (terms from their table): the items that cover it cheapest,
 // where they cost less than kSmallGain of its blocks, most of which are padding
 // just past a multiple of 32.  64 models of 10 x 13 x 40 terms, the whole call,
 // blocks / tiles: 33 x 33 67.0 / 57.7 us, 39 x 21 48.2 / 43.0, 44 x 44 68.6 /
 // 68.1, 70 x 70 117.0 / 105.9, and where the rule keeps the blocks 28 x 40 52.0 /
-// 57.7.  Each tiling is one more launch, serial with the others: in a batch of
-// several kinds only one that saves more than kSmallLaunchNs on the whole chip is
-// taken (30 models of mixed sizes: 51.0 us with three, 49.0 with none).
+// 57.7.  Each tiling is one more launch: choose_tilings.
 constexpr int kSmallMinChunks = 2;
 constexpr double kSmallGain = 0.9;
-constexpr double kSmallLaunchNs = 6000.0;
+// ns of one SIMD per term: matrix instructions, exponentials and the loop; terms
+// computed in place on top.  In place, 4096 models of 13000 terms: 12 x 12 pixels
+// 9.9 ns, 20 x 20 16.9, 24 x 24 20.4, the block 26.6.
+constexpr double kTermInPlaceNs = 4.5;
+double block_ns(int BX, int BY) { return 14.5 * BX * BY + 4.1 * BX + 2.9 * BY; }
+constexpr int kSmallSides[3] = {3, 5, 6};
+double tiles_ns(int X, int Y) {
+  const int tx = kSmallSides[X], ty = kSmallSides[Y];
+  return 0.256 * tx * ty + 0.51 * tx + 0.35 * ty + 1.2;
+}
 struct SmallTiles {
   int tiling = -1;              // -1: 32 x 32 blocks
   int nx = 1, ny = 1, w = 0, h = 0;   // items along x and y, their pixels
-  double gain = 0.0;                  // ns of one SIMD over the blocks
 };
 SmallTiles small_tiles(const GeomHost &g, const NumChoice &c) {
   SmallTiles s;
@@ -701,30 +707,43 @@ SmallTiles small_tiles(const GeomHost &g, const NumChoice &c) {
     s.tiling = 3 * size(g.n_ux) + size(g.n_uy);
     return s;
   }
-  // ns per term: matrix instructions, exponentials, and per item the loop
   double best = 0.0;
-  for (const WaveTile &t : c.tiles)
-    best += 14.5 * t.BX * t.BY + 4.1 * t.BX + 2.9 * t.BY;
-  const double blocks = best;
-  best *= kSmallGain;
-  constexpr int n4[3] = {3, 5, 6};
+  for (const WaveTile &t : c.tiles) best += kSmallGain * block_ns(t.BX, t.BY);
   for (int X = 0; X < 3; ++X)
     for (int Y = 0; Y < 3; ++Y) {
-      const int tx = n4[X], ty = n4[Y];
-      const int nx = (g.n_ux + 4 * tx - 1) / (4 * tx), ny = (g.n_uy + 4 * ty - 1) / (4 * ty);
-      const double cost = nx * ny * (0.256 * tx * ty + 0.51 * tx + 0.35 * ty + 1.2);
+      const int w = 4 * kSmallSides[X], h = 4 * kSmallSides[Y];
+      const int nx = (g.n_ux + w - 1) / w, ny = (g.n_uy + h - 1) / h;
+      const double cost = nx * ny * tiles_ns(X, Y);
       if (cost < best) {
         best = cost;
-        s.gain = (blocks - cost) * g.T;
-        s.tiling = 9 + 3 * X + Y;
-        s.nx = nx;
-        s.ny = ny;
-        s.w = 4 * tx;
-        s.h = 4 * ty;
+        s = SmallTiles{9 + 3 * X + Y, nx, ny, w, h};
       }
     }
   return s;
 }
+
+// Time of one launch in ns: its items' sum in ns of one SIMD over the chip, and
+// the longest item, which a block's four waves share and which takes 1.4 times as
+// long on a CU of its own.  256, 512, 1024, 4096 items of 13000 terms on 12 x 12
+// pixels: 55, 87, 151 and 535 us here, 54, 84, 147 and 515 measured.  Launches of
+// one stream run one after the other, so in a batch of many kinds each kind's own
+// kernel is the slower choice until a launch fills the chip several times.
+struct LaunchLoad {
+  double sum = 0.0, longest = 0.0;
+  void add(double items, double item_ns) {
+    sum += items * item_ns;
+    longest = std::max(longest, item_ns);
+  }
+  void add(const LaunchLoad &o) {
+    sum += o.sum;
+    longest = std::max(longest, o.longest);
+  }
+  double ns(int n_cu) const {
+    if (sum == 0.0) return 0.0;
+    const double alone = 1.4 * longest / 4.0;
+    return 7000.0 + std::max(alone, sum / (4.0 * n_cu) + 0.35 * alone);
+  }
+};
 
 NumChoice choose_numerator(const GeomHost &g, const Tune &t, int gran) {
   NumChoice c;
@@ -955,6 +974,127 @@ int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &
   return (gain_f > simds * kChebLatencyNs ? 1 : 0) | (gain_a > 0.0 ? 2 : 0);
 }
 
+// The tilings of a batch's maps, by geometry (n_models of each in the batch; gran
+// as in the plan).  A model may run in any tiling at least as large as its map, with
+// the same sums, or in the 32 x 32 blocks' kernel, which is launched anyway where
+// others need it.  In place: the set of tilings with the least time over all
+// launches.  From the table: then each tiling that lowers it further.
+// Measured, models of 13000 terms on maps of 8 .. 32 pixels a side drawn at random,
+// forward call, a launch for every tiling / this: 16 models 64 / 26 us, 256 705 /
+// 124, 1024 903 / 424.
+std::vector<SmallTiles> choose_tilings(const jam_ctx *ctx, const std::vector<int> &n_models,
+                                       const Tune &tune) {
+  const size_t ng = ctx->gh.size();
+  std::vector<SmallTiles> out(ng);
+  LaunchLoad blocks;                           // what has no choice
+  std::vector<LaunchLoad> place(9 * 10);       // in place: [own tiling][tiling, or 9 the blocks]
+  std::vector<LaunchLoad> table(9), table_blocks(9);
+  bool used[9] = {};
+  for (size_t i = 0; i < ng; ++i) {
+    if (!n_models[i]) continue;
+    const GeomHost &g = ctx->gh[i];
+    const NumChoice c = choose_numerator(g, tune, tune.gran);
+    if (c.kind != 2) continue;
+    const SmallTiles s = out[i] = small_tiles(g, c);
+    const double items = (double)n_models[i] * c.n_slices, terms = (double)g.T / c.n_slices;
+    LaunchLoad b;
+    for (const WaveTile &t : c.tiles)
+      b.add(items, terms * (block_ns(t.BX, t.BY) + (c.gen ? kTermInPlaceNs : 0.0)));
+    if (s.tiling < 0) {
+      blocks.add(b);
+    } else if (s.tiling < 9) {
+      used[s.tiling] = true;
+      for (int t = 0; t < 9; ++t)
+        place[10 * s.tiling + t].add(items, terms * (tiles_ns(t / 3, t % 3) + kTermInPlaceNs));
+      place[10 * s.tiling + 9].add(b);
+    } else {
+      table[s.tiling - 9].add(items * s.nx * s.ny, terms * tiles_ns((s.tiling - 9) / 3, s.tiling % 3));
+      table_blocks[s.tiling - 9].add(b);
+    }
+  }
+  // in place: every set of tilings, each kind in the cheapest of the set that holds it
+  int present = 0;
+  for (int t = 0; t < 9; ++t) present |= used[t] << t;
+  double best = 1e300;
+  int to[9];
+  LaunchLoad best_blocks = blocks;
+  for (int set = 0; set < 512; ++set) {
+    if (set & ~present) continue;              // a larger tiling than any kind's own is never cheaper
+    LaunchLoad load[10];
+    load[9] = blocks;
+    int at[9];
+    for (int k = 0; k < 9; ++k) {
+      if (!used[k]) continue;
+      at[k] = 9;
+      for (int t = 0; t < 9; ++t)
+        if ((set >> t & 1) && t / 3 >= k / 3 && t % 3 >= k % 3 &&
+            place[10 * k + t].sum < place[10 * k + at[k]].sum)
+          at[k] = t;
+      load[at[k]].add(place[10 * k + at[k]]);
+    }
+    double ns = 0.0;
+    for (const LaunchLoad &l : load) ns += l.ns(ctx->n_cu);
+    if (ns < best) {
+      best = ns;
+      best_blocks = load[9];
+      std::copy(at, at + 9, to);
+    }
+  }
+  // from the table
+  bool keep[9];
+  for (int t = 0; t < 9; ++t) {
+    LaunchLoad with = best_blocks;
+    for (int o = t + 1; o < 9; ++o) with.add(table_blocks[o]);
+    LaunchLoad merged = with;
+    merged.add(table_blocks[t]);
+    keep[t] = table[t].ns(ctx->n_cu) + with.ns(ctx->n_cu) < merged.ns(ctx->n_cu);
+    if (!keep[t]) best_blocks.add(table_blocks[t]);
+  }
+  for (SmallTiles &s : out) {
+    if (s.tiling >= 9)
+      s.tiling = keep[s.tiling - 9] ? s.tiling : -1;
+    else if (s.tiling >= 0)
+      s.tiling = to[s.tiling] == 9 ? -1 : to[s.tiling];
+  }
+  return out;
+}
+
+// The y quads of the small maps' adjoint kernel that each number of quads runs in
+// (at least as many; the padding adds zeros): the partition of the quads into runs
+// with the least time over the launches.  Per term 21 (12 x 12 pixels) to 64 ns (32
+// x 32) of one SIMD, fitted; with six quads and more two waves a SIMD for three.
+// The batches above, chi^2 and gradient, a launch for every number of quads (and
+// every tiling) / this: 256 models 1416 / 361 us, 1024 2107 / 1236.
+struct AdjKind {
+  double terms = 0.0, longest = 0.0, x_terms = 0.0;   // x_terms: terms times quads of x
+};
+void choose_quads(int n_cu, const AdjKind (&kinds)[jam::kSmallQuads + 1],
+                  int (&to)[jam::kSmallQuads + 1]) {
+  constexpr int Q = jam::kSmallQuads;
+  double best[Q + 1] = {};       // of the quads up to q
+  int first[Q + 1] = {};
+  for (int q = 1; q <= Q; ++q) {
+    best[q] = 1e300;
+    const double f = q > 5 ? 1.15 : 1.0;
+    LaunchLoad l;
+    for (int p = q; p >= 1; --p) {             // one launch of q for p .. q
+      const AdjKind &k = kinds[p];
+      if (k.terms > 0.0) {
+        const double per = f * (12.0 + 0.45 * q + (0.75 + 0.55 * q) * k.x_terms / k.terms);
+        l.sum += k.terms * per;
+        l.longest = std::max(l.longest, k.longest * per);
+      }
+      const double ns = best[p - 1] + l.ns(n_cu);
+      if (ns < best[q]) {
+        best[q] = ns;
+        first[q] = p;
+      }
+    }
+  }
+  for (int q = Q; q >= 1; q = first[q] - 1)
+    for (int p = first[q]; p <= q; ++p) to[p] = q;
+}
+
 // h_limit: a group of compressed models is closed once its H takes this many
 // doubles (a single model's is never split).
 jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tune &tune_in,
@@ -1052,24 +1192,11 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   };
   // spherical forward: the potential grid (form 1: sums at every node)
   const bool use_sgrid = spherical && ctx->opt.form != 1;
-  std::vector<SmallTiles> tiles_of(spherical ? 0 : ctx->gh.size());
+  std::vector<SmallTiles> tiles_of;
   if (!spherical) {
     std::vector<int> models(ctx->gh.size(), 0);
     for (int m = 0; m < n; ++m) ++models[geom_idx[m]];
-    double gain[jam::kSmallTilings] = {};
-    int count[jam::kSmallTilings] = {};
-    for (size_t i = 0; i < models.size(); ++i) {
-      if (!models[i]) continue;
-      const GeomHost &g = ctx->gh[i];
-      SmallTiles &s = tiles_of[i] = small_tiles(g, choose_numerator(g, tune, tune.gran));
-      if (s.tiling < 0) continue;
-      gain[s.tiling] += models[i] * s.gain;
-      count[s.tiling] += models[i];
-    }
-    for (SmallTiles &s : tiles_of)
-      if (s.tiling >= 9 && count[s.tiling] < n &&
-          gain[s.tiling] < 4.0 * ctx->n_cu * kSmallLaunchNs)
-        s.tiling = -1;
+    tiles_of = choose_tilings(ctx, models, tune);
   }
   for (int m = 0; m < n; ++m) {
     const int gi = geom_idx[m];
@@ -1317,6 +1444,18 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   sort_by_cost(it_num, c_num);
   std::stable_sort(it_numsm.begin(), it_numsm.end(),
                    [](const jam::Item &a, const jam::Item &b) { return a.c < b.c; });
+  AdjKind kinds[jam::kSmallQuads + 1];
+  for (const jam::Item &t : it_adj) {
+    const GeomHost &g = ctx->gh[geom_idx[t.m]];
+    AdjKind &k = kinds[t.c];
+    const double terms = (double)((t.b >> 16) - (t.b & 0xffff)) * g.n_u;
+    k.terms += terms;
+    k.x_terms += terms * ((g.n_ux + 3) / 4);
+    k.longest = std::max(k.longest, terms);
+  }
+  int quads_to[jam::kSmallQuads + 1];
+  choose_quads(ctx->n_cu, kinds, quads_to);
+  for (jam::Item &t : it_adj) t.c = quads_to[t.c];
   std::stable_sort(it_adj.begin(), it_adj.end(),
                    [](const jam::Item &a, const jam::Item &b) { return a.c < b.c; });
   for (const jam::Item &t : it_adj) ++p->adj_ptr[t.c];

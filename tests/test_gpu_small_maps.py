@@ -106,6 +106,66 @@ def test_items_of_tiles_in_a_mixed_batch():
     ctx.close()
 
 
+def _mixed(sizes, n_u, dev):
+    """(context, index list, device arguments, models) of a batch of several
+    sizes of small maps, count of them each."""
+    gs, ps = zip(*[_model(nx, ny, n_u) for nx, ny, _ in sizes])
+    idx = np.repeat(np.arange(len(sizes), dtype=np.int32), [c for _, _, c in sizes])
+    w = inputs.Workload("x", list(gs), idx, [ps[i] for i in idx])
+    par = binding.pack_params(w, dev, amplitudes=True)
+    return binding.Context(list(gs)), idx, (idx, par["inc"], par["mass_scale"], par["m_bh"],
+                                            par["beta"], par["lum_I0"], par["mass_S0"]), gs, ps
+
+
+def test_few_maps_run_in_the_larger_ones_kernels():
+    """Sizes with few models share the tilings, blocks and adjoint kernels of
+    larger ones: each against the oracle."""
+    dev = _dev()
+    sizes = ((24, 24, 900), (12, 12, 3), (5, 23, 2), (20, 9, 2), (32, 9, 2), (3, 31, 2))
+    ctx, idx, args, gs, ps = _mixed(sizes, 40, dev)
+    cot = np.random.default_rng(8).standard_normal(3)
+    V, st = ctx.eval_batch(*args)
+    gr = ctx.vjp(*args, V, torch.as_tensor(np.tile(cot, len(idx)), device=dev))
+    torch.cuda.synchronize()
+    assert (st.cpu().numpy() == 0).all()
+    V = V.cpu().numpy().reshape(len(idx), 3)
+    gr = {k: gr[k].cpu().numpy().reshape(len(idx), -1) for k in KEYS}
+    for i, (g, p) in enumerate(zip(gs, ps)):
+        m = int(np.flatnonzero(idx == i)[-1])
+        rV, rg = ojam.vrms2_and_grad(g, p, cot)
+        a, b = _flat({k: gr[k][m] for k in KEYS}), _flat({k: v.numpy() for k, v in rg.items()})
+        assert np.max(np.abs(V[m] / rV.numpy() - 1)) <= 1e-6, sizes[i]
+        assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), sizes[i]
+    ctx.close()
+
+
+def test_mixed_sizes_take_no_longer_than_the_largest():
+    """256 models on rectangles of all small sizes against 256 on the largest:
+    less work, so no more than half as long again (a launch for every tiling one
+    after the other took five times as long)."""
+    dev = _dev()
+    rng = np.random.default_rng(4)
+    mixed = [(int(a), int(b), 2) for a, b in rng.integers(8, 33, (128, 2))]
+    took = []
+    for sizes in (mixed, [(32, 32, 256)]):
+        ctx, _, args, _, _ = _mixed(sizes, 400, dev)
+        for _ in range(3):
+            ctx.eval_batch(*args)
+        best = np.inf
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                ctx.eval_batch(*args)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        took.append(best)
+        ctx.close()
+    print(f"mixed {took[0] * 100:.1f} us, largest {took[1] * 100:.1f} us")
+    assert took[0] <= 1.5 * took[1]
+
+
 @pytest.mark.parametrize("nx,ny,n_u,n", [
     (28, 40, 20, 700),     # one 32 x 64 tile
     (64, 64, 12, 400),     # whole blocks
