@@ -98,7 +98,8 @@ typedef struct {
 } jam_geometry;
 
 /* form: 0 = automatic, 1 = per-pixel VALU quadrature kernels only,
- *       2 = separable matrix-core (MFMA) kernels.
+ *       2 = separable matrix-core (MFMA) kernels that sum the terms directly
+ *       (0 also takes the compressed form, whichever is faster).
  * autotune (form 0 only): 1 = when a batch composition is first prepared,
  *       time the candidate numerator schedules (kernel variant, 64x64-tile
  *       pairing threshold, terms per work item, per-item or persistent launch)

@@ -963,7 +963,7 @@ constexpr double kShareTerms = 512.0;
 // terms 51.6 and 50.3.  The adjoint's launches are the direct one's.
 constexpr double kChebLatencyNs = 17000.0;
 int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
-  if (t.rule != 1 || ctx->opt.alignment == 1) return 0;
+  if (t.rule != 1 || ctx->opt.alignment == 1 || ctx->opt.form == 2) return 0;
   double gain_f = 0.0, gain_a = 0.0;
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
@@ -2236,7 +2236,7 @@ jam_status jam_create(int32_t n_geom, const jam_geometry *geoms, const jam_optio
           try {
             build_geometry(geoms[i], ctx->gh[i]);
             build_spherical(ctx->gh[i]);
-            if (ctx->opt.alignment == 0 && ctx->opt.form != 1) build_cheb(ctx->gh[i]);
+            if (ctx->opt.alignment == 0 && ctx->opt.form == 0) build_cheb(ctx->gh[i]);
           } catch (...) {   // out of host memory: reported below, never past the thread
             failed[t] = i;
             return;

@@ -182,3 +182,24 @@ def test_bins_beyond_a_blocks_table(n_bins):
     a = np.concatenate([np.ravel(gr[k].cpu().numpy()) for k in keys])
     b = np.concatenate([np.ravel(np.asarray(rg[k])) for k in keys])
     assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("form,n_mass,n_u", [(0, 3, 16), (2, 3, 16), (2, 12, 60)])
+def test_direct_adjoint_of_large_maps(form, n_mass, n_u):
+    """Maps of 160 and more distinct rows whose adjoint contracts the terms
+    directly, four tile columns at a time and a part of the last: few terms, and
+    any number with form = 2, which takes no other form."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=61, n_lum=3, n_mass=n_mass, nx=150, ny=170, n_u=n_u, psf_n=3,
+                              pixsize=0.03, n_bins=6, xc=0.011, yc=-0.007)
+    p = inputs.small_params(g, seed=62)
+    ctx = binding.Context([g], form=form)
+    for n in (1, 24):
+        ps = [inputs.with_overrides(p, m_bh=p.m_bh * (1.0 + 1e-3 * (n - 1 - m))) for m in range(n)]
+        w = inputs.Workload("large", [g], np.zeros(n, np.int32), ps)
+        assert ctx.plan_info(w.geom_idx)["num_kernel"] == 1
+        cot = np.random.default_rng(3).standard_normal(g.n_bins)
+        got = _split_grads(_gpu_grads(ctx, w, [cot] * n, dev), w)[-1]
+        _, ref = ojam.vrms2_and_grad(g, p, cot)
+        _check(got, {k: v.numpy() for k, v in ref.items()}, f"form {form}, {n} models")
+    ctx.close()
