@@ -308,19 +308,69 @@ void build_spherical(GeomHost &o) {
   }
 }
 
+std::vector<std::pair<int, int>> axis_tiles(int n, int tau) {
+  const int nb = (n + 31) / 32;
+  std::vector<std::pair<int, int>> out;   // (first block, blocks)
+  for (int b = 0; b < nb;) {
+    const int w = (n >= tau && b + 1 < nb) ? 2 : 1;
+    out.push_back({b, w});
+    b += w;
+  }
+  return out;
+}
+
+// ns of one SIMD per term: matrix instructions, exponentials and the loop; terms
+// computed in place on top.  In place, 4096 models of 13000 terms: 12 x 12 pixels
+// 9.9 ns, 20 x 20 16.9, 24 x 24 20.4, the block 26.6.
+constexpr double kTermInPlaceNs = 4.5;
+double block_ns(int BX, int BY) { return 14.5 * BX * BY + 4.1 * BX + 2.9 * BY; }
+constexpr int kSmallSides[3] = {3, 5, 6};
+double tiles_ns(int X, int Y) {
+  const int tx = kSmallSides[X], ty = kSmallSides[Y];
+  return 0.256 * tx * ty + 0.51 * tx + 0.35 * ty + 1.2;
+}
+constexpr double kSmallGain = 0.9;
+// The cheapest cover of a larger map by 4 x 4 tilings, ns per term of the map, where
+// it costs less than kSmallGain of its blocks (choose_tilings); otherwise its blocks.
+struct MapCover {
+  double ns = 0.0;
+  int X = -1, Y = -1;           // tiling; -1: 32 x 32 blocks
+};
+MapCover cover_of(int n_ux, int n_uy, int tau) {
+  MapCover c;
+  for (const auto &x : axis_tiles(n_ux, tau))
+    for (const auto &y : axis_tiles(n_uy, tau)) c.ns += block_ns(x.second, y.second);
+  double best = kSmallGain * c.ns;
+  for (int X = 0; X < 3; ++X)
+    for (int Y = 0; Y < 3; ++Y) {
+      const int w = 4 * kSmallSides[X], h = 4 * kSmallSides[Y];
+      const double cost = ((n_ux + w - 1) / w) * ((n_uy + h - 1) / h) * tiles_ns(X, Y);
+      if (cost < best) {
+        best = cost;
+        c = MapCover{cost, X, Y};
+      }
+    }
+  return c;
+}
+
 // The compressed form's cost against the direct forms', in ns of one SIMD per
-// tracer, forward and adjoint: the direct forms pay per (term, 32x32 block);
-// the compressed form per term, per panel (set-up, node transforms), per panel
-// and 16 map rows (the node contraction and its exponentials), and per panel
-// and block (FP64 MFMAs, about half of the pairs being reached).
+// tracer.  Direct: per term the map's tiles, in the adjoint its blocks; compressed:
+// per term, per panel (set-up, node transforms), per panel and 16 map rows (the node
+// contraction and its exponentials), and per panel and block (FP64 MFMAs).  Fitted
+// by least squares to the difference of whole calls, forced into one form and the
+// other, of batches of 4 to 600 models that fill the chip: 24 to 129 distinct
+// coordinates an axis, 360 to 5460 terms per tracer.  Compressed / direct there, 360
+// terms 0.34 to 1.1 of the speed, 1300 terms 0.73 to 1.0 on maps of up to 2 x 2
+// blocks and 1.4 to 2 beyond, 5248 terms 1.2 to 4.4.  Near the break-even the direct
+// form is taken (kChebGain): it needs less workspace and shorter lists.
 struct ChebCost { double direct, term, panel, row, tile; };
-// Fitted to forward and adjoint times of 1 to 256 models, 26 to 202 distinct
-// coordinates an axis and 48 to 7808 terms per tracer.
-constexpr ChebCost kChebFwd{24.0, 24.0, 1500.0, 380.0, 370.0};
-constexpr ChebCost kChebAdj{40.0, 45.0, 5200.0, 520.0, 600.0};
-double cheb_direct_ns(const GeomHost &o, const ChebCost &c) {
-  const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32;
-  return c.direct * o.J1 * o.n_u * bx * by;
+constexpr ChebCost kChebFwd{1.075, 15.0, 3600.0, 236.0, 52.0};   // direct: per ns of the tiles
+constexpr ChebCost kChebAdj{30.7, 20.0, 7040.0, 486.0, 0.0};     // per term and block
+constexpr double kChebGain = 0.95;
+double cheb_direct_ns(const GeomHost &o, bool adjoint) {
+  const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32, terms = (double)o.J1 * o.n_u;
+  return terms * (adjoint ? kChebAdj.direct * bx * by
+                          : kChebFwd.direct * cover_of(o.n_ux, o.n_uy, 0).ns);
 }
 double cheb_ns(const GeomHost &o, const ChebCost &c, int panels) {
   const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32;
@@ -367,8 +417,8 @@ void build_cheb(GeomHost &o) {
   int np = 0;
   for (int e = 0; e <= top; ++e)
     if (count[e]) index[e] = np++;
-  o.cheb_fwd = cheb_ns(o, kChebFwd, np) < cheb_direct_ns(o, kChebFwd);
-  o.cheb_adj = cheb_ns(o, kChebAdj, np) < cheb_direct_ns(o, kChebAdj);
+  o.cheb_fwd = cheb_ns(o, kChebFwd, np) < kChebGain * cheb_direct_ns(o, false);
+  o.cheb_adj = cheb_ns(o, kChebAdj, np) < kChebGain * cheb_direct_ns(o, true);
   if (!o.cheb_fwd && !o.cheb_adj) return;
   o.cheb_lo.assign(2 * np, 0.0);
   o.cheb_ptr.assign(np + 1, 0);
@@ -658,17 +708,6 @@ struct NumChoice {
   double tile_units(int i) const { return kind == 0 ? 1.0 : tiles[i].BX * tiles[i].BY; }
 };
 
-std::vector<std::pair<int, int>> axis_tiles(int n, int tau) {
-  const int nb = (n + 31) / 32;
-  std::vector<std::pair<int, int>> out;   // (first block, blocks)
-  for (int b = 0; b < nb;) {
-    const int w = (n >= tau && b + 1 < nb) ? 2 : 1;
-    out.push_back({b, w});
-    b += w;
-  }
-  return out;
-}
-
 // Maps in items of 4 x 4 tiles, 12, 20 or 24 pixels wide and high, instead of 32 x
 // 32 blocks.  Of a map of one block, where the items compute the terms in place:
 // one item rounded up to those sizes (28 x 28, 49 tiles, would cost about the block
@@ -683,22 +722,11 @@ std::vector<std::pair<int, int>> axis_tiles(int n, int tau) {
 // 68.1, 70 x 70 117.0 / 105.9, and where the rule keeps the blocks 28 x 40 52.0 /
 // 57.7.  Each tiling is one more launch: choose_tilings.
 constexpr int kSmallMinChunks = 2;
-constexpr double kSmallGain = 0.9;
-// ns of one SIMD per term: matrix instructions, exponentials and the loop; terms
-// computed in place on top.  In place, 4096 models of 13000 terms: 12 x 12 pixels
-// 9.9 ns, 20 x 20 16.9, 24 x 24 20.4, the block 26.6.
-constexpr double kTermInPlaceNs = 4.5;
-double block_ns(int BX, int BY) { return 14.5 * BX * BY + 4.1 * BX + 2.9 * BY; }
-constexpr int kSmallSides[3] = {3, 5, 6};
-double tiles_ns(int X, int Y) {
-  const int tx = kSmallSides[X], ty = kSmallSides[Y];
-  return 0.256 * tx * ty + 0.51 * tx + 0.35 * ty + 1.2;
-}
 struct SmallTiles {
   int tiling = -1;              // -1: 32 x 32 blocks
   int nx = 1, ny = 1, w = 0, h = 0;   // items along x and y, their pixels
 };
-SmallTiles small_tiles(const GeomHost &g, const NumChoice &c) {
+SmallTiles small_tiles(const GeomHost &g, const NumChoice &c, int tau) {
   SmallTiles s;
   if (c.kind != 2 || c.units < 4 * kSmallMinChunks * c.n_slices) return s;
   if (c.gen) {
@@ -707,18 +735,13 @@ SmallTiles small_tiles(const GeomHost &g, const NumChoice &c) {
     s.tiling = 3 * size(g.n_ux) + size(g.n_uy);
     return s;
   }
-  double best = 0.0;
-  for (const WaveTile &t : c.tiles) best += kSmallGain * block_ns(t.BX, t.BY);
-  for (int X = 0; X < 3; ++X)
-    for (int Y = 0; Y < 3; ++Y) {
-      const int w = 4 * kSmallSides[X], h = 4 * kSmallSides[Y];
-      const int nx = (g.n_ux + w - 1) / w, ny = (g.n_uy + h - 1) / h;
-      const double cost = nx * ny * tiles_ns(X, Y);
-      if (cost < best) {
-        best = cost;
-        s = SmallTiles{9 + 3 * X + Y, nx, ny, w, h};
-      }
-    }
+  const MapCover m = cover_of(g.n_ux, g.n_uy, tau);
+  if (m.X < 0) return s;
+  s.tiling = 9 + 3 * m.X + m.Y;
+  s.w = 4 * kSmallSides[m.X];
+  s.h = 4 * kSmallSides[m.Y];
+  s.nx = (g.n_ux + s.w - 1) / s.w;
+  s.ny = (g.n_uy + s.h - 1) / s.h;
   return s;
 }
 
@@ -959,19 +982,28 @@ constexpr double kShareTerms = 512.0;
 // forward has one launch more than the direct one and, in a single model,
 // fewer workgroups to hide its latency, so its gain on the whole chip has to
 // exceed kChebLatencyNs: one model of 102 x 102 distinct pixels, 16 x 31 x 112
-// terms takes 45.7 us compressed and 49.3 direct, 66 x 66 with 12 x 61 x 128
-// terms 51.6 and 50.3.  The adjoint's launches are the direct one's.
-constexpr double kChebLatencyNs = 17000.0;
-int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
-  if (t.rule != 1 || ctx->opt.alignment == 1 || ctx->opt.form == 2) return 0;
-  double gain_f = 0.0, gain_a = 0.0;
+// terms takes 45.7 us compressed and 49.3 direct (gain 14 us), 66 x 66 with 12 x 61 x
+// 128 terms 51.6 and 50.3 (11).  Its two launches beside a direct one take
+// kChebGroupNs with their tails.  The adjoint's launches are the direct one's.
+constexpr double kChebLatencyNs = 12500.0;
+constexpr double kChebGroupNs = 20000.0;
+double cheb_gain_ns(const jam_ctx *ctx, int n, const int32_t *geom_idx, bool adjoint, bool *all) {
+  double gain = 0.0;
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
-    if (g.cheb_fwd) gain_f += g.K * (cheb_direct_ns(g, kChebFwd) - cheb_ns(g, kChebFwd, g.cheb_np));
-    if (g.cheb_adj) gain_a += g.K * (cheb_direct_ns(g, kChebAdj) - cheb_ns(g, kChebAdj, g.cheb_np));
+    if (adjoint ? g.cheb_adj : g.cheb_fwd)
+      gain += g.K * (cheb_direct_ns(g, adjoint) - cheb_ns(g, adjoint ? kChebAdj : kChebFwd, g.cheb_np));
+    else
+      *all = false;
   }
-  const double simds = 4.0 * ctx->n_cu;
-  return (gain_f > simds * kChebLatencyNs ? 1 : 0) | (gain_a > 0.0 ? 2 : 0);
+  return gain / (4.0 * ctx->n_cu);
+}
+int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
+  if (t.rule != 1 || ctx->opt.alignment == 1 || ctx->opt.form == 2) return 0;
+  bool all = true, unused = true;
+  const double fwd = cheb_gain_ns(ctx, n, geom_idx, false, &all);
+  const double adj = cheb_gain_ns(ctx, n, geom_idx, true, &unused);
+  return (fwd > (all ? kChebLatencyNs : kChebGroupNs) ? 1 : 0) | (adj > 0.0 ? 2 : 0);
 }
 
 // The tilings of a batch's maps, by geometry (n_models of each in the batch; gran
@@ -995,7 +1027,7 @@ std::vector<SmallTiles> choose_tilings(const jam_ctx *ctx, const std::vector<int
     const GeomHost &g = ctx->gh[i];
     const NumChoice c = choose_numerator(g, tune, tune.gran);
     if (c.kind != 2) continue;
-    const SmallTiles s = out[i] = small_tiles(g, c);
+    const SmallTiles s = out[i] = small_tiles(g, c, tune.tau);
     const double items = (double)n_models[i] * c.n_slices, terms = (double)g.T / c.n_slices;
     LaunchLoad b;
     for (const WaveTile &t : c.tiles)

@@ -116,8 +116,8 @@ def test_thin_mass_seen_edge_on(q, n_u, margin):
     linear panel's stretches): all of them thin and seen edge-on, or one, as
     wide as the field, next to the deprojection limit."""
     dev = _dev()
-    g = inputs.small_geometry(seed=320, n_lum=2, n_mass=13, nx=66, ny=66, n_u=n_u, pixsize=0.08,
-                              psf_n=3, n_bins=5)
+    g = inputs.small_geometry(seed=320, n_lum=2, n_mass=13, nx=100, ny=100, n_u=n_u,
+                              pixsize=0.054, psf_n=3, n_bins=5)
     p = inputs.small_params(g, seed=420)
     g.lum_q[:] = 0.8
     if q is not None:
@@ -125,7 +125,7 @@ def test_thin_mass_seen_edge_on(q, n_u, margin):
         p = inputs.with_overrides(p, inc=np.pi / 2)
     else:
         j = int(np.argmin(g.mass_q))
-        g.mass_sigma[j] = 0.9 * 33 * 0.08
+        g.mass_sigma[j] = 0.9 * 50 * 0.054
         p = inputs.with_overrides(p, inc=float(np.arccos(g.mass_q[j] - margin)))
     cot = np.random.default_rng(7).standard_normal(g.n_bins)
     V, grad, kernel = _run(g, p, cot, dev)
@@ -192,3 +192,35 @@ def test_noalloc_takes_what_the_direct_forms_fit():
     torch.cuda.synchronize()
     assert torch.equal(V, V2) and torch.equal(st, st2)
     ctx.close()
+
+
+def _call_us(g, n, form, dev):
+    ps = [inputs.small_params(g, seed=600 + m) for m in range(n)]
+    w = inputs.Workload("timed", [g], np.zeros(n, np.int32), ps)
+    ctx = binding.Context([g], form=form)
+    t = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, t["inc"], t["mass_scale"], t["m_bh"], t["beta"], t["lum_I0"], t["mass_S0"])
+    best = np.inf
+    for _ in range(6):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            ctx.eval_batch(*args)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, 100.0 * a.elapsed_time(b))
+    ctx.close()
+    return best
+
+
+@pytest.mark.parametrize("nx,n", [(84, 232)])
+def test_automatic_form_is_not_the_slower_one(nx, n):
+    """Maps of two blocks a side with 1300 terms per tracer, near the break-even
+    of the compressed form: the automatic choice within a fifth of the direct
+    forms (the compressed one took half as long again)."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=330, n_lum=10, n_mass=12, nx=nx, ny=nx, n_u=100, pixsize=0.05,
+                              psf_n=9, n_bins=20)
+    auto, direct = _call_us(g, n, 0, dev), _call_us(g, n, 2, dev)
+    print(f"{nx} x {nx}, {n} models: automatic {auto:.0f} us, direct {direct:.0f} us")
+    assert auto <= 1.2 * direct
