@@ -797,6 +797,16 @@ NumChoice choose_numerator(const GeomHost &g, const Tune &t, int gran) {
   return c;
 }
 
+// Doubles of a model's split-term partial maps, padded to whole blocks.
+int64_t part_doubles(const GeomHost &g, const NumChoice &c) {
+  return (int64_t)c.n_slices * (32 * ((g.n_ux + 31) / 32)) * (32 * ((g.n_uy + 31) / 32));
+}
+// A single slice of a matrix-core form goes straight into the N map.  (A map of one
+// block keeps its 8 KB.)
+int64_t part_size(const GeomHost &g, const NumChoice &c) {
+  return c.kind == 2 && c.n_slices == 1 && !c.gen ? 0 : part_doubles(g, c);
+}
+
 // Relative cost of one numerator item, for largest-first ordering and the
 // schedule model: the kernels' chunk loop plus a fixed per-item cost (the
 // partial-tile store and its reduction).  `tile` indexes c's tiles.
@@ -849,6 +859,20 @@ int num_slots(const jam_ctx *ctx, const Tune &) { return std::max(1, ctx->n_cu);
 // under the list-scheduling model.  Candidates are geometric around a few
 // jobs per worker, plus the exact splits of the largest model, so a uniform
 // item list can fill whole rounds of workers.
+// Modelled time of the numerator launch with slices of `gran`; 1e300 for more items
+// than most_items.
+double gran_makespan(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t, int gran,
+                     size_t most_items) {
+  std::vector<double> cost;
+  for (int m = 0; m < n; ++m) {
+    const GeomHost &g = ctx->gh[geom_idx[m]];
+    const NumChoice c = choose_numerator(g, t, gran);
+    for (int sl = 0; sl < c.n_slices; ++sl)
+      for (int tl = 0; tl < c.n_tiles(); ++tl) cost.push_back(num_item_cost(g, c, sl, tl));
+  }
+  return cost.size() > most_items ? 1e300 : list_schedule_makespan(cost, num_slots(ctx, t));
+}
+
 int default_gran(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
   const int slots = num_slots(ctx, t);
   double work = 0.0, big_work = -1.0;
@@ -878,17 +902,9 @@ int default_gran(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune 
   cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
   double best = 1e300;
   int best_g = (int)g0;
-  std::vector<double> cost;
   for (int gr : cands) {
-    cost.clear();
-    for (int m = 0; m < n; ++m) {
-      const GeomHost &g = ctx->gh[geom_idx[m]];
-      const NumChoice c = choose_numerator(g, t, gr);
-      for (int sl = 0; sl < c.n_slices; ++sl)
-        for (int tl = 0; tl < c.n_tiles(); ++tl) cost.push_back(num_item_cost(g, c, sl, tl));
-    }
-    if (cost.size() > (size_t)(64 * per_slot) * slots + (size_t)4 * n) continue;   // too fine
-    const double mk = list_schedule_makespan(cost, slots);
+    const double mk = gran_makespan(ctx, n, geom_idx, t, gr, (size_t)(64 * per_slot) * slots + (size_t)4 * n);
+    if (mk >= 1e300) continue;   // too fine
     if (mk < best * (1.0 - 1e-9) || (mk <= best * (1.0 + 1e-9) && gr > best_g)) {
       best = mk;
       best_g = gr;
@@ -984,9 +1000,12 @@ constexpr double kShareTerms = 512.0;
 // exceed kChebLatencyNs: one model of 102 x 102 distinct pixels, 16 x 31 x 112
 // terms takes 45.7 us compressed and 49.3 direct (gain 14 us), 66 x 66 with 12 x 61 x
 // 128 terms 51.6 and 50.3 (11).  Its two launches beside a direct one take
-// kChebGroupNs with their tails.  The adjoint's launches are the direct one's.
+// kChebBesideNs with their tails, another pair for another group of models
+// kChebGroupNs (160 models of 68 x 68, 10 x 13 x 100 terms: one group 276 us, eight
+// 531).  The adjoint's launches are the direct one's.
 constexpr double kChebLatencyNs = 12500.0;
-constexpr double kChebGroupNs = 20000.0;
+constexpr double kChebBesideNs = 20000.0;
+constexpr double kChebGroupNs = 36000.0;
 double cheb_gain_ns(const jam_ctx *ctx, int n, const int32_t *geom_idx, bool adjoint, bool *all) {
   double gain = 0.0;
   for (int m = 0; m < n; ++m) {
@@ -1003,7 +1022,7 @@ int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &
   bool all = true, unused = true;
   const double fwd = cheb_gain_ns(ctx, n, geom_idx, false, &all);
   const double adj = cheb_gain_ns(ctx, n, geom_idx, true, &unused);
-  return (fwd > (all ? kChebLatencyNs : kChebGroupNs) ? 1 : 0) | (adj > 0.0 ? 2 : 0);
+  return (fwd > (all ? kChebLatencyNs : kChebBesideNs) ? 1 : 0) | (adj > 0.0 ? 2 : 0);
 }
 
 // The tilings of a batch's maps, by geometry (n_models of each in the batch; gran
@@ -1299,8 +1318,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
     if (spherical) terms64 += (int64_t)tsph * jam::kSphTermDoubles;
     terms += spherical ? tsph + tsph / 4 : (small || (cheb && cadj) ? 0 : jam::padded_terms(g.T));
     pixd += 4 * (int64_t)g.n_pix;
-    // padded to whole blocks
-    part += (int64_t)d.n_slices * (32 * d.n_xt) * (32 * d.n_yt);
+    part += part_size(g, nc);
     const int np = g.cheb_np;
     if (cheb || cadj)
       for (int k = 0; k < g.K; ++k)
@@ -1915,14 +1933,52 @@ jam_status autotune(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Tune &best
   return JAM_OK;
 }
 
-// All maps of seven 32-blocks an axis, few enough for the fixed scratch.
-bool large_maps(const jam_ctx *ctx, int n, const int32_t *geom_idx) {
-  if (n > 40) return false;
+// Forward workspace of a cylindrical batch in the direct forms, as build_plan lays
+// it out (all_parts: with the partial maps of single slices too); `fixed` the regions
+// that no schedule changes.
+size_t direct_ws(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t, bool all_parts,
+                 size_t *fixed) {
+  int64_t gauss = 0, terms = 0, pix = 0, part = 0, bins = 0, total_bins = 0;
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
-    if ((g.n_ux + 31) / 32 != 7 || (g.n_uy + 31) / 32 != 7) return false;
+    const NumChoice c = choose_numerator(g, t, t.gran);
+    gauss += jam::gauss_size(g.K, g.J1);
+    terms += c.gen ? 0 : jam::padded_terms(g.T);
+    pix += 4 * (int64_t)g.n_pix;
+    part += all_parts ? part_doubles(g, c) : part_size(g, c);
+    bins += 2 * (int64_t)g.n_bins;
+    total_bins += g.n_bins;
   }
-  return ctx->opt.alignment != 1;
+  size_t w = align256(sizeof(int) * n);
+  w = align256(w + sizeof(int) * 2);
+  w = align256(w + sizeof(double) * gauss);
+  w = align256(w + sizeof(float4) * terms);
+  w = align256(w + sizeof(double) * pix);
+  w = align256(w + sizeof(double) * bins);
+  w = align256(w + sizeof(double) * total_bins);
+  *fixed = w;
+  return align256(w + sizeof(double) * part);
+}
+
+// Lengthens a direct schedule's slices (t.gran given) until the partial maps fit the
+// fixed scratch.  False if they never do, or if that costs the launch more than
+// kLongerSlices of its modelled time (130 models of 50 x 50, 20 x 10 x 113 terms: 326
+// us, 489 with the slices that would fit).
+constexpr double kLongerSlices = 1.1;
+bool lengthen_slices(const jam_ctx *ctx, int n, const int32_t *geom_idx, Tune &t) {
+  size_t fixed = 0;
+  for (int gran = t.gran; gran < (1 << 24); gran += 1 + gran / 8) {
+    Tune longer = t;
+    longer.gran = gran;
+    if (direct_ws(ctx, n, geom_idx, longer, false, &fixed) <= kScratchBytes) {
+      const double time = gran_makespan(ctx, n, geom_idx, t, gran, SIZE_MAX);
+      if (time > kLongerSlices * gran_makespan(ctx, n, geom_idx, t, t.gran, SIZE_MAX)) return false;
+      t = longer;
+      return true;
+    }
+    if (fixed > kScratchBytes) return false;
+  }
+  return false;
 }
 
 jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan *&out) {
@@ -1962,36 +2018,40 @@ jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan 
   std::unique_ptr<Plan> p;
   jam_status s = build_plan(ctx, n, geom_idx, t, p);
   if (s != JAM_OK) return s;
-  if (p->n_cheb && p->ws_fwd > kScratchBytes) {
-    // A batch whose direct forms fit the allocation-free entry point's
-    // scratch has to fit it in the compressed form too: with its models in
-    // groups that share the H region if that suffices, else direct.
-    Tune td = t;
-    td.cheb = p->tune.cheb & ~1;
-    std::unique_ptr<Plan> direct;
-    if ((s = build_plan(ctx, n, geom_idx, td, direct)) != JAM_OK) return s;
-    if (direct->ws_fwd <= kScratchBytes) {
-      // closing a group at h_limit leaves it at most one model over
-      const size_t rest = p->off_cheb + 4096;   // the regions before H
-      int64_t big = 0;
-      for (int m = 0; m < n; ++m)
-        if (ctx->gh[geom_idx[m]].cheb_fwd)
-          big = std::max(big, (int64_t)ctx->gh[geom_idx[m]].cheb_h.back() * 512);
-      const int64_t room = rest < kScratchBytes ? (int64_t)((kScratchBytes - rest) / 8) : 0;
-      if (room >= big && (s = build_plan(ctx, n, geom_idx, t, p, room - big)) != JAM_OK) return s;
-      if (p->ws_fwd > kScratchBytes) p = std::move(direct);
+  // The allocation-free entry point's scratch.  A direct batch takes it with slices as
+  // long as its partial maps need.  A compressed one that the direct forms fit goes in
+  // groups of models that share the H region, two or as many as still pay, and
+  // otherwise in those.
+  if (p->ws_fwd > kScratchBytes && p->tune.rule == 1 && !p->spherical) {
+    if (p->n_cheb == 0) {
+      Tune td = p->tune;
+      if (lengthen_slices(ctx, n, geom_idx, td) && (s = build_plan(ctx, n, geom_idx, td, p)) != JAM_OK)
+        return s;
+    } else {
+      Tune td = t;
+      td.cheb = p->tune.cheb & ~1;
+      if (td.gran <= 0) td.gran = default_gran(ctx, n, geom_idx, td);
+      size_t fixed = 0;
+      if (direct_ws(ctx, n, geom_idx, td, true, &fixed) <= kScratchBytes) {
+        // closing a group at h_limit leaves it at most one model over
+        const size_t rest = p->off_cheb + 4096;   // the regions before H
+        int64_t big = 0, all_h = 0;
+        for (int m = 0; m < n; ++m)
+          if (ctx->gh[geom_idx[m]].cheb_fwd) {
+            const int64_t h = (int64_t)ctx->gh[geom_idx[m]].cheb_h.back() * 512;
+            big = std::max(big, h);
+            all_h += h;
+          }
+        const int64_t room = rest < kScratchBytes ? (int64_t)((kScratchBytes - rest) / 8) - big : 0;
+        const int64_t more = room > 0 ? (all_h - 1) / room : INT32_MAX;   // groups but the first
+        bool all = true;
+        if (more > 1 && cheb_gain_ns(ctx, n, geom_idx, false, &all) < kChebGroupNs * more)
+          s = build_plan(ctx, n, geom_idx, td, p);
+        else
+          s = build_plan(ctx, n, geom_idx, t, p, room);
+        if (s != JAM_OK) return s;
+      }
     }
-  }
-  // the same for large maps' tiles, whose partial maps shrink with longer slices
-  for (int gran = p->tune.gran; !p->n_cheb && t.rule == 1 && p->ws_fwd > kScratchBytes &&
-                                gran < (1 << 20) && large_maps(ctx, n, geom_idx);) {
-    Tune tl = p->tune;
-    tl.gran = gran *= 2;
-    std::unique_ptr<Plan> longer;
-    if ((s = build_plan(ctx, n, geom_idx, tl, longer)) != JAM_OK) return s;
-    const bool less = longer->ws_fwd < p->ws_fwd;
-    if (longer->ws_fwd <= kScratchBytes) p = std::move(longer);
-    if (!less) break;
   }
   out = p.get();
   ctx->plans.push_front(std::move(p));

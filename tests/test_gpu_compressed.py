@@ -213,14 +213,16 @@ def _call_us(g, n, form, dev):
     return best
 
 
-@pytest.mark.parametrize("nx,n", [(84, 232)])
+@pytest.mark.parametrize("nx,n", [(84, 232), (130, 70), (130, 150)])
 def test_automatic_form_is_not_the_slower_one(nx, n):
-    """Maps of two blocks a side with 1300 terms per tracer, near the break-even
-    of the compressed form: the automatic choice within a fifth of the direct
-    forms (the compressed one took half as long again)."""
+    """Maps of two and three blocks a side with 1300 terms per tracer, near the
+    break-even of the compressed form: the automatic choice within a tenth of the
+    direct forms (the compressed one took a third longer), also where its workspace
+    exceeds the allocation-free scratch and the direct forms' does not (in many
+    groups of models it took a fifth longer)."""
     dev = _dev()
     g = inputs.small_geometry(seed=330, n_lum=10, n_mass=12, nx=nx, ny=nx, n_u=100, pixsize=0.05,
                               psf_n=9, n_bins=20)
     auto, direct = _call_us(g, n, 0, dev), _call_us(g, n, 2, dev)
     print(f"{nx} x {nx}, {n} models: automatic {auto:.0f} us, direct {direct:.0f} us")
-    assert auto <= 1.2 * direct
+    assert auto <= 1.1 * direct

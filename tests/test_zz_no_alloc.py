@@ -91,3 +91,20 @@ def test_noalloc_refuses_unprepared_and_oversized():
                                        pb["m_bh"], pb["beta"], None, None, Vb, None, s)
     assert e.value.status == JAM_E_WORKSPACE
     ctx.close()
+
+
+def test_noalloc_takes_longer_slices_and_no_partial_map():
+    """Compositions whose partial maps alone exceed the scratch: a few models'
+    slices are taken longer, on any map size, and many models' single slices have
+    no partial map."""
+    dev = _dev()
+    s = torch.cuda.current_stream(dev).cuda_stream
+    for n, kw in ((130, dict(n_lum=8, n_mass=3, nx=200, ny=200, n_u=83)),
+                  (41, dict(n_lum=1, n_mass=0, nx=205, ny=205, n_u=48, xc=0.011, yc=-0.007)),
+                  (36, dict(n_lum=4, n_mass=0, nx=222, ny=222, n_u=15, xc=0.011, yc=-0.007))):
+        g = inputs.small_geometry(seed=73, psf_n=3, n_bins=4, pixsize=0.03, **kw)
+        ps = [inputs.small_params(g, seed=700 + m) for m in range(n)]
+        w = inputs.Workload("slices", [g], np.zeros(n, np.int32), ps)
+        ctx = binding.Context([g])
+        _compare(ctx, w, dev, s)
+        ctx.close()
