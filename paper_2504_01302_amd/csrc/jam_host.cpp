@@ -1853,12 +1853,14 @@ void save_tune_file(const jam_ctx *ctx) {
 jam_status autotune(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Tune &best) {
   std::vector<Tune> cands;
   Tune base;
+  base.cheb = choose_cheb(ctx, n, geom_idx, base);   // its models have no slices
   const int g0 = default_gran(ctx, n, geom_idx, base);
   for (int launch = 0; launch < 2; ++launch)
     for (int tau : {0, 1 << 30})
       for (double mul : {0.5, 0.75, 1.0, 1.5, 2.0}) {
         Tune t;
         t.rule = 1;
+        t.cheb = base.cheb;
         t.tau = tau;
         t.gran = std::max(1, (int)std::lround(g0 * mul));
         t.launch = launch;

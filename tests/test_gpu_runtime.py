@@ -186,3 +186,19 @@ def test_autotuner_and_cache_file(tmp_path):
     assert os.path.getmtime(cache) == mtime
     a.close()
     b.close()
+
+
+def test_autotuner_starts_from_the_default_slices():
+    """The candidates' slices are half to twice the default schedule's, also where
+    the maps would suit the compressed form and the batch is too small for it."""
+    _dev()
+    g = inputs.small_geometry(seed=81, n_lum=12, n_mass=60, nx=132, ny=132, n_u=128, psf_n=1,
+                              pixsize=0.03, n_bins=6)
+    idx = np.zeros(1, np.int32)
+    plain, tuned = binding.Context([g]), binding.Context([g], form=0, autotune=1)
+    want, got = plain.plan_info(idx), tuned.plan_info(idx)
+    assert want["num_kernel"] == 1
+    if got["rule"] == 1:
+        assert got["gran"] in [int(want["gran"] * m + 0.5) for m in (0.5, 0.75, 1, 1.5, 2)]
+    plain.close()
+    tuned.close()
