@@ -1822,10 +1822,13 @@ std::string tune_key(const jam_ctx *ctx, int n, const int32_t *geom_idx) {
   };
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
-    mix((uint64_t)g.n_ux | ((uint64_t)g.n_uy << 20) | ((uint64_t)g.T << 40));
+    mix((uint64_t)g.n_ux | ((uint64_t)g.n_uy << 20) | ((uint64_t)g.n_u << 40));
+    // the forms a map takes depend on these and not on their product alone
+    mix((uint64_t)g.K | ((uint64_t)g.J1 << 32));
+    mix((uint64_t)g.cheb_np);
   }
   char buf[128];
-  snprintf(buf, sizeof buf, "gfx950/v2/n%d/%016llx", n, (unsigned long long)h);
+  snprintf(buf, sizeof buf, "gfx950/v3/n%d/%016llx", n, (unsigned long long)h);
   return buf;
 }
 
@@ -1932,6 +1935,7 @@ jam_status autotune(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Tune &best
   cleanup();
   if (e != hipSuccess) return fail(JAM_E_DEVICE, "autotune: %s", hipGetErrorString(e));
   best = plans[best_i]->tune;
+  best.cheb = -1;   // derived from the batch, not tuned
   return JAM_OK;
 }
 

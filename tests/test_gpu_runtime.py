@@ -202,3 +202,17 @@ def test_autotuner_starts_from_the_default_slices():
         assert got["gran"] in [int(want["gran"] * m + 0.5) for m in (0.5, 0.75, 1, 1.5, 2)]
     plain.close()
     tuned.close()
+
+
+def test_autotuner_keeps_an_entry_per_expansion(tmp_path):
+    """Two compositions with the same maps, nodes and term counts, but other
+    expansions, have entries of their own."""
+    _dev()
+    cache = str(tmp_path / "tune.txt")
+    for n_lum, n_mass in ((12, 60), (6, 121)):      # 12 x 61 = 6 x 122 pairs
+        g = inputs.small_geometry(seed=81, n_lum=n_lum, n_mass=n_mass, nx=40, ny=40, n_u=16,
+                                  psf_n=1, pixsize=0.03, n_bins=6)
+        ctx = binding.Context([g], form=0, autotune=1, tune_cache=cache)
+        ctx.plan_info(np.zeros(1, np.int32))
+        ctx.close()
+    assert len({line.split()[0] for line in open(cache)}) == 2
