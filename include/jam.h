@@ -122,7 +122,8 @@ typedef struct {
  *       tracer-independent potential sums G, G_theta at the characteristic
  *       nodes from a per-model polar grid (384 radii x 64 angles, the (j, u)
  *       terms summed at every point, 6 x 8-point Lagrange interpolation, within
- *       1e-7 of G at axial ratios of 0.05 and more); with form = 1 it sums the
+ *       1e-7 of G at axial ratios of 0.05 and more; 1e-8 in cos i inside the
+ *       deprojection limit V stays within 2e-6 and the gradient within 1e-5); with form = 1 it sums the
  *       terms at every node instead.  The adjoint differentiates the same grid
  *       model (with form = 1, the direct sums); when jam_vjp recomputes V it
  *       takes it from the forward path (bitwise equal to jam_eval's V).  The

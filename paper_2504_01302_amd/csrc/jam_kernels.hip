@@ -2341,8 +2341,10 @@ __global__ void __launch_bounds__(256) k_sph_terms(const GeomDev *__restrict__ g
     const bool grid = md.sgrid_slices > 0;
     if (grid && it.a == 0 && threadIdx.x < 64) {
       const double *tab = gauss + md.gauss_off, *e2 = tab + 4 * g.K + g.J1;
-      double s0 = 1.0, sk2 = 0.0;            // min q_j^2, max sigma_k^2
-      for (int j = threadIdx.x; j < g.J1; j += 64) s0 = fmin(s0, 1.0 - e2[j]);
+      // smallest h = 1 - e_j^2 u^2 over the nodes, max sigma_k^2
+      double s0 = 1.0, sk2 = 0.0;
+      const double um = g.u[g.n_u - 1];
+      for (int j = threadIdx.x; j < g.J1; j += 64) s0 = fmin(s0, fma(-e2[j], um * um, 1.0));
       for (int k = threadIdx.x; k < g.K; k += 64) sk2 = fmax(sk2, 0.5 / tab[k]);
       for (int o = 32; o > 0; o >>= 1) {
         s0 = fmin(s0, __shfl_xor(s0, o, 64));

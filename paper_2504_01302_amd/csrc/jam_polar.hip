@@ -13,15 +13,22 @@
 //
 // Rows: x = 2 + (ln r' - ln r_0) iX, r_0 the table's first radius, r_max =
 // sqrt(r_hi^2 + 50 max sigma_k^2), the farthest node, at x = kPolN - 4.
-// Columns: y = iC log(1 + cos^2 theta' / s0) with s0 the smallest q_j^2 of
-// the mass Gaussians, y = kPolC - 8 on the axis; column slot s holds y = s - 3.
+// Columns: y = iC log(1 + cos^2 theta' / s0) with s0 the smallest h = 1 - e_j^2 u^2
+// of the terms, y = kPolC - 8 on the axis; column slot s holds y = s - 3.
 // Both variables are analytic with unit scale whatever the model: a term is
-// exp(-v r'^2 - d r'^2 cos^2 theta') with d <= v (1 / s0 - 1), bounded for
-// |Im ln r'| < pi / 4 and |Im y / iC| < pi / 2 (slots 0 .. 2 take cos^2 theta'
-// down to -s0, where the term is still below one).  Lagrange interpolation on
+// exp(-v r'^2 - d r'^2 cos^2 theta') with d = v (1 / h - 1) <= v (1 / s0 - 1),
+// bounded for |Im ln r'| < pi / 4 and |Im y / iC| < pi / 2 (slots 0 .. 2 take cos^2
+// theta' down to -s0, where the term is still below one).  Lagrange interpolation on
 // 6 x 8 points of the 384 x 64 grid leaves at most 1e-7 of G at q_j >= 0.05
 // (FP64 sums, five mass models, 6000 points each) where 4 x 4 points of a 512
-// x 512 grid in R and z left 1e-6 to 1e-5.
+// x 512 grid in R and z left 1e-6 to 1e-5; and of G_theta at q_j = 0.05 up to 3e-4 of
+// its largest value at the same radius, where that radius is far outside the thin
+// Gaussian and a few terms make it up.  s0 has to be that of the terms: the smallest
+// q_j^2 goes to zero at the deprojection limit and stretches the columns with it,
+// while u < 1 keeps h from it.  Against 64 bits, models of 3 + 12 tracers 1e-4, 1e-6
+// and 1e-8 in cos i inside the limit, V / gradient at most: s0 = min q_j^2 8e-7 / 9e-6,
+// 4e-5 / 2e-4, 3e-4 / 9e-4, this 5e-7 / 6e-6, 2e-6 / 4e-6, 2e-6 / 4e-6, the R, z grid
+// 1e-6 / 2e-6, 3e-6 / 4e-5, 5e-6 / 1e-4.
 #include "jam_device.h"
 #include "jam_internal.h"
 #include "jam_sph_math.h"

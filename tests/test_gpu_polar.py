@@ -124,3 +124,53 @@ def test_gradient_does_not_depend_on_the_tracers_order(n_lum):
     for k in KEYS:
         a, b = out[0][k], out[1][k]
         assert np.linalg.norm(a - b) <= 1e-9 * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("margin", [1e-4, 1e-6, 1e-8, 1e-12])
+def test_near_the_deprojection_limit(margin):
+    """The flattest mass Gaussian's q^2 down to 1e-12: the grid's columns have to
+    follow the terms' 1 / h, which u < 1 bounds.  Against the direct sums, at the
+    bars against the oracle (1e-5 per bin, 1e-4 of the gradient's norm)."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=3, n_lum=3, n_mass=4, nx=15, ny=15, n_bins=5, n_u=100,
+                              pixsize=0.06)
+    p = inputs.small_params(g, seed=12)
+    q = float(np.concatenate([g.lum_q, g.mass_q]).min())
+    p = inputs.with_overrides(p, inc=float(np.arccos(q - margin)))
+    w = inputs.Workload("l", [g], np.zeros(1, np.int32), [p])
+    out = []
+    for form in (0, 1):
+        ctx = binding.Context([g], alignment=1, form=form)
+        pk = binding.pack_params(w, dev, amplitudes=True)
+        args = (w.geom_idx, pk["inc"], pk["mass_scale"], pk["m_bh"], pk["beta"], pk["lum_I0"],
+                pk["mass_S0"])
+        V, st = ctx.eval_batch(*args)
+        assert int(st[0]) == 0
+        gr = ctx.vjp(*args, V, torch.ones_like(V))
+        out.append((V.cpu().numpy(), np.concatenate([gr[k].cpu().numpy() for k in KEYS])))
+        ctx.close()
+    (Va, ga), (Vb, gb) = out
+    err, gerr = np.max(np.abs(Va / Vb - 1)), np.linalg.norm(ga - gb) / np.linalg.norm(gb)
+    print(f"{margin:.0e} inside: forward {err:.2e}, gradient {gerr:.2e}")
+    assert err <= 1e-5 and gerr <= 1e-4
+
+
+def test_flattening_that_rounds_to_zero():
+    """q^2 = q'^2 - cos^2 i above zero, but 1 - e^2 = 0 in FP64: a valid model, whose
+    grid must not lose its columns."""
+    dev = _dev()
+    g, w = _workload(2, 3, 64, "plain", seed=5)
+    g.mass_q[0] = 0.01
+    inc = float(np.arccos(0.01))
+    seen = 0
+    for _ in range(40):                       # a few ulp around the limit
+        p = inputs.with_overrides(w.params[0], inc=inc)
+        one = inputs.Workload("z", [g], np.zeros(1, np.int32), [p])
+        ctx = binding.Context([g], alignment=1)
+        V, st = _eval(ctx, one, dev)
+        if int(st[0]) == 0:
+            assert np.all(np.isfinite(V)), inc
+            seen += 1
+        ctx.close()
+        inc = np.nextafter(inc, np.pi)
+    assert seen > 10
