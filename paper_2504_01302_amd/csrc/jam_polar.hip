@@ -88,6 +88,11 @@ template <int Q> __device__ __forceinline__ void rotate8(double (&w)[8], int d) 
 // radius) adds exact zeros everywhere and is left out: narrow tracers at large
 // radii, a fifth of the pairs of 48 models of 10 tracers.  Measured there with
 // them / without: moments 800 + 1230 / 684 + 1179 us, spread 1520 / 1240.
+// The radius always as pol_radius2: what the moments leave out the spread must not
+// read.
+__device__ __forceinline__ double pol_radius2(const GeomDev &g, int ir) {
+  return exp(2.0 * fma((double)ir, g.sph_dlnr, g.sph_lnr0));
+}
 __device__ __forceinline__ bool pol_empty(double alpha, double alphaq, double r2) {
   return fmin(alpha, alphaq) * r2 > 750.0;
 }
@@ -346,7 +351,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
     const double *tab = gauss + md.gauss_off;
     const PolScale sc = pol_scale(pol, md);
     const double rs0 = 1.0 / sc.s0, iC = sc.iC;
-    const double lnr = g.sph_lnr0 + ir * g.sph_dlnr, r = exp(lnr);
+    const double lnr = g.sph_lnr0 + ir * g.sph_dlnr, r = exp(lnr), r2 = pol_radius2(g, ir);
     const double glx = g.gl8_x[nd], glw = g.gl8_w[nd];
     const PolGrid<kJac> *sg = sgrid + (kJac ? md.sgrid3_off : md.sgrid_off);
     double Ar[3], At[3], Ap[3];             // lanes nd == 0: cells 8 t + tl
@@ -359,7 +364,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))
       if constexpr (kJac)
         jac = sph_adj_layout(sens + md.sens_off, K, g.n_pix, sph_terms_padded(g.J1, g.n_u),
                              md.n_sens_parts).jac + ((int64_t)k * kSphCells + ir * kSphNT) * 8;
-      if (pol_empty(alpha, alphaq, r * r)) {        // uniform per wave
+      if (pol_empty(alpha, alphaq, r2)) {           // uniform per wave
         if constexpr (kJac)
 #pragma unroll
           for (int e = 0; e < 3; ++e) jac[64 * e + lane] = 0.0;
@@ -679,7 +684,7 @@ __global__ void __launch_bounds__(256, 3) k_pol_spread(
       if (ch < chunks) {
         k = k0 + (ch >> 1);
         const int ir = 2 * lane + (ch & 1);
-        const double r2 = exp(2.0 * (g.sph_lnr0 + ir * g.sph_dlnr));
+        const double r2 = pol_radius2(g, ir);
         hs = 0.5 * log1p(50.0 * (0.5 / tab[k]) / r2) / kSphSeg;
         // the pair's nodes lie within [x0, x0 + kSphSeg hs iX]
         const double x0 = fma(ir * g.sph_dlnr, sc.iX, 2.0), x1 = fma(kSphSeg * hs, sc.iX, x0);

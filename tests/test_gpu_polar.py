@@ -174,3 +174,33 @@ def test_flattening_that_rounds_to_zero():
         ctx.close()
         inc = np.nextafter(inc, np.pi)
     assert seen > 10
+
+
+def test_tracers_that_just_underflow():
+    """Tracers whose exponent at one of the table's radii is that from which a
+    (tracer, radius) is left out, to the last bit: the moments and the spread have to
+    agree on which are, or the spread reads nodes that nothing wrote (the workspace
+    is filled with NaN)."""
+    dev = _dev()
+    g = inputs.small_geometry(seed=8, n_lum=60, n_mass=3, nx=9, ny=9, psf_n=1, n_bins=4, n_u=32)
+    g.lum_q[:] = 1.0
+    g.lum_sigma[0] = 2.0
+    x = (np.arange(9) - 4) * g.pixsize
+    rs = np.hypot(x[:, None], x[None, :])
+    lo, hi = 0.5 * rs[rs > 0].min(), 12.0 * 2.0
+    r = np.exp(np.log(lo) + np.arange(128) * (np.log(hi) - np.log(lo)) / 127)
+    # exponent r^2 / 2 sigma^2 = 750, a few ulp to either side
+    g.lum_sigma[1:] = r[20:79] / np.sqrt(1500.0) * (1.0 + 1.1e-16 * (np.arange(59) % 9 - 4))
+    p = inputs.small_params(g, seed=8)
+    w = inputs.Workload("u", [g], np.zeros(1, np.int32), [p])
+    ctx = binding.Context([g], alignment=1)
+    pk = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, pk["inc"], pk["mass_scale"], pk["m_bh"], pk["beta"], pk["lum_I0"],
+            pk["mass_S0"])
+    V, st = ctx.eval_batch(*args)
+    assert int(st[0]) == 0
+    ctx.workspace(w.geom_idx, True, dev).fill_(255)
+    gr = ctx.vjp(*args, V, torch.ones_like(V))
+    for k in KEYS:
+        assert torch.isfinite(gr[k]).all(), k
+    ctx.close()
