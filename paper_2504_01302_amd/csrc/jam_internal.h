@@ -399,8 +399,8 @@ void launch_sph_chain(const GeomDev *g, const ModelDev *m, int n, const Item *it
 // 64 cells the rows' sums (d/dbeta, d/dalphaq, d/dnu0) [K][cells/64][3],
 // line-of-sight
 // partials (d/di at fixed node scale, d/d node scale) per 64-pixel block,
-// per-term sensitivities per point range [n_rng][Tp][6] and of the cell
-// points per 256-cell part [kSphCellParts][Tp][3], per-term chain values
+// per-term sensitivities per point range [n_rng][Tp][4] and of the cell
+// points per 256-cell part [kSphCellParts][Tp][2], per-term chain values
 // (d/de2, d/dKp) [Tp][2], the table
 // cotangent's fixed-point scale [1], the cotangent-free node sums of the
 // characteristic integrals' adjoint per (tracer, cell) [K][cells][8] and
@@ -416,7 +416,7 @@ struct SphAdj {
 };
 __host__ __device__ inline int64_t sph_adj_size(int K, int n_pix, int Tp, int n_rng) {
   return 3LL * kSphCells + 3LL * kSphRowParts * K + 2LL * ((n_pix + 63) / 64) +
-         6LL * n_rng * Tp + (3LL * kSphCellParts + 2) * Tp + 1 + 8LL * kSphCells * K + kSphCells;
+         4LL * n_rng * Tp + (2LL * kSphCellParts + 2) * Tp + 1 + 8LL * kSphCells * K + kSphCells;
 }
 __host__ __device__ inline SphAdj sph_adj_layout(double *base, int K, int n_pix, int Tp,
                                                  int n_rng) {
@@ -425,8 +425,8 @@ __host__ __device__ inline SphAdj sph_adj_layout(double *base, int K, int n_pix,
   a.rows = a.dtab + 3LL * kSphCells;
   a.losp = a.rows + 3LL * kSphRowParts * K;
   a.sparts = a.losp + 2LL * ((n_pix + 63) / 64);
-  a.cparts = a.sparts + 6LL * n_rng * Tp;
-  a.tchain = a.cparts + 3LL * kSphCellParts * Tp;
+  a.cparts = a.sparts + 4LL * n_rng * Tp;
+  a.tchain = a.cparts + 2LL * kSphCellParts * Tp;
   a.dscale = a.tchain + 2LL * Tp;
   a.jac = a.dscale + 1;
   a.gphi = a.jac + 8LL * kSphCells * K;

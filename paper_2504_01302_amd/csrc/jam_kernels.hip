@@ -3269,8 +3269,8 @@ __device__ inline void sph_point_cot(const GeomDev &g, const GeomDev *__restrict
 // Term-major sensitivities.  Item (m, 256-term tile, point range); thread =
 // term.  Each 256-point chunk of the range is regenerated (thread = point):
 // node position and the cotangents phi = dL/dG, psi = dL/dG_theta at the
-// node; then every term sums phi E, psi E and their R'^2, z'^2 moments over
-// the chunk in FP32, folded into FP64.
+// node; then every term sums phi E, psi E and their z'^2 moments over the chunk in
+// FP32, folded into FP64.
 __global__ void __launch_bounds__(256) k_sph_sens(const GeomDev *__restrict__ geoms,
                                                   const ModelDev *__restrict__ models,
                                                   const Item *__restrict__ items, int n_it,
@@ -3279,7 +3279,7 @@ __global__ void __launch_bounds__(256) k_sph_sens(const GeomDev *__restrict__ ge
                                                   const int *__restrict__ st_ws,
                                                   double *__restrict__ sens) {
   __shared__ float4 pa[256];   // (R'^2, z'^2, phi, psi)
-  __shared__ float4 pb[256];   // (phi R'^2, psi R'^2, phi z'^2, psi z'^2)
+  __shared__ float2 pb[256];   // (phi z'^2, psi z'^2)
   __shared__ double sc[2][kSphNT];   // sin, cos of the table's polar angles
   if (threadIdx.x < kSphNT) {
     const double th = threadIdx.x * (0.5 * kPi / (kSphNT - 1));
@@ -3300,52 +3300,48 @@ __global__ void __launch_bounds__(256) k_sph_sens(const GeomDev *__restrict__ ge
     const float4 c = tv ? terms[md.term_off + t] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int64_t len = sph_range_len(K, md.n_sens_parts), P = sph_points(K);
     const int64_t p0 = (int64_t)it.b * len, p1 = min(P, p0 + len);
-    double SP = 0.0, ST = 0.0, SxP = 0.0, SxT = 0.0, SyP = 0.0, SyT = 0.0;
+    double SP = 0.0, ST = 0.0, SyP = 0.0, SyT = 0.0;
     for (int64_t c0 = p0; c0 < p1; c0 += 256) {
       // regenerate this chunk's points
       const int64_t p = c0 + threadIdx.x;
-      float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
+      float4 va = make_float4(0.f, 0.f, 0.f, 0.f);
+      float2 vb = make_float2(0.f, 0.f);
       if (p < p1) {
         double Rp, zp, phi, psi;
         sph_point_cot(g, geoms + md.geom, tab, adj, sc[0], p, Rp, zp, phi, psi);
         const float R2 = (float)(Rp * Rp), Z2 = (float)(zp * zp);
         const float fphi = (float)phi, fpsi = (float)psi;
         va = make_float4(R2, Z2, fphi, fpsi);
-        vb = make_float4(fphi * R2, fpsi * R2, fphi * Z2, fpsi * Z2);
+        vb = make_float2(fphi * Z2, fpsi * Z2);
       }
       __syncthreads();
       pa[threadIdx.x] = va;
       pb[threadIdx.x] = vb;
       __syncthreads();
-      float sP = 0.f, sT = 0.f, sxP = 0.f, sxT = 0.f, syP = 0.f, syT = 0.f;
+      float sP = 0.f, sT = 0.f, syP = 0.f, syT = 0.f;
       if (tv) {
 #pragma unroll 16
         for (int j = 0; j < 256; ++j) {   // points past the range are zero
-          const float4 A = pa[j], B = pb[j];
+          const float4 A = pa[j];
+          const float2 B = pb[j];
           const float e = fast_exp2(fmaf(c.x, A.x, c.y * A.y));
           sP = fmaf(A.z, e, sP);
           sT = fmaf(A.w, e, sT);
-          sxP = fmaf(B.x, e, sxP);
-          sxT = fmaf(B.y, e, sxT);
-          syP = fmaf(B.z, e, syP);
-          syT = fmaf(B.w, e, syT);
+          syP = fmaf(B.x, e, syP);
+          syT = fmaf(B.y, e, syT);
         }
       }
       SP += (double)sP;
       ST += (double)sT;
-      SxP += (double)sxP;
-      SxT += (double)sxT;
       SyP += (double)syP;
       SyT += (double)syT;
     }
     if (tv) {
-      double *o = adj.sparts + ((int64_t)it.b * Tp + t) * 6;
+      double *o = adj.sparts + ((int64_t)it.b * Tp + t) * 4;
       o[0] = SP;
       o[1] = ST;
-      o[2] = SxP;
-      o[3] = SxT;
-      o[4] = SyP;
-      o[5] = SyT;
+      o[2] = SyP;
+      o[3] = SyT;
     }
     __syncthreads();
   }
@@ -3378,7 +3374,7 @@ __global__ void __launch_bounds__(256) k_sph_sens_cells(const GeomDev *__restric
     const bool tv = t < Tp;
     const SphTerm *tc = reinterpret_cast<const SphTerm *>(terms64 + md.term64_off);
     const double cx = tv ? tc[t].cx : 0.0, cy = tv ? tc[t].cy : 0.0;
-    double sF = 0.0, sx = 0.0, sy = 0.0;
+    double sF = 0.0, sy = 0.0;
     {
       const int cell = part * 256 + threadIdx.x;
       double r, sth, cth;
@@ -3395,16 +3391,14 @@ __global__ void __launch_bounds__(256) k_sph_sens_cells(const GeomDev *__restric
           const double2 x = px[j];
           const double e = pc[j] * (double)fast_exp2((float)fma(cx, x.x, cy * x.y));
           sF += e;
-          sx = fma(x.x, e, sx);
           sy = fma(x.y, e, sy);
         }
       }
     }
     if (tv) {
-      double *o = adj.cparts + ((int64_t)part * Tp + t) * 3;
+      double *o = adj.cparts + ((int64_t)part * Tp + t) * 2;
       o[0] = sF;
-      o[1] = sx;
-      o[2] = sy;
+      o[1] = sy;
     }
     __syncthreads();
   }
@@ -3429,18 +3423,18 @@ __global__ void __launch_bounds__(256) k_sph_chain(const GeomDev *__restrict__ g
     const int Tp = sph_terms_padded(g.J1, g.n_u), T = g.J1 * g.n_u;
     const int t = it.a * 256 + threadIdx.x;
     if (t >= T) continue;
-    double S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    double S[4] = {0.0, 0.0, 0.0, 0.0};
     for (int rg = 0; rg < md.n_sens_parts; ++rg) {
-      const double *o = adj.sparts + ((int64_t)rg * Tp + t) * 6;
+      const double *o = adj.sparts + ((int64_t)rg * Tp + t) * 4;
 #pragma unroll
-      for (int c = 0; c < 6; ++c) S[c] += o[c];
+      for (int c = 0; c < 4; ++c) S[c] += o[c];
     }
     // the cell parts in order
-    double cp[3] = {0.0, 0.0, 0.0};
+    double cp[2] = {0.0, 0.0};
     for (int pt = 0; pt < kSphCellParts; ++pt) {
-      const double *o = adj.cparts + ((int64_t)pt * Tp + t) * 3;
+      const double *o = adj.cparts + ((int64_t)pt * Tp + t) * 2;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) cp[c] += o[c];
+      for (int c = 0; c < 2; ++c) cp[c] += o[c];
     }
     const double *mt = gauss + md.gauss_off + 4 * g.K;
     const int j = t / g.n_u, n = t % g.n_u;
@@ -3452,7 +3446,7 @@ __global__ void __launch_bounds__(256) k_sph_chain(const GeomDev *__restrict__ g
     const double T1 = w * e2 * 4.0 * rj * rj * u2 * u2 * u2 / (h15 * h);
     const double F1 = w * e2 * 2.0 * rj * u2 * u2 / h15;
     const double cy = -rj * u2 / h * kLog2e;
-    const double dcy = kLn2 * Kp * (P1 * S[4] + T1 * S[5] + F1 * cp[2]);   // dL/dc_y
+    const double dcy = kLn2 * Kp * (P1 * S[2] + T1 * S[3] + F1 * cp[1]);   // dL/dc_y
     const double dP1 = P1 * 1.5 * u2 / h;
     const double dT1 = w * 4.0 * rj * rj * u2 * u2 * u2 * (1.0 / (h15 * h) + e2 * 2.5 * u2 / (h15 * h * h));
     const double dF1 = w * 2.0 * rj * u2 * u2 * (1.0 / h15 + e2 * 1.5 * u2 / (h15 * h));

@@ -861,11 +861,10 @@ __global__ void __launch_bounds__(256) k_pol_cot_sum(const GeomDev *__restrict__
 // Term sensitivities from the grid cotangent: item (m, 512-term tile, part of
 // kPolN / kPolParts rows); thread = two terms, which share each point's LDS
 // reads (wave-wide broadcasts; with one term per thread the reads are the
-// bound).  Per term S_phi = sum phi E, S_psi and their R'^2 and z'^2 moments,
-// FP32 over a row of 64 points, FP64 across rows.  On a row r'^2 is fixed: the
-// exponent, in FP64 as in k_pol_grid_adj, is one multiply-add from c.x r'^2, and
-// the R'^2 = r'^2 - z'^2 moments need no sums of their own.  An FP64 multiply-add,
-// an exponential and four FP32 multiply-adds per term and point bound it.
+// bound).  Per term S_phi = sum phi E, S_psi and their z'^2 moments, FP32 over a
+// row of 64 points, FP64 across rows.  On a row r'^2 is fixed: the exponent, in FP64
+// as in k_pol_grid_adj, is one multiply-add from c.x r'^2.  An FP64 multiply-add, an
+// exponential and four FP32 multiply-adds per term and point bound it.
 // Measured (48 models of 1300 terms / one of 5248): on the 512 x 512 grid with
 // matrix cores 1132 / 129 us, here 400 / 64 (325 / 52 with FP32 exponents).
 __global__ void __launch_bounds__(256) k_pol_sens(const GeomDev *__restrict__ geoms,
@@ -893,13 +892,13 @@ __global__ void __launch_bounds__(256) k_pol_sens(const GeomDev *__restrict__ ge
     const float2 *fl = reinterpret_cast<const float2 *>(
         pcot + md.sgcot_off + pol_nodes(K) + (int64_t)pol_cot_groups(K) * kPolBins * kPolTile);
     const SphTerm *tc = reinterpret_cast<const SphTerm *>(terms64 + md.term64_off);
-    double cx[2], dz[2], SP[2], ST[2], ZP[2], ZT[2], RP[2], RT[2];
+    double cx[2], dz[2], SP[2], ST[2], ZP[2], ZT[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int t = it.a * 512 + 256 * u + threadIdx.x;
       cx[u] = t < Tp ? tc[t].cx : 0.0;
       dz[u] = t < Tp ? tc[t].cy - cx[u] : 0.0;
-      SP[u] = ST[u] = ZP[u] = ZT[u] = RP[u] = RT[u] = 0.0;
+      SP[u] = ST[u] = ZP[u] = ZT[u] = 0.0;
     }
     const double c2 = pol_col_c2(sc, lane), reach = pol_reach(sc);
     double cmax = fmax(cx[0], cx[1]);
@@ -937,8 +936,6 @@ __global__ void __launch_bounds__(256) k_pol_sens(const GeomDev *__restrict__ ge
           ST[u] += (double)sT[u];
           ZP[u] += (double)zP[u];
           ZT[u] += (double)zT[u];
-          RP[u] += r * (double)sP[u] - (double)zP[u];
-          RT[u] += r * (double)sT[u] - (double)zT[u];
         }
       }
     }
@@ -947,13 +944,11 @@ __global__ void __launch_bounds__(256) k_pol_sens(const GeomDev *__restrict__ ge
       const int t = it.a * 512 + 256 * u + threadIdx.x;
       if (t >= Tp) continue;
       double *o = sph_adj_layout(sens + md.sens_off, K, g.n_pix, Tp, md.n_sens_parts).sparts +
-                  ((int64_t)it.b * Tp + t) * 6;
+                  ((int64_t)it.b * Tp + t) * 4;
       o[0] = SP[u];
       o[1] = ST[u];
-      o[2] = RP[u];
-      o[3] = RT[u];
-      o[4] = ZP[u];
-      o[5] = ZT[u];
+      o[2] = ZP[u];
+      o[3] = ZT[u];
     }
   }
 }
