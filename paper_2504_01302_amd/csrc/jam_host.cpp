@@ -570,6 +570,7 @@ struct Plan {
   int numsm_ptr[jam::kSmallTilings + 1] = {};   // small-map items by tiling
   int adj_ptr[jam::kSmallQuads + 1] = {};       // and the adjoint's by y quads (1 ..)
   int n_bins_wave = 0;   // leading bin items summed one bin per wave
+  int n_pro_fwd = 0;     // leading prologue items, all that the forward needs
   bool spherical = false;
   bool fused_prologue = true;
   int grid_num = 1, grid_sens = 1;
@@ -1484,8 +1485,16 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   p->fused_prologue = n <= kFusedPrologueModels;
   if (p->fused_prologue)
     for (int m = 0; m < n; ++m) it_pro.push_back({m, 0, 0, 0});
-  for (const jam::Item &t : it_terms) it_pro.push_back({t.m, t.a, 0, p->fused_prologue ? 1 : 3});
+  // (last the terms of models that only the adjoint sums directly)
+  auto push_terms = [&](bool compressed) {
+    for (const jam::Item &t : it_terms)
+      if (spherical || (md[t.m].form == 5) == compressed)
+        it_pro.push_back({t.m, t.a, 0, p->fused_prologue ? 1 : 3});
+  };
+  push_terms(false);
   for (const jam::Item &t : it_sbpro) it_pro.push_back({t.m, t.a, t.b, 2});
+  p->n_pro_fwd = (int)it_pro.size();
+  if (!spherical) push_terms(true);
   // bin items: the one-bin-per-wave ones first (a launch of 256-thread
   // blocks), then the one-bin-per-block ones (1024-thread blocks)
   std::stable_partition(it_bins.begin(), it_bins.end(), [](const jam::Item &t) { return t.c == 1; });
@@ -1634,7 +1643,7 @@ void launch_numerator(jam_ctx *ctx, Plan *p, char *ws, hipStream_t st) {
 }
 
 // Set-up, term table and SB map; optionally the numerator map.  Leaves N and
-// I in the workspace pix region.
+// I in the workspace pix region.  adjoint: with the terms that only the adjoint reads.
 void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_t *status,
                          char *ws, hipStream_t st, bool need_numerator, bool capturing,
                          bool adjoint = false) {
@@ -1653,8 +1662,9 @@ void launch_forward_maps(jam_ctx *ctx, Plan *p, const jam::ParamsDev &pd, int32_
   } else {
     if (!p->fused_prologue)
       jam::launch_setup(ctx->d_geoms, p->d_models, p->n, pd, gauss, st_ws, status, queue, st);
-    if (p->n_pro)
-      jam::launch_prologue(ctx->d_geoms, p->d_models, p->d_pro, p->n_pro, pd, gauss, st_ws, status,
+    const int n_pro = adjoint ? p->n_pro : p->n_pro_fwd;
+    if (n_pro)
+      jam::launch_prologue(ctx->d_geoms, p->d_models, p->d_pro, n_pro, pd, gauss, st_ws, status,
                          queue, terms, pix, p->fused_prologue, st);
   }
   if (p->spherical) {
@@ -1734,7 +1744,7 @@ void launch_vjp(jam_ctx *ctx, Plan *p, const jam_batch *b, const double *vrms2, 
       jam::launch_sph_num(ctx->d_geoms, p->d_models, p->d_red, p->n_red, gauss, st_ws, tabs, pix,
                           st);
   } else {
-    launch_forward_maps(ctx, p, pd, nullptr, w, st, recompute, capturing);
+    launch_forward_maps(ctx, p, pd, nullptr, w, st, recompute, capturing, true);
   }
   // V per bin: the caller's forward output, or recomputed into workspace.
   const double *V = vrms2;
