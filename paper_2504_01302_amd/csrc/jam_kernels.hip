@@ -1424,8 +1424,8 @@ __global__ void __launch_bounds__(256) k_sens(const GeomDev *__restrict__ geoms,
 // XT = 4), the next four steps' operands read and their exponentials taken
 // behind the current MFMAs.  Item (m, part p | XT << 16 covering x tiles 4p ..
 // 4p + XT - 1, first 32-term group, end group); eight waves, two per SIMD,
-// so that one wave's exponentials and epilogue run beside the other's
-// MFMAs; wave w takes the item's groups w, w + 8, ...; output per part,
+// so that one wave's LDS reads, waits and dependent epilogue pass behind the
+// other's instructions (matrix and vector issue of a SIMD add up); wave w takes the item's groups w, w + 8, ...; output per part,
 // [S0 | S1 | Sg] (T doubles each), as sens_mfma_item's per x tile.
 // ---------------------------------------------------------------------------
 constexpr int kWideTiles = 4;
