@@ -92,28 +92,6 @@ constexpr NodeTables make_tables() {
 static_assert(kChebP == 8, "dblk and the (b, i) rows are laid out for 8 nodes");
 __device__ const NodeTables kTab = make_tables();
 
-// log of a positive normal number to about 1e-15 (the interpolation variable
-// takes no more): mantissa in [sqrt(1/2), sqrt 2), odd series in
-// (m - 1) / (m + 1).
-__device__ __forceinline__ double log64(double x) {
-  int e = __builtin_amdgcn_frexp_exp(x);
-  double m = __builtin_amdgcn_frexp_mant(x);         // [1/2, 1)
-  const bool low = m < 0.70710678118654752440;
-  m = low ? 2.0 * m : m;
-  e = low ? e - 1 : e;
-  const double t = (m - 1.0) * rcp64(m + 1.0), t2 = t * t;
-  double q = 2.0 / 19.0;
-  q = fma(q, t2, 2.0 / 17.0);
-  q = fma(q, t2, 2.0 / 15.0);
-  q = fma(q, t2, 2.0 / 13.0);
-  q = fma(q, t2, 2.0 / 11.0);
-  q = fma(q, t2, 2.0 / 9.0);
-  q = fma(q, t2, 2.0 / 7.0);
-  q = fma(q, t2, 2.0 / 5.0);
-  q = fma(q, t2, 2.0 / 3.0);
-  return fma((double)e, 0.69314718055994530942, t * fma(q, t2, 2.0));
-}
-
 // What a (model, tracer, panel) unit needs of the set-up, and its range of d
 // in n_sub equal stretches of the interpolation variable z = (lin ? d : log
 // d) scale + shift in [0, n_sub], with 16 nodes each.  On the linear panel z

@@ -39,6 +39,28 @@ __device__ inline double rsq64(double x) {
   return fma(0.5 * y, e, y);
 }
 
+// log of a positive normal number to about 1e-15 (the interpolation variable
+// takes no more): mantissa in [sqrt(1/2), sqrt 2), odd series in
+// (m - 1) / (m + 1).
+__device__ __forceinline__ double log64(double x) {
+  int e = __builtin_amdgcn_frexp_exp(x);
+  double m = __builtin_amdgcn_frexp_mant(x);         // [1/2, 1)
+  const bool low = m < 0.70710678118654752440;
+  m = low ? 2.0 * m : m;
+  e = low ? e - 1 : e;
+  const double t = (m - 1.0) * rcp64(m + 1.0), t2 = t * t;
+  double q = 2.0 / 19.0;
+  q = fma(q, t2, 2.0 / 17.0);
+  q = fma(q, t2, 2.0 / 15.0);
+  q = fma(q, t2, 2.0 / 13.0);
+  q = fma(q, t2, 2.0 / 11.0);
+  q = fma(q, t2, 2.0 / 9.0);
+  q = fma(q, t2, 2.0 / 7.0);
+  q = fma(q, t2, 2.0 / 5.0);
+  q = fma(q, t2, 2.0 / 3.0);
+  return fma((double)e, 0.69314718055994530942, t * fma(q, t2, 2.0));
+}
+
 // A load through a pointer that the compiler cannot see to be global (one read
 // from a descriptor), which would otherwise be a flat load and wait for LDS too.
 __device__ __forceinline__ double load_global(const double *p) {
