@@ -856,24 +856,32 @@ double list_schedule_makespan(std::vector<double> &cost, int slots) {
 // and its jobs the workgroup items.
 int num_slots(const jam_ctx *ctx, const Tune &) { return std::max(1, ctx->n_cu); }
 
-// Default slice length: the one whose item list the workers finish first
-// under the list-scheduling model.  Candidates are geometric around a few
-// jobs per worker, plus the exact splits of the largest model, so a uniform
-// item list can fill whole rounds of workers.
 // Modelled time of the numerator launch with slices of `gran`; 1e300 for more items
 // than most_items.
 double gran_makespan(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t, int gran,
                      size_t most_items) {
+  std::vector<std::vector<double>> of(ctx->gh.size());   // a geometry's items
+  std::vector<char> known(ctx->gh.size(), 0);
   std::vector<double> cost;
   for (int m = 0; m < n; ++m) {
-    const GeomHost &g = ctx->gh[geom_idx[m]];
-    const NumChoice c = choose_numerator(g, t, gran);
-    for (int sl = 0; sl < c.n_slices; ++sl)
-      for (int tl = 0; tl < c.n_tiles(); ++tl) cost.push_back(num_item_cost(g, c, sl, tl));
+    const int i = geom_idx[m];
+    if (!known[i]) {
+      const GeomHost &g = ctx->gh[i];
+      const NumChoice c = choose_numerator(g, t, gran);
+      for (int sl = 0; sl < c.n_slices; ++sl)
+        for (int tl = 0; tl < c.n_tiles(); ++tl) of[i].push_back(num_item_cost(g, c, sl, tl));
+      known[i] = 1;
+    }
+    if (cost.size() + of[i].size() > most_items) return 1e300;
+    cost.insert(cost.end(), of[i].begin(), of[i].end());
   }
-  return cost.size() > most_items ? 1e300 : list_schedule_makespan(cost, num_slots(ctx, t));
+  return list_schedule_makespan(cost, num_slots(ctx, t));
 }
 
+// Default slice length: the one whose item list the workers finish first
+// under the list-scheduling model.  Candidates are geometric around a few
+// jobs per worker, plus the exact splits of the largest model, so a uniform
+// item list can fill whole rounds of workers.
 int default_gran(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
   const int slots = num_slots(ctx, t);
   double work = 0.0, big_work = -1.0;
@@ -1955,15 +1963,18 @@ jam_status autotune(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Tune &best
 size_t direct_ws(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t, bool all_parts,
                  size_t *fixed) {
   int64_t gauss = 0, terms = 0, pix = 0, part = 0, bins = 0, total_bins = 0;
-  for (int m = 0; m < n; ++m) {
-    const GeomHost &g = ctx->gh[geom_idx[m]];
+  std::vector<int64_t> models(ctx->gh.size(), 0);
+  for (int m = 0; m < n; ++m) ++models[geom_idx[m]];
+  for (size_t i = 0; i < models.size(); ++i) {
+    if (models[i] == 0) continue;
+    const GeomHost &g = ctx->gh[i];
     const NumChoice c = choose_numerator(g, t, t.gran);
-    gauss += jam::gauss_size(g.K, g.J1);
-    terms += c.gen ? 0 : jam::padded_terms(g.T);
-    pix += 4 * (int64_t)g.n_pix;
-    part += all_parts ? part_doubles(g, c) : part_size(g, c);
-    bins += 2 * (int64_t)g.n_bins;
-    total_bins += g.n_bins;
+    gauss += models[i] * jam::gauss_size(g.K, g.J1);
+    terms += models[i] * (c.gen ? 0 : jam::padded_terms(g.T));
+    pix += models[i] * 4 * g.n_pix;
+    part += models[i] * (all_parts ? part_doubles(g, c) : part_size(g, c));
+    bins += models[i] * 2 * g.n_bins;
+    total_bins += models[i] * g.n_bins;
   }
   size_t w = align256(sizeof(int) * n);
   w = align256(w + sizeof(int) * 2);
@@ -1982,19 +1993,21 @@ size_t direct_ws(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune 
 // us, 489 with the slices that would fit).
 constexpr double kLongerSlices = 1.1;
 bool lengthen_slices(const jam_ctx *ctx, int n, const int32_t *geom_idx, Tune &t) {
+  std::vector<int> grans;
+  for (int gran = t.gran; gran < (1 << 24); gran += 1 + gran / 8) grans.push_back(gran);
   size_t fixed = 0;
-  for (int gran = t.gran; gran < (1 << 24); gran += 1 + gran / 8) {
-    Tune longer = t;
+  Tune longer = t;
+  auto fits = [&](int gran) {
     longer.gran = gran;
-    if (direct_ws(ctx, n, geom_idx, longer, false, &fixed) <= kScratchBytes) {
-      const double time = gran_makespan(ctx, n, geom_idx, t, gran, SIZE_MAX);
-      if (time > kLongerSlices * gran_makespan(ctx, n, geom_idx, t, t.gran, SIZE_MAX)) return false;
-      t = longer;
-      return true;
-    }
-    if (fixed > kScratchBytes) return false;
-  }
-  return false;
+    return direct_ws(ctx, n, geom_idx, longer, false, &fixed) <= kScratchBytes;
+  };
+  if (grans.empty() || !fits(grans.back())) return false;
+  // the partial maps only shrink as the slices grow
+  longer.gran = *std::partition_point(grans.begin(), grans.end(), [&](int gran) { return !fits(gran); });
+  const double time = gran_makespan(ctx, n, geom_idx, t, longer.gran, SIZE_MAX);
+  if (time > kLongerSlices * gran_makespan(ctx, n, geom_idx, t, t.gran, SIZE_MAX)) return false;
+  t = longer;
+  return true;
 }
 
 jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan *&out) {
@@ -2046,9 +2059,15 @@ jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan 
     } else {
       Tune td = t;
       td.cheb = p->tune.cheb & ~1;
-      if (td.gran <= 0) td.gran = default_gran(ctx, n, geom_idx, td);
       size_t fixed = 0;
-      if (direct_ws(ctx, n, geom_idx, td, true, &fixed) <= kScratchBytes) {
+      auto fits = [&]() { return direct_ws(ctx, n, geom_idx, td, true, &fixed) <= kScratchBytes; };
+      bool direct = true;
+      if (td.gran <= 0) {
+        td.gran = 1 << 24;   // the smallest partial maps
+        direct = fits();
+        if (direct) td.gran = default_gran(ctx, n, geom_idx, td);
+      }
+      if (direct && fits()) {
         // closing a group at h_limit leaves it at most one model over
         const size_t rest = p->off_cheb + 4096;   // the regions before H
         int64_t big = 0, all_h = 0;
