@@ -35,8 +35,9 @@ def _args():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=5)
-    ap.add_argument("--form", type=int, default=2,
-                    help="1 per-pixel VALU kernel, 2 matrix-core kernel (0 = library default)")
+    ap.add_argument("--form", type=int, default=0,
+                    help="0 (default) the library's choice, 1 per-pixel VALU kernel, 2 matrix-core "
+                         "kernels that sum the terms directly")
     ap.add_argument("--launch", type=int, default=0,
                     help="0 one worker per work item, 1 persistent work-queue grid")
     ap.add_argument("--graph", type=int, default=1,

@@ -9,6 +9,9 @@ Bars: the interpolants of one term are within 2 rho^-8, rho = 9 (eight nodes
 an octave in v: exp(-z e^s) is bounded by 1 for |Im s| < pi / 2), about 5e-8 of
 the term, with alternating signs over the terms; V per bin within 1e-7, the
 gradient in norm within 1e-7 (the FP32 forms are held to 1e-5 and 1e-4)."""
+import json
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -226,3 +229,66 @@ def test_automatic_form_is_not_the_slower_one(nx, n):
     auto, direct = _call_us(g, n, 0, dev), _call_us(g, n, 2, dev)
     print(f"{nx} x {nx}, {n} models: automatic {auto:.0f} us, direct {direct:.0f} us")
     assert auto <= 1.1 * direct
+
+
+def _golden(name):
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", name)
+    if not os.path.exists(path):
+        pytest.skip(f"{name} not generated")
+    return json.load(open(path))
+
+
+@pytest.mark.parametrize("name,make", [("cfg2_seed0.json", inputs.config2),
+                                       ("composite_seed0.json", inputs.config_composite)])
+def test_full_size_maps_in_the_automatic_form(name, make):
+    """The IFU-scale and the composite model's sampled maps."""
+    dev = _dev()
+    gd = _golden(name)
+    w = make(seed=0)
+    g = w.geometries[0]
+    ctx = binding.Context(w.geometries)
+    assert ctx.plan_info(w.geom_idx)["num_kernel"] == 4
+    p = binding.pack_params(w, dev)
+    N, I, st = ctx.eval_maps(w.geom_idx, p["inc"], p["mass_scale"], p["m_bh"], p["beta"])
+    torch.cuda.synchronize()
+    assert int(st.cpu()[0]) == 0
+    shape = (g.ny * g.supersample + g.psf_n - 1, g.nx * g.supersample + g.psf_n - 1)
+    at = np.array(gd["pix_iy"]), np.array(gd["pix_ix"])
+    rN = np.abs(N.cpu().numpy().reshape(shape)[at] / np.array(gd["N"]) - 1).max()
+    rI = np.abs(I.cpu().numpy().reshape(shape)[at] / np.array(gd["I"]) - 1).max()
+    print(f"{name}: N {rN:.2e}, I {rI:.2e}")
+    ctx.close()
+    assert rN <= 1e-7 and rI <= 1e-12
+
+
+def test_full_size_model_from_recorded_graphs():
+    """The IFU-scale model: all bins against the stored oracle values, and forward
+    and adjoint replayed from recorded graphs against the eager calls."""
+    dev = _dev()
+    ref = np.array(_golden("cfg2_seed0.json")["vrms2"])
+    w = inputs.config2(seed=0)
+    p = binding.pack_params(w, dev, amplitudes=True)
+    args = (w.geom_idx, p["inc"], p["mass_scale"], p["m_bh"], p["beta"], p["lum_I0"], p["mass_S0"])
+    cot = torch.as_tensor(inputs.cotangent(len(ref), 1)[0], device=dev)
+    eager = binding.Context(w.geometries)
+    assert eager.plan_info(w.geom_idx)["num_kernel"] == 4
+    V, st = eager.eval_batch(*args)
+    want = eager.vjp(*args, V, cot)
+    torch.cuda.synchronize()
+    rel = np.abs(V.cpu().numpy() / ref - 1).max()
+    print(f"all bins: {rel:.2e}")
+    assert int(st.cpu()[0]) == 0 and rel <= 1e-7
+    ctx = binding.Context(w.geometries, graph=1)
+    out = torch.empty_like(V)
+    for rep in range(4):
+        out.fill_(-1.0)
+        ctx.eval_batch(*args, out=out, status=st)
+        got = ctx.vjp(*args, out, cot)
+        torch.cuda.synchronize()
+        assert torch.equal(out, V), rep
+        for k in KEYS:
+            assert torch.equal(got[k], want[k]), (rep, k)
+        eager.eval_batch(*args)               # eager work of the program between replays
+        torch.cuda.synchronize()
+    ctx.close()
+    eager.close()
