@@ -99,6 +99,8 @@ struct GeomHost {
   double gl8_x[8] = {}, gl8_w[8] = {};
   // compressed cylindrical form (GeomDev)
   int cheb_np = 0, cheb_pieces = 0;
+  // gain over the direct forms, forward and adjoint, and the forward's direct cost (ChebCost)
+  double cheb_gain[2] = {}, cheb_direct = 0.0;
   bool cheb_fwd = false, cheb_adj = false;   // the faster form in a large batch
   std::vector<double> cheb_lo, cheb_xi, cheb_E, cheb_Ek, cheb_Gk;
   std::vector<int> cheb_ptr, cheb_id, cheb_h, cheb_ch, cheb_pc, cheb_jp, cheb_jx;
@@ -353,29 +355,29 @@ MapCover cover_of(int n_ux, int n_uy, int tau) {
   return c;
 }
 
-// The compressed form's cost against the direct forms', in ns of one SIMD per
-// tracer.  Direct: per term the map's tiles, in the adjoint its blocks; compressed:
-// per term, per panel (set-up, node transforms), per panel and 16 map rows (the node
-// contraction and its exponentials), and per panel and block (FP64 MFMAs).  Fitted
-// by least squares to the difference of whole calls, forced into one form and the
-// other, of batches of 4 to 600 models that fill the chip: 24 to 129 distinct
-// coordinates an axis, 360 to 5460 terms per tracer.  Compressed / direct there, 360
-// terms 0.34 to 1.1 of the speed, 1300 terms 0.73 to 1.0 on maps of up to 2 x 2
-// blocks and 1.4 to 2 beyond, 5248 terms 1.2 to 4.4.  Near the break-even the direct
-// form is taken (kChebGain): it needs less workspace and shorter lists.
-struct ChebCost { double direct, term, panel, row, tile; };
-constexpr ChebCost kChebFwd{1.075, 15.0, 3600.0, 236.0, 52.0};   // direct: per ns of the tiles
-constexpr ChebCost kChebAdj{30.7, 20.0, 7040.0, 486.0, 0.0};     // per term and block
-constexpr double kChebGain = 0.95;
-double cheb_direct_ns(const GeomHost &o, bool adjoint) {
-  const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32, terms = (double)o.J1 * o.n_u;
-  return terms * (adjoint ? kChebAdj.direct * bx * by
-                          : kChebFwd.direct * cover_of(o.n_ux, o.n_uy, 0).ns);
-}
-double cheb_ns(const GeomHost &o, const ChebCost &c, int panels) {
+// The compressed form's cost against the direct forms', in ns of one SIMD for a model.
+// Direct: per term the map's tiles, in the adjoint its blocks; compressed: per term,
+// per (tracer, panel) unit, per unit and 32 map rows that it reaches (the node
+// contraction and its exponentials), per unit and tile that it reaches (FP64 MFMAs) and
+// per tile (the sum of the partials).  Fitted by least squares to the difference of
+// whole calls, forced into one form and the other, of 450 batches drawn at random: 1 to
+// 800 models of 3 to 60 x 2 to 95 Gaussians, 33 to 300 distinct coordinates an axis, 72
+// to 15000 terms per tracer, pixels of 0.02 to 0.08".  The form taken (choose_cheb) is
+// there 0.3 % (forward) and 1 % (adjoint) slower than the better one on average; by more
+// than a tenth in 3 and 19 of them, calls below 100 us but for two.
+struct ChebCost { double direct, term, unit, row, tile, map; };
+constexpr ChebCost kChebFwd{1.06, 7.8, 2000.0, 1130.0, 787.0, 6580.0};   // direct: per ns of the tiles
+constexpr ChebCost kChebAdj{32.0, 17.1, 2160.0, 4210.0, 936.0, 0.0};     // per term and block
+struct ChebWork { double terms, units, rows, tiles; };   // of all tracers
+double cheb_ns(const GeomHost &o, const ChebCost &c, const ChebWork &w) {
   const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32;
-  return c.term * o.J1 * o.n_u + panels * (c.panel + c.row * 2.0 * by + c.tile * bx * by);
+  return c.term * w.terms + c.unit * w.units + c.row * w.rows + c.tile * w.tiles + c.map * bx * by;
 }
+// The adjoint takes the compressed form in every model where all together lose less
+// than this against the direct one, whose two launches are the longer ones of a small
+// batch (6 models of 86 x 86, 7 x 8 x 70 terms: 77 us, 107 direct).  Such models keep
+// the form's tables up to twice their direct cost.
+constexpr double kChebAdjNs = 5000.0;
 
 // Tables of the compressed cylindrical form (GeomDev): panels of v = r u^2,
 // the first [0, 1 / M2) with M2 the map's largest squared coordinate, then a
@@ -417,9 +419,6 @@ void build_cheb(GeomHost &o) {
   int np = 0;
   for (int e = 0; e <= top; ++e)
     if (count[e]) index[e] = np++;
-  o.cheb_fwd = cheb_ns(o, kChebFwd, np) < kChebGain * cheb_direct_ns(o, false);
-  o.cheb_adj = cheb_ns(o, kChebAdj, np) < kChebGain * cheb_direct_ns(o, true);
-  if (!o.cheb_fwd && !o.cheb_adj) return;
   o.cheb_lo.assign(2 * np, 0.0);
   o.cheb_ptr.assign(np + 1, 0);
   for (int e = 0; e <= top; ++e) {
@@ -428,6 +427,56 @@ void build_cheb(GeomHost &o) {
     o.cheb_lo[P] = edge[e];
     o.cheb_lo[np + P] = edge[e + 1];
     o.cheb_ptr[P + 1] = o.cheb_ptr[P] + count[e];
+  }
+  const int ntx = (o.n_ux + 31) / 32, nty = (o.n_uy + 31) / 32, ldx = 32 * ntx, ldy = 32 * nty;
+  o.cheb_px.assign((size_t)o.K * ntx, 0);
+  o.cheb_py.assign((size_t)o.K * nty, 0);
+  o.cheb_ux.assign((size_t)o.K * np, 0);
+  o.cheb_h.assign((size_t)o.K * np + 1, 0);
+  ChebWork fwd{}, adj{};
+  for (int k = 0; k < o.K; ++k) {
+    const double a = 0.5 / (o.lum_sigma[k] * o.lum_sigma[k]), ay = a / (o.lum_q[k] * o.lum_q[k]);
+    // panels reaching a tile: by its smallest coordinate (d >= v, so the
+    // panel's lower end in v bounds its decay in y too)
+    auto reach = [&](double alpha, double q) {
+      int c = 0;
+      while (c < np && (alpha + o.cheb_lo[c]) * (q * q) <= kChebCut) ++c;
+      return (unsigned char)c;
+    };
+    unsigned char *px = o.cheb_px.data() + (size_t)k * ntx, *py = o.cheb_py.data() + (size_t)k * nty;
+    for (int t = 0; t < ntx; ++t) px[t] = reach(a, o.xs[32 * t]);
+    for (int t = 0; t < nty; ++t) py[t] = reach(ay, o.ys[32 * t]);
+    for (int P = 0; P < np; ++P) {
+      int tiles = 0, cols = 0;
+      while (cols < ntx && px[cols] > P) ++cols;
+      if (cols > 0)
+        while (tiles < nty && py[tiles] > P) ++tiles;
+      o.cheb_ux[(size_t)k * np + P] = (unsigned short)cols;
+      o.cheb_h[(size_t)k * np + P + 1] = o.cheb_h[(size_t)k * np + P] + tiles;
+      if (tiles > 0) {
+        fwd.units += 1.0;
+        fwd.terms += o.cheb_ptr[P + 1] - o.cheb_ptr[P];
+      }
+    }
+    for (int ty = 0; ty < nty; ++ty)
+      for (int tx = 0; tx < ntx; ++tx) fwd.tiles += std::min(px[tx], py[ty]);
+  }
+  fwd.rows = adj.rows = o.cheb_h.back();
+  adj.tiles = fwd.tiles;
+  adj.terms = o.T;
+  adj.units = (double)o.K * np;
+  const double direct_adj = kChebAdj.direct * (double)o.T * ntx * nty;
+  o.cheb_direct = kChebFwd.direct * (double)o.T * cover_of(o.n_ux, o.n_uy, 0).ns;
+  o.cheb_gain[0] = o.cheb_direct - cheb_ns(o, kChebFwd, fwd);
+  o.cheb_gain[1] = direct_adj - cheb_ns(o, kChebAdj, adj);
+  o.cheb_fwd = o.cheb_gain[0] > 0.0;
+  o.cheb_adj = o.cheb_gain[1] > 0.0;
+  if (!o.cheb_fwd && o.cheb_gain[1] < -direct_adj) {
+    for (auto *v : {&o.cheb_ptr, &o.cheb_h}) v->clear();
+    for (auto *v : {&o.cheb_px, &o.cheb_py}) v->clear();
+    o.cheb_lo.clear();
+    o.cheb_ux.clear();
+    return;
   }
   o.cheb_id.resize(nt);
   o.cheb_xi.resize(nt);
@@ -459,7 +508,6 @@ void build_cheb(GeomHost &o) {
     o.cheb_jx.insert(o.cheb_jx.end(), v.begin(), v.end());
     o.cheb_jp.push_back((int)o.cheb_jx.size());
   }
-  const int ntx = (o.n_ux + 31) / 32, nty = (o.n_uy + 31) / 32, ldx = 32 * ntx, ldy = 32 * nty;
   o.cheb_E.assign((size_t)np * 2 * jam::kChebP * ldx, 0.0);
   for (int P = 0; P < np; ++P)
     for (int m = 0; m < jam::kChebP; ++m) {
@@ -475,31 +523,10 @@ void build_cheb(GeomHost &o) {
     }
   o.cheb_Ek.assign((size_t)o.K * ldx, 0.0);
   o.cheb_Gk.assign((size_t)o.K * ldy, 0.0);
-  o.cheb_px.assign((size_t)o.K * ntx, 0);
-  o.cheb_py.assign((size_t)o.K * nty, 0);
-  o.cheb_ux.assign((size_t)o.K * np, 0);
-  o.cheb_h.assign((size_t)o.K * np + 1, 0);
   for (int k = 0; k < o.K; ++k) {
     const double a = 0.5 / (o.lum_sigma[k] * o.lum_sigma[k]), ay = a / (o.lum_q[k] * o.lum_q[k]);
     for (int i = 0; i < o.n_ux; ++i) o.cheb_Ek[(size_t)k * ldx + i] = std::exp(-a * (o.xs[i] * o.xs[i]));
     for (int i = 0; i < o.n_uy; ++i) o.cheb_Gk[(size_t)k * ldy + i] = std::exp(-ay * (o.ys[i] * o.ys[i]));
-    // panels reaching a tile: by its smallest coordinate (d >= v, so the
-    // panel's lower end in v bounds its decay in y too)
-    auto reach = [&](double alpha, double q) {
-      int c = 0;
-      while (c < np && (alpha + o.cheb_lo[c]) * (q * q) <= kChebCut) ++c;
-      return (unsigned char)c;
-    };
-    for (int t = 0; t < ntx; ++t) o.cheb_px[(size_t)k * ntx + t] = reach(a, o.xs[32 * t]);
-    for (int t = 0; t < nty; ++t) o.cheb_py[(size_t)k * nty + t] = reach(ay, o.ys[32 * t]);
-    for (int P = 0; P < np; ++P) {
-      int tiles = 0, cols = 0;
-      while (cols < ntx && o.cheb_px[(size_t)k * ntx + cols] > P) ++cols;
-      if (cols > 0)
-        while (tiles < nty && o.cheb_py[(size_t)k * nty + tiles] > P) ++tiles;
-      o.cheb_ux[(size_t)k * np + P] = (unsigned short)cols;
-      o.cheb_h[(size_t)k * np + P + 1] = o.cheb_h[(size_t)k * np + P] + tiles;
-    }
   }
   o.cheb_np = np;
 }
@@ -1003,35 +1030,53 @@ void for_cheb_tiles(const GeomHost &g, F f) {
 
 constexpr double kShareTerms = 512.0;
 
-// Whether a batch takes the compressed form, forward (1) and adjoint (2).  The
-// forward has one launch more than the direct one and, in a single model,
-// fewer workgroups to hide its latency, so its gain on the whole chip has to
-// exceed kChebLatencyNs: one model of 102 x 102 distinct pixels, 16 x 31 x 112
-// terms takes 45.7 us compressed and 49.3 direct (gain 14 us), 66 x 66 with 12 x 61 x
-// 128 terms 51.6 and 50.3 (11).  Its two launches beside a direct one take
-// kChebBesideNs with their tails, another pair for another group of models
-// kChebGroupNs (160 models of 68 x 68, 10 x 13 x 100 terms: one group 276 us, eight
-// 531).  The adjoint's launches are the direct one's.
-constexpr double kChebLatencyNs = 12500.0;
+// Whether a batch takes the compressed form, forward (1) and adjoint (2: where it is
+// the faster one, 4: in every model).  The forward has one launch more than the direct
+// one and, in a few models, fewer workgroups to hide its latency, which a gain on the
+// whole chip of kChebLatencyNs covers, the less the longer the direct call is (a
+// decay over kChebLatencyOver): one model of 102 x 102 distinct pixels, 16 x 31 x 112
+// terms takes 45.7 us compressed and 49.3 direct, 66 x 66 with 12 x 61 x 128 terms 51.6
+// and 50.3; 300 models of 34 x 36, 3 x 14 x 160 terms 153 and 169, 72 of 72 x 43, 20 x
+// 10 x 120 terms 220 and 224.  Its two launches beside a direct one take kChebBesideNs
+// with their tails, another pair for another group of models kChebGroupNs (160 models of
+// 68 x 68, 10 x 13 x 100 terms: one group 276 us, eight 531).
+constexpr double kChebLatencyNs = 15000.0;
+constexpr double kChebLatencyOver = 30000.0;
 constexpr double kChebBesideNs = 20000.0;
 constexpr double kChebGroupNs = 36000.0;
-double cheb_gain_ns(const jam_ctx *ctx, int n, const int32_t *geom_idx, bool adjoint, bool *all) {
+// (their direct cost, and whether all models gain)
+double cheb_gain_ns(const jam_ctx *ctx, int n, const int32_t *geom_idx, double *direct, bool *all) {
   double gain = 0.0;
+  *direct = 0.0;
+  *all = true;
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
-    if (adjoint ? g.cheb_adj : g.cheb_fwd)
-      gain += g.K * (cheb_direct_ns(g, adjoint) - cheb_ns(g, adjoint ? kChebAdj : kChebFwd, g.cheb_np));
-    else
+    if (g.cheb_fwd) {
+      gain += g.cheb_gain[0] / (4.0 * ctx->n_cu);
+      *direct += g.cheb_direct / (4.0 * ctx->n_cu);
+    } else {
       *all = false;
+    }
   }
-  return gain / (4.0 * ctx->n_cu);
+  return gain;
 }
 int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
   if (t.rule != 1 || ctx->opt.alignment == 1 || ctx->opt.form == 2) return 0;
-  bool all = true, unused = true;
-  const double fwd = cheb_gain_ns(ctx, n, geom_idx, false, &all);
-  const double adj = cheb_gain_ns(ctx, n, geom_idx, true, &unused);
-  return (fwd > (all ? kChebLatencyNs : kChebBesideNs) ? 1 : 0) | (adj > 0.0 ? 2 : 0);
+  bool all;
+  double direct;
+  const double fwd = cheb_gain_ns(ctx, n, geom_idx, &direct, &all);
+  const double least = all ? kChebLatencyNs * std::exp(-direct / kChebLatencyOver) : kChebBesideNs;
+  double gain = 0.0, loss = 0.0;
+  bool tables = true;
+  for (int m = 0; m < n; ++m) {
+    const GeomHost &g = ctx->gh[geom_idx[m]];
+    (g.cheb_adj ? gain : loss) += g.cheb_gain[1] / (4.0 * ctx->n_cu);
+    tables = tables && g.cheb_np > 0;
+  }
+  int forms = fwd > least ? 1 : 0;
+  if (gain > 0.0) forms |= 2;
+  if (tables && loss > -kChebAdjNs) forms |= 6;
+  return forms;
 }
 
 // The tilings of a batch's maps, by geometry (n_models of each in the batch; gran
@@ -1181,7 +1226,7 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   // compressed form: units per map item, two items per compute unit where
   // the batch is small enough (a unit on a tile is 16 FP64 MFMAs of a wave)
   auto fwd_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && (tune.cheb & 1) && g.cheb_fwd; };
-  auto adj_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && (tune.cheb & 2) && g.cheb_adj; };
+  auto adj_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && ((tune.cheb & 4) || ((tune.cheb & 2) && g.cheb_adj)); };
   int64_t cheb_units = 0, cheb_panels = 0, cadj_panels = 0;
   int cheb_most = 0;   // terms of the largest panel
   int64_t small_terms = 0;
@@ -1843,7 +1888,7 @@ std::string tune_key(const jam_ctx *ctx, int n, const int32_t *geom_idx) {
     mix((uint64_t)g.n_ux | ((uint64_t)g.n_uy << 20) | ((uint64_t)g.n_u << 40));
     // the forms a map takes depend on these and not on their product alone
     mix((uint64_t)g.K | ((uint64_t)g.J1 << 32));
-    mix((uint64_t)g.cheb_np);
+    mix((uint64_t)g.cheb_np | (g.cheb_fwd ? 1ull << 32 : 0) | (g.cheb_adj ? 1ull << 33 : 0));
   }
   char buf[128];
   snprintf(buf, sizeof buf, "gfx950/v3/n%d/%016llx", n, (unsigned long long)h);
@@ -2079,8 +2124,9 @@ jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan 
           }
         const int64_t room = rest < kScratchBytes ? (int64_t)((kScratchBytes - rest) / 8) - big : 0;
         const int64_t more = room > 0 ? (all_h - 1) / room : INT32_MAX;   // groups but the first
-        bool all = true;
-        if (more > 1 && cheb_gain_ns(ctx, n, geom_idx, false, &all) < kChebGroupNs * more)
+        bool all;
+        double ns;
+        if (more > 1 && cheb_gain_ns(ctx, n, geom_idx, &ns, &all) < kChebGroupNs * more)
           s = build_plan(ctx, n, geom_idx, td, p);
         else
           s = build_plan(ctx, n, geom_idx, t, p, room);

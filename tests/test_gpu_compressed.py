@@ -216,16 +216,18 @@ def _call_us(g, n, form, dev):
     return best
 
 
-@pytest.mark.parametrize("nx,n", [(84, 232), (130, 70), (130, 150)])
-def test_automatic_form_is_not_the_slower_one(nx, n):
-    """Maps of two and three blocks a side with 1300 terms per tracer, near the
-    break-even of the compressed form: the automatic choice within a tenth of the
-    direct forms (the compressed one took a third longer), also where its workspace
-    exceeds the allocation-free scratch and the direct forms' does not (in many
-    groups of models it took a fifth longer)."""
+@pytest.mark.parametrize("nx,n,n_mass,n_u", [(84, 232, 12, 100), (130, 70, 12, 100),
+                                             (130, 150, 12, 100), (280, 200, 4, 60),
+                                             (430, 36, 6, 40)])
+def test_automatic_form_is_not_the_slower_one(nx, n, n_mass, n_u):
+    """Maps of two and three blocks a side with 1300 terms per tracer and of five and
+    seven with 300, near the break-even of the compressed form: the automatic choice
+    within a tenth of the direct forms (the compressed one took a third longer), also
+    where its workspace exceeds the allocation-free scratch and the direct forms' does
+    not (in many groups of models it took a fifth longer)."""
     dev = _dev()
-    g = inputs.small_geometry(seed=330, n_lum=10, n_mass=12, nx=nx, ny=nx, n_u=100, pixsize=0.05,
-                              psf_n=9, n_bins=20)
+    g = inputs.small_geometry(seed=330, n_lum=10, n_mass=n_mass, nx=nx, ny=nx, n_u=n_u,
+                              pixsize=0.05 if nx < 200 else 0.025, psf_n=9, n_bins=20)
     auto, direct = _call_us(g, n, 0, dev), _call_us(g, n, 2, dev)
     print(f"{nx} x {nx}, {n} models: automatic {auto:.0f} us, direct {direct:.0f} us")
     assert auto <= 1.1 * direct
