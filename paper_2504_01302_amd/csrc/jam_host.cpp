@@ -101,7 +101,6 @@ struct GeomHost {
   int cheb_np = 0, cheb_pieces = 0;
   // gain over the direct forms, forward and adjoint, and the forward's direct cost (ChebCost)
   double cheb_gain[2] = {}, cheb_direct = 0.0;
-  bool cheb_fwd = false, cheb_adj = false;   // the faster form in a large batch
   std::vector<double> cheb_lo, cheb_xi, cheb_E, cheb_Ek, cheb_Gk;
   std::vector<int> cheb_ptr, cheb_id, cheb_h, cheb_ch, cheb_pc, cheb_jp, cheb_jx;
   std::vector<unsigned char> cheb_px, cheb_py;
@@ -373,11 +372,15 @@ double cheb_ns(const GeomHost &o, const ChebCost &c, const ChebWork &w) {
   const double bx = (o.n_ux + 31) / 32, by = (o.n_uy + 31) / 32;
   return c.term * w.terms + c.unit * w.units + c.row * w.rows + c.tile * w.tiles + c.map * bx * by;
 }
-// The adjoint takes the compressed form in every model where all together lose less
-// than this against the direct one, whose two launches are the longer ones of a small
-// batch (6 models of 86 x 86, 7 x 8 x 70 terms: 77 us, 107 direct).  Such models keep
-// the form's tables up to twice their direct cost.
-constexpr double kChebAdjNs = 5000.0;
+// The models of a batch that take the compressed form (Tune::cheb), forward or adjoint:
+// those that gain, or all that have its tables, which are built up to twice the direct
+// adjoint's cost.
+constexpr int kChebFwdGain = 1, kChebAdjGain = 2, kChebFwdAll = 4, kChebAdjAll = 8;
+constexpr int kChebAnyFwd = kChebFwdGain | kChebFwdAll;
+bool takes_cheb(const GeomHost &g, int cheb, bool adjoint) {
+  return g.cheb_np > 0 && ((cheb & (adjoint ? kChebAdjAll : kChebFwdAll)) ||
+                           ((cheb & (adjoint ? kChebAdjGain : kChebFwdGain)) && g.cheb_gain[adjoint] > 0.0));
+}
 
 // Tables of the compressed cylindrical form (GeomDev): panels of v = r u^2,
 // the first [0, 1 / M2) with M2 the map's largest squared coordinate, then a
@@ -469,9 +472,7 @@ void build_cheb(GeomHost &o) {
   o.cheb_direct = kChebFwd.direct * (double)o.T * cover_of(o.n_ux, o.n_uy, 0).ns;
   o.cheb_gain[0] = o.cheb_direct - cheb_ns(o, kChebFwd, fwd);
   o.cheb_gain[1] = direct_adj - cheb_ns(o, kChebAdj, adj);
-  o.cheb_fwd = o.cheb_gain[0] > 0.0;
-  o.cheb_adj = o.cheb_gain[1] > 0.0;
-  if (!o.cheb_fwd && o.cheb_gain[1] < -direct_adj) {
+  if (o.cheb_gain[0] <= 0.0 && o.cheb_gain[1] < -direct_adj) {
     for (auto *v : {&o.cheb_ptr, &o.cheb_h}) v->clear();
     for (auto *v : {&o.cheb_px, &o.cheb_py}) v->clear();
     o.cheb_lo.clear();
@@ -544,8 +545,7 @@ struct Tune {
   int launch = 0;   // 0 one workgroup per item; 1 persistent grid pulling items from a
                     // device queue
   int cheb = -1;    // derived from the batch, not tuned (-1: still to be derived): the
-                    // compressed form for the forward (1) and the adjoint (2) of the models
-                    // whose geometry it suits
+                    // models in the compressed form (takes_cheb)
 };
 
 // Every pointer a captured graph was recorded with (parameters, outputs,
@@ -808,7 +808,7 @@ NumChoice choose_numerator(const GeomHost &g, const Tune &t, int gran) {
     return c;
   }
   const int chunks = (g.T + 63) / 64;
-  if ((t.cheb & 1) && g.cheb_fwd) {
+  if (takes_cheb(g, t.cheb, false)) {
     c.kind = 5;
     c.n_slices = 0;
     c.units = 0;
@@ -1030,52 +1030,65 @@ void for_cheb_tiles(const GeomHost &g, F f) {
 
 constexpr double kShareTerms = 512.0;
 
-// Whether a batch takes the compressed form, forward (1) and adjoint (2: where it is
-// the faster one, 4: in every model).  The forward has one launch more than the direct
-// one and, in a few models, fewer workgroups to hide its latency, which a gain on the
-// whole chip of kChebLatencyNs covers, the less the longer the direct call is (a
-// decay over kChebLatencyOver): one model of 102 x 102 distinct pixels, 16 x 31 x 112
+// Which models of a batch take the compressed form: of direct, all and those that gain
+// the choice with the least modelled time, for the forward and the adjoint.  All: the
+// forward has one launch more than the direct one and, in a few models, fewer workgroups
+// to hide its latency, which costs kChebLatencyNs, the less the longer the direct call is
+// (a decay over kChebLatencyOver): one model of 102 x 102 distinct pixels, 16 x 31 x 112
 // terms takes 45.7 us compressed and 49.3 direct, 66 x 66 with 12 x 61 x 128 terms 51.6
 // and 50.3; 300 models of 34 x 36, 3 x 14 x 160 terms 153 and 169, 72 of 72 x 43, 20 x
-// 10 x 120 terms 220 and 224.  Its two launches beside a direct one take kChebBesideNs
-// with their tails, another pair for another group of models kChebGroupNs (160 models of
-// 68 x 68, 10 x 13 x 100 terms: one group 276 us, eight 531).
+// 10 x 120 terms 220 and 224.  The direct adjoint's two launches are the longer ones of
+// a small batch (6 models of 86 x 86, 7 x 8 x 70 terms: 77 us, 107 direct), worth
+// kChebAdjNs.  Beside other models' launches, one after the other, with their tails, the
+// form's own cost kChebBesideNs and kChebBesideAdjNs: 63 models of 67 to 203 pixels a
+// side, 5 x 8 x 90 terms, adjoint 317 us direct, 226 compressed and 411 with those
+// compressed that gain.  Another pair of forward launches for another group of models
+// takes kChebGroupNs (160 models of 68 x 68, 10 x 13 x 100 terms: one group 276 us, eight
+// 531).
 constexpr double kChebLatencyNs = 15000.0;
 constexpr double kChebLatencyOver = 30000.0;
+constexpr double kChebAdjNs = 5000.0;
 constexpr double kChebBesideNs = 20000.0;
+constexpr double kChebBesideAdjNs = 80000.0;
 constexpr double kChebGroupNs = 36000.0;
-// (their direct cost, and whether all models gain)
-double cheb_gain_ns(const jam_ctx *ctx, int n, const int32_t *geom_idx, double *direct, bool *all) {
-  double gain = 0.0;
-  *direct = 0.0;
-  *all = true;
+struct ChebBatch {
+  double all = 0.0, some = 0.0, direct = 0.0;   // gain on the whole chip; the direct cost
+  bool every = true, small = false;             // every larger map has the tables; small maps
+};
+ChebBatch cheb_batch(const jam_ctx *ctx, int n, const int32_t *geom_idx, bool adjoint) {
+  ChebBatch b;
   for (int m = 0; m < n; ++m) {
     const GeomHost &g = ctx->gh[geom_idx[m]];
-    if (g.cheb_fwd) {
-      gain += g.cheb_gain[0] / (4.0 * ctx->n_cu);
-      *direct += g.cheb_direct / (4.0 * ctx->n_cu);
+    if (g.cheb_np > 0) {
+      const double gain = g.cheb_gain[adjoint] / (4.0 * ctx->n_cu);
+      b.all += gain;
+      b.some += std::max(0.0, gain);
+      b.direct += g.cheb_direct / (4.0 * ctx->n_cu);
+    } else if (g.n_ux <= kSmallMap && g.n_uy <= kSmallMap && g.J1 <= jam::kSmallAdjMass) {
+      b.small = true;
     } else {
-      *all = false;
+      b.every = false;
     }
   }
-  return gain;
+  return b;
 }
 int choose_cheb(const jam_ctx *ctx, int n, const int32_t *geom_idx, const Tune &t) {
   if (t.rule != 1 || ctx->opt.alignment == 1 || ctx->opt.form == 2) return 0;
-  bool all;
-  double direct;
-  const double fwd = cheb_gain_ns(ctx, n, geom_idx, &direct, &all);
-  const double least = all ? kChebLatencyNs * std::exp(-direct / kChebLatencyOver) : kChebBesideNs;
-  double gain = 0.0, loss = 0.0;
-  bool tables = true;
-  for (int m = 0; m < n; ++m) {
-    const GeomHost &g = ctx->gh[geom_idx[m]];
-    (g.cheb_adj ? gain : loss) += g.cheb_gain[1] / (4.0 * ctx->n_cu);
-    tables = tables && g.cheb_np > 0;
+  int forms = 0;
+  for (const bool adjoint : {false, true}) {
+    const ChebBatch b = cheb_batch(ctx, n, geom_idx, adjoint);
+    const double beside = adjoint ? kChebBesideAdjNs : kChebBesideNs;
+    double all = adjoint ? b.all + kChebAdjNs
+                         : b.all - (b.small ? kChebBesideNs
+                                            : kChebLatencyNs * std::exp(-b.direct / kChebLatencyOver));
+    if (!b.every || b.direct == 0.0) all = 0.0;
+    const double some = b.some - beside;
+    if (std::max(all, some) <= 0.0) continue;
+    if (all >= some)
+      forms |= adjoint ? kChebAdjAll : kChebFwdAll;
+    else
+      forms |= adjoint ? kChebAdjGain : kChebFwdGain;
   }
-  int forms = fwd > least ? 1 : 0;
-  if (gain > 0.0) forms |= 2;
-  if (tables && loss > -kChebAdjNs) forms |= 6;
   return forms;
 }
 
@@ -1225,8 +1238,8 @@ jam_status build_plan(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, const Tu
   const bool spherical = ctx->opt.alignment == 1;
   // compressed form: units per map item, two items per compute unit where
   // the batch is small enough (a unit on a tile is 16 FP64 MFMAs of a wave)
-  auto fwd_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && (tune.cheb & 1) && g.cheb_fwd; };
-  auto adj_cheb = [&](const GeomHost &g) { return !(ctx->opt.alignment == 1) && ((tune.cheb & 4) || ((tune.cheb & 2) && g.cheb_adj)); };
+  auto fwd_cheb = [&](const GeomHost &g) { return takes_cheb(g, tune.cheb, false); };
+  auto adj_cheb = [&](const GeomHost &g) { return takes_cheb(g, tune.cheb, true); };
   int64_t cheb_units = 0, cheb_panels = 0, cadj_panels = 0;
   int cheb_most = 0;   // terms of the largest panel
   int64_t small_terms = 0;
@@ -1888,7 +1901,7 @@ std::string tune_key(const jam_ctx *ctx, int n, const int32_t *geom_idx) {
     mix((uint64_t)g.n_ux | ((uint64_t)g.n_uy << 20) | ((uint64_t)g.n_u << 40));
     // the forms a map takes depend on these and not on their product alone
     mix((uint64_t)g.K | ((uint64_t)g.J1 << 32));
-    mix((uint64_t)g.cheb_np | (g.cheb_fwd ? 1ull << 32 : 0) | (g.cheb_adj ? 1ull << 33 : 0));
+    mix((uint64_t)g.cheb_np | (g.cheb_gain[0] > 0.0 ? 1ull << 32 : 0) | (g.cheb_gain[1] > 0.0 ? 1ull << 33 : 0));
   }
   char buf[128];
   snprintf(buf, sizeof buf, "gfx950/v3/n%d/%016llx", n, (unsigned long long)h);
@@ -2103,7 +2116,7 @@ jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan 
         return s;
     } else {
       Tune td = t;
-      td.cheb = p->tune.cheb & ~1;
+      td.cheb = p->tune.cheb & ~kChebAnyFwd;
       size_t fixed = 0;
       auto fits = [&]() { return direct_ws(ctx, n, geom_idx, td, true, &fixed) <= kScratchBytes; };
       bool direct = true;
@@ -2117,16 +2130,16 @@ jam_status get_plan_impl(jam_ctx *ctx, int32_t n, const int32_t *geom_idx, Plan 
         const size_t rest = p->off_cheb + 4096;   // the regions before H
         int64_t big = 0, all_h = 0;
         for (int m = 0; m < n; ++m)
-          if (ctx->gh[geom_idx[m]].cheb_fwd) {
+          if (takes_cheb(ctx->gh[geom_idx[m]], p->tune.cheb, false)) {
             const int64_t h = (int64_t)ctx->gh[geom_idx[m]].cheb_h.back() * 512;
             big = std::max(big, h);
             all_h += h;
           }
         const int64_t room = rest < kScratchBytes ? (int64_t)((kScratchBytes - rest) / 8) - big : 0;
         const int64_t more = room > 0 ? (all_h - 1) / room : INT32_MAX;   // groups but the first
-        bool all;
-        double ns;
-        if (more > 1 && cheb_gain_ns(ctx, n, geom_idx, &ns, &all) < kChebGroupNs * more)
+        const ChebBatch b = cheb_batch(ctx, n, geom_idx, false);
+        const double gain = p->tune.cheb & kChebFwdAll ? b.all : b.some;
+        if (more > 1 && gain < kChebGroupNs * more)
           s = build_plan(ctx, n, geom_idx, td, p);
         else
           s = build_plan(ctx, n, geom_idx, t, p, room);
