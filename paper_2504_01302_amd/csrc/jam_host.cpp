@@ -363,7 +363,7 @@ MapCover cover_of(int n_ux, int n_uy, int tau) {
 // 800 models of 3 to 60 x 2 to 95 Gaussians, 33 to 300 distinct coordinates an axis, 72
 // to 15000 terms per tracer, pixels of 0.02 to 0.08".  The form taken (choose_cheb) is
 // there 0.3 % (forward) and 1 % (adjoint) slower than the better one on average; by more
-// than a tenth in 3 and 19 of them, calls below 100 us but for two.
+// than a tenth in 3 and 19 of them.
 struct ChebCost { double direct, term, unit, row, tile, map; };
 constexpr ChebCost kChebFwd{1.06, 7.8, 2000.0, 1130.0, 787.0, 6580.0};   // direct: per ns of the tiles
 constexpr ChebCost kChebAdj{32.0, 17.1, 2160.0, 4210.0, 936.0, 0.0};     // per term and block
