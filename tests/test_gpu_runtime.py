@@ -192,7 +192,7 @@ def test_autotuner_starts_from_the_default_slices():
     """The candidates' slices are half to twice the default schedule's, also where
     the maps would suit the compressed form and the batch is too small for it."""
     _dev()
-    g = inputs.small_geometry(seed=81, n_lum=12, n_mass=60, nx=132, ny=132, n_u=128, psf_n=1,
+    g = inputs.small_geometry(seed=81, n_lum=12, n_mass=30, nx=132, ny=132, n_u=128, psf_n=1,
                               pixsize=0.03, n_bins=6)
     idx = np.zeros(1, np.int32)
     plain, tuned = binding.Context([g]), binding.Context([g], form=0, autotune=1)
